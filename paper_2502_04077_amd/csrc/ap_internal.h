@@ -85,7 +85,7 @@ __host__ __device__ constexpr int predictor_tap(int half, int out, int q) {
 // placed kMfmaTableFloatOffset floats into the weight buffer (the fp32 section is 10*8 + 9*64 + 2*8 + 1 = 673
 // floats; 676 keeps 16-byte alignment): layer 2 [half 2][K-step 6][lane 64][8 f16], then layer 1
 // [half 2][lane 64][8 f16]; what a lane's entries stand for is said in predict_inc8.h.
-//   layer 2  lane (m = 8 o + c2, h) of K-step s: entries e = 0..3 belong to the step's first (y1 row q, tap kw)
+//   layer 2  lane (m = 8 o + c2, h; outputs 1, 2 of the bottom half swapped, see mfma16_phys) of K-step s: entries e = 0..3 belong to the step's first (y1 row q, tap kw)
 //            pair, 4..7 to its second, input channel 4 h + e % 4; the pairs of step s are (ri_pair_q(s, 0), kw) and
 //            (ri_pair_q(s, 1), kw) with kw = ri_pair_kw(s): centre taps first (their operands are registers as
 //            they come out of layer 1), then the two outer taps

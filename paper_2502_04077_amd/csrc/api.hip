@@ -188,7 +188,7 @@ int ap_set_weights(ap_ctx* ctx, const float* blob, size_t n_floats, void* stream
             const int q = ap::ri_pair_q(s, e / 4), ci = 4 * h + e % 4;
             float v = 0.f;
             if (m < 24) {
-              const int kh = ap::predictor_tap(half, m / 8, q);
+              const int kh = ap::predictor_tap(half, ap::mfma16_phys(half, m / 8), q);
               if (kh >= 0) v = w2[(((size_t)(m % 8) * c1 + ci) * 3 + kh) * 3 + kw];
             }
             t[((half * 6 + s) * 64 + lane) * 8 + e] = (_Float16)v;

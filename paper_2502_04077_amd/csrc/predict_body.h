@@ -39,8 +39,9 @@ template <int C1, int C2> struct Weights {
 // Row type of history row r (which kernel rows of the second layer fall inside the window).
 __device__ __forceinline__ int row_type(int r, int H) { return (r == 0 ? 1 : 0) + (r == H - 1 ? 2 : 0); }
 
+// Slot of logical row r, -1 (the row that just left) .. H - 1 (the newest).
 __device__ __forceinline__ int ring_slot(int newest_slot, int H, int R, int r) {
-  int slot = (newest_slot - (H - 1 - r)) % R;   // logical row r (H-1 = newest, -1 = the row that just left)
+  const int slot = newest_slot - (H - 1 - r);           // > -R: at most one turn of the ring away
   return slot < 0 ? slot + R : slot;
 }
 

@@ -1,33 +1,44 @@
 // Incremental predictor for 8/8 channels on MFMA with both layers held in registers (see predict.hip for the
 // method: the interior state moves by (row entering) - (row leaving), the four border rows are evaluated afresh).
 //
-// A wave owns 32 consecutive history columns at a time (lane l: column n = l % 32, channel half h = l / 32) and
-// works one half of the method on them: waves 0,1 the top half (leaving row, rows 0, 1), waves 2,3 the bottom half
-// (entering row, rows H-2, H-1).  v_mfma_f32_32x32x16_f16 computes D[32 x 32] += A[32 x 16] * B[16 x 32]; lane l
-// supplies row / column l % 32 and K entries 8 (l / 32) .. + 7 and receives D rows 8 (v / 4) + 4 (l / 32) + v % 4
-// (v = 0..15) of column l % 32.  What makes the registers enough:
+// Only columns that can contribute are evaluated.  In the difference form of ap_internal.h a history that is zero
+// around a column gives exactly zero there (d1 = max(min(b1, 0), -max(b1, 0)) = 0, and the same for d2), and the rows
+// that sparse steps push are zero outside the selection.  So a pass of up to kRiPassCols columns starts with one bit per
+// column and half of the method: is one of the half's five values other than zero.  An output column has such a
+// value within two columns, or lies at an end of the tile (where y1 = 0 beside the tile stands for d1 = lo1); the
+// list a wave then works off holds the outputs and their direct neighbours, in ascending order, so that lanes next to
+// each other hold neighbouring columns wherever an output needs them: of 2050 columns with 64 selected in runs, some
+// 200 a half.  With dense rows it would hold every column and is not written at all.
+//
+// A wave owns 32 list entries at a time (lane l: entry n = l % 32, channel half h = l / 32) and works one half of the
+// method on them: waves 0,1 the top half (leaving row, rows 0, 1), waves 2,3 the bottom half (entering row, rows H-2,
+// H-1; the outputs of a half are numbered so that 1 is the row whose window leaves the history: row 0, row H-1).
+// v_mfma_f32_32x32x16_f16 computes D[32 x 32] += A[32 x 16] * B[16 x 32]; lane l supplies row / column l % 32 and
+// K entries 8 (l / 32) .. + 7 and receives D rows 8 (v / 4) + 4 (l / 32) + v % 4 (v = 0..15) of column l % 32.  What
+// makes the registers enough:
 //   layer 1  rows = (staged y1 row q, channel c1), K = 16 = 15 (x row, tap) pairs + a constant 1 that carries the
 //            accumulator start.  The ten history rows of a pass of columns go from global memory straight to LDS
-//            (global_load_lds, no registers), asked for a whole pass ahead; at the start of the pass they are
-//            converted once - scaled by 2^12, rounded to f16 - into the words a lane's K slots are made of, so
-//            that an operand is four 4-byte LDS reads and no arithmetic.
+//            (global_load_lds, no registers), asked for a whole pass ahead into the other of two buffers; a lane
+//            scales the eight values its K slots are made of by 2^12 and rounds them to f16 as it reads them.
 //   layer 2  the result of layer 1 is, per lane, channels 4h .. 4h+3 of the four y1 rows of its own column: exactly
 //            half of the K entries of a layer-2 step whose 16 entries are two (y1 row, tap) pairs of 8 channels.
 //            The centre tap takes those registers as they are, the outer taps the same registers moved by one
 //            lane with DPP wave shifts (16 moves): K = 96 in six steps, no LDS and no barrier.
 //   head     fp32: clamp (the ReLU in difference form), weight, sum the four channels of the lane, and one
 //            half-wave swap adds the two channel halves.
-// Columns next to the ends of the 32 get wrong neighbours, so a block yields 28 outputs (lanes 2..29) and blocks
-// overlap by four columns.  All arithmetic is in the difference form of ap_internal.h: accumulators start at
-// 2^8 init, the ReLUs are clamps at 2^8 lo, y1 is kept as f16 of 2^8 d1.  f16 operands, fp32 accumulation.
-// Measured alternatives that came out within 3 % of their baseline at cfg2's shape: the outer taps through a
-// wave-private piece of LDS instead of DPP moves, the head as a third MFMA on the clamped f16 result, a load or
-// two per block instead of a staged pass, five waves per SIMD instead of four, staggered first passes.  What did
-// pay: no 64-bit address arithmetic or predication on the pass's loads, and the loads a pass ahead.
-// The two halves of a column meet once per pass of up to kRiPassCols columns, through LDS: the state and pred
-// are written by a short epilogue after the pass's last barrier.  The leaving row is evaluated by the same instruction
-// sequence on the same values as when it entered (both halves run this code, and a block always covers the same
-// columns), so it cancels exactly.
+// The entries at either end of the 32 get wrong neighbours, so a piece yields 30 outputs and pieces overlap by two.
+// All arithmetic is in the difference form of ap_internal.h: accumulators start at 2^8 init, the ReLUs are clamps at
+// 2^8 lo, y1 is kept as f16 of 2^8 d1.  f16 operands, fp32 accumulation.
+// The two halves of a column meet once per pass, through LDS: the state and pred are written by a short epilogue after
+// the pass's second barrier (the first one is between the bits and the lists).  The
+// leaving row is evaluated by the same instruction sequence on the same values as when it entered, so it cancels exactly.
+//
+// Measured at 2048 instances x 2050 columns (0.20 GB to move: 31 us at the rate a plain read reaches), histories of 64
+// selected blocks in runs: 46-48 us, with all columns evaluated 72; an all-zero history 35 us (66), 128 instances x 8194
+// columns 15 us (23.5).  Histories that are dense in all ten rows take 84-87 us (77): every piece then comes with the
+// bits on top, and the SIMDs are full of vector instructions (four cycles each: 78 a piece, 53 us of the 87) and MFMAs
+// (27 us), which overlap in part only.  That holds for the first five steps after a prefill; with a dense row every 32
+// steps the average is 52 us.
 #pragma once
 
 #include <type_traits>
@@ -37,18 +48,20 @@
 namespace ap {
 namespace {
 
-constexpr int kRiOut = 28;                              // outputs per 32-column block
-constexpr int kRiPassBlocks = 15;                       // most blocks whose halves meet in one pass
-constexpr int kRiPassCols = kRiOut * kRiPassBlocks;     // 420 output columns per pass
-constexpr int kRiStageCols = kRiPassCols + 8;           // staged history columns: four more on either side (428)
-constexpr int kRiRawSegs = (kRiStageCols + kWave - 1) / kWave;   // a raw history row arrives in wave-wide pieces (7)
-constexpr int kRiRawStride = kRiRawSegs * kWave;        // floats per raw row in LDS (448)
-// LDS words: the ten raw history rows of the next pass [row][kRiRawStride]; staged x operands
-// [x01 | x2][half 2][lane half 2][kRiStageCols]; the partial sums [half][column of the pass][moving | border]
+constexpr int kRiOut = 30;                              // outputs per 32 list entries
+constexpr int kRiRawSegs = 6;                           // a raw history row of a pass arrives in wave-wide pieces
+constexpr int kRiRawStride = kRiRawSegs * kWave;        // staged history columns of a pass, four more than outputs on either side
+constexpr int kRiPassCols = kRiRawStride - 8;           // most output columns per pass (four workgroups' LDS fits a CU)
+// LDS words: two buffers of ten raw history rows [row][kRiRawStride], the pass at hand and the next one; the partial
+// sums [half][column of the pass][moving | border]; the waves' column lists (16 bits an entry); one bit per staged
+// column [half][2 zero words | column / 32 | zero words]; and two masks of output columns
 constexpr int kRiRawWords = 10 * kRiRawStride;
-constexpr int kRiStageWords = 2 * 2 * 2 * kRiStageCols;
 constexpr int kRiPartWords = 2 * kRiPassCols * 2;
-constexpr int kPredRegLdsFloats = kRiRawWords + kRiStageWords + kRiPartWords;
+constexpr int kRiListWords = kRiRawStride / 2;
+constexpr int kRiBitWords = 20;
+constexpr int kPredRegLdsFloats = 2 * kRiRawWords + kRiPartWords + 4 * kRiListWords + 2 * kRiBitWords + 16 + 2 * 16;
+static_assert(2 * kRiRawSegs <= 16 && 2 + 16 + 1 <= kRiBitWords, "a lane of a row of 16 per 32 columns");
+constexpr uint32_t kRiIsOutput = 0x8000u;               // list entry: staged column | this if it is an output
 
 // Every lane is written (a lane without a source lane gets 0), so no previous value has to be set up.
 template <int CTRL> __device__ __forceinline__ uint32_t dpp_all(uint32_t v) {
@@ -57,40 +70,79 @@ template <int CTRL> __device__ __forceinline__ uint32_t dpp_all(uint32_t v) {
 constexpr int kWaveShr1 = 0x138, kWaveShl1 = 0x130;     // lane l reads lane l - 1 / l + 1 of the whole wave
 
 // 64 consecutive floats of LDS starting at `dst` (wave-uniform) are filled from global memory, lane l from
-// row[byte_off / 4] of its own choosing, without passing through registers; completion is counted by vmcnt.
-__device__ __forceinline__ void load_to_lds(const float* row, uint32_t byte_off, float* dst) {
+// base[byte_off / 4] of its own choosing, without passing through registers; completion is counted by vmcnt.
+__device__ __forceinline__ void load_to_lds(const float* base, uint32_t byte_off, float* dst) {
   typedef const __attribute__((address_space(1))) void* gptr_t;
   typedef __attribute__((address_space(3))) void* lptr_t;
-  __builtin_amdgcn_global_load_lds((gptr_t)(reinterpret_cast<const char*>(row) + byte_off), (lptr_t)dst, 4, 0, 0);
+  __builtin_amdgcn_global_load_lds((gptr_t)(reinterpret_cast<const char*>(base) + byte_off), (lptr_t)dst, 4, 0, 0);
 }
 
-// One float at a 32-bit byte offset from a wave-uniform row pointer (scalar base + vector offset addressing).
-__device__ __forceinline__ float ld_row(const float* row, uint32_t byte_off) {
-  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + byte_off);
+// Bits [lo, hi) of a row of bits, as far as they lie in its 32-bit word w.
+__device__ __forceinline__ uint32_t bits_from(int n) { return n <= 0 ? ~0u : n >= 32 ? 0u : ~0u << n; }
+__device__ __forceinline__ uint32_t bit_range(int lo, int hi, int w) { return bits_from(lo - 32 * w) & ~bits_from(hi - 32 * w); }
+
+// Workgroup barrier for data in LDS only: __syncthreads() would also wait for the loads in flight (vmcnt), among
+// them the next pass's rows.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
-// Workgroup `chunk` of `n_chunks` of instance `inst` (256 threads); smem: kPredRegLdsFloats floats.
+// Every instance's columns are cut into n_pass passes of equal length (at most kRiPassCols columns); a workgroup of
+// 256 threads takes a run of consecutive passes of all instances, so that the operands are fetched and the first
+// rows waited for once per workgroup.   smem: kPredRegLdsFloats floats.
 __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ hist, const float* __restrict__ wts_global,
-                                                     int R, int H, int newest_slot, int nb_cur, int nb_cap, int inst,
-                                                     int chunk, int n_chunks, int advance, float* __restrict__ pstate,
+                                                     int R, int H, int newest_slot, int nb_cur, int nb_cap, int inst0,
+                                                     int ninst, int n_pass, int advance, float* __restrict__ pstate,
                                                      float* __restrict__ pred, float* smem) {
   constexpr int C = 8;
   constexpr float kXScale = 4096.f, kAccScale = 256.f;
   typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
-  const int n_blocks = (nb_cur + kRiOut - 1) / kRiOut;
-  const int per_wg = (n_blocks + n_chunks - 1) / n_chunks;
-  const int b_begin = chunk * per_wg;
-  const int b_end = min(n_blocks, b_begin + per_wg);
-  if (b_begin >= b_end) return;                          // (the whole workgroup: no barrier is skipped by part of it)
-
-  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int total = ninst * n_pass;
+  const int pass_cols = (nb_cur + n_pass - 1) / n_pass;
+  const int tid_all = threadIdx.x;
+  int tid = tid_all, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int hf = wave >> 1, wsub = wave & 1;
   const int n = lane & 31, hsel = lane >> 5;
-  const float* hist_inst = hist + (size_t)inst * R * nb_cap;
-  float* pstate_inst = pstate + (size_t)inst * nb_cap;
-  float* pred_inst = pred + (size_t)inst * nb_cap;
+
+  // Ring rows of the ten staged x rows, as byte offsets into an instance's ring: staged rows 0..4 of the top half are history
+  // rows -1..3, of the bottom half H-5..H-1.  (Wave-uniform: they live in scalar registers.)
+  uint32_t row_off[2][5];
+#pragma unroll
+  for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+    for (int r = 0; r < 5; ++r)
+      row_off[h2][r] = (uint32_t)__builtin_amdgcn_readfirstlane(ring_slot(newest_slot, H, R, h2 ? H - 5 + r : r - 1)) * (uint32_t)nb_cap * 4u;
+  // The raw rows of a pass are asked for a whole pass ahead and go straight to LDS: of the six pieces of 64 columns
+  // wave w brings piece w of all ten rows and piece 4 + w / 2 of one half's rows (every address is clamped into the
+  // tile; what lies outside only reaches lanes that mask it).  Staged column i is history column c0 - 4 + i.
+  auto fetch_pass = [&](int inst, int c0, float* s_raw) __attribute__((always_inline)) {
+    const int n_staged = min(nb_cur - c0, pass_cols) + 8;
+    const float* hist_inst = hist + (size_t)inst * R * nb_cap;
+    if (wave * kWave < n_staged) {                         // (wave-uniform)
+      const uint32_t off = (uint32_t)min(max(c0 - 4 + wave * kWave + lane, 0), nb_cur - 1) * 4u;
+#pragma unroll
+      for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+        for (int r = 0; r < 5; ++r)
+          load_to_lds(hist_inst, off + row_off[h2][r], s_raw + (h2 * 5 + r) * kRiRawStride + wave * kWave);
+    }
+    const int k = 4 + hf;
+    if (k * kWave < n_staged) {
+      const uint32_t off = (uint32_t)min(max(c0 - 4 + k * kWave + lane, 0), nb_cur - 1) * 4u;
+#pragma unroll
+      for (int r = 0; r < 5; ++r)
+        load_to_lds(hist_inst, off + (wsub ? row_off[1][r] : row_off[0][r]), s_raw + (wsub * 5 + r) * kRiRawStride + k * kWave);
+    }
+  };
+  const int per_wg = (total + gridDim.x - 1) / gridDim.x;
+  const int g_begin = blockIdx.x * per_wg, g_end = min(total, g_begin + per_wg);
+  if (g_begin >= g_end) return;                          // (the whole workgroup: no barrier is skipped by part of it)
+  int inst = inst0 + g_begin / n_pass, c0 = (g_begin % n_pass) * pass_cols;
+  fetch_pass(inst, c0, smem);
 
   // Operand tables and per-lane constants.
   const half8* tab2 = reinterpret_cast<const half8*>(wts_global + kMfmaTableFloatOffset) + (size_t)hf * 6 * kWave;
@@ -99,125 +151,169 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
 #pragma unroll
   for (int s = 0; s < 6; ++s) A2[s] = tab2[s * kWave + lane];
   const half8 A1 = tab1[lane];
-  const float* dc = wts_global + delta_const_offset(C, C);
+  // (constants come four channels at a time: every group of four starts on 16 bytes)
+  static_assert(delta_const_offset(C, C) % 4 == 0 && (10 * C + 9 * C * C + C) % 4 == 0, "16-byte constants");
+  const float4* dc = reinterpret_cast<const float4*>(wts_global + delta_const_offset(C, C)) + hsel;
+  auto scaled = [](float4 v, float* dst) __attribute__((always_inline)) {
+    dst[0] = kAccScale * v.x; dst[1] = kAccScale * v.y; dst[2] = kAccScale * v.z; dst[3] = kAccScale * v.w;
+  };
   float16v b2init;                                       // entry v is D row 8 (v / 4) + c, c = 4 hsel + v % 4
   half4 lo1h;
-  float lo2v[12], w3v[4];
+  float lo2v[8], w3v[4];                                 // (outputs 0 and 2 share their clamps)
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int ty = hf ? inc_row_type(1, v / 4) : inc_row_type(0, v / 4);
-    b2init[v] = v < 12 ? kAccScale * dc[2 * C + ty * C + 4 * hsel + v % 4] : 0.f;
-    if (v < 12) lo2v[v] = kAccScale * dc[2 * C + (4 + ty) * C + 4 * hsel + v % 4];
+  for (int k = 0; k < 3; ++k) {
+    const int ty = k != 1 ? kRowAll : hf ? kRowBot : kRowTop;
+    float start[4];
+    scaled(dc[(2 * C + ty * C) / 4], start);
+    if (k < 2) scaled(dc[(2 * C + (4 + ty) * C) / 4], lo2v + 4 * k);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b2init[4 * k + j] = start[j];
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    lo1h[j] = (_Float16)(kAccScale * dc[C + 4 * hsel + j]);
-    w3v[j] = wts_global[10 * C + 9 * C * C + C + 4 * hsel + j];
+  for (int j = 12; j < 16; ++j) b2init[j] = 0.f;
+  {
+    float lo1[4];
+    scaled(dc[C / 4], lo1);
+    const float4 w3 = reinterpret_cast<const float4*>(wts_global + 10 * C + 9 * C * C + C)[hsel];
+    w3v[0] = w3.x; w3v[1] = w3.y; w3v[2] = w3.z; w3v[3] = w3.w;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) lo1h[j] = (_Float16)lo1[j];
   }
   float inf = INFINITY;                                  // opaque, so that med3(a, lo, inf) stays one instruction
   asm volatile("" : "+v"(inf));
   const float inv_H = 1.f / (float)H;                    // the time mean as a multiplication
   constexpr float kUnscale = 1.f / kAccScale;            // the head sums come out times 2^8 (exact to undo)
-  // Ring rows of the ten staged x rows: staged rows 0..4 of the top half are history rows -1..3, of the bottom
-  // half H-5..H-1.  (Wave-uniform pointers: they live in scalar registers.)
-  const float* row_base[2][5];
-#pragma unroll
-  for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-    for (int r = 0; r < 5; ++r)
-      row_base[h2][r] = hist_inst + (size_t)__builtin_amdgcn_readfirstlane(ring_slot(newest_slot, H, R, h2 ? H - 5 + r : r - 1)) * nb_cap;
-  float* s_raw = smem;                                   // [staged row of top half 0..4 | of bottom half 0..4][kRiRawStride]
-  uint32_t* s_x01 = reinterpret_cast<uint32_t*>(smem + kRiRawWords);   // [half][lane half][column]: (row 0 | row 1) or (row 3 | row 4)
-  uint32_t* s_x2 = s_x01 + 2 * 2 * kRiStageCols;         // [half][lane half][column]: row 2 (col - 1 | col) or (col + 1 | 1)
-  float2* s_part = reinterpret_cast<float2*>(smem + kRiRawWords + kRiStageWords);   // [half][column]: (moving, border)
-  const uint32_t* my_x01 = s_x01 + (hf * 2 + hsel) * kRiStageCols + n;
-  const uint32_t* my_x2 = s_x2 + (hf * 2 + hsel) * kRiStageCols + n;
 
-  // Passes of equal length, as few as the LDS allows.
-  const int n_pass = (b_end - b_begin + kRiPassBlocks - 1) / kRiPassBlocks;
-  const int pass_blocks = (b_end - b_begin + n_pass - 1) / n_pass;
-  // The raw rows of a pass are asked for a whole pass ahead and go straight to LDS: wave w brings pieces w and
-  // w + 4 of each of the ten rows (every address is clamped into the tile; what lies outside is masked when the
-  // rows are converted).
-  auto fetch_pass = [&](int pb) __attribute__((always_inline)) {
-    const int col0 = pb * kRiOut;
-    const int n_cols = (min(b_end, pb + pass_blocks) - pb) * kRiOut + 8;   // staged columns of that pass
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int k = wave + 4 * kk;
-      if (k < kRiRawSegs && k * kWave <= n_cols) {         // (wave-uniform; the conversion reads one column past the staged ones)
-        const uint32_t off = (uint32_t)min(max(col0 - 4 + k * kWave + lane, 0), nb_cur - 1) * 4u;
-#pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-          for (int r = 0; r < 5; ++r) load_to_lds(row_base[h2][r], off, s_raw + (h2 * 5 + r) * kRiRawStride + k * kWave);
-      }
-    }
-  };
-  fetch_pass(b_begin);
+  float2* s_part = reinterpret_cast<float2*>(smem + 2 * kRiRawWords);   // [half][column]: (moving, border)
+  uint16_t* s_list = reinterpret_cast<uint16_t*>(smem + 2 * kRiRawWords + kRiPartWords) + wave * kRiRawStride;
+  uint32_t* s_bits = reinterpret_cast<uint32_t*>(smem + 2 * kRiRawWords + kRiPartWords + 4 * kRiListWords);
+  uint32_t* s_outs = s_bits + 2 * kRiBitWords;           // the outputs of a whole pass, one bit per staged column
+  uint32_t* s_epi = s_outs + 16;                         // [half][column / 32]: the outputs of the pass at hand
+  if (tid < 2 * kRiBitWords) s_bits[tid] = 0u;           // (the words around a row stay zero)
+  if (tid < 16) s_outs[tid] = bit_range(4, 4 + pass_cols, tid);
   __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0): this wave's pieces of the first pass are in LDS
+  __syncthreads();
+
+
+  int buf = 0;
 #pragma unroll 1
-  for (int pb = b_begin; pb < b_end; pb += pass_blocks) {
-    const int pe = min(b_end, pb + pass_blocks);
-    const int col0 = pb * kRiOut;                        // first output column of the pass
-    const int col_end = min(nb_cur, pe * kRiOut);
-    // Every wave has seen its own pieces of this pass's raw rows arrive (before the loop, or before the last
-    // barrier of the pass before).
-    __syncthreads();
-    // Raw rows -> the words a lane's K slots are made of: x scaled by 2^12 and rounded to f16, zero outside the
-    // tile.  Thread tid takes staged columns tid and tid + 256.
-    {
-      constexpr int kChunks = (kRiStageCols + 255) / 256;
-#pragma unroll
-      for (int ch = 0; ch < kChunks; ++ch) {
-        const int i = ch * 256 + tid;
-        if (i < (pe - pb) * kRiOut + 8) {                  // the staged columns of this pass
-          const int c = col0 - 4 + i;
-          const float sc = (uint32_t)c < (uint32_t)nb_cur ? kXScale : 0.f;
-          const float sm = (uint32_t)(c - 1) < (uint32_t)nb_cur ? kXScale : 0.f;
-          const float sp = (uint32_t)(c + 1) < (uint32_t)nb_cur ? kXScale : 0.f;
-          const int im = max(i - 1, 0);
-#pragma unroll
-          for (int h2 = 0; h2 < 2; ++h2) {
-            const float* x = s_raw + h2 * 5 * kRiRawStride;
-            const half2v a01 = {(_Float16)(x[i] * sc), (_Float16)(x[kRiRawStride + i] * sc)};
-            const half2v a34 = {(_Float16)(x[3 * kRiRawStride + i] * sc), (_Float16)(x[4 * kRiRawStride + i] * sc)};
-            const half2v a2l = {(_Float16)(x[2 * kRiRawStride + im] * sm), (_Float16)(x[2 * kRiRawStride + i] * sc)};
-            const half2v a2r = {(_Float16)(x[2 * kRiRawStride + i + 1] * sp), (_Float16)1};
-            s_x01[(h2 * 2 + 0) * kRiStageCols + i] = __builtin_bit_cast(uint32_t, a01);
-            s_x01[(h2 * 2 + 1) * kRiStageCols + i] = __builtin_bit_cast(uint32_t, a34);
-            s_x2[(h2 * 2 + 0) * kRiStageCols + i] = __builtin_bit_cast(uint32_t, a2l);
-            s_x2[(h2 * 2 + 1) * kRiStageCols + i] = __builtin_bit_cast(uint32_t, a2r);
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // The raw rows are free again: the next pass's loads, and the state of this thread's columns, are asked for
-    // now and have the block loop to arrive in.
-    if (pb + pass_blocks < b_end) fetch_pass(pb + pass_blocks);
+  for (int left = g_end - g_begin; left > 0; --left, buf ^= 1) {
+    // (worked out again in every pass: what follows from them would otherwise sit in registers through all of it)
+    tid = tid_all;
+    asm volatile("" : "+v"(tid));
+    lane = tid & (kWave - 1);
+    const int w = lane & 15, w_half = (lane >> 4) & 1;   // the word of bits this lane works on, and its half
+    const int len = min(nb_cur - c0, pass_cols);         // output columns of the pass: staged columns 4 .. 4 + len - 1
+    const bool at_end = c0 == 0 || c0 + len == nb_cur;   // the pass holds an end of the tile
+    float* pstate_pass = pstate + ((size_t)inst * nb_cap + c0);
+    float* pred_pass = pred + ((size_t)inst * nb_cap + c0);
+    // Every wave has seen its own pieces of this pass's rows arrive before the last barrier, and is done with the
+    // pass before: the other buffer is free.  The next pass's rows and the state of this thread's columns are asked
+    // for now and have the whole pass to arrive in.
+    float* s_raw = smem + buf * kRiRawWords;
+    int inst_next = inst, c0_next = c0 + pass_cols;
+    if (c0_next >= nb_cur) { ++inst_next; c0_next = 0; }
+    if (left > 1) fetch_pass(inst_next, c0_next, smem + (buf ^ 1) * kRiRawWords);
     constexpr int kPerThread = (kRiPassCols + 255) / 256;
     float pst[kPerThread];
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) pst[i] = pstate_inst[min(col0 + tid + 256 * i, nb_cur - 1)];
+    for (int i = 0; i < kPerThread; ++i) pst[i] = pstate_pass[(uint32_t)min(tid + 256 * i, len - 1)];
 
-    // One block.  BORDER: the block reaches beyond the tile, where x is zero and y1 = 0 (d1 = lo1); the other
-    // blocks skip those selects.
-    auto block = [&](int b, auto border_tag) __attribute__((always_inline)) {
+    // One bit per staged column and half: is one of the five values other than zero.  Where one of 64 columns has such
+    // a value they are turned into what layer 1 reads, in place (a thread touches its own column only): f16 of 2^12 x,
+    // zero outside the tile, rows (0 | 1) in the place of row 0, (3 | 4) in that of row 1, (2 | 0) in that of row 2.
+    // Zeros are that already.
+#pragma unroll
+    for (int ch = 0; ch < 2; ++ch) {
+      const int seg = ch * 4 + wave;
+      if (seg < kRiRawSegs) {                            // (wave-uniform)
+        const int i = seg * kWave + lane;
+        float sc = kXScale;
+        if (at_end) sc = (uint32_t)(c0 - 4 + i) < (uint32_t)nb_cur ? kXScale : 0.f;
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) {
+          float* x = s_raw + h2 * 5 * kRiRawStride + i;
+          const float x0 = x[0], x1 = x[kRiRawStride], x2 = x[2 * kRiRawStride], x3 = x[3 * kRiRawStride], x4 = x[4 * kRiRawStride];
+          const uint32_t any = (__float_as_uint(x0) | __float_as_uint(x1) | __float_as_uint(x2) | __float_as_uint(x3) |
+                                __float_as_uint(x4)) << 1;
+          const unsigned long long m = __ballot(any != 0u && sc != 0.f);
+          if (__ballot(any != 0u) != 0ull) {             // (with -0, or a column outside the tile, too)
+            const half2v a01 = {(_Float16)(x0 * sc), (_Float16)(x1 * sc)}, a34 = {(_Float16)(x3 * sc), (_Float16)(x4 * sc)};
+            const half2v a2 = {(_Float16)(x2 * sc), (_Float16)0};
+            x[0] = __builtin_bit_cast(float, a01);
+            x[kRiRawStride] = __builtin_bit_cast(float, a34);
+            x[2 * kRiRawStride] = __builtin_bit_cast(float, a2);
+          }
+          if (lane < 2) s_bits[h2 * kRiBitWords + 2 + seg * 2 + lane] = (uint32_t)(m >> (32 * lane));
+        }
+      }
+    }
+    lds_barrier();
+    // Which columns are outputs, which are listed, and how many come before: lane w of a row of 16 lanes works on
+    // columns 32 w .. 32 w + 31, the even rows on the top half, the odd ones on the bottom half.
+    int count;
+    bool dense;                                          // every column of the pass: entry e is column 3 + e, an output but for the ends
+    {
+      const uint32_t* bits = s_bits + w_half * kRiBitWords + 2 + w;
+      const uint32_t am = bits[-1], a0 = bits[0], ap = bits[1];
+      // column i takes the bits of columns i - 2 .. i + 2
+      uint32_t out = a0 | __builtin_amdgcn_alignbit(a0, am, 31) | __builtin_amdgcn_alignbit(a0, am, 30) |
+                     __builtin_amdgcn_alignbit(ap, a0, 1) | __builtin_amdgcn_alignbit(ap, a0, 2);
+      if (at_end) {
+        out &= bit_range(4, 4 + len, w);
+        if (c0 == 0) out |= bit_range(4, 5, w);
+        if (c0 + len == nb_cur) out |= bit_range(4 + len - 1, 4 + len, w);
+      } else {
+        out &= s_outs[w];
+      }
+      const uint32_t prev = __builtin_amdgcn_update_dpp(0, out, 0x111, 0xF, 0xF, true);   // row_shr:1: word w - 1
+      const uint32_t next = __builtin_amdgcn_update_dpp(0, out, 0x101, 0xF, 0xF, true);   // row_shl:1: word w + 1
+      if (wave == 0 && lane < 32) s_epi[lane] = out;       // (read after the pass's last barrier)
+      const uint32_t listed = out | __builtin_amdgcn_alignbit(out, prev, 31) | __builtin_amdgcn_alignbit(next, out, 1);
+      const int own = __builtin_popcount(listed);
+      int incl = own;                                    // inclusive sums over each row of 16 lanes
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xF, 0xF, true);
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xF, 0xF, true);
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xF, 0xF, true);
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xF, 0xF, true);
+      const int row0 = hf * 16;                          // first lane of this wave's half
+      count = __builtin_amdgcn_readlane(incl, row0 + 15);
+      dense = count == len + 2;
+      if (!dense && count != 0) {
+#pragma unroll
+        for (int s = 0; s < kRiRawSegs; ++s) {
+          const uint32_t lo = __builtin_amdgcn_readlane(listed, row0 + 2 * s), hi = __builtin_amdgcn_readlane(listed, row0 + 2 * s + 1);
+          if ((lo | hi) == 0u) continue;
+          const uint32_t olo = __builtin_amdgcn_readlane(out, row0 + 2 * s), ohi = __builtin_amdgcn_readlane(out, row0 + 2 * s + 1);
+          const int base = __builtin_amdgcn_readlane(incl - own, row0 + 2 * s);
+          const uint32_t rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, base));
+          const uint32_t col = s * kWave + lane;
+          if (__builtin_amdgcn_inverse_ballot_w64(((unsigned long long)hi << 32) | lo))
+            s_list[rank] = (uint16_t)(__builtin_amdgcn_inverse_ballot_w64(((unsigned long long)ohi << 32) | olo) ? col | kRiIsOutput : col);
+        }
+      }
+    }
+    asm volatile("" ::: "memory");                       // a wave reads what it has just written, in order
+
+    // 32 list entries: this lane's staged column `at` (3 .. 4 + len, or, beyond the end of a dense list, anything finite
+    // to read that no output depends on).  BORDER: one of them lies beside the tile, where y1 = 0 (d1 = lo1);
+    // the others skip those selects.
+    auto piece = [&](int at, bool output, auto border_tag) __attribute__((always_inline)) {
       constexpr bool BORDER = decltype(border_tag)::value;
-      const int X0 = b * kRiOut - 2;                     // history column of lane n = 0
-      const int col = X0 + n;
-      const bool inside = !BORDER || (col >= 0 && col < nb_cur);
-      // Layer 1 operand: the K slots of this lane half (ri_slot_row / ri_slot_kw), as staged.
-      const int at = (b - pb) * kRiOut + 2;              // staged index of column X0
+      const int col = c0 - 4 + at;
+      // Layer 1 operand: the K slots of this lane half (ri_slot_row / ri_slot_kw).
+      const uint32_t* x = reinterpret_cast<const uint32_t*>(s_raw) + hf * 5 * kRiRawStride + at;
       uint4v b1;
-      b1[0] = my_x01[at - 1];
-      b1[1] = my_x01[at];
-      b1[2] = my_x01[at + 1];
-      b1[3] = my_x2[at];
+#pragma unroll
+      for (int kw = 0; kw < 3; ++kw) b1[kw] = x[hsel * kRiRawStride + kw - 1];         // rows (0 | 1), or (3 | 4)
+      const uint32_t side = x[2 * kRiRawStride + 2 * hsel - 1];                        // row 2, column - 1 or + 1
+      uint32_t mid = x[2 * kRiRawStride];
+      asm volatile("" : "+v"(mid));                      // (read by every lane: no branch around the load)
+      b1[3] = __builtin_amdgcn_perm(hsel ? 0x3c00u : mid, side, 0x05040100u);          // (side | column), or (side | 1)
       float16v acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(A1, __builtin_bit_cast(half8, b1), acc, 0, 0, 0);
       // y1 row q, channels 4 hsel .. + 3 of this lane's column: f16 of 2^8 d1
+      const bool inside = !BORDER || (col >= 0 && col < nb_cur);
       half4 y[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -252,36 +348,47 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
       for (int k = 0; k < 3; ++k) {
         float t = 0.f;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) t = fmaf(w3v[jj], __builtin_amdgcn_fmed3f(acc[4 * k + jj], lo2v[4 * k + jj], inf), t);
+        for (int jj = 0; jj < 4; ++jj) t = fmaf(w3v[jj], __builtin_amdgcn_fmed3f(acc[4 * k + jj], lo2v[4 * (k & 1) + jj], inf), t);
         p[k] = t;
       }
       // Sum the two channel halves: afterwards lanes 0..31 hold the moving row, lanes 32..63 the two border rows.
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[0]), __float_as_uint(p[1] + p[2]), false, false);
       const float total = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-      if (n >= 2 && n < 2 + kRiOut)
-        reinterpret_cast<float*>(s_part)[(hf * kRiPassCols + (b - pb) * kRiOut + n - 2) * 2 + hsel] = total;
+      if (n >= 1 && n <= kRiOut && output)
+        reinterpret_cast<float*>(s_part)[(hf * kRiPassCols + at - 4) * 2 + hsel] = total;
     };
+    // (The first and the last entry of a list that is not empty are neighbours, not outputs.)
 #pragma unroll 1
-    for (int b = pb + wsub; b < pe; b += 2) {
-      if (b == 0 || b * kRiOut + 30 > nb_cur) block(b, std::true_type{});   // (the same for the whole wave)
-      else block(b, std::false_type{});
+    for (int e0 = wsub * kRiOut; e0 + 2 < count; e0 += 2 * kRiOut) {
+      const int e = e0 + n, lo = c0 - 1 + e0;              // (lo: lowest column of a dense list's piece)
+      if (dense && lo >= 0 && lo + 31 < nb_cur) {          // (the same for the whole wave)
+        piece(3 + e, e <= len, std::false_type{});
+      } else {
+        const uint32_t entry = dense ? (uint32_t)min(3 + e, 4 + len) | (e > 0 ? kRiIsOutput : 0u) : s_list[min(e, count - 1)];
+        piece(entry & ~kRiIsOutput, e < count - 1 && (entry & kRiIsOutput), std::true_type{});
+      }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wave's pieces of the next pass are in LDS
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kPerThread; ++i) {
-      const int rel = tid + 256 * i, c = col0 + rel;
-      if (rel < kRiPassCols && c < col_end) {
-        const float2 top = s_part[rel], bot = s_part[kRiPassCols + rel];
+      const uint32_t rel = tid + 256 * i;
+      if (rel < (uint32_t)len) {
+        float2 top = s_part[rel], bot = s_part[kRiPassCols + rel];
+        const uint32_t word = (rel + 4) >> 5, bit = (rel + 4) & 31;
+        const bool has_top = (s_epi[word] >> bit) & 1u, has_bot = (s_epi[16 + word] >> bit) & 1u;
+        if (!has_top) top = make_float2(0.f, 0.f);       // (a column that is no output has no partial sums)
+        if (!has_bot) bot = make_float2(0.f, 0.f);
         float st = pst[i];
-        if (advance) {
+        if (advance && (has_top || has_bot)) {
           st = (st - top.x * kUnscale) + bot.x * kUnscale;
-          pstate_inst[c] = st;
+          pstate_pass[rel] = st;
         }
-        pred_inst[c] = (st + (top.y + bot.y) * kUnscale) * inv_H;
+        pred_pass[rel] = (st + (top.y + bot.y) * kUnscale) * inv_H;
       }
     }
-    // (the next pass writes its partials after its own first barrier, which every thread reaches after this loop)
+    inst = inst_next;
+    c0 = c0_next;
   }
 }
 

@@ -1,0 +1,90 @@
+"""Predictor on histories that are zero almost everywhere (what sparse steps push): the kernels leave out what is
+zero, so values are planted where leaving out can go wrong - ends of the tile, ends of passes, of 32- and 64-column
+words, next to and two columns from each other - and every column is checked against a float64 evaluation."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import n_weight_floats
+
+pytestmark = pytest.mark.gpu
+
+
+def _reference(hist, blob, c1, c2):
+    """(score relative to the all-zero history's, bound on an f16-operand evaluation's error), [n][nb], float64.
+    The error: x, w1, y1, b1 and w2 each carry a relative rounding of at most 2^-11 and the ReLUs are 1-Lipschitz, so it
+    is below 5 * 2^-11 times the same sums over absolute values, b1 counting wherever a value (or the tile's end) is
+    within reach; fp32 sums and f16 subnormals stay below the 1e-7 added by the caller."""
+    n, H, nb = hist.shape
+    b = torch.from_numpy(blob.astype(np.float64))
+    o = np.cumsum([0, 9 * c1, c1, 9 * c1 * c2, c2, c2, 1])
+    w1, b1, w2, b2, w3 = (b[o[i]:o[i + 1]] for i in range(5))
+    w1, w2 = w1.view(c1, 1, 3, 3), w2.view(c2, c1, 3, 3)
+    conv = torch.nn.functional.conv2d
+
+    def net(x):
+        y = torch.relu(conv(x[:, None], w1, b1, padding=1))
+        return (torch.relu(conv(y, w2, b2, padding=1)).sum(dim=2) / H * w3.view(1, -1, 1)).sum(dim=1)
+
+    p0 = net(torch.zeros((1, H, 9), dtype=torch.float64))[0, 4]
+    x = hist.double()
+    near = torch.nn.functional.max_pool2d((x != 0).double()[:, None], 3, 1, 1)
+    near[:, :, :, 0] = near[:, :, :, -1] = 1.0
+    reach = conv(x.abs()[:, None], w1.abs(), padding=1) + b1.abs().view(1, -1, 1, 1) * near
+    size = (conv(reach, w2.abs(), padding=1).sum(dim=2) / H * w3.abs().view(1, -1, 1)).sum(dim=1)
+    return net(x) - p0, 5 * 2.0 ** -11 * size
+
+
+def _sparse_row(rng, n, nb, marks):
+    """One row per instance: one to three values at marked columns, most of them different for every instance."""
+    row = np.zeros((n, nb), dtype=np.float32)
+    for i in range(n):
+        for j in range(1 + i % 3):
+            row[i, marks[(i * 7 + j * (1 + i % 5)) % len(marks)]] = rng.uniform(1e-5, 0.6)
+        if i % 11 == 0:
+            row[i] = rng.uniform(0, 1e-2, nb)             # and now and then a dense one
+    return row
+
+
+@pytest.mark.parametrize("c1,c2", [(8, 8), (16, 32)])
+@pytest.mark.parametrize("n,nb,H", [
+    (1040, 752, 8),      # more passes than the chip holds workgroups: two of 376 columns per instance
+    (1040, 377, 6),      # a column more than a pass
+    (9, 1130, 64),       # few instances: many short passes
+    (5, 5, 6), (5, 1, 7), (3, 30, 9), (3, 31, 9), (3, 33, 9), (3, 64, 9),
+])
+def test_sparse_history_every_column(n, nb, H, c1, c2):
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    if c1 == 16 and n > 100:
+        n = 130                                           # (its tiles do not depend on the number of instances)
+    b = 8
+    ctx = ap.Context(n_inst=n, g=1, head_dim=64, block=b, hist_len=H, t_cap=(nb + 3) * b, k_blocks=2, n_sink=1, n_local=1,
+                     c1=c1, c2=c2, kv_dtype="bf16")
+    R, cap = ctx.hist_slots(), ctx.nb_cap()
+    rng = np.random.default_rng(nb * 100 + H)
+    blob = (rng.standard_normal(n_weight_floats(c1, c2)) * 0.2).astype(np.float32)
+    ctx.set_weights(blob)
+    ends = [0, 1, 2, 3, nb - 4, nb - 3, nb - 2, nb - 1]
+    inner = [x for m in (28, 30, 32, 60, 62, 64, 112, 124, 128, 188, 251, 313, 342, 376, 384) for x in range(m - 5, m + 5)]
+    marks = sorted({x for x in ends + inner + list(range(0, nb, 37)) if 0 <= x < nb})
+    hist = torch.zeros((n, R, cap), device=dev)
+    row, pred, pstate = (torch.zeros((n, cap), device=dev) for _ in range(3))
+    ws = torch.zeros((max(16, ctx.workspace_bytes()),), dtype=torch.uint8, device=dev)
+    window = np.zeros((n, H, nb), dtype=np.float32)
+    n_pushed = 0
+    for step in range(H + 9):                             # the planted rows reach every place of the window and leave it
+        r = _sparse_row(rng, n, nb, marks) if step % 4 == 0 or step < 3 else np.zeros((n, nb), dtype=np.float32)
+        row[:, :nb] = torch.from_numpy(r)
+        ctx.update_history(hist, n_pushed, row)
+        n_pushed += 1
+        window = np.concatenate([window[:, 1:], r[:, None]], axis=1)
+        modes = [ap.AP_PRED_ADVANCE] if step > 0 else [ap.AP_PRED_REBASE]
+        if step in (1, H // 2, H + 8):
+            modes.append(ap.AP_PRED_REBASE)
+        ref, bound = _reference(torch.from_numpy(window), blob, c1, c2)
+        for mode in modes:
+            ctx.predict_incremental(hist, n_pushed, nb, nb, mode, pstate, pred, ws)
+            got = pred[:, :nb].cpu().double()
+            off = (got - ref).abs() - bound * (2 if mode == ap.AP_PRED_ADVANCE else 1) - 1e-7
+            assert off.max() <= 0, f"step {step} mode {mode}: {(off > 0).sum()} columns, worst {off.max():.3g} at {np.unravel_index(int(off.argmax()), off.shape)}"
