@@ -20,57 +20,102 @@ void sparse_decode_kernel(SparseArgs a) {
   sparse_decode_body<T, D, G, NW, PIECED>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
 }
 
+// Brings the partial softmax statistics of one instance - ml[part * G + h] = (maximum, sum relative to it), part < n_part -
+// to factors scale[part * G + h] = exp(m - M) / L in LDS (0 for an empty part or an empty whole).  Every value is fetched by
+// a thread of its own, all at once: a thread that walks the parts of a head waits for memory once per part.  Calibration
+// merge: 33 -> 11 us for 128 instances of 129 chunks, 10 -> 4 us for 8 of 33; sparse decode: 6.4 -> 3.8 us for 8 instances
+// of 16 splits, 12.7 -> 8.9 us for 128 of 17.  Called by every thread of the workgroup; ends with a barrier.
+template <int G>
+__device__ __forceinline__ void merge_scales(const float2* __restrict__ ml, int n_part, float* scale) {
+  __shared__ float s_ml[2 * G];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  float2 first = make_float2(-INFINITY, 0.f);            // (most merges have no more values than threads)
+  if ((int)threadIdx.x < n_part * G) first = ml[threadIdx.x];
+  // Wave h / .. of head h: lane l holds parts l, l + 64, ..  (the values are in cache by now)
+  for (int h = wave; h < G; h += kAttnWaves) {
+    float M = -INFINITY;
+    for (int p = lane; p < n_part; p += kWave) M = fmaxf(M, ml[p * G + h].x);
+    M = wave_max(M);
+    float L = 0.f;
+    for (int p = lane; p < n_part; p += kWave) {
+      const float2 v = ml[p * G + h];
+      L += v.x == -INFINITY ? 0.f : v.y * __expf(v.x - M);
+    }
+    L = wave_sum(L);
+    if (lane == 0) { s_ml[2 * h] = M; s_ml[2 * h + 1] = L > 0.f ? 1.f / L : 0.f; }
+  }
+  __syncthreads();
+  for (int o = threadIdx.x; o < n_part * G; o += kAttnThreads) {
+    const float m = o == (int)threadIdx.x ? first.x : ml[o].x;
+    const int h = o % G;
+    scale[o] = m == -INFINITY ? 0.f : __expf(m - s_ml[2 * h]) * s_ml[2 * h + 1];
+  }
+  __syncthreads();
+}
+
 // Merges the splits of one instance: global (M, L) per head, normalised output, pooled row.  The row is nb_cap
 // columns long (8K at a 128K context) and all but `cnt` of them are zero, so it is cut into chunks of
-// kCombineCols columns, one workgroup each (blockIdx.x = chunk, blockIdx.y = instance): the chunk is put together
+// kCombineCols columns, one workgroup each (blockIdx.x - 1 = chunk, blockIdx.y = instance): the chunk is put together
 // in LDS - zeros, then the values of the listed blocks that fall into it - and written out whole and coalesced.
-// Every workgroup works out the split scales for itself (n_split x G values); chunk 0 also writes the output.
+// Workgroup 0 of an instance writes the output.  Every workgroup works out the split scales for itself (n_split x G
+// values).  It is a launch of a few microseconds whose length is the chain of dependent loads, so whatever does
+// not depend on anything is asked for first.
 constexpr int kCombineCols = 1024;
 
 template <int D, int G>
 __global__ __launch_bounds__(kAttnThreads) void sparse_combine_kernel(SparseArgs a) {
   extern __shared__ __align__(16) float smem[];
-  const int inst = a.inst0 + blockIdx.y, chunk = blockIdx.x;
-  const int cnt = min(max(a.cnt[inst], 0), a.k);
+  const int inst = a.inst0 + blockIdx.y;
   float* s_scale = smem;                               // [n_split][G]  exp(m_s - M) / L
-  float* s_row = s_scale + a.n_split * G;              // [kCombineCols]
-  const int c0 = chunk * kCombineCols, c1 = min(a.nb_cap, c0 + kCombineCols);
-
-  for (int j = threadIdx.x; j < c1 - c0; j += kAttnThreads) s_row[j] = 0.f;
-  if (threadIdx.x < G) {
-    const int h = threadIdx.x;
-    const float* ml = a.part_ml + ((size_t)inst * a.n_split * G + h) * 2;
-    float M = -INFINITY;
-    for (int s = 0; s < a.n_split; ++s) M = fmaxf(M, ml[(size_t)s * G * 2]);
-    float L = 0.f;
-    for (int s = 0; s < a.n_split; ++s) {
-      const float m = ml[(size_t)s * G * 2];
-      const float sc = (m == -INFINITY) ? 0.f : __expf(m - M);
-      s_scale[s * G + h] = sc;
-      L += ml[(size_t)s * G * 2 + 1] * sc;
-    }
-    const float invL = L > 0.f ? 1.f / L : 0.f;          // an empty list gives a zero output
-    for (int s = 0; s < a.n_split; ++s) s_scale[s * G + h] *= invL;
-  }
-  __syncthreads();
-  if (chunk == 0) {
+  const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + (size_t)inst * a.n_split * G;
+  if (blockIdx.x == 0) {
+    merge_scales<G>(ml, a.n_split, s_scale);
+    const float* acc = a.part_acc + (size_t)inst * a.n_split * G * D;
     for (int o = threadIdx.x; o < G * D; o += kAttnThreads) {
       const int h = o / D;
       float v = 0.f;
-      for (int s = 0; s < a.n_split; ++s)
-        v = fmaf(a.part_acc[((size_t)inst * a.n_split + s) * G * D + o], s_scale[s * G + h], v);
+      int s = 0;
+      for (; s + 8 <= a.n_split; s += 8) {             // (eight loads on their way; added up in the order of the splits)
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = acc[(size_t)(s + i) * G * D + o];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v = fmaf(x[i], s_scale[(s + i) * G + h], v);
+      }
+      for (; s < a.n_split; ++s) v = fmaf(acc[(size_t)s * G * D + o], s_scale[s * G + h], v);
       a.out[(size_t)inst * G * D + o] = v;
     }
+    return;
   }
+  float* s_row = s_scale + a.n_split * G;              // [kCombineCols]
+  const int c0 = (blockIdx.x - 1) * kCombineCols, c1 = min(a.nb_cap, c0 + kCombineCols);
+  const int cnt = min(max(a.cnt[inst], 0), a.k);
+  // This thread's first list position, with its block maxima (a position costs a load of its index and one per head).
+  const float* bmp = a.part_bmp + (size_t)inst * G * a.k;
+  auto block_of = [&](int jb) __attribute__((always_inline)) {
+    return min(max(a.idx[(size_t)inst * a.k + jb], 0), a.nb_cur - 1);
+  };
+  int blk = -1;
+  float bm[G];
+  if ((int)threadIdx.x < cnt) {
+    blk = block_of(threadIdx.x);
+#pragma unroll
+    for (int h = 0; h < G; ++h) bm[h] = bmp[(size_t)h * a.k + threadIdx.x];
+  }
+  for (int j = threadIdx.x; j < c1 - c0; j += kAttnThreads) s_row[j] = 0.f;
+  merge_scales<G>(ml, a.n_split, s_scale);
   // pooled probability of list position jb: max over heads of (block max relative to its split) * split scale
   for (int jb = threadIdx.x; jb < cnt; jb += kAttnThreads) {
-    const int blk = min(max(a.idx[(size_t)inst * a.k + jb], 0), a.nb_cur - 1);
+    if (jb != (int)threadIdx.x) {
+      blk = block_of(jb);
+#pragma unroll
+      for (int h = 0; h < G; ++h) bm[h] = bmp[(size_t)h * a.k + jb];
+    }
     if (blk >= c0 && blk < c1) {
       const int s = jb / a.blk_per_split;
       float mx = 0.f;
 #pragma unroll
-      for (int h = 0; h < G; ++h)
-        mx = fmaxf(mx, a.part_bmp[((size_t)inst * G + h) * a.k + jb] * s_scale[s * G + h]);
+      for (int h = 0; h < G; ++h) mx = fmaxf(mx, bm[h] * s_scale[s * G + h]);
       s_row[blk - c0] = mx;                            // (a block listed twice: either of two equal values)
     }
   }
@@ -139,34 +184,33 @@ __global__ __launch_bounds__(kAttnThreads) void calibrate_kernel(CalibArgs a) {
   }
 }
 
+// Merges the chunks of one instance into the dense row, kCombineCols columns per workgroup (blockIdx.x; blockIdx.y =
+// instance); the block maxima do not wait for the scales.
 template <int G>
 __global__ __launch_bounds__(kAttnThreads) void calibrate_finish_kernel(CalibArgs a) {
   extern __shared__ __align__(16) float smem[];
-  const int inst = blockIdx.x;
+  constexpr int PER = kCombineCols / kAttnThreads;
+  const int inst = blockIdx.y, c0 = blockIdx.x * kCombineCols;
   float* s_scale = smem;                // [n_chunks][G]
-  if (threadIdx.x < G) {
-    const int h = threadIdx.x;
-    const float* ml = a.cal_ml + ((size_t)inst * a.chunk_slots * G + h) * 2;
-    float M = -INFINITY;
-    for (int c = 0; c < a.n_chunks; ++c) M = fmaxf(M, ml[(size_t)c * G * 2]);
-    float L = 0.f;
-    for (int c = 0; c < a.n_chunks; ++c) {
-      const float sc = __expf(ml[(size_t)c * G * 2] - M);
-      s_scale[c * G + h] = sc;
-      L += ml[(size_t)c * G * 2 + 1] * sc;
-    }
-    const float invL = 1.f / L;
-    for (int c = 0; c < a.n_chunks; ++c) s_scale[c * G + h] *= invL;
+  const float* bmp = a.cal_bmp + (size_t)inst * G * a.nb_cap;
+  float bm[PER][G];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = c0 + i * kAttnThreads + threadIdx.x;
+#pragma unroll
+    for (int h = 0; h < G; ++h) bm[i][h] = j < a.nb_cur ? bmp[(size_t)h * a.nb_cap + j] : 0.f;
   }
-  __syncthreads();
+  merge_scales<G>(reinterpret_cast<const float2*>(a.cal_ml) + (size_t)inst * a.chunk_slots * G, a.n_chunks, s_scale);
   float* row = a.row + (size_t)inst * a.nb_cap;
-  for (int j = threadIdx.x; j < a.nb_cap; j += kAttnThreads) {
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = c0 + i * kAttnThreads + threadIdx.x;
+    if (j >= a.nb_cap) continue;
     float mx = 0.f;
     if (j < a.nb_cur) {
       const int c = j / a.chunk_blocks;
 #pragma unroll
-      for (int h = 0; h < G; ++h)
-        mx = fmaxf(mx, a.cal_bmp[((size_t)inst * G + h) * a.nb_cap + j] * s_scale[c * G + h]);
+      for (int h = 0; h < G; ++h) mx = fmaxf(mx, bm[i][h] * s_scale[c * G + h]);
     }
     row[j] = mx;
   }
@@ -219,7 +263,7 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_split == 1) return e;
   const size_t lds2 = sizeof(float) * ((size_t)a.n_split * G + kCombineCols);
-  sparse_combine_kernel<D, G><<<dim3((a.nb_cap + kCombineCols - 1) / kCombineCols, ninst), kAttnThreads, lds2, st>>>(a);
+  sparse_combine_kernel<D, G><<<dim3(1 + (a.nb_cap + kCombineCols - 1) / kCombineCols, ninst), kAttnThreads, lds2, st>>>(a);
   return hipGetLastError();
 }
 
@@ -234,7 +278,8 @@ hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
   calibrate_kernel<T, D, G><<<dim3(a.n_units < slots ? a.n_units : slots), kAttnThreads, lds, st>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  calibrate_finish_kernel<G><<<dim3(s.n_inst), kAttnThreads, sizeof(float) * a.n_chunks * G, st>>>(a);
+  calibrate_finish_kernel<G><<<dim3((a.nb_cap + kCombineCols - 1) / kCombineCols, s.n_inst), kAttnThreads,
+                               sizeof(float) * a.n_chunks * G, st>>>(a);
   return hipGetLastError();
 }
 
