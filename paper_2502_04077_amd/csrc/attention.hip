@@ -20,6 +20,14 @@ void sparse_decode_kernel(SparseArgs a) {
   sparse_decode_body<T, D, G, NW, PIECED>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
 }
 
+// Waves per SIMD the registers are to leave room for: g d / 16 accumulators beside 16 of K and V rows each.
+template <int D, int G>
+__global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(G <= 4 ? 4 : 3)))
+void sparse_stream_kernel(SparseArgs a) {
+  extern __shared__ __align__(16) float smem[];
+  sparse_stream_body<D, G>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
+}
+
 // Brings the partial softmax statistics of one instance - ml[part * G + h] = (maximum, sum relative to it), part < n_part -
 // to factors scale[part * G + h] = exp(m - M) / L in LDS (0 for an empty part or an empty whole).  Every value is fetched by
 // a thread of its own, all at once: a thread that walks the parts of a head waits for memory once per part.  Calibration
@@ -228,8 +236,54 @@ template <class Fn> int resident_workgroups(Fn fn, int nt, size_t lds) {
   return per_cu * prop.multiProcessorCount;
 }
 
+template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, hipStream_t st) {
+  const size_t lds = sizeof(float) * ((size_t)a.n_split * G + kCombineCols);
+  sparse_combine_kernel<D, G><<<dim3(1 + (a.nb_cap + kCombineCols - 1) / kCombineCols, ninst), kAttnThreads, lds, st>>>(a);
+  return hipGetLastError();
+}
+
+// Workgroups per instance the streaming form uses, of the a.n_split that the workspace has room for.  More of them than
+// it takes to keep memory busy only add start-ups and a longer merge: 256 workgroups (one a CU) of up to 4096
+// tokens, 512 for longer lists, none shorter than two passes a wave (128 tokens), 64 to merge at most.  From 256
+// instances on one each; g = 1, whose passes have the least arithmetic to cover the start with, and 512 or more
+// instances with g = 8, three of whose workgroups fit a CU, take what the workspace has.  (Decode + merge, us, bf16, d = 128;
+// splits: time.  8 x 1024 tokens 16: 11.7, 8: 10.8, 4: 13.4; 128 x 2048 8: 31.1, 2: 29.7; 128 x 32800 17: 361, 8: 339,
+// 4: 328; 256 x 1024 4: 31.5, 1: 28.5; 700 x 1024 4: 68.9, 1: 64.2; g = 8, 640 x 2048 2: 123, 1: 127; g = 1, 300 x 1024
+// 4: 30.6, 1: 32.8.)
+int stream_splits(const SparseArgs& a, int ninst, int g) {
+  const long tokens = (long)a.k * a.b;
+  if (ninst >= 256 && (g == 1 || (g == 8 && ninst >= 512))) return a.n_split;
+  long want = (256 + ninst - 1) / ninst;
+  if (tokens > 4096 * want) want = (512 + ninst - 1) / ninst;
+  if (want > tokens / 128) want = tokens / 128;
+  if (want > 64) want = 64;
+  const long least = (g * tokens + 40959) / 40960;       // (a list's largest logits, one float per head and four tokens, in 40 KiB)
+  if (want < least) want = least;
+  return want > a.n_split ? a.n_split : want < 1 ? 1 : (int)want;
+}
+
+template <int D, int G>
+hipError_t run_stream(int ninst, SparseArgs a, hipStream_t st) {
+  int want = a.n_split > 1 ? stream_splits(a, ninst, G) : 1;
+  // (a row with so many blocks that their bits beside the list's logits exceed 64 KiB is left to the merge)
+  if (want == 1 && a.n_split > 1 && sizeof(float) * sparse_stream_lds_floats<D, G>(a.k, a.b, a.nb_cap) > 65536) want = 2;
+  a.blk_per_split = (a.k + want - 1) / want;
+  a.n_split = (a.k + a.blk_per_split - 1) / a.blk_per_split;
+  const size_t lds = sizeof(float) * sparse_stream_lds_floats<D, G>(a.blk_per_split, a.b, a.n_split == 1 ? a.nb_cap : 0);
+  sparse_stream_kernel<D, G><<<dim3(a.n_split, ninst), kAttnThreads, lds, st>>>(a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.n_split == 1) return e;
+  return run_combine<D, G>(ninst, a, st);
+}
+
 template <typename T, int D, int G>
 hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
+  // The streaming form: bf16 lists cut into splits, and whole lists with g = 8 (1024 instances 120 -> 99 us, 1700
+  // 172 -> 162; the phased form has no narrow variants for it).
+  if constexpr (std::is_same<T, bf16_t>::value && G == 8) return run_stream<D, G>(ninst, a, st);
+  else {
+  if constexpr (std::is_same<T, bf16_t>::value)
+    if (a.n_split > 1) return run_stream<D, G>(ninst, a, st);
   const int nblk_cap = (a.n_split == 1) ? a.k : a.blk_per_split;
   a.piece_blocks = nblk_cap;
   const size_t lds = sizeof(float) * sparse_lds_floats<D, G, kAttnWaves>(nblk_cap, nblk_cap, a.b, a.nb_cap);
@@ -262,9 +316,8 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   sparse_decode_kernel<T, D, G, kAttnWaves, false><<<dim3(a.n_split, ninst), kAttnThreads, lds, st>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_split == 1) return e;
-  const size_t lds2 = sizeof(float) * ((size_t)a.n_split * G + kCombineCols);
-  sparse_combine_kernel<D, G><<<dim3(1 + (a.nb_cap + kCombineCols - 1) / kCombineCols, ninst), kAttnThreads, lds2, st>>>(a);
-  return hipGetLastError();
+  return run_combine<D, G>(ninst, a, st);
+  }
 }
 
 template <typename T, int D, int G>

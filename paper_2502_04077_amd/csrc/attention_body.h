@@ -583,5 +583,364 @@ template <int D, int G, int NW> inline size_t sparse_lds_floats(int nblk_cap, in
          2 * nblk_cap + 2 * (size_t)((nb_cap + 31) / 32);
 }
 
+// f(integral_constant<int, 0>) .. f(integral_constant<int, G - 1>)
+template <int G, int H = 0, class F> __device__ __forceinline__ void for_heads(F& f) {
+  f(std::integral_constant<int, H>{});
+  if constexpr (H + 1 < G) for_heads<G, H + 1>(f);
+}
+
+// Broadcast of lane LANE of every row of 16 lanes to that row.
+template <int LANE> __device__ __forceinline__ float row_bcast(float v) { return dpp_move<0x150 + LANE>(v); }
+
+// v of this lane combined with that of the lane 16 / 32 lanes away, on register swaps.
+template <class Op> __device__ __forceinline__ float across_16(float v, Op op) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+template <class Op> __device__ __forceinline__ float across_32(float v, Op op) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+
+// LDS floats a wave stages 16 K rows in, later its output partial; and those of the query rows, padded like them.
+template <int D, int G> constexpr int wave_tile_floats() {
+  constexpr int stage = kGroupTokens * (D * 2 + kStageRowPad) / 4;
+  return stage > G * D ? stage : G * D;
+}
+template <int D, int G> constexpr int query_floats() { return G * (D * 2 + kStageRowPad) / 4; }
+// How far a logit may exceed the maximum that the running sums are relative to before they are rescaled: exp(8) = 2981
+// leaves fp32 sums their relative precision, and after the first pass hardly any pass has to touch the accumulators.
+constexpr float kRescaleAt = 8.f;
+
+// Sparse decode of instance `inst`, split `split`, by one workgroup of four waves, bf16.
+// Every wave works off 16-token passes of the list by itself, from K rows to acc += p * V, with running softmax
+// statistics (a maximum and a sum per head and per row of 16 lanes, i.e. per token slot), so that no wave waits for
+// another between the list at the start and the merge at the end: K rows of the next pass are asked for as soon as the
+// present ones are staged, V rows as soon as the present ones are used, and a wave always has some 8 KiB on its way.
+// sparse_decode_body goes through phases instead - all logits, softmax, all V - with barriers between them and the
+// probabilities of the list in LDS.  With few instances, where nothing else fills the gaps, this form is the faster one
+// (decode + merge, 1024-token lists, d = 128, g = 4: 8 instances 13.5 -> 10.0 us, 256 instances 31.8 -> 28.5 us; 640 x 2048
+// tokens, g = 8: 142 -> 126 us).  With 1024 instances and more, g <= 4, the phases win (2048 instances: 177 against 190 us;
+// 4096, g = 1: 337 against 373): on scattered blocks a stream that alternates between K and V reaches 5.85 TB/s,
+// however many waves have loads on their way, and one that stays in one of the two for a while 6.25.
+//
+// The g x d by d x 16-token contraction runs on v_mfma_f32_16x16x32_bf16 (A = 16 K rows, B = q^T repeated to 16
+// columns, fp32 accumulate).  In the operand layout lane l supplies token l % 16 and, the order of the contraction index
+// being free as long as A and B agree, dims (l / 16) d/4 .. + d/4 - 1, eight per K-step.  The result comes back as lane
+// (head = l % 16, tokens 4 (l / 16) + v), v = 0..3: a row of 16 lanes holds the logits of four tokens, which are, for
+// d = 128, the tokens whose V rows the row reads, and the probability of a head is a DPP broadcast away.
+// smem: sparse_stream_lds_floats(...) floats of LDS, 16-byte aligned.
+template <int D, int G>
+__device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst, int split, float* smem) {
+  using T = bf16_t;
+  using Ge = Geom<T, D, G>;
+  constexpr int NW = kAttnWaves;
+  constexpr int E = Ge::E, LPT = Ge::LPT, TPI = Ge::TPI, NL = Ge::NL, NT = NW * kWave, KS = D / 32;
+  constexpr int TILE = wave_tile_floats<D, G>();
+  constexpr int RS = D * 2 + kStageRowPad;               // bytes of a staged K row
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int dpart = lane % LPT, tslot = lane / LPT;
+  const int head = lane & 15, row16 = lane >> 4;         // what this lane's logits are of
+
+  const int cnt = min(max(a.cnt[inst], 0), a.k);
+  // With one workgroup per instance the whole list is local; otherwise this split's slice.
+  const bool whole_row = a.n_split == 1;
+  const int j0 = whole_row ? 0 : min(cnt, split * a.blk_per_split);
+  const int j1 = whole_row ? cnt : min(cnt, j0 + a.blk_per_split);
+  const int nblk = j1 - j0;
+  const int nblk_cap = whole_row ? a.k : a.blk_per_split;
+  const int qpb = a.b >> 2;                              // groups of four tokens per block
+
+  float* s_tile = smem + wave * TILE;                    // [waves][TILE] staged K rows, then the wave's sum of p V
+  char* s_q = reinterpret_cast<char*>(smem + NW * TILE); // [G] query rows, padded like the K rows
+  float* s_qmax = smem + NW * TILE + query_floats<D, G>();          // [G][nblk_cap * qpb] largest logit of four tokens
+  float* s_m = s_qmax + G * nblk_cap * qpb;              // [waves][G] maximum, then the factor that brings a wave's sums to the whole
+  float* s_l = s_m + NW * G;                             // [waves][G] sum relative to it
+  float* s_ml = s_l + NW * G;                            // [G][2] maximum and sum of the workgroup
+  int* s_idx = reinterpret_cast<int*>(s_ml + 2 * G);     // [nblk_cap] logical block of each position
+  int* s_phys = s_idx + nblk_cap;                        // [nblk_cap] its place in K / V
+  // For the pooled row, written whole by the workgroup that has the whole list: one bit per block (is it
+  // listed) and, per 32-block word, the number of listed blocks before it, so that a column finds its list
+  // position without a search.
+  const int nwords = whole_row ? (a.nb_cap + 31) / 32 : 0;
+  uint32_t* s_listed = reinterpret_cast<uint32_t*>(s_phys + nblk_cap);   // [nwords]
+  uint16_t* s_rank = reinterpret_cast<uint16_t*>(s_listed + nwords);     // [nwords]
+
+  if (whole_row) {
+    for (int w = threadIdx.x; w < nwords; w += NT) s_listed[w] = 0u;
+    __syncthreads();
+  }
+  for (int j = threadIdx.x; j < nblk; j += NT) {
+    const int blk = min(max(a.idx[(size_t)inst * a.k + j0 + j], 0), a.nb_cur - 1);
+    s_idx[j] = blk;
+    s_phys[j] = a.table ? min(max(a.table[(size_t)inst * a.nb_cap + blk], 0), a.n_phys - 1) : blk;
+    if (whole_row) atomicOr(&s_listed[blk >> 5], 1u << (blk & 31));
+  }
+  // The query operand stays in LDS and is read again in every pass, which is what keeps d = 128, g = 4 within 128
+  // registers.
+  const T* q_inst = static_cast<const T*>(a.q) + (size_t)inst * G * D;
+  for (int o = threadIdx.x; o < G * D / 8; o += NT)
+    *reinterpret_cast<uint4*>(s_q + (o / (D / 8)) * RS + (o % (D / 8)) * 16) = reinterpret_cast<const uint4*>(q_inst)[o];
+  __syncthreads();
+
+  // Contiguous cache: [n_inst][t_cap][d].  Paged cache: one pool [n_phys][b][d] for all instances.
+  const size_t kv_off = a.table ? 0 : (size_t)inst * a.t_cap * D;
+  const T* K_inst = static_cast<const T*>(a.K) + kv_off;
+  const T* V_inst = static_cast<const T*>(a.V) + kv_off;
+
+  const float scale = rsqrtf((float)D);
+  const int ntok = nblk * a.b, npass = (ntok + kGroupTokens - 1) / kGroupTokens;
+
+  // A pass's 16 tokens are two runs of eight, each inside one block (a block holds at least eight).  K rows: load i
+  // brings rows i TPI .. + TPI - 1 of the pass.  V rows: lane group tslot takes tokens tslot NL .. + NL - 1, load i the
+  // i-th of every group.
+  struct Pass { int row[2], off[2], last[2]; };          // wave-uniform, per run: first row of its block in the cache, its
+                                                         // place in the block, last row of the block inside the context
+  auto pass_at = [&](int ps) __attribute__((always_inline)) {
+    Pass r;
+    const int tau = ps * kGroupTokens;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (u == 0 || a.b == 8) {
+        const int jb = min((tau + 8 * u) >> a.log2b, nblk - 1);   // (the missing run of an odd list of 8-token blocks is masked)
+        const int blk = __builtin_amdgcn_readfirstlane(s_idx[jb]);
+        r.row[u] = __builtin_amdgcn_readfirstlane(s_phys[jb]) * a.b;
+        r.off[u] = tau & (a.b - 1);
+        r.last[u] = min(a.t_cur - 1 - blk * a.b, a.b - 1);
+      } else {
+        r.row[1] = r.row[0];
+        r.off[1] = r.off[0] + 8;
+        r.last[1] = r.last[0];
+      }
+    }
+    return r;
+  };
+  uint4 kw[NL], vw[NL];
+  auto load_k = [&](const Pass& r) __attribute__((always_inline)) {
+    constexpr int kPerRun = 8 / TPI;                     // loads per run of eight rows; a load is TPI whole rows
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int first = r.row[i / kPerRun] + r.off[i / kPerRun] + (i % kPerRun) * TPI;
+      kw[i] = ld_stream(K_inst + (size_t)first * D + (uint32_t)lane * E);
+    }
+  };
+  auto load_v = [&](const Pass& r) __attribute__((always_inline)) {
+    // Tokens at or beyond t_cur (the tail of the newest block) carry probability 0, but their V rows may hold
+    // anything, NaN included, and 0 * NaN is NaN: such a token reads the block's last real row instead.
+    const bool upper = tslot * NL >= 8;
+    const int row = upper ? r.row[1] : r.row[0], last = upper ? r.last[1] : r.last[0];
+    const int at = (upper ? r.off[1] - 8 : r.off[0]) + tslot * NL;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) vw[i] = ld_stream(V_inst + (size_t)(row + min(at + i, last)) * D + dpart * E);
+  };
+
+  Pass next;                                             // the pass whose rows are on their way
+  if (wave < npass) {                                    // (before the query: nothing else is on its way yet)
+    next = pass_at(wave);
+    load_k(next);
+    load_v(next);
+  }
+
+  float m = -INFINITY, l = 0.f;                          // running statistics of this lane's head and row of 16 lanes
+  float acc[G][E];
+#pragma unroll
+  for (int h = 0; h < G; ++h)
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[h][e] = 0.f;
+
+  // MORE: the wave has another pass after this one, whose rows are asked for on the way.  (Two copies of the code, so that
+  // the registers of a row have one source on the way round the loop and no copy has to wait for the load.)
+  auto pass = [&](int ps, auto more_tag) __attribute__((always_inline)) {
+    constexpr bool MORE = decltype(more_tag)::value;
+    const int tau0 = ps * kGroupTokens;
+    // Tokens of this pass that exist and lie inside the context: bit t of `live` (wave-uniform).
+    uint32_t live;
+    {
+      const int n0 = min(max(next.last[0] - next.off[0] + 1, 0), 8);
+      const int n1 = tau0 + 8 < ntok ? min(max(next.last[1] - next.off[1] + 1, 0), 8) : 0;
+      live = ((1u << n0) - 1u) | (((1u << n1) - 1u) << 8);
+    }
+    if constexpr (MORE) next = pass_at(ps + NW);
+    char* stage = reinterpret_cast<char*>(s_tile);
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      *reinterpret_cast<uint4*>(stage + (i * TPI + lane / LPT) * RS + (lane % LPT) * 16) = kw[i];
+    asm volatile("" ::: "memory");                     // a wave's LDS accesses stay in order; so must the compiler
+    if constexpr (MORE) load_k(next);
+    float4v lg = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const uint4 w = *reinterpret_cast<const uint4*>(stage + head * RS + (row16 * (D / 4) + s * 8) * 2);
+      // (columns of B beyond the g heads repeat them: their logits are not used)
+      const uint4 wq = *reinterpret_cast<const uint4*>(s_q + (head & (G - 1)) * RS + (row16 * (D / 4) + s * 8) * 2);
+      lg = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, wq), lg, 0, 0, 0);
+    }
+    asm volatile("" ::: "memory");                     // the next pass overwrites the tile read above
+    float p[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) p[v] = lg[v] * scale;
+    if (live != 0xffffu) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) p[v] = ((live >> (4 * row16 + v)) & 1u) ? p[v] : -INFINITY;
+    }
+    const float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
+    if (head < G && tau0 + 4 * row16 < ntok) s_qmax[head * (nblk * qpb) + ps * 4 + row16] = mx;
+    const bool above = head < G && mx > m + kRescaleAt;
+    if (__any(above)) {
+      const float m_new = above ? mx : m;
+      const float al = above ? __expf(m - m_new) : 1.f;      // (0 for the first maximum)
+      m = m_new;
+      l *= al;
+      auto rescale = [&](auto hc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+        const float f = row_bcast<h>(al);
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[h][e] *= f;
+      };
+      for_heads<G>(rescale);
+    }
+    const float m_ref = m == -INFINITY ? 0.f : m;          // (nothing but masked tokens so far)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) p[v] = __expf(p[v] - m_ref);
+    l += (p[0] + p[1]) + (p[2] + p[3]);
+    // acc += p V: token i of this lane's group is, of the row's four tokens, i (d = 128) or 2 (tslot % 2) + i (d = 64)
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      float vf[E];
+      unpack16(vw[i], vf, T{});
+      auto add = [&](auto hc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+        float ph = row_bcast<h>(p[i]);
+        if constexpr (NL == 2) {                       // (both broadcasts by every lane: the source must be active)
+          const float odd = row_bcast<h>(p[2 + i]);
+          ph = (tslot & 1) ? odd : ph;
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[h][e] = fmaf(ph, vf[e], acc[h][e]);
+      };
+      for_heads<G>(add);
+    }
+    if constexpr (MORE) load_v(next);
+  };
+  int ps = wave;
+#pragma unroll 1
+  for (; ps + NW < npass; ps += NW) pass(ps, std::true_type{});
+  if (ps < npass) pass(ps, std::false_type{});
+
+  // The token slots of a wave: bring them to one maximum per head, add them up, leave the wave's share in LDS.
+  const auto larger = [](float x, float y) { return fmaxf(x, y); };
+  const auto plus = [](float x, float y) { return x + y; };
+  const float mw = across_32(across_16(m, larger), larger);
+  const float sc = m == -INFINITY ? 0.f : __expf(m - mw);
+  const float lw = across_32(across_16(l * sc, plus), plus);
+  if (lane < G) { s_m[wave * G + lane] = mw; s_l[wave * G + lane] = lw; }
+  auto gather = [&](auto hc) __attribute__((always_inline)) {
+    constexpr int h = decltype(hc)::value;
+    const float f = row_bcast<h>(sc);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      float v = acc[h][e] * f;
+      if constexpr (LPT <= 8) v += dpp_move<0x128>(v);   // row_ror:8
+      acc[h][e] = across_32(across_16(v, plus), plus);
+    }
+  };
+  for_heads<G>(gather);
+  if (tslot == 0) {
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int e = 0; e < E; ++e) s_tile[h * D + dpart * E + e] = acc[h][e];
+  }
+  if (whole_row && wave == NW - 1) {                     // exclusive prefix sum of the words' bit counts
+    const int per_lane = (nwords + kWave - 1) / kWave;
+    const int w0 = lane * per_lane;
+    int mine = 0;
+    for (int i = 0; i < per_lane; ++i)
+      if (w0 + i < nwords) mine += __popc(s_listed[w0 + i]);
+    int incl = mine;                                   // inclusive prefix sum over the lanes, on DPP moves
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xF, 0xF, true);   // row_shr:1
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xF, 0xF, true);   // row_shr:2
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xF, 0xF, true);   // row_shr:4
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xF, 0xF, true);   // row_shr:8
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xA, 0xF, true);   // row_bcast:15 into rows 1 and 3
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xC, 0xF, true);   // row_bcast:31 into rows 2 and 3
+    int run = incl - mine;
+    for (int i = 0; i < per_lane; ++i)
+      if (w0 + i < nwords) { s_rank[w0 + i] = (uint16_t)run; run += __popc(s_listed[w0 + i]); }
+  }
+  __syncthreads();
+
+  // The waves: one maximum and sum per head, and the factor for each wave's share.
+  if (threadIdx.x < G) {
+    const int h = threadIdx.x;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w * G + h]);
+    float L = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float mw = s_m[w * G + h], f = mw == -INFINITY ? 0.f : __expf(mw - M);
+      L += s_l[w * G + h] * f;
+      s_m[w * G + h] = f;
+    }
+    s_ml[2 * h] = M;
+    s_ml[2 * h + 1] = L;
+  }
+  __syncthreads();
+
+  auto block_max = [&](int h, int jb) __attribute__((always_inline)) {
+    const float* qm = s_qmax + h * (nblk * qpb) + jb * qpb;
+    float mx = qm[0];
+#pragma unroll 1
+    for (int i = 1; i < qpb; ++i) mx = fmaxf(mx, qm[i]);
+    return __expf(mx - s_ml[2 * h]);                     // (a listed block has a token inside the context: M is finite)
+  };
+  if (whole_row) {
+    for (int o = threadIdx.x; o < G * D; o += NT) {
+      const int h = o / D;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v = fmaf(smem[w * TILE + o], s_m[w * G + h], v);
+      const float L = s_ml[2 * h + 1];
+      a.out[(size_t)inst * G * D + o] = L > 0.f ? v / L : 0.f;      // an empty list gives a zero output
+    }
+    // Pooled row: column j of a listed block gets the largest block maximum over the heads, the rest zero.
+    float* row = a.row + (size_t)inst * a.row_stride;
+    for (int j = threadIdx.x; j < a.nb_cap; j += NT) {
+      const uint32_t word = s_listed[j >> 5];
+      float mx = 0.f;
+      if ((word >> (j & 31)) & 1u) {
+        const int pos = min((int)s_rank[j >> 5] + __popc(word & ((1u << (j & 31)) - 1u)), nblk - 1);
+#pragma unroll
+        for (int h = 0; h < G; ++h) mx = fmaxf(mx, block_max(h, pos) / s_ml[2 * h + 1]);
+      }
+      row[j] = mx;
+    }
+  } else {
+    const size_t ps = (size_t)inst * a.n_split + split;
+    for (int o = threadIdx.x; o < G * D; o += NT) {
+      const int h = o / D;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v = fmaf(smem[w * TILE + o], s_m[w * G + h], v);
+      a.part_acc[ps * G * D + o] = v;
+    }
+    if (threadIdx.x < 2 * G) a.part_ml[ps * G * 2 + threadIdx.x] = s_ml[threadIdx.x];
+    for (int pair = threadIdx.x; pair < G * nblk; pair += NT) {
+      const int h = pair / nblk, jb = pair - h * nblk;
+      a.part_bmp[((size_t)inst * G + h) * a.k + j0 + jb] = block_max(h, jb);
+    }
+  }
+}
+
+// LDS floats sparse_stream_body needs for a list of up to nblk_cap blocks of b tokens; nb_cap: blocks of the pooled row
+// where the workgroup writes it, else 0.
+template <int D, int G> inline size_t sparse_stream_lds_floats(int nblk_cap, int b, int nb_cap) {
+  const size_t words = (size_t)((nb_cap + 31) / 32);
+  return (size_t)kAttnWaves * wave_tile_floats<D, G>() + query_floats<D, G>() + (size_t)G * nblk_cap * (b / 4) +
+         2 * kAttnWaves * G + 2 * G + 2 * nblk_cap + words + (words + 1) / 2;
+}
+
 }  // namespace
 }  // namespace ap
