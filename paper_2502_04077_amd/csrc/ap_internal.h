@@ -15,7 +15,7 @@ constexpr int kAttnWaves = kAttnThreads / kWave;
 constexpr int kNarrowPieceTokens = 512;       // tokens whose probabilities a two- or one-wave sparse-decode workgroup holds in LDS at a time
 constexpr int kMaxHist = 256;                 // longest history ap_create accepts
 constexpr int kGroupTokens = 16;              // tokens one wave covers per load group (4 x dwordx4 loads)
-constexpr int kCalibChunkTokens = 1024;       // tokens per calibration workgroup
+constexpr int kCalibChunkTokens = 1024;       // tokens per calibration chunk, fp32 (bf16: Shape::calib_chunk_tokens)
 
 // Device-side layout of the predictor weights (all fp32), re-packed by ap_set_weights so that the
 // weights one inner loop iteration needs are contiguous:
@@ -37,9 +37,10 @@ struct Shape {
   int predictor_mfma; // incremental predictor on f16 MFMA (8/8 and 16/32 channels)
   int n_split;        // workgroups per instance in sparse decode
   Occupancy* occ;     // owned by the context, never null
-  int calib_chunks;   // max workgroups per instance in calibrate
+  int calib_chunk_tokens, calib_chunks;   // calibrate: tokens that leave one (maximum, sum); most such chunks per instance
   const int32_t* table;  // device block table of a paged K/V cache [n_inst][nb_cap], or null (caller-owned)
   int n_phys;            // physical blocks in the pool
+  bool k_on_host;        // launch_calibrate: K is pinned host memory
 };
 
 // Difference form of the predictor.  With an all-zero history the first layer gives c[ci] = relu(b1[ci]) at every

@@ -53,6 +53,18 @@ static int choose_split(const Shape& s) {
   return (s.k + per - 1) / per;
 }
 
+// Tokens of a calibration unit (and of the chunks the merge sees): 1024, or in bf16 512 or 256 where that leaves the chip
+// without a workgroup for every place it has (8 instances at 32K: 1032 units of 256 tokens instead of 264 of 1024), unless
+// the merge would have more than 60000 bytes of factors.  At least four blocks, one per wave.
+static int choose_calib_chunk(const Shape& s) {
+  int tokens = kCalibChunkTokens;
+  if (s.kv_dtype != AP_BF16) return tokens;
+  while (tokens > 256 && (size_t)s.n_inst * s.t_cap / tokens < 1024 &&
+         (2 * (size_t)s.t_cap / tokens + 2) * s.g * sizeof(float) <= 60000)
+    tokens /= 2;
+  return tokens;
+}
+
 }  // namespace ap
 
 using ap::Shape;
@@ -100,11 +112,16 @@ int ap_create(const ap_config* c, ap_ctx** out) {
     const size_t comb = (size_t)s.n_split * s.g + 1024;     // (sparse_combine_kernel: scales + a chunk of the row)
     if (attn * sizeof(float) > 65536 || comb * sizeof(float) > 65536) { delete ctx; return AP_ERR_UNSUPPORTED; }
   }
-  const int chunk_blocks = ap::kCalibChunkTokens / s.b;
-  s.calib_chunks = (s.nb_cap + chunk_blocks - 1) / chunk_blocks;
-  if ((size_t)s.calib_chunks * s.g * sizeof(float) > 60000) { delete ctx; return AP_ERR_UNSUPPORTED; }
+  {
+    const int chunk_blocks = ap::kCalibChunkTokens / s.b;
+    const size_t chunks = (s.nb_cap + chunk_blocks - 1) / chunk_blocks;
+    if (chunks * s.g * sizeof(float) > 60000) { delete ctx; return AP_ERR_UNSUPPORTED; }
+  }
+  s.calib_chunk_tokens = ap::choose_calib_chunk(s);
+  s.calib_chunks = (s.nb_cap + s.calib_chunk_tokens / s.b - 1) / (s.calib_chunk_tokens / s.b);
   s.table = nullptr;
   s.n_phys = 0;
+  s.k_on_host = false;
   ctx->dweights = nullptr;
   ctx->have_weights = false;
   ctx->score_offset = 0.0;
@@ -456,13 +473,14 @@ int ap_sparse_decode_noalloc(ap_ctx* ctx, const void* q, const void* K, const vo
 // A pointer a kernel may read: device memory, or host memory that is pinned and mapped.  Pageable host memory
 // would fault the GPU, so it is refused here.  The runtime is asked on every call: an answer remembered from an
 // earlier call could outlive the buffer it was given for.
-static int check_device_readable(const void* p) {
+static int check_device_readable(const void* p, bool* on_host = nullptr) {
   hipPointerAttribute_t a;
   if (hipPointerGetAttributes(&a, p) != hipSuccess) {
     (void)hipGetLastError();
     return AP_ERR_ARG;
   }
   const bool ok = a.type == hipMemoryTypeHost || a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged;
+  if (on_host != nullptr) *on_host = a.type == hipMemoryTypeHost;
   return ok ? AP_OK : AP_ERR_ARG;
 }
 
@@ -471,8 +489,11 @@ int ap_calibrate(ap_ctx* ctx, const void* q, const void* K, int32_t t_cur, float
   AP_REQUIRE_PTR(q); AP_REQUIRE_PTR(K); AP_REQUIRE_PTR(row); AP_REQUIRE_PTR(ws);
   const Shape& s = ctx->s;
   if (t_cur < 1 || t_cur > s.t_cap) return AP_ERR_RANGE;
-  if (check_device_readable(K) != AP_OK) return AP_ERR_ARG;
-  hipError_t e = ap::launch_calibrate(s, q, K, t_cur, row, static_cast<float*>(ws), static_cast<hipStream_t>(stream));
+  bool on_host = false;
+  if (check_device_readable(K, &on_host) != AP_OK) return AP_ERR_ARG;
+  Shape sk = s;
+  sk.k_on_host = on_host;
+  hipError_t e = ap::launch_calibrate(sk, q, K, t_cur, row, static_cast<float*>(ws), static_cast<hipStream_t>(stream));
   return e == hipSuccess ? AP_OK : AP_ERR_HIP;
 }
 
@@ -618,7 +639,8 @@ int ap_offload_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, c
   if (!ctx->have_weights || !ctx->have_events) return AP_ERR_STATE;      // ap_offload_begin comes first
   if (pred_mode != AP_PRED_REBASE && pred_mode != AP_PRED_ADVANCE) return AP_ERR_ARG;
   if (n_pushed < 0 || t_cur < 1 || t_cur > s.t_cap) return AP_ERR_RANGE;
-  if (check_device_readable(K_src) != AP_OK || check_device_readable(V_src) != AP_OK) return AP_ERR_ARG;
+  bool on_host = false;
+  if (check_device_readable(K_src, &on_host) != AP_OK || check_device_readable(V_src) != AP_OK) return AP_ERR_ARG;
   hipStream_t cs = static_cast<hipStream_t>(compute_stream), ps = static_cast<hipStream_t>(copy_stream);
   if (hipStreamWaitEvent(cs, ctx->ev_staged, 0) != hipSuccess) return AP_ERR_HIP;
   if (ap::launch_append_row(s, k_new, v_new, t_cur - 1, block_table, state, pool_K, pool_V, cs) != hipSuccess)
@@ -633,6 +655,7 @@ int ap_offload_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, c
   if (calibrate) {
     Shape flat = s;                      // the dense pass reads the full cache where it lives
     flat.table = nullptr;
+    flat.k_on_host = on_host;
     if (ap::launch_calibrate(flat, q, K_src, t_cur, row, static_cast<float*>(ws), cs) != hipSuccess) return AP_ERR_HIP;
     if (ap::launch_push_row(s, hist, (int)(n_pushed % s.R), row, cs) != hipSuccess) return AP_ERR_HIP;
   }

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_combine_kernel(SparseArgs
 struct CalibArgs {
   const void* q; const void* K;
   float* row; float* cal_ml; float* cal_bmp;
-  int* counter;                   // next (instance, chunk) unit to hand out; zero at launch
+  int* counter;                   // next unit to hand out, zero at launch; null: every workgroup has one unit
   int n_units;                    // n_inst * n_chunks
   int t_cap, nb_cap, b, log2b, t_cur, nb_cur, chunk_blocks, n_chunks, chunk_slots;
   const int32_t* table;
@@ -147,9 +147,10 @@ __global__ void zero_counter_kernel(int* counter) { *counter = 0; }
 // Workgroups are dealt to the XCDs in turn, and the XCDs do not stream equally fast (in the sparse-decode kernel the
 // slowest ends 12 % after the mean): a launch of one workgroup per chunk ends with its slowest XCD.  So the
 // grid is what the chip holds at once, and every workgroup takes (instance, chunk) units off a counter until
-// none is left; a unit is 1024 tokens, 30-40 us of streaming.
-template <typename T, int D, int G>
-__global__ __launch_bounds__(kAttnThreads) void calibrate_kernel(CalibArgs a) {
+// none is left; a unit is 1024 tokens, 30-40 us of streaming.  (fp32)
+template <int D, int G>
+__global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a) {
+  using T = float;
   extern __shared__ __align__(16) float smem[];
   __shared__ int s_unit;
   for (;;) {
@@ -167,16 +168,14 @@ __global__ __launch_bounds__(kAttnThreads) void calibrate_kernel(CalibArgs a) {
     float* s_m = s_bmp + G * a.chunk_blocks;
     float* s_l = s_m + G;
     int* s_phys = reinterpret_cast<int*>(s_l + G);   // [chunk_blocks] place of each block of the chunk in K
-    float* s_stage = smem + (((reinterpret_cast<float*>(s_phys + a.chunk_blocks) - smem) + 3) & ~3);
 
     for (int j = threadIdx.x; j < nblk; j += kAttnThreads)
       s_phys[j] = a.table ? min(max(a.table[(size_t)inst * a.nb_cap + c0 + j], 0), a.n_phys - 1) : c0 + j;
     __syncthreads();
     const T* q_inst = static_cast<const T*>(a.q) + (size_t)inst * G * D;
     const T* K_inst = static_cast<const T*>(a.K) + (a.table ? 0 : (size_t)inst * a.t_cap * D);
-    constexpr int kStage = std::is_same<T, bf16_t>::value ? kGroupTokens : 0;
-    qk_logits<T, D, G, kStage>(q_inst, K_inst, a.b, a.log2b, a.t_cur, ntok, [&](int jb) { return c0 + jb; },
-                       [&](int jb) { return s_phys[jb]; }, s_p, ld, s_stage);
+    qk_logits<T, D, G, 0>(q_inst, K_inst, a.b, a.log2b, a.t_cur, ntok, [&](int jb) { return c0 + jb; },
+                         [&](int jb) { return s_phys[jb]; }, s_p, ld, nullptr);
     __syncthreads();
     softmax_stats<G>(s_p, ld, ntok, a.b, nblk, s_m, s_l, s_bmp);
     for (int pair = threadIdx.x; pair < G * nblk; pair += kAttnThreads) {
@@ -189,6 +188,181 @@ __global__ __launch_bounds__(kAttnThreads) void calibrate_kernel(CalibArgs a) {
       ml[1] = s_l[threadIdx.x];
     }
     __syncthreads();                                     // the next unit overwrites s_unit and the tiles
+  }
+}
+
+// The same for bf16, streaming: the four waves of a workgroup take 16-token passes of a unit in turn (whole blocks, where a
+// block is longer) - so that together they read consecutive memory, which streams better than four places at once -
+// with the K rows of a wave's next pass, of the next unit's first one too, on their way while it works on the present one
+// (logits on MFMA as in sparse_stream_body; no probabilities are kept, one largest logit per four tokens goes to LDS for
+// the block maxima).  The waves meet once per unit, to bring their maxima and sums together and to hear the id of the unit
+// after the next.  A launch with no more units than the chip holds workgroups gives each its own and needs no counter.
+// Measured with the merge, against the phased form (all logits of a unit, then softmax, barriers between; four workgroups
+// a CU, first units off the counter too): 8 instances at 32K 31.8 -> 17.2 us (units of 256 tokens instead of 1024, no
+// launch to clear the counter, the merge), 64 at 50K 157 -> 144, 256 at 50K 535 -> 520 (6.3 TB/s), 128 at 128K 723 -> 685,
+// 1024 at 32K 1379 -> 1352, 256 at 50K with g = 1 521 -> 500.
+struct CalibUnit { int inst, chunk, nblk, c0; };
+
+template <int D, int G>
+__global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void calibrate_stream_kernel(CalibArgs a) {
+  using T = bf16_t;
+  using Ge = Geom<T, D, G>;
+  constexpr int NW = kAttnWaves, E = Ge::E, LPT = Ge::LPT, TPI = Ge::TPI, NL = Ge::NL, KS = D / 32;
+  constexpr int RS = D * 2 + kStageRowPad, TILE = kGroupTokens * RS, QROWS = G * RS;
+  extern __shared__ __align__(16) char smem_c[];
+  __shared__ int s_next[2];
+  __shared__ float s_ml[2][NW][2 * G];                           // [unit parity][wave][maxima | sums]
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int head = lane & 15, row16 = lane >> 4;
+  const int log2gran = max(a.log2b, 4);                          // tokens a wave takes at a time: a pass, or a whole block
+  const int qpb = a.b >> 2, quads = (a.chunk_blocks * qpb + 4 * NW - 1) / NW;   // groups of four tokens: per block, per wave (at most)
+  char* stage = smem_c + wave * TILE;
+  char* s_q = smem_c + NW * TILE + wave * QROWS;                 // (a wave may be a unit ahead, in another instance)
+  float* s_qmax = reinterpret_cast<float*>(smem_c + NW * (TILE + QROWS)) + wave * G * quads;   // [G][quads]
+
+  auto unit_of = [&](int unit) __attribute__((always_inline)) {
+    CalibUnit u;
+    u.inst = unit / a.n_chunks;
+    u.chunk = unit - u.inst * a.n_chunks;
+    u.c0 = u.chunk * a.chunk_blocks;
+    u.nblk = min(a.nb_cur - u.c0, a.chunk_blocks);
+    return u;
+  };
+  // Passes of this wave in a unit, and the token of the unit that one starts at.
+  auto passes = [&](const CalibUnit& u) __attribute__((always_inline)) {
+    const int grains = (u.nblk * a.b + (1 << log2gran) - 1) >> log2gran;
+    return grains > wave ? ((grains - wave + NW - 1) / NW) << (log2gran - 4) : 0;
+  };
+  auto token_of = [&](int ps) __attribute__((always_inline)) {
+    const int per = log2gran - 4;
+    return ((((ps >> per) * NW + wave) << per) + (ps & ((1 << per) - 1))) * kGroupTokens;
+  };
+  // Where the blocks of a unit lie in K: themselves, or for a paged cache block jb < 64 in lane jb.
+  auto place_of = [&](const CalibUnit& u, int jb) __attribute__((always_inline)) {
+    return min(max(a.table[(size_t)u.inst * a.nb_cap + min(u.c0 + jb, a.nb_cur - 1)], 0), a.n_phys - 1);
+  };
+  auto places = [&](const CalibUnit& u) __attribute__((always_inline)) { return a.table ? place_of(u, lane) : 0; };
+  auto lookup = [&](const CalibUnit& u, int place, int jb) __attribute__((always_inline)) {
+    if (!a.table) return u.c0 + jb;
+    return jb < kWave ? __builtin_amdgcn_readlane(place, jb) : __builtin_amdgcn_readfirstlane(place_of(u, jb));
+  };
+  uint4 kw[NL];
+  // Rows of a wave's pass ps: two runs of eight rows, each inside one block.  (A wave without a pass reads a valid row.)
+  auto load_k = [&](const CalibUnit& u, int place, int ps) __attribute__((always_inline)) {
+    const T* K_inst = static_cast<const T*>(a.K) + (a.table ? 0 : (size_t)u.inst * a.t_cap * D);
+    constexpr int kPerRun = 8 / TPI;
+    const int tau = token_of(ps), last = u.nblk - 1;
+    const int row0 = lookup(u, place, min(tau >> a.log2b, last)) * a.b + (tau & (a.b - 1));
+    const int row1 = a.b > 8 ? row0 + 8 : lookup(u, place, min((tau + 8) >> a.log2b, last)) * a.b;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int first = (i < kPerRun ? row0 : row1) + (i % kPerRun) * TPI;
+      kw[i] = ld_stream(K_inst + (size_t)first * D + (uint32_t)lane * E);
+    }
+  };
+
+  // The first two units of a workgroup are fixed, the others come off the counter: a thousand workgroups that all ask for
+  // their first unit wait 13 us for the last answer (and 40 us where each asks for three).
+  const bool handed_out = a.counter != nullptr;
+  const int unit = blockIdx.x;
+  if (threadIdx.x == 0) { s_next[0] = unit; s_next[1] = unit + (int)gridDim.x; }
+  __syncthreads();
+  if (unit >= a.n_units) return;                         // (the whole workgroup)
+  CalibUnit u = unit_of(unit);
+  int place = places(u);
+  load_k(u, place, 0);
+  int q_inst = -1;
+  const float scale = rsqrtf((float)D);
+
+#pragma unroll 1
+  for (int round = 0;; ++round) {
+    // The next unit's id was written before the last barrier; the one after it is asked for now.
+    int next = a.n_units;
+    if (handed_out) next = __builtin_amdgcn_readfirstlane(s_next[(round + 1) & 1]);
+    int asked = 0;
+    if (handed_out && threadIdx.x == 0) asked = 2 * (int)gridDim.x + atomicAdd(a.counter, 1);
+    const bool more = next < a.n_units;
+    const CalibUnit v = more ? unit_of(next) : u;
+    const int place_v = more ? places(v) : place;
+    if (u.inst != q_inst) {
+      const T* q = static_cast<const T*>(a.q) + (size_t)u.inst * G * D;
+      for (int o = lane; o < G * D / 8; o += kWave)
+        *reinterpret_cast<uint4*>(s_q + (o / (D / 8)) * RS + (o % (D / 8)) * 16) = reinterpret_cast<const uint4*>(q)[o];
+      q_inst = u.inst;
+      asm volatile("" ::: "memory");                     // a wave's LDS accesses stay in order; so must the compiler
+    }
+    const int npass = passes(u), n_valid = min(a.t_cur - u.c0 * a.b, u.nblk * a.b);    // tokens of the unit inside the context
+    float m = -INFINITY, l = 0.f;
+#pragma unroll 1
+    for (int ps = 0; ps < max(npass, 1); ++ps) {         // (a wave without a pass hands its loads on)
+#pragma unroll
+      for (int i = 0; i < NL; ++i)
+        *reinterpret_cast<uint4*>(stage + (i * TPI + lane / LPT) * RS + (lane % LPT) * 16) = kw[i];
+      asm volatile("" ::: "memory");
+      {
+        const bool inside = ps + 1 < npass;              // (one load site: the rows have one source on the way round)
+        const CalibUnit w = inside ? u : v;
+        load_k(w, inside ? place : place_v, inside ? ps + 1 : 0);
+      }
+      float4v lg = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const uint4 wk = *reinterpret_cast<const uint4*>(stage + head * RS + (row16 * (D / 4) + s * 8) * 2);
+        const uint4 wq = *reinterpret_cast<const uint4*>(s_q + (head & (G - 1)) * RS + (row16 * (D / 4) + s * 8) * 2);
+        lg = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wk), __builtin_bit_cast(bf16x8, wq), lg, 0, 0, 0);
+      }
+      asm volatile("" ::: "memory");                     // the next pass overwrites the tile read above
+      const int n_in = ps < npass ? n_valid - token_of(ps) - 4 * row16 : 0;
+      float p[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = i < n_in ? lg[i] * scale : -INFINITY;
+      const float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
+      if (head < G && ps < npass) s_qmax[head * quads + ps * 4 + row16] = mx;
+      const float m_new = fmaxf(m, mx), m_ref = m_new == -INFINITY ? 0.f : m_new;      // (nothing but masked tokens so far)
+      l = l * __expf(m - m_ref) + ((__expf(p[0] - m_ref) + __expf(p[1] - m_ref)) + (__expf(p[2] - m_ref) + __expf(p[3] - m_ref)));
+      m = m_new;
+    }
+    const auto larger = [](float x, float y) { return fmaxf(x, y); };
+    const auto plus = [](float x, float y) { return x + y; };
+    const float mw = across_32(across_16(m, larger), larger);
+    const float lw = across_32(across_16(m == -INFINITY ? 0.f : l * __expf(m - mw), plus), plus);
+    float (*ml)[2 * G] = s_ml[round & 1];
+    if (lane < G) { ml[wave][lane] = mw; ml[wave][G + lane] = lw; }
+    if (threadIdx.x == 0) s_next[round & 1] = asked;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (not __syncthreads(): that would wait for the K rows on their way)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    // The unit's maximum and sum, of head lane % G; block maxima relative to that maximum.
+    {
+      const int h = lane & (G - 1);
+      float M = -INFINITY, L = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) M = fmaxf(M, ml[w][h]);             // (a unit has a token inside the context)
+#pragma unroll
+      for (int w = 0; w < NW; ++w) L += ml[w][G + h] * __expf(ml[w][h] - M);
+      if (wave == 0 && lane < G) {
+        float* to = a.cal_ml + (((size_t)u.inst * a.chunk_slots + u.chunk) * G + lane) * 2;
+        to[0] = M;
+        to[1] = L;
+      }
+      // This wave's blocks: head lane % G, block lane / G and on (one column of a head after the other by neighbouring lanes)
+      const int per_grain = 1 << (log2gran - a.log2b);
+      const int mine = (npass >> (log2gran - 4)) * per_grain;
+      for (int i = lane / G; i < mine; i += kWave / G) {
+        const int jb = ((i / per_grain) * NW + wave) * per_grain + i % per_grain;
+        const float* qm = s_qmax + h * quads + i * qpb;
+        float mx = qm[0];
+#pragma unroll 1
+        for (int k = 1; k < qpb; ++k) mx = fmaxf(mx, qm[k]);
+        if (jb < u.nblk) a.cal_bmp[((size_t)u.inst * G + h) * a.nb_cap + u.c0 + jb] = __expf(mx - M);
+      }
+      asm volatile("" ::: "memory");                     // the next unit overwrites what was read
+    }
+    if (!more) break;                                    // (the same for every wave)
+    u = v;
+    place = place_v;
   }
 }
 
@@ -322,13 +496,33 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
 
 template <typename T, int D, int G>
 hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
-  const size_t stage = std::is_same<T, bf16_t>::value ? 4 + k_stage_floats<D>() : 0;     // + alignment slack
-  const size_t lds = sizeof(float) * ((size_t)G * a.chunk_blocks * a.b + G * a.chunk_blocks + 2 * G + a.chunk_blocks + stage);
-  if (s.occ->calib_slots < 0) s.occ->calib_slots = resident_workgroups(calibrate_kernel<T, D, G>, kAttnThreads, lds);
-  a.n_units = a.n_chunks * s.n_inst;
-  const int slots = s.occ->calib_slots > 0 ? s.occ->calib_slots : 2048;
-  zero_counter_kernel<<<1, 1, 0, st>>>(a.counter);
-  calibrate_kernel<T, D, G><<<dim3(a.n_units < slots ? a.n_units : slots), kAttnThreads, lds, st>>>(a);
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    const size_t quads = (a.chunk_blocks * (a.b / 4) + 4 * kAttnWaves - 1) / kAttnWaves;
+    const size_t lds = (size_t)kAttnWaves * ((kGroupTokens + G) * (D * 2 + kStageRowPad) + sizeof(float) * G * quads);
+    if (s.occ->calib_slots < 0) s.occ->calib_slots = resident_workgroups(calibrate_stream_kernel<D, G>, kAttnThreads, lds);
+    a.n_units = a.n_chunks * s.n_inst;
+    // As many units as fit at once: one workgroup each, no counter.  More: two workgroups a CU take them off the counter.
+    // Eight waves a CU keep memory busy, and more of them only spread the reads over more places (256 instances at
+    // 50K, us: six workgroups a CU 547, four 534, three 528, two 520, one 697).
+    int grid = a.n_units;
+    // Over PCIe 16 workgroups fill the link, and a thousand places at once cost it 15 % (8 instances at 32K, 67 MB, us: 16
+    // workgroups 1178, 64 1190, 256 1272, 512 1358).
+    const int most = s.k_on_host ? 16 : 512;
+    if (a.n_units <= (s.k_on_host ? most : s.occ->calib_slots)) {
+      a.counter = nullptr;
+    } else {
+      if (grid > most) grid = most;
+      zero_counter_kernel<<<1, 1, 0, st>>>(a.counter);
+    }
+    calibrate_stream_kernel<D, G><<<dim3(grid), kAttnThreads, lds, st>>>(a);
+  } else {
+    const size_t lds = sizeof(float) * ((size_t)G * a.chunk_blocks * a.b + G * a.chunk_blocks + 2 * G + a.chunk_blocks);
+    if (s.occ->calib_slots < 0) s.occ->calib_slots = resident_workgroups(calibrate_f32_kernel<D, G>, kAttnThreads, lds);
+    const int slots = s.occ->calib_slots > 0 ? s.occ->calib_slots : 2048;
+    a.n_units = a.n_chunks * s.n_inst;
+    zero_counter_kernel<<<1, 1, 0, st>>>(a.counter);
+    calibrate_f32_kernel<D, G><<<dim3(a.n_units < slots ? a.n_units : slots), kAttnThreads, lds, st>>>(a);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   calibrate_finish_kernel<G><<<dim3((a.nb_cap + kCombineCols - 1) / kCombineCols, s.n_inst), kAttnThreads,
@@ -402,7 +596,8 @@ hipError_t launch_calibrate(const Shape& s, const void* q, const void* K, int t_
   a.counter = reinterpret_cast<int*>(ws + wl.counters);
   a.t_cap = s.t_cap; a.nb_cap = s.nb_cap; a.b = s.b; a.log2b = ilog2(s.b); a.t_cur = t_cur;
   a.nb_cur = (t_cur + s.b - 1) / s.b;
-  a.chunk_blocks = kCalibChunkTokens / s.b;
+  a.chunk_blocks = s.calib_chunk_tokens / s.b;
+  a.n_units = 0;
   a.n_chunks = (a.nb_cur + a.chunk_blocks - 1) / a.chunk_blocks;
   a.chunk_slots = s.calib_chunks;
   a.table = s.table; a.n_phys = s.n_phys;

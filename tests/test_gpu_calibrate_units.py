@@ -1,0 +1,45 @@
+"""Dense calibration where its units and passes end: contexts a token short of or beyond a pass, a unit of 256, 512 or 1024
+tokens, blocks longer than a pass, more units than workgroups (handed out by a counter), paged caches, against float64.
+Tolerance: fp32 logits of bf16 products (2^-24 sqrt(128) x a few relative to the logit, which is below 16 here) and fp32 sums
+of up to 40000 exponentials: 2e-5 of the row's largest value."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,g,d,b,t,paged", [
+    (1, 4, 128, 16, 1, False), (1, 4, 128, 8, 15, False), (2, 1, 64, 8, 257, True), (3, 8, 128, 32, 255, False),
+    (2, 2, 64, 64, 1025, True), (1, 4, 128, 16, 4097, False), (33, 4, 128, 16, 32001, False), (70, 2, 128, 8, 16385, True),
+    (2000, 4, 64, 16, 1030, False), (1600, 1, 128, 64, 2049, True), (5, 8, 64, 16, 40000, False),
+])
+def test_calibrate_vs_float64(n, g, d, b, t, paged):
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    nb = -(-t // b)
+    cap = nb + 2
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=b, hist_len=8, t_cap=cap * b, k_blocks=1, n_sink=0, n_local=0, c1=4, c2=4,
+                     kv_dtype="bf16")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n + t)
+    K = torch.randn((n, cap * b, d), generator=gen, device=dev).to(torch.bfloat16)
+    q = (2 * torch.randn((n, g, d), generator=gen, device=dev)).to(torch.bfloat16)
+    K[:, t:] = float("nan")
+    Ka = K
+    if paged:
+        table = torch.randperm(n * cap, generator=gen, device=dev, dtype=torch.int32).view(n, cap)
+        Ka = torch.empty((n * cap, b, d), dtype=K.dtype, device=dev)
+        Ka[table.view(-1).long()] = K.view(-1, b, d)
+        ctx.set_block_table(table, n * cap)
+    ws = torch.full((max(16, ctx.workspace_bytes()),), 255, dtype=torch.uint8, device=dev)
+    for again in range(2):
+        row = torch.full((n, cap), 7.0, device=dev)
+        ctx.calibrate(q, Ka, t, row, ws)
+        for i in sorted({0, 1, n // 2, n - 1} & set(range(n))):
+            p = torch.softmax(q[i].double() @ K[i, :t].double().T.contiguous() / math.sqrt(d), dim=1)
+            ref = torch.zeros((g, cap * b), dtype=torch.float64, device=dev)
+            ref[:, :t] = p
+            ref = ref.view(g, cap, b).amax(dim=(0, 2))
+            assert (row[i].double() - ref).abs().max() <= 2e-5 * ref.max(), (i, again)
