@@ -439,11 +439,15 @@ int stream_splits(const SparseArgs& a, int ninst, int g) {
 template <int D, int G>
 hipError_t run_stream(int ninst, SparseArgs a, hipStream_t st) {
   int want = a.n_split > 1 ? stream_splits(a, ninst, G) : 1;
-  // (a row with so many blocks that their bits beside the list's logits exceed 64 KiB is left to the merge)
-  if (want == 1 && a.n_split > 1 && sizeof(float) * sparse_stream_lds_floats<D, G>(a.k, a.b, a.nb_cap) > 65536) want = 2;
+  // (Lists of so many blocks, or rows with so many, that their entries beside the logits exceed 64 KiB take more splits; with
+  // those the workspace is laid out for they fit.)
+  auto lds_of = [&](int splits) {
+    return sizeof(float) * sparse_stream_lds_floats<D, G>((a.k + splits - 1) / splits, a.b, splits == 1 ? a.nb_cap : 0);
+  };
+  while (want < a.n_split && lds_of(want) > 65536) ++want;
   a.blk_per_split = (a.k + want - 1) / want;
   a.n_split = (a.k + a.blk_per_split - 1) / a.blk_per_split;
-  const size_t lds = sizeof(float) * sparse_stream_lds_floats<D, G>(a.blk_per_split, a.b, a.n_split == 1 ? a.nb_cap : 0);
+  const size_t lds = lds_of(want);
   sparse_stream_kernel<D, G><<<dim3(a.n_split, ninst), kAttnThreads, lds, st>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_split == 1) return e;

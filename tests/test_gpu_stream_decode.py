@@ -70,3 +70,32 @@ def test_stream_decode_vs_oracle(n, g, d, b, k, t, paged):
         ref_row[:nb] = orc.pooled_row(A, b)
         assert np.abs(o[i] - ref).max() <= 2e-5 * np.abs(ref).max(), i
         assert np.abs(r[i] - ref_row).max() <= 2e-5 * ref_row.max(), i
+
+
+@pytest.mark.parametrize("n,g,d,k", [(128, 4, 128, 5000), (256, 2, 64, 5000)])
+def test_long_lists_of_small_blocks(n, g, d, k):
+    """Lists of so many blocks that their entries exceed a workgroup's LDS at the usual number of splits take more.  The
+    blocks share 64 physical ones through the table.  Tolerance: 40000 terms, 2^-24 sqrt(40000) x a few."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    b, phys = 8, 64
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=b, hist_len=8, t_cap=k * b, k_blocks=k, n_sink=0, n_local=0, c1=4, c2=4,
+                     kv_dtype="bf16")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(k)
+    K = torch.randn((phys, b, d), generator=gen, device=dev).to(torch.bfloat16)
+    V = torch.randn((phys, b, d), generator=gen, device=dev).to(torch.bfloat16)
+    q = (3 * torch.randn((n, g, d), generator=gen, device=dev)).to(torch.bfloat16)
+    table = torch.randint(0, phys, (n, k), generator=gen, device=dev, dtype=torch.int32)
+    ctx.set_block_table(table, phys)
+    idx = torch.arange(k, dtype=torch.int32, device=dev).repeat(n, 1).contiguous()
+    cnt = torch.full((n,), k, dtype=torch.int32, device=dev)
+    out, row = torch.empty((n, g, d), device=dev), torch.empty((n, k), device=dev)
+    ws = torch.full((max(16, ctx.workspace_bytes()),), 255, dtype=torch.uint8, device=dev)
+    ctx.sparse_decode(q, K, V, k * b - 3, idx, cnt, out, row, ws)
+    for i in (0, n // 2, n - 1):
+        Kd, Vd = (to_f64(x[table[i].long()].reshape(k * b, d)) for x in (K, V))
+        ref, A = orc.sparse_attention(to_f64(q[i]), Kd, Vd, np.arange(k), b, k * b - 3)
+        ref_row = orc.pooled_row(A, b)
+        assert np.abs(out[i].cpu().double().numpy() - ref).max() <= 6e-5 * np.abs(ref).max(), i
+        assert np.abs(row[i].cpu().double().numpy() - ref_row).max() <= 6e-5 * ref_row.max(), i
