@@ -1,10 +1,11 @@
 // Block-sparse GQA decode attention and dense calibration for gfx950.
 //
-// Both kernels share the same first two phases:
+// Two forms.  The streaming one (sparse_stream_body; calibrate_stream_kernel in attention.hip) is described where it stands.
+// The phased one - sparse decode of whole bf16 lists with g <= 4 and of fp32 lists, fp32 calibration - goes through
 //   1. logits  l[h][tok] = (q_h . K_tok) / sqrt(d) for the tokens of a list of blocks, fp32
 //      accumulate, written to LDS (tokens at or beyond t_cur get -inf);
 //   2. per head: M = max l, p = exp(l - M) in place, L = sum p; per (head, block) the max p.
-// The sparse kernel continues with  3. acc[h][:] = sum_tok p[h][tok] * V_tok  and either finishes
+// Sparse decode continues with  3. acc[h][:] = sum_tok p[h][tok] * V_tok  and either finishes
 // (one workgroup per instance) or leaves (M, L, acc, block maxima) for the combine kernel.
 // Softmax definition: Sec. 3.1; block max-pooling of the probabilities: Algorithm 1 steps 1-2
 // (softmax is monotone, so the pooled probability of a block is exp(max logit - M) / L).
@@ -109,12 +110,11 @@ template <typename T, int D, int G> struct Geom {
 // lanes with head < G hold the logits.
 // The K rows do not come from global memory in that layout (a row would get 64 bytes per load instruction):
 // they are fetched whole - LPT adjacent lanes read one row with non-temporal loads, as V rows are - and pass
-// through a wave-private LDS tile of STAGE rows from which the operand layout is read.  A plain streaming read
+// through a wave-private LDS tile from which the operand layout is read.  A plain streaming read
 // of this machine is 14 % faster with non-temporal loads, but only if an instruction covers whole 128-byte lines;
 // a non-temporal load of part of a line fetches the line again for the other part.
-//   STAGE = 16  one tile per 16-token group (calibration, which has the LDS to spare)
-//   STAGE = 8   an 8-row tile, two passes per 16 tokens through an MFMA whose other eight rows repeat the tile:
-//               it fits into the region that holds the output partials later (sparse decode)
+// The tile has 8 rows, two passes per 16 tokens through an MFMA whose other eight rows repeat the tile: it fits into the
+// region that holds the output partials later.
 // fp32 K/V keeps the VALU form: LPT adjacent lanes share one row, 16 bytes each.
 constexpr int kStageRowPad = 16;   // bytes added to a staged K row so that 16 rows spread over the LDS banks
 template <int D, int ROWS = kGroupTokens, int NW = kAttnWaves> constexpr int k_stage_floats() {
@@ -140,7 +140,7 @@ __device__ __forceinline__ void qk_logits(const T* __restrict__ q_inst, const T*
       qb[s] = __builtin_bit_cast(bf16x8, w);
     }
     {
-      static_assert(STAGE == 8 || STAGE == 16, "bf16 K rows go through a staged tile of 8 or 16 rows");
+      static_assert(STAGE == 8, "bf16 K rows go through a staged tile of 8 rows");
       constexpr int ROWS = STAGE;                        // tokens per pass
       constexpr int NPRE = 2;                            // passes of a wave in flight (3, 4 and 6 measured the same)
       constexpr int LPT = D / 8, TPI = kWave / LPT, NLK = ROWS / TPI, RS = D * 2 + kStageRowPad;
