@@ -407,7 +407,7 @@ hipError_t run_inc(const Shape& s, int inst0, int ninst, const float* dweights, 
     const size_t lds = sizeof(float) * kPredRegLdsFloats;
     // Workgroups the chip holds at once: four a CU (LDS and registers), 256 CUs.  Passes per instance: what makes the
     // rounds of them shortest, a pass costing as much as some 100 columns besides its own, down to 112 columns (two
-    // pieces of a dense list for either wave of a half).
+    // pieces of a dense list for either wave of a half; down to 60 the same: 7.6 us at 8 instances, 14.1 at 128 x 8194).
     constexpr int kSlots = 1024, kPassCost = 100;
     int n_pass = 1;
     long best = -1;
