@@ -204,7 +204,9 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
     lane = tid & (kWave - 1);
     const int w = lane & 15, w_half = (lane >> 4) & 1;   // the word of bits this lane works on, and its half
     const int len = min(nb_cur - c0, pass_cols);         // output columns of the pass: staged columns 4 .. 4 + len - 1
-    const bool at_end = c0 == 0 || c0 + len == nb_cur;   // the pass holds an end of the tile
+    // Staged columns lie beyond the tile: the pass holds an end of it, or the last pass is shorter than what is staged beside
+    // this one.
+    const bool at_end = c0 == 0 || c0 + len + 4 > nb_cur;
     float* pstate_pass = pstate + ((size_t)inst * nb_cap + c0);
     float* pred_pass = pred + ((size_t)inst * nb_cap + c0);
     // Every wave has seen its own pieces of this pass's rows arrive before the last barrier, and is done with the

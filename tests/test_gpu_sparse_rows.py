@@ -46,6 +46,19 @@ def _sparse_row(rng, n, nb, marks):
     return row
 
 
+def _passes(n, nb):
+    """(columns of a pass, of an instance's last one) as the 8/8 step predictor cuts nb columns of n instances."""
+    best = None
+    for p in range(-(-nb // 376), -(-nb // 112) + 1):
+        cols = -(-nb // p)
+        cost = -(-n * -(-nb // cols) // 1024) * (cols + 100)
+        if best is None or cost < best[0]:
+            best = (cost, cols)
+    used = -(-nb // best[1])
+    cols = -(-nb // used)
+    return cols, nb - (used - 1) * cols
+
+
 @pytest.mark.parametrize("c1,c2", [(8, 8), (16, 32)])
 @pytest.mark.parametrize("n,nb,H", [
     (1040, 752, 8),      # more passes than the chip holds workgroups: two of 376 columns per instance
@@ -88,3 +101,30 @@ def test_sparse_history_every_column(n, nb, H, c1, c2):
             got = pred[:, :nb].cpu().double()
             off = (got - ref).abs() - bound * (2 if mode == ap.AP_PRED_ADVANCE else 1) - 1e-7
             assert off.max() <= 0, f"step {step} mode {mode}: {(off > 0).sum()} columns, worst {off.max():.3g} at {np.unravel_index(int(off.argmax()), off.shape)}"
+
+
+@pytest.mark.parametrize("n,nb,last", [(6, 12433, 1), (8, 12881, 1), (2, 12434, 2), (1, 12435, 3), (1, 12436, 4), (3, 500, 100)])
+def test_tile_end_beside_a_short_last_pass(n, nb, last):
+    """Large values in the last five columns of the tile and nowhere else: what lies beyond the tile counts as zero, also for
+    a pass that ends a column or two before the tile does.  (A column beyond the tile read as a copy of the last one moves
+    scores by up to some 0.01; the bound there is a few 0.001.)"""
+    import paper_2502_04077_amd as ap
+    assert _passes(n, nb)[1] == last
+    dev = torch.device("cuda:0")
+    c, b, H = 8, 8, 6
+    ctx = ap.Context(n_inst=n, g=1, head_dim=64, block=b, hist_len=H, t_cap=(nb + 3) * b, k_blocks=2, n_sink=1, n_local=1,
+                     c1=c, c2=c, kv_dtype="bf16")
+    rng = np.random.default_rng(nb)
+    blob = (rng.standard_normal(n_weight_floats(c, c)) * 0.2).astype(np.float32)
+    ctx.set_weights(blob)
+    hist = torch.zeros((n, H + 1, ctx.nb_cap()), device=dev)
+    hist[:, :, nb - 5:nb] = torch.from_numpy(rng.uniform(0.5, 1.0, (n, H + 1, 5)).astype(np.float32)).to(dev)
+    hist[:, :, nb:] = 7.0                                 # (capacity beyond the context: not read)
+    pred, pstate = (torch.zeros((n, ctx.nb_cap()), device=dev) for _ in range(2))
+    ws = torch.zeros((max(16, ctx.workspace_bytes()),), dtype=torch.uint8, device=dev)
+    window = hist[:, :H, :nb].cpu()                       # (2 H + 1 pushes: rows H + 1 .. 2 H are in slots 0 .. H - 1)
+    ref, bound = _reference(window, blob, c, c)
+    ctx.predict_incremental(hist, 2 * H + 1, nb, nb, ap.AP_PRED_REBASE, pstate, pred, ws)
+    off = (pred[:, :nb].cpu().double() - ref).abs() - bound - 1e-7
+    assert off.max() <= 0, f"{(off > 0).sum()} columns, worst {off.max():.3g} at {np.unravel_index(int(off.argmax()), off.shape)}"
+    assert bound.max() < 0.1
