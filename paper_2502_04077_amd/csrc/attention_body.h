@@ -660,12 +660,9 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
   float* s_ml = s_l + NW * G;                            // [G][2] maximum and sum of the workgroup
   int* s_idx = reinterpret_cast<int*>(s_ml + 2 * G);     // [nblk_cap] logical block of each position
   int* s_phys = s_idx + nblk_cap;                        // [nblk_cap] its place in K / V
-  // For the pooled row, written whole by the workgroup that has the whole list: one bit per block (is it
-  // listed) and, per 32-block word, the number of listed blocks before it, so that a column finds its list
-  // position without a search.
+  // For the pooled row, written whole by the workgroup that has the whole list: one bit per block, is it listed.
   const int nwords = whole_row ? (a.nb_cap + 31) / 32 : 0;
   uint32_t* s_listed = reinterpret_cast<uint32_t*>(s_phys + nblk_cap);   // [nwords]
-  uint16_t* s_rank = reinterpret_cast<uint16_t*>(s_listed + nwords);     // [nwords]
 
   if (whole_row) {
     for (int w = threadIdx.x; w < nwords; w += NT) s_listed[w] = 0u;
@@ -852,23 +849,6 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
 #pragma unroll
       for (int e = 0; e < E; ++e) s_tile[h * D + dpart * E + e] = acc[h][e];
   }
-  if (whole_row && wave == NW - 1) {                     // exclusive prefix sum of the words' bit counts
-    const int per_lane = (nwords + kWave - 1) / kWave;
-    const int w0 = lane * per_lane;
-    int mine = 0;
-    for (int i = 0; i < per_lane; ++i)
-      if (w0 + i < nwords) mine += __popc(s_listed[w0 + i]);
-    int incl = mine;                                   // inclusive prefix sum over the lanes, on DPP moves
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xF, 0xF, true);   // row_shr:1
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xF, 0xF, true);   // row_shr:2
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xF, 0xF, true);   // row_shr:4
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xF, 0xF, true);   // row_shr:8
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xA, 0xF, true);   // row_bcast:15 into rows 1 and 3
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xC, 0xF, true);   // row_bcast:31 into rows 2 and 3
-    int run = incl - mine;
-    for (int i = 0; i < per_lane; ++i)
-      if (w0 + i < nwords) { s_rank[w0 + i] = (uint16_t)run; run += __popc(s_listed[w0 + i]); }
-  }
   __syncthreads();
 
   // The waves: one maximum and sum per head, and the factor for each wave's share.
@@ -905,17 +885,16 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
       const float L = s_ml[2 * h + 1];
       a.out[(size_t)inst * G * D + o] = L > 0.f ? v / L : 0.f;      // an empty list gives a zero output
     }
-    // Pooled row: column j of a listed block gets the largest block maximum over the heads, the rest zero.
+    // Pooled row: a listed block's column gets the largest block maximum over the heads, the rest zero.  The values go
+    // where the list says, so entries that come twice (after clamping) or out of order have theirs too, as in the merge of splits.
     float* row = a.row + (size_t)inst * a.row_stride;
-    for (int j = threadIdx.x; j < a.nb_cap; j += NT) {
-      const uint32_t word = s_listed[j >> 5];
+    for (int j = threadIdx.x; j < a.nb_cap; j += NT)
+      if (!((s_listed[j >> 5] >> (j & 31)) & 1u)) row[j] = 0.f;
+    for (int jb = threadIdx.x; jb < nblk; jb += NT) {
       float mx = 0.f;
-      if ((word >> (j & 31)) & 1u) {
-        const int pos = min((int)s_rank[j >> 5] + __popc(word & ((1u << (j & 31)) - 1u)), nblk - 1);
 #pragma unroll
-        for (int h = 0; h < G; ++h) mx = fmaxf(mx, block_max(h, pos) / s_ml[2 * h + 1]);
-      }
-      row[j] = mx;
+      for (int h = 0; h < G; ++h) mx = fmaxf(mx, block_max(h, jb) / s_ml[2 * h + 1]);
+      row[s_idx[jb]] = mx;                               // (a block listed twice: either of two equal values)
     }
   } else {
     const size_t ps = (size_t)inst * a.n_split + split;
@@ -939,7 +918,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
 template <int D, int G> inline size_t sparse_stream_lds_floats(int nblk_cap, int b, int nb_cap) {
   const size_t words = (size_t)((nb_cap + 31) / 32);
   return (size_t)kAttnWaves * wave_tile_floats<D, G>() + query_floats<D, G>() + (size_t)G * nblk_cap * (b / 4) +
-         2 * kAttnWaves * G + 2 * G + 2 * nblk_cap + words + (words + 1) / 2;
+         2 * kAttnWaves * G + 2 * G + 2 * nblk_cap + words;
 }
 
 }  // namespace
