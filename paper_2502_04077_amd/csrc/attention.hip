@@ -29,12 +29,13 @@ void sparse_stream_kernel(SparseArgs a) {
 }
 
 // Brings the partial softmax statistics of one instance - ml[part * G + h] = (maximum, sum relative to it), part < n_part -
-// to factors scale[part * G + h] = exp(m - M) / L in LDS (0 for an empty part or an empty whole).  Every value is fetched by
+// to factors scale[part * G + h] = exp2((m - M) unit) / L in LDS (0 for an empty part or an empty whole); unit is 1 where the
+// maxima are in units of log2, log2(e) for natural ones.  Every value is fetched by
 // a thread of its own, all at once: a thread that walks the parts of a head waits for memory once per part.  Calibration
 // merge: 33 -> 11 us for 128 instances of 129 chunks, 10 -> 4 us for 8 of 33; sparse decode: 6.4 -> 3.8 us for 8 instances
 // of 16 splits, 12.7 -> 8.9 us for 128 of 17.  Called by every thread of the workgroup; ends with a barrier.
 template <int G>
-__device__ __forceinline__ void merge_scales(const float2* __restrict__ ml, int n_part, float* scale) {
+__device__ __forceinline__ void merge_scales(const float2* __restrict__ ml, int n_part, float unit, float* scale) {
   __shared__ float s_ml[2 * G];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   float2 first = make_float2(-INFINITY, 0.f);            // (most merges have no more values than threads)
@@ -47,7 +48,7 @@ __device__ __forceinline__ void merge_scales(const float2* __restrict__ ml, int 
     float L = 0.f;
     for (int p = lane; p < n_part; p += kWave) {
       const float2 v = ml[p * G + h];
-      L += v.x == -INFINITY ? 0.f : v.y * __expf(v.x - M);
+      L += v.x == -INFINITY ? 0.f : v.y * exp2_fast((v.x - M) * unit);
     }
     L = wave_sum(L);
     if (lane == 0) { s_ml[2 * h] = M; s_ml[2 * h + 1] = L > 0.f ? 1.f / L : 0.f; }
@@ -56,7 +57,7 @@ __device__ __forceinline__ void merge_scales(const float2* __restrict__ ml, int 
   for (int o = threadIdx.x; o < n_part * G; o += kAttnThreads) {
     const float m = o == (int)threadIdx.x ? first.x : ml[o].x;
     const int h = o % G;
-    scale[o] = m == -INFINITY ? 0.f : __expf(m - s_ml[2 * h]) * s_ml[2 * h + 1];
+    scale[o] = m == -INFINITY ? 0.f : exp2_fast((m - s_ml[2 * h]) * unit) * s_ml[2 * h + 1];
   }
   __syncthreads();
 }
@@ -77,7 +78,7 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_combine_kernel(SparseArgs
   float* s_scale = smem;                               // [n_split][G]  exp(m_s - M) / L
   const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + (size_t)inst * a.n_split * G;
   if (blockIdx.x == 0) {
-    merge_scales<G>(ml, a.n_split, s_scale);
+    merge_scales<G>(ml, a.n_split, a.ml_unit, s_scale);
     const float* acc = a.part_acc + (size_t)inst * a.n_split * G * D;
     for (int o = threadIdx.x; o < G * D; o += kAttnThreads) {
       const int h = o / D;
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_combine_kernel(SparseArgs
     for (int h = 0; h < G; ++h) bm[h] = bmp[(size_t)h * a.k + threadIdx.x];
   }
   for (int j = threadIdx.x; j < c1 - c0; j += kAttnThreads) s_row[j] = 0.f;
-  merge_scales<G>(ml, a.n_split, s_scale);
+  merge_scales<G>(ml, a.n_split, a.ml_unit, s_scale);
   // pooled probability of list position jb: max over heads of (block max relative to its split) * split scale
   for (int jb = threadIdx.x; jb < cnt; jb += kAttnThreads) {
     if (jb != (int)threadIdx.x) {
@@ -140,6 +141,7 @@ struct CalibArgs {
   int t_cap, nb_cap, b, log2b, t_cur, nb_cur, chunk_blocks, n_chunks, chunk_slots;
   const int32_t* table;
   int n_phys;
+  float ml_unit;                  // the chunks' maxima times this are exponents of 2
 };
 
 __global__ void zero_counter_kernel(int* counter) { *counter = 0; }
@@ -274,7 +276,7 @@ void calibrate_stream_kernel(CalibArgs a) {
   int place = places(u);
   load_k(u, place, 0);
   int q_inst = -1;
-  const float scale = rsqrtf((float)D);
+  using Unit = LogitUnit<D>;
 
 #pragma unroll 1
   for (int round = 0;; ++round) {
@@ -317,17 +319,18 @@ void calibrate_stream_kernel(CalibArgs a) {
       const int n_in = ps < npass ? n_valid - token_of(ps) - 4 * row16 : 0;
       float p[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) p[i] = i < n_in ? lg[i] * scale : -INFINITY;
+      for (int i = 0; i < 4; ++i) p[i] = i < n_in ? lg[i] : -INFINITY;
       const float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
       if (head < G && ps < npass) s_qmax[head * quads + ps * 4 + row16] = mx;
-      const float m_new = fmaxf(m, mx), m_ref = m_new == -INFINITY ? 0.f : m_new;      // (nothing but masked tokens so far)
-      l = l * __expf(m - m_ref) + ((__expf(p[0] - m_ref) + __expf(p[1] - m_ref)) + (__expf(p[2] - m_ref) + __expf(p[3] - m_ref)));
+      const float m_new = fmaxf(m, Unit::reference(mx)), m_ref = m_new == -INFINITY ? 0.f : m_new;      // (nothing but masked tokens so far)
+      auto rel = [&](float x) __attribute__((always_inline)) { return Unit::exp_of(x, m_ref); };
+      l = l * exp2_fast(m - m_ref) + ((rel(p[0]) + rel(p[1])) + (rel(p[2]) + rel(p[3])));
       m = m_new;
     }
     const auto larger = [](float x, float y) { return fmaxf(x, y); };
     const auto plus = [](float x, float y) { return x + y; };
     const float mw = across_32(across_16(m, larger), larger);
-    const float lw = across_32(across_16(m == -INFINITY ? 0.f : l * __expf(m - mw), plus), plus);
+    const float lw = across_32(across_16(m == -INFINITY ? 0.f : l * exp2_fast(m - mw), plus), plus);
     float (*ml)[2 * G] = s_ml[round & 1];
     if (lane < G) { ml[wave][lane] = mw; ml[wave][G + lane] = lw; }
     if (threadIdx.x == 0) s_next[round & 1] = asked;
@@ -341,7 +344,7 @@ void calibrate_stream_kernel(CalibArgs a) {
 #pragma unroll
       for (int w = 0; w < NW; ++w) M = fmaxf(M, ml[w][h]);             // (a unit has a token inside the context)
 #pragma unroll
-      for (int w = 0; w < NW; ++w) L += ml[w][G + h] * __expf(ml[w][h] - M);
+      for (int w = 0; w < NW; ++w) L += ml[w][G + h] * exp2_fast(ml[w][h] - M);
       if (wave == 0 && lane < G) {
         float* to = a.cal_ml + (((size_t)u.inst * a.chunk_slots + u.chunk) * G + lane) * 2;
         to[0] = M;
@@ -356,7 +359,7 @@ void calibrate_stream_kernel(CalibArgs a) {
         float mx = qm[0];
 #pragma unroll 1
         for (int k = 1; k < qpb; ++k) mx = fmaxf(mx, qm[k]);
-        if (jb < u.nblk) a.cal_bmp[((size_t)u.inst * G + h) * a.nb_cap + u.c0 + jb] = __expf(mx - M);
+        if (jb < u.nblk) a.cal_bmp[((size_t)u.inst * G + h) * a.nb_cap + u.c0 + jb] = Unit::exp_of(mx, M);
       }
       asm volatile("" ::: "memory");                     // the next unit overwrites what was read
     }
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(kAttnThreads) void calibrate_finish_kernel(CalibArg
 #pragma unroll
     for (int h = 0; h < G; ++h) bm[i][h] = j < a.nb_cur ? bmp[(size_t)h * a.nb_cap + j] : 0.f;
   }
-  merge_scales<G>(reinterpret_cast<const float2*>(a.cal_ml) + (size_t)inst * a.chunk_slots * G, a.n_chunks, s_scale);
+  merge_scales<G>(reinterpret_cast<const float2*>(a.cal_ml) + (size_t)inst * a.chunk_slots * G, a.n_chunks, a.ml_unit, s_scale);
   float* row = a.row + (size_t)inst * a.nb_cap;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -438,6 +441,7 @@ int stream_splits(const SparseArgs& a, int ninst, int g) {
 
 template <int D, int G>
 hipError_t run_stream(int ninst, SparseArgs a, hipStream_t st) {
+  a.ml_unit = 1.f;
   int want = a.n_split > 1 ? stream_splits(a, ninst, G) : 1;
   // (Lists of so many blocks, or rows with so many, that their entries beside the logits exceed 64 KiB take more splits; with
   // those the workspace is laid out for they fit.)
@@ -501,6 +505,7 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
 template <typename T, int D, int G>
 hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
   if constexpr (std::is_same<T, bf16_t>::value) {
+    a.ml_unit = 1.f;
     const size_t quads = (a.chunk_blocks * (a.b / 4) + 4 * kAttnWaves - 1) / kAttnWaves;
     const size_t lds = (size_t)kAttnWaves * ((kGroupTokens + G) * (D * 2 + kStageRowPad) + sizeof(float) * G * quads);
     if (s.occ->calib_slots < 0) s.occ->calib_slots = resident_workgroups(calibrate_stream_kernel<D, G>, kAttnThreads, lds);
@@ -567,6 +572,7 @@ hipError_t launch_sparse_decode(const Shape& s, int inst0, int ninst, const void
   a.blk_per_split = (s.k + s.n_split - 1) / s.n_split;
   a.inst0 = inst0;
   a.piece_blocks = s.k;
+  a.ml_unit = kLog2E;
   a.table = s.table; a.n_phys = s.n_phys;
   AP_DISPATCH(run_sparse, s, ninst, a, st)
 }
@@ -602,6 +608,7 @@ hipError_t launch_calibrate(const Shape& s, const void* q, const void* K, int t_
   a.nb_cur = (t_cur + s.b - 1) / s.b;
   a.chunk_blocks = s.calib_chunk_tokens / s.b;
   a.n_units = 0;
+  a.ml_unit = kLog2E;
   a.n_chunks = (a.nb_cur + a.chunk_blocks - 1) / a.chunk_blocks;
   a.chunk_slots = s.calib_chunks;
   a.table = s.table; a.n_phys = s.n_phys;

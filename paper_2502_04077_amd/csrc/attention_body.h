@@ -342,6 +342,7 @@ struct SparseArgs {
   const int32_t* table;           // block table [n_inst][nb_cap] of a paged cache, or null
   int n_phys;                     // blocks in the pool (table entries are clamped into it)
   int piece_blocks;               // list positions whose probabilities are in LDS at a time
+  float ml_unit;                  // the splits' maxima times this are exponents of 2
 };
 
 // Sparse decode of instance `inst`, split `split`, by one workgroup of NW waves.
@@ -608,9 +609,24 @@ template <int D, int G> constexpr int wave_tile_floats() {
   return stage > G * D ? stage : G * D;
 }
 template <int D, int G> constexpr int query_floats() { return G * (D * 2 + kStageRowPad) / 4; }
-// How far a logit may exceed the maximum that the running sums are relative to before they are rescaled: exp(8) = 2981
-// leaves fp32 sums their relative precision, and after the first pass hardly any pass has to touch the accumulators.
-constexpr float kRescaleAt = 8.f;
+// The streaming forms keep logits as they come out of the contraction and refer probabilities to whole numbers m, in units of
+// log2: with c = log2(e) / sqrt(d) a probability is exp2(fma(logit, c, -m)), whose exponent is rounded once instead of three
+// times, and the factors that bring sums from one reference to another are powers of two, which round nothing.
+constexpr float kLog2E = 1.44269504088896340736f;
+__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+template <int D> struct LogitUnit {
+  static_assert(D == 64 || D == 128, "log2(e) / sqrt(d) for the compiled head sizes");
+  static constexpr float kC = D == 64 ? 1.4426950408889634 / 8.0 : 1.4426950408889634 / 11.313708498984761;
+  static __device__ __forceinline__ float reference(float logit) { return ceilf(logit * kC); }
+  static __device__ __forceinline__ float exp_of(float logit, float m) { return exp2_fast(fmaf(logit, kC, -m)); }
+};
+// How far (in units of log2) a logit may exceed the maximum that the running sums are relative to before they are rescaled:
+// 2^11 leaves fp32 sums their relative precision, and after the first pass hardly any pass has to touch the accumulators.
+constexpr float kRescaleAt = 11.f;
+// Passes of a wave whose sums go into one set of accumulators (32 additions each at d = 128, 16 at d = 64) before these are added
+// to a second set: the roundings of a long chain of additions were most of the error of long lists (128 lists of 32790 tokens in four
+// splits, relative to 64 bits: 7.3e-7 with 512 in a chain, 3.9e-7 now, 4.7e-7 in 17 splits without a second set).
+constexpr int kChainPasses = 8;
 
 // Sparse decode of instance `inst`, split `split`, by one workgroup of four waves, bf16.
 // Every wave works off 16-token passes of the list by itself, from K rows to acc += p * V, with running softmax
@@ -686,7 +702,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
   const T* K_inst = static_cast<const T*>(a.K) + kv_off;
   const T* V_inst = static_cast<const T*>(a.V) + kv_off;
 
-  const float scale = rsqrtf((float)D);
+  using Unit = LogitUnit<D>;
   const int ntok = nblk * a.b, npass = (ntok + kGroupTokens - 1) / kGroupTokens;
 
   // A pass's 16 tokens are two runs of eight, each inside one block (a block holds at least eight).  K rows: load i
@@ -776,17 +792,17 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     asm volatile("" ::: "memory");                     // the next pass overwrites the tile read above
     float p[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) p[v] = lg[v] * scale;
+    for (int v = 0; v < 4; ++v) p[v] = lg[v];
     if (live != 0xffffu) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) p[v] = ((live >> (4 * row16 + v)) & 1u) ? p[v] : -INFINITY;
     }
     const float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
     if (head < G && tau0 + 4 * row16 < ntok) s_qmax[head * (nblk * qpb) + ps * 4 + row16] = mx;
-    const bool above = head < G && mx > m + kRescaleAt;
+    const bool above = head < G && mx * Unit::kC > m + kRescaleAt;
     if (__any(above)) {
-      const float m_new = above ? mx : m;
-      const float al = above ? __expf(m - m_new) : 1.f;      // (0 for the first maximum)
+      const float m_new = above ? Unit::reference(mx) : m;
+      const float al = above ? exp2_fast(m - m_new) : 1.f;   // (0 for the first maximum)
       m = m_new;
       l *= al;
       auto rescale = [&](auto hc) __attribute__((always_inline)) {
@@ -799,7 +815,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     }
     const float m_ref = m == -INFINITY ? 0.f : m;          // (nothing but masked tokens so far)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) p[v] = __expf(p[v] - m_ref);
+    for (int v = 0; v < 4; ++v) p[v] = Unit::exp_of(p[v], m_ref);
     l += (p[0] + p[1]) + (p[2] + p[3]);
     // acc += p V: token i of this lane's group is, of the row's four tokens, i (d = 128) or 2 (tslot % 2) + i (d = 64)
 #pragma unroll
@@ -820,35 +836,63 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     }
     if constexpr (MORE) load_v(next);
   };
-  int ps = wave;
-#pragma unroll 1
-  for (; ps + NW < npass; ps += NW) pass(ps, std::true_type{});
-  if (ps < npass) pass(ps, std::false_type{});
-
-  // The token slots of a wave: bring them to one maximum per head, add them up, leave the wave's share in LDS.
+  // Second set of accumulators: the token slots added up, relative to one maximum per head (m_sum), each lane holding its
+  // share of the dims: dims dpart E + first .. + NS - 1.
+  constexpr int NS = E / TPI;
+  const int first = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + (TPI == 8 ? (lane >> 3) & 1 : 0);
+  float m_sum = -INFINITY, l_sum = 0.f, sum[G][NS];
+#pragma unroll
+  for (int h = 0; h < G; ++h)
+#pragma unroll
+    for (int j = 0; j < NS; ++j) sum[h][j] = 0.f;
   const auto larger = [](float x, float y) { return fmaxf(x, y); };
   const auto plus = [](float x, float y) { return x + y; };
-  const float mw = across_32(across_16(m, larger), larger);
-  const float sc = m == -INFINITY ? 0.f : __expf(m - mw);
-  const float lw = across_32(across_16(l * sc, plus), plus);
-  if (lane < G) { s_m[wave * G + lane] = mw; s_l[wave * G + lane] = lw; }
-  auto gather = [&](auto hc) __attribute__((always_inline)) {
-    constexpr int h = decltype(hc)::value;
-    const float f = row_bcast<h>(sc);
+  auto fold = [&]() __attribute__((always_inline)) {
+    const float mw = across_32(across_16(m, larger), larger);
+    const float f_acc = m == -INFINITY ? 0.f : exp2_fast(m - mw), f_sum = m_sum == -INFINITY ? 0.f : exp2_fast(m_sum - mw);
+    m = m_sum = mw;
+    l_sum = fmaf(l_sum, f_sum, across_32(across_16(l * f_acc, plus), plus));
+    l = 0.f;
+    auto head_share = [&](auto hc) __attribute__((always_inline)) {
+      constexpr int h = decltype(hc)::value;
+      const float f = row_bcast<h>(f_acc), fs = row_bcast<h>(f_sum);
+      float x[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      float v = acc[h][e] * f;
-      if constexpr (LPT <= 8) v += dpp_move<0x128>(v);   // row_ror:8
-      acc[h][e] = across_32(across_16(v, plus), plus);
-    }
+      for (int e = 0; e < E; ++e) { x[e] = acc[h][e] * f; acc[h][e] = 0.f; }
+      // Lanes 32 and up take elements 4..7, lanes below 0..3; odd rows of 16 the upper two of these, and so on.
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[e]), __float_as_uint(x[e + 4]), false, false);
+        x[e] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[e]), __float_as_uint(x[e + 2]), false, false);
+        x[e] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+      }
+      if constexpr (TPI == 8) {
+        const bool upper = (lane >> 3) & 1;
+        x[0] = (upper ? x[1] : x[0]) + dpp_move<0x128>(upper ? x[0] : x[1]);     // row_ror:8
+      }
+#pragma unroll
+      for (int j = 0; j < NS; ++j) sum[h][j] = fmaf(sum[h][j], fs, x[j]);
+    };
+    for_heads<G>(head_share);
   };
-  for_heads<G>(gather);
-  if (tslot == 0) {
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int e = 0; e < E; ++e) s_tile[h * D + dpart * E + e] = acc[h][e];
+  int ps = wave, chain = 0;
+#pragma unroll 1
+  for (; ps + NW < npass; ps += NW) {
+    pass(ps, std::true_type{});
+    if (++chain == kChainPasses) { fold(); chain = 0; }
   }
+  if (ps < npass) pass(ps, std::false_type{});
+  fold();
+
+  if (lane < G) { s_m[wave * G + lane] = m; s_l[wave * G + lane] = l_sum; }
+#pragma unroll
+  for (int h = 0; h < G; ++h)
+#pragma unroll
+    for (int j = 0; j < NS; ++j) s_tile[h * D + dpart * E + first + j] = sum[h][j];
   __syncthreads();
 
   // The waves: one maximum and sum per head, and the factor for each wave's share.
@@ -860,7 +904,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     float L = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float mw = s_m[w * G + h], f = mw == -INFINITY ? 0.f : __expf(mw - M);
+      const float mw = s_m[w * G + h], f = mw == -INFINITY ? 0.f : exp2_fast(mw - M);
       L += s_l[w * G + h] * f;
       s_m[w * G + h] = f;
     }
@@ -874,7 +918,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     float mx = qm[0];
 #pragma unroll 1
     for (int i = 1; i < qpb; ++i) mx = fmaxf(mx, qm[i]);
-    return __expf(mx - s_ml[2 * h]);                     // (a listed block has a token inside the context: M is finite)
+    return Unit::exp_of(mx, s_ml[2 * h]);                // (a listed block has a token inside the context: M is finite)
   };
   if (whole_row) {
     for (int o = threadIdx.x; o < G * D; o += NT) {

@@ -1,5 +1,5 @@
 """Lists as the header allows them - entries outside the context, which are clamped into it and may then come twice - give the
-same attention and the same pooled row whichever form of sparse decode takes the call: a column holds the largest probability
+same attention and the same pooled row whether a list is cut into splits or streamed whole: a column holds the largest probability
 of its block, wherever in the list the block stands.  Against float64; tolerance as in test_gpu_stream_decode.py."""
 import math
 
