@@ -419,30 +419,34 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
   return hipGetLastError();
 }
 
-// Workgroups per instance the streaming form uses, of the a.n_split that the workspace has room for.  More of them than
-// it takes to keep memory busy only add start-ups and a longer merge: 256 workgroups (one a CU) of up to 4096
-// tokens, 512 for longer lists, none shorter than two passes a wave (128 tokens), 64 to merge at most.  From 256
-// instances on one each; g = 1, whose passes have the least arithmetic to cover the start with, and 512 or more
-// instances with g = 8, three of whose workgroups fit a CU, take what the workspace has.  (Decode + merge, us, bf16, d = 128;
-// splits: time.  8 x 1024 tokens 16: 11.7, 8: 10.8, 4: 13.4; 128 x 2048 8: 31.1, 2: 29.7; 128 x 32800 17: 361, 8: 339,
-// 4: 328; 256 x 1024 4: 31.5, 1: 28.5; 700 x 1024 4: 68.9, 1: 64.2; g = 8, 640 x 2048 2: 123, 1: 127; g = 1, 300 x 1024
-// 4: 30.6, 1: 32.8.)
-int stream_splits(const SparseArgs& a, int ninst, int g) {
+// Workgroups per instance the streaming form uses, of the a.n_split that the workspace has room for: the number with the least
+// time by this reckoning.  The fullest of 256 CUs has r = ceil(workgroups / 256) of them and takes r shares of a list, at 32 KB
+// a us where it has one workgroup (20 at d = 64, whose workgroups have half the bytes on their way), 29 with two and 22.5
+// with more, when all of memory is busy; a merge costs 3.6 us and 0.03 a split.  So few instances are split until every
+// CU has work, and 280 are not left with two lists on 24 CUs and one on the others.  No split is shorter than two passes a wave (128
+// tokens), 64 to merge at most unless LDS asks for more.  (Over 1 to 1000 instances, lists of 256 to 16384 tokens, g = 1 to 8,
+// both head sizes, wherever it takes 14 us or more, the choice is 1.3 % from the best one.  Decode + merge in us, d = 128, bf16,
+// splits: time.  128 x 8192 tokens, g = 4, 1: 120, 2: 87, 8: 90; 144 x 8192, g = 1, 1: 109, 2: 118, 3: 97, 5: 95; 280 x 4096,
+// g = 2, 1: 116, 4: 98; 512 x 8192, g = 4, 1: 318, 2: 334; 8 x 1024, g = 4, 4: 13.4, 8: 10.8.)
+template <int D> int stream_splits(const SparseArgs& a, int ninst, int g) {
   const long tokens = (long)a.k * a.b;
-  if (ninst >= 256 && (g == 1 || (g == 8 && ninst >= 512))) return a.n_split;
-  long want = (256 + ninst - 1) / ninst;
-  if (tokens > 4096 * want) want = (512 + ninst - 1) / ninst;
-  if (want > tokens / 128) want = tokens / 128;
-  if (want > 64) want = 64;
   const long least = (g * tokens + 40959) / 40960;       // (a list's largest logits, one float per head and four tokens, in 40 KiB)
-  if (want < least) want = least;
-  return want > a.n_split ? a.n_split : want < 1 ? 1 : (int)want;
+  int best = least < 1 ? 1 : (int)least;
+  if (best >= a.n_split) return a.n_split;
+  double best_us = 0.0;
+  for (int u = best, first = best; u <= a.n_split && (u == first || (u <= 64 && tokens >= 128L * u)); ++u) {
+    const long r = ((long)u * ninst + 255) / 256;
+    const double kb_per_us = r == 1 ? (D == 128 ? 32.0 : 20.0) : r == 2 ? 29.0 : 22.5;
+    const double us = r * (4e-3 * D * tokens / u) / kb_per_us + (u > 1 ? 3.6 + 0.03 * u : 0.0);
+    if (u == first || us < best_us) { best = u; best_us = us; }
+  }
+  return best;
 }
 
 template <int D, int G>
 hipError_t run_stream(int ninst, SparseArgs a, hipStream_t st) {
   a.ml_unit = 1.f;
-  int want = a.n_split > 1 ? stream_splits(a, ninst, G) : 1;
+  int want = a.n_split > 1 ? stream_splits<D>(a, ninst, G) : 1;
   // (Lists of so many blocks, or rows with so many, that their entries beside the logits exceed 64 KiB take more splits; with
   // those the workspace is laid out for they fit.)
   auto lds_of = [&](int splits) {
