@@ -268,11 +268,11 @@ __global__ __launch_bounds__(2 * IW) void predict_inc_kernel(const float* __rest
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))   // four workgroups per CU: 128 VGPRs
 void predict_inc_mfma_kernel(const float* __restrict__ hist, const float* __restrict__ wts_global, int R, int H,
-                             int newest_slot, int nb_cur, int nb_cap, int inst0, int ninst, int n_pass, int advance,
+                             int newest_slot, int nb_cur, int nb_cap, int inst0, PassPlan plan, int advance,
                              float* __restrict__ pstate, float* __restrict__ pred) {
   extern __shared__ __align__(16) float smem[];
-  predict_inc_reg_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0, ninst, n_pass, advance, pstate,
-                       pred, smem);
+  predict_inc_reg_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0, plan, advance, pstate, pred,
+                       smem);
 }
 
 __global__ __launch_bounds__(256) void predict_inc_mfma16_kernel(const float* __restrict__ hist,
@@ -407,19 +407,28 @@ hipError_t run_inc(const Shape& s, int inst0, int ninst, const float* dweights, 
     const size_t lds = sizeof(float) * kPredRegLdsFloats;
     // Workgroups the chip holds at once: four a CU (LDS and registers), 256 CUs.  Passes per instance: what makes the
     // rounds of them shortest, a pass costing as much as some 100 columns besides its own, down to 112 columns (two
-    // pieces of a dense list for either wave of a half; down to 60 the same: 7.6 us at 8 instances, 14.1 at 128 x 8194).
+    // pieces of a dense list for either wave of a half; down to 60 the same: 7.6 us at 8 instances, 14.1 at 128 x 8194).  Of the
+    // numbers that make as many rounds the largest is the best one: the others need not be looked at.
     constexpr int kSlots = 1024, kPassCost = 100;
     int n_pass = 1;
     long best = -1;
     const int least = (nb_cur + kRiPassCols - 1) / kRiPassCols, most = (nb_cur + 111) / 112;
     for (int p = least; p <= most; ++p) {
+      const long same = ((long)ninst * p + kSlots - 1) / kSlots * kSlots / ninst;
+      p = same < most ? (int)same : most;
       const int cols = (nb_cur + p - 1) / p, used = (nb_cur + cols - 1) / cols;     // (no pass without columns)
       const long rounds = ((long)ninst * used + kSlots - 1) / kSlots, cost = rounds * (cols + kPassCost);
       if (best < 0 || cost < best) { best = cost; n_pass = used; }
     }
-    const long passes = (long)ninst * n_pass;
-    predict_inc_mfma_kernel<<<dim3(passes < kSlots ? (int)passes : kSlots), 256, lds, st>>>(
-        hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, ninst, n_pass, advance, pstate, pred);
+    PassPlan plan;
+    plan.n_pass = n_pass;
+    plan.cols = (nb_cur + n_pass - 1) / n_pass;
+    plan.total = ninst * n_pass;
+    const int grid = plan.total < kSlots ? plan.total : kSlots;
+    plan.per_wg = (plan.total + grid - 1) / grid;
+    plan.inv_pass = (uint32_t)((0x100000000ull + n_pass - 1) / n_pass);
+    predict_inc_mfma_kernel<<<dim3(grid), 256, lds, st>>>(hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan,
+                                                          advance, pstate, pred);
     return hipGetLastError();
   }
   if (C1 == 16 && C2 == 32 && s.predictor_mfma) {

@@ -18,8 +18,9 @@
 // makes the registers enough:
 //   layer 1  rows = (staged y1 row q, channel c1), K = 16 = 15 (x row, tap) pairs + a constant 1 that carries the
 //            accumulator start.  The ten history rows of a pass of columns go from global memory straight to LDS
-//            (global_load_lds, no registers), asked for a whole pass ahead into the other of two buffers; a lane
-//            scales the eight values its K slots are made of by 2^12 and rounds them to f16 as it reads them.
+//            (global_load_lds, no registers), asked for a whole pass ahead into the other of two buffers; at the start
+//            of a pass a column's values are scaled by 2^12 and rounded to f16 once, in place, into the words that the
+//            K slots are made of.
 //   layer 2  the result of layer 1 is, per lane, channels 4h .. 4h+3 of the four y1 rows of its own column: exactly
 //            half of the K entries of a layer-2 step whose 16 entries are two (y1 row, tap) pairs of 8 channels.
 //            The centre tap takes those registers as they are, the outer taps the same registers moved by one
@@ -34,11 +35,12 @@
 // leaving row is evaluated by the same instruction sequence on the same values as when it entered, so it cancels exactly.
 //
 // Measured at 2048 instances x 2050 columns (0.20 GB to move: 31 us at the rate a plain read reaches), histories of 64
-// selected blocks in runs: 46-48 us, with all columns evaluated 72; an all-zero history 35 us (66), 128 instances x 8194
-// columns 15 us (23.5).  Histories that are dense in all ten rows take 84-87 us (77): every piece then comes with the
-// bits on top, and the SIMDs are full of vector instructions (four cycles each: 78 a piece, 53 us of the 87) and MFMAs
-// (27 us), which overlap in part only.  That holds for the first five steps after a prefill; with a dense row every 32
-// steps the average is 52 us.
+// selected blocks in runs: 45.5 us, with all columns evaluated 67-69; an all-zero history 37 us (66), 128 instances x 8194
+// columns 14.2 us (22.9).  Where both halves have a value in every column of a pass (the first five steps after a prefill) nothing is
+// looked up and the pieces inside the tile take a loop of their own, without a test or an address of their own: 76 us, against 73
+// for a kernel that only knows dense histories and reads the f16 words of row 2 in pairs (82-84 us with the lists made in any
+// case); there the SIMDs are full of vector instructions (62 a piece at four cycles) and MFMAs, which overlap in part
+// only.  A single pass per workgroup, 1 to 8 instances, takes 0.2 us longer than in that kernel: bits, barrier, list.
 #pragma once
 
 #include <type_traits>
@@ -54,12 +56,12 @@ constexpr int kRiRawStride = kRiRawSegs * kWave;        // staged history column
 constexpr int kRiPassCols = kRiRawStride - 8;           // most output columns per pass (four workgroups' LDS fits a CU)
 // LDS words: two buffers of ten raw history rows [row][kRiRawStride], the pass at hand and the next one; the partial
 // sums [half][column of the pass][moving | border]; the waves' column lists (16 bits an entry); one bit per staged
-// column [half][2 zero words | column / 32 | zero words]; and two masks of output columns
+// column [half][2 zero words | column / 32 | zero words]; two masks of output columns; and a constant
 constexpr int kRiRawWords = 10 * kRiRawStride;
 constexpr int kRiPartWords = 2 * kRiPassCols * 2;
 constexpr int kRiListWords = kRiRawStride / 2;
 constexpr int kRiBitWords = 20;
-constexpr int kPredRegLdsFloats = 2 * kRiRawWords + kRiPartWords + 4 * kRiListWords + 2 * kRiBitWords + 16 + 2 * 16;
+constexpr int kPredRegLdsFloats = 2 * kRiRawWords + kRiPartWords + 4 * kRiListWords + 2 * kRiBitWords + 16 + 2 * 16 + 2 * kRiOut + 1;
 static_assert(2 * kRiRawSegs <= 16 && 2 + 16 + 1 <= kRiBitWords, "a lane of a row of 16 per 32 columns");
 constexpr uint32_t kRiIsOutput = 0x8000u;               // list entry: staged column | this if it is an output
 
@@ -91,17 +93,23 @@ __device__ __forceinline__ void lds_barrier() {
 
 // Every instance's columns are cut into n_pass passes of equal length (at most kRiPassCols columns); a workgroup of
 // 256 threads takes a run of consecutive passes of all instances, so that the operands are fetched and the first
-// rows waited for once per workgroup.   smem: kPredRegLdsFloats floats.
+// rows waited for once per workgroup.  (Divisions would be a tenth of a call that has one pass a workgroup: the host makes them.)
+struct PassPlan {
+  int n_pass, cols;                                      // passes per instance, columns of a pass
+  int total, per_wg;                                     // passes of all instances, of a workgroup
+  uint32_t inv_pass;                                     // ceil(2^32 / n_pass) where n_pass > 1: quotients at most one too large
+};
+
+// smem: kPredRegLdsFloats floats.
 __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ hist, const float* __restrict__ wts_global,
                                                      int R, int H, int newest_slot, int nb_cur, int nb_cap, int inst0,
-                                                     int ninst, int n_pass, int advance, float* __restrict__ pstate,
+                                                     const PassPlan& plan, int advance, float* __restrict__ pstate,
                                                      float* __restrict__ pred, float* smem) {
   constexpr int C = 8;
   constexpr float kXScale = 4096.f, kAccScale = 256.f;
   typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
-  const int total = ninst * n_pass;
-  const int pass_cols = (nb_cur + n_pass - 1) / n_pass;
+  const int pass_cols = plan.cols;
   const int tid_all = threadIdx.x;
   int tid = tid_all, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -138,10 +146,15 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
         load_to_lds(hist_inst, off + (wsub ? row_off[1][r] : row_off[0][r]), s_raw + (wsub * 5 + r) * kRiRawStride + k * kWave);
     }
   };
-  const int per_wg = (total + gridDim.x - 1) / gridDim.x;
-  const int g_begin = blockIdx.x * per_wg, g_end = min(total, g_begin + per_wg);
+  const int g_begin = blockIdx.x * plan.per_wg, g_end = min(plan.total, g_begin + plan.per_wg);
   if (g_begin >= g_end) return;                          // (the whole workgroup: no barrier is skipped by part of it)
-  int inst = inst0 + g_begin / n_pass, c0 = (g_begin % n_pass) * pass_cols;
+  int at_inst = g_begin, at_pass = 0;
+  if (plan.n_pass > 1) {
+    at_inst = __umulhi((uint32_t)g_begin, plan.inv_pass);
+    at_pass = g_begin - at_inst * plan.n_pass;
+    if (at_pass < 0) { --at_inst; at_pass += plan.n_pass; }
+  }
+  int inst = inst0 + at_inst, c0 = at_pass * pass_cols;
   fetch_pass(inst, c0, smem);
 
   // Operand tables and per-lane constants.
@@ -189,6 +202,9 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
   uint32_t* s_bits = reinterpret_cast<uint32_t*>(smem + 2 * kRiRawWords + kRiPartWords + 4 * kRiListWords);
   uint32_t* s_outs = s_bits + 2 * kRiBitWords;           // the outputs of a whole pass, one bit per staged column
   uint32_t* s_epi = s_outs + 16;                         // [half][column / 32]: the outputs of the pass at hand
+  // f16 1 in the place of a row-2 word, for the lane half whose K slot is the constant (read with an offset of two pieces too)
+  uint32_t* s_one = s_epi + 32;
+  if (tid <= 2 * kRiOut) s_one[tid] = 0x3c00u;
   if (tid < 2 * kRiBitWords) s_bits[tid] = 0u;           // (the words around a row stay zero)
   if (tid < 16) s_outs[tid] = bit_range(4, 4 + pass_cols, tid);
   __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0): this wave's pieces of the first pass are in LDS
@@ -224,49 +240,50 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
     // One bit per staged column and half: is one of the five values other than zero.  Where one of 64 columns has such
     // a value they are turned into what layer 1 reads, in place (a thread touches its own column only): f16 of 2^12 x,
     // zero outside the tile, rows (0 | 1) in the place of row 0, (3 | 4) in that of row 1, (2 | 0) in that of row 2.
-    // Zeros are that already.
+    // Zeros are that already.  (Six pieces of 64 columns, two halves: three of these for every wave.)
 #pragma unroll
-    for (int ch = 0; ch < 2; ++ch) {
-      const int seg = ch * 4 + wave;
-      if (seg < kRiRawSegs) {                            // (wave-uniform)
-        const int i = seg * kWave + lane;
-        float sc = kXScale;
-        if (at_end) sc = (uint32_t)(c0 - 4 + i) < (uint32_t)nb_cur ? kXScale : 0.f;
-#pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2) {
-          float* x = s_raw + h2 * 5 * kRiRawStride + i;
-          const float x0 = x[0], x1 = x[kRiRawStride], x2 = x[2 * kRiRawStride], x3 = x[3 * kRiRawStride], x4 = x[4 * kRiRawStride];
-          const uint32_t any = (__float_as_uint(x0) | __float_as_uint(x1) | __float_as_uint(x2) | __float_as_uint(x3) |
-                                __float_as_uint(x4)) << 1;
-          const unsigned long long m = __ballot(any != 0u && sc != 0.f);
-          if (__ballot(any != 0u) != 0ull) {             // (with -0, or a column outside the tile, too)
-            const half2v a01 = {(_Float16)(x0 * sc), (_Float16)(x1 * sc)}, a34 = {(_Float16)(x3 * sc), (_Float16)(x4 * sc)};
-            const half2v a2 = {(_Float16)(x2 * sc), (_Float16)0};
-            x[0] = __builtin_bit_cast(float, a01);
-            x[kRiRawStride] = __builtin_bit_cast(float, a34);
-            x[2 * kRiRawStride] = __builtin_bit_cast(float, a2);
-          }
-          if (lane < 2) s_bits[h2 * kRiBitWords + 2 + seg * 2 + lane] = (uint32_t)(m >> (32 * lane));
-        }
+    for (int u = 0; u < kRiRawSegs / 2; ++u) {
+      const int seg = u * 2 + hf, h2 = wsub;             // (wave-uniform)
+      const int i = seg * kWave + lane;
+      float* x = s_raw + h2 * 5 * kRiRawStride + i;
+      const float x0 = x[0], x1 = x[kRiRawStride], x2 = x[2 * kRiRawStride], x3 = x[3 * kRiRawStride], x4 = x[4 * kRiRawStride];
+      const uint32_t any = (__float_as_uint(x0) | __float_as_uint(x1) | __float_as_uint(x2) | __float_as_uint(x3) |
+                            __float_as_uint(x4)) << 1;
+      const unsigned long long nonzero = __ballot(any != 0u);
+      unsigned long long m = nonzero;
+      float sc = kXScale;
+      if (at_end) {
+        const bool inside = (uint32_t)(c0 - 4 + i) < (uint32_t)nb_cur;
+        m &= __ballot(inside);
+        sc = inside ? kXScale : 0.f;
       }
+      if (nonzero != 0ull) {                             // (with a column outside the tile, too)
+        const half2v a01 = {(_Float16)(x0 * sc), (_Float16)(x1 * sc)}, a34 = {(_Float16)(x3 * sc), (_Float16)(x4 * sc)};
+        const half2v a2 = {(_Float16)(x2 * sc), (_Float16)0};
+        x[0] = __builtin_bit_cast(float, a01);
+        x[kRiRawStride] = __builtin_bit_cast(float, a34);
+        x[2 * kRiRawStride] = __builtin_bit_cast(float, a2);
+      }
+      if (lane < 2) s_bits[h2 * kRiBitWords + 2 + seg * 2 + lane] = (uint32_t)(m >> (32 * lane));
     }
     lds_barrier();
     // Which columns are outputs, which are listed, and how many come before: lane w of a row of 16 lanes works on
     // columns 32 w .. 32 w + 31, the even rows on the top half, the odd ones on the bottom half.
-    int count;
-    bool dense;                                          // every column of the pass: entry e is column 3 + e, an output but for the ends
-    {
-      const uint32_t* bits = s_bits + w_half * kRiBitWords + 2 + w;
-      const uint32_t am = bits[-1], a0 = bits[0], ap = bits[1];
+    // First of all: has every column of the pass a value in either half?  Then there is nothing to look up.
+    int count = len + 2;
+    bool dense = true;                                   // every column of the pass: entry e is column 3 + e, an output but for the ends
+    const uint32_t* bits = s_bits + w_half * kRiBitWords + 2 + w;
+    const uint32_t a0 = bits[0], whole = at_end ? bit_range(4, 4 + len, w) : s_outs[w];
+    const bool all_dense = (uint32_t)__ballot((a0 & whole) == whole) == ~0u;     // (lanes 0 .. 31: the words of both halves)
+    if (!all_dense) {
+      const uint32_t am = bits[-1], ap = bits[1];
       // column i takes the bits of columns i - 2 .. i + 2
       uint32_t out = a0 | __builtin_amdgcn_alignbit(a0, am, 31) | __builtin_amdgcn_alignbit(a0, am, 30) |
                      __builtin_amdgcn_alignbit(ap, a0, 1) | __builtin_amdgcn_alignbit(ap, a0, 2);
+      out &= whole;
       if (at_end) {
-        out &= bit_range(4, 4 + len, w);
         if (c0 == 0) out |= bit_range(4, 5, w);
         if (c0 + len == nb_cur) out |= bit_range(4 + len - 1, 4 + len, w);
-      } else {
-        out &= s_outs[w];
       }
       const uint32_t prev = __builtin_amdgcn_update_dpp(0, out, 0x111, 0xF, 0xF, true);   // row_shr:1: word w - 1
       const uint32_t next = __builtin_amdgcn_update_dpp(0, out, 0x101, 0xF, 0xF, true);   // row_shl:1: word w + 1
@@ -298,20 +315,22 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
     asm volatile("" ::: "memory");                       // a wave reads what it has just written, in order
 
     // 32 list entries: this lane's staged column `at` (3 .. 4 + len, or, beyond the end of a dense list, anything finite
-    // to read that no output depends on).  BORDER: one of them lies beside the tile, where y1 = 0 (d1 = lo1);
-    // the others skip those selects.
-    auto piece = [&](int at, bool output, auto border_tag) __attribute__((always_inline)) {
-      constexpr bool BORDER = decltype(border_tag)::value;
-      const int col = c0 - 4 + at;
-      // Layer 1 operand: the K slots of this lane half (ri_slot_row / ri_slot_kw).
+    // to read that no output depends on), whose words the pointers stand for (moved by `off`).  One of them may lie beside
+    // the tile, where y1 = 0 (d1 = lo1).  INNER: none does, and entries 1 .. 30 are all outputs.
+    struct Words { const uint32_t *rows, *side, *mid; float* part; };
+    auto words_of = [&](int at) __attribute__((always_inline)) {
       const uint32_t* x = reinterpret_cast<const uint32_t*>(s_raw) + hf * 5 * kRiRawStride + at;
+      // rows (0 | 1) or (3 | 4); row 2, column - 1 or + 1; row 2 or the constant
+      return Words{x + hsel * kRiRawStride, x + 2 * kRiRawStride + 2 * hsel - 1, hsel ? s_one : x + 2 * kRiRawStride,
+                   reinterpret_cast<float*>(s_part) + (hf * kRiPassCols + at - 4) * 2 + hsel};
+    };
+    auto piece = [&](const Words& ptr, int off, int col, bool output, auto inner_tag) __attribute__((always_inline)) {
+      constexpr bool BORDER = !decltype(inner_tag)::value;
+      // Layer 1 operand: the K slots of this lane half (ri_slot_row / ri_slot_kw).
       uint4v b1;
 #pragma unroll
-      for (int kw = 0; kw < 3; ++kw) b1[kw] = x[hsel * kRiRawStride + kw - 1];         // rows (0 | 1), or (3 | 4)
-      const uint32_t side = x[2 * kRiRawStride + 2 * hsel - 1];                        // row 2, column - 1 or + 1
-      uint32_t mid = x[2 * kRiRawStride];
-      asm volatile("" : "+v"(mid));                      // (read by every lane: no branch around the load)
-      b1[3] = __builtin_amdgcn_perm(hsel ? 0x3c00u : mid, side, 0x05040100u);          // (side | column), or (side | 1)
+      for (int kw = 0; kw < 3; ++kw) b1[kw] = ptr.rows[off + kw - 1];
+      b1[3] = __builtin_amdgcn_perm(ptr.mid[off], ptr.side[off], 0x05040100u);         // (side | column), or (side | 1)
       float16v acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(A1, __builtin_bit_cast(half8, b1), acc, 0, 0, 0);
       // y1 row q, channels 4 hsel .. + 3 of this lane's column: f16 of 2^8 d1
@@ -357,18 +376,37 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[0]), __float_as_uint(p[1] + p[2]), false, false);
       const float total = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
       if (n >= 1 && n <= kRiOut && output)
-        reinterpret_cast<float*>(s_part)[(hf * kRiPassCols + at - 4) * 2 + hsel] = total;
+        ptr.part[2 * off] = total;
     };
     // (The first and the last entry of a list that is not empty are neighbours, not outputs.)
+    int e0 = wsub * kRiOut, e_next = e0 + 2 * kRiOut;
+    if (dense) {                                           // (the same for the whole wave)
+      const bool head = c0 == 0 && wsub == 0;              // its first piece holds the column beside the tile
+      int e = head ? e_next : e0;
+      const int last = min(count, nb_cur - c0 + 1) - 32;   // first entry of the last piece inside the tile and the list
+      Words ptr = words_of(3 + e + n);
 #pragma unroll 1
-    for (int e0 = wsub * kRiOut; e0 + 2 < count; e0 += 2 * kRiOut) {
-      const int e = e0 + n, lo = c0 - 1 + e0;              // (lo: lowest column of a dense list's piece)
-      if (dense && lo >= 0 && lo + 31 < nb_cur) {          // (the same for the whole wave)
-        piece(3 + e, e <= len, std::false_type{});
-      } else {
-        const uint32_t entry = dense ? (uint32_t)min(3 + e, 4 + len) | (e > 0 ? kRiIsOutput : 0u) : s_list[min(e, count - 1)];
-        piece(entry & ~kRiIsOutput, e < count - 1 && (entry & kRiIsOutput), std::true_type{});
+      for (; e + 2 * kRiOut <= last; e += 4 * kRiOut) {
+        piece(ptr, 0, 0, true, std::true_type{});
+        piece(ptr, 2 * kRiOut, 0, true, std::true_type{});
+        ptr.rows += 4 * kRiOut;
+        ptr.side += 4 * kRiOut;
+        ptr.mid += hsel ? 0 : 4 * kRiOut;
+        ptr.part += 8 * kRiOut;
       }
+      if (e <= last) {
+        piece(ptr, 0, 0, true, std::true_type{});
+        e += 2 * kRiOut;
+      }
+      if (head) e_next = e;
+      else { e0 = e; e_next = e + 2 * kRiOut; }
+    }
+#pragma unroll 1
+    for (; e0 + 2 < count; e0 = e_next, e_next += 2 * kRiOut) {
+      const int e = e0 + n;
+      const uint32_t entry = dense ? (uint32_t)min(3 + e, 4 + len) | (e > 0 ? kRiIsOutput : 0u) : s_list[min(e, count - 1)];
+      const int at = entry & ~kRiIsOutput;
+      piece(words_of(at), 0, c0 - 4 + at, e < count - 1 && (entry & kRiIsOutput), std::false_type{});
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wave's pieces of the next pass are in LDS
     __syncthreads();
@@ -377,10 +415,14 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
       const uint32_t rel = tid + 256 * i;
       if (rel < (uint32_t)len) {
         float2 top = s_part[rel], bot = s_part[kRiPassCols + rel];
-        const uint32_t word = (rel + 4) >> 5, bit = (rel + 4) & 31;
-        const bool has_top = (s_epi[word] >> bit) & 1u, has_bot = (s_epi[16 + word] >> bit) & 1u;
-        if (!has_top) top = make_float2(0.f, 0.f);       // (a column that is no output has no partial sums)
-        if (!has_bot) bot = make_float2(0.f, 0.f);
+        bool has_top = true, has_bot = true;
+        if (!all_dense) {                                // a column that is no output has no partial sums
+          const uint32_t word = (rel + 4) >> 5, bit = (rel + 4) & 31;
+          has_top = (s_epi[word] >> bit) & 1u;
+          has_bot = (s_epi[16 + word] >> bit) & 1u;
+          if (!has_top) top = make_float2(0.f, 0.f);
+          if (!has_bot) bot = make_float2(0.f, 0.f);
+        }
         float st = pst[i];
         if (advance && (has_top || has_bot)) {
           st = (st - top.x * kUnscale) + bot.x * kUnscale;

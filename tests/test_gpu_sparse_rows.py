@@ -128,3 +128,37 @@ def test_tile_end_beside_a_short_last_pass(n, nb, last):
     off = (pred[:, :nb].cpu().double() - ref).abs() - bound - 1e-7
     assert off.max() <= 0, f"{(off > 0).sum()} columns, worst {off.max():.3g} at {np.unravel_index(int(off.argmax()), off.shape)}"
     assert bound.max() < 0.1
+
+
+@pytest.mark.parametrize("n,nb,H", [(1024, 376, 6), (128, 2735, 6), (1040, 377, 7), (6, 12433, 6), (3, 31, 9), (2, 33, 6), (1, 1, 6),
+                                    (9, 500, 64)])
+def test_dense_history_every_column(n, nb, H):
+    """Passes in which every column has a value look nothing up: all of them, all but one column in one half, all but a run in
+    both, changing as the rows move on; every column against float64."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    c, b = 8, 8
+    ctx = ap.Context(n_inst=n, g=1, head_dim=64, block=b, hist_len=H, t_cap=(nb + 3) * b, k_blocks=2, n_sink=1, n_local=1,
+                     c1=c, c2=c, kv_dtype="bf16")
+    rng = np.random.default_rng(nb + H)
+    blob = (rng.standard_normal(n_weight_floats(c, c)) * 0.2).astype(np.float32)
+    ctx.set_weights(blob)
+    R, cap = ctx.hist_slots(), ctx.nb_cap()
+    hist = torch.zeros((n, R, cap), device=dev)
+    hist[:, :, :nb] = torch.from_numpy(rng.uniform(1e-3, 0.5, (n, R, nb)).astype(np.float32)).to(dev)
+    n_pushed = 3 * R
+    hist[0, [(n_pushed + i) % R for i in range(5)], nb // 2] = 0.0          # the top half's rows, or most of them
+    hist[n - 1, :, nb // 3:nb // 3 + 40] = 0.0
+    row, pred, pstate = (torch.zeros((n, cap), device=dev) for _ in range(3))
+    ws = torch.zeros((max(16, ctx.workspace_bytes()),), dtype=torch.uint8, device=dev)
+    for step in range(4):
+        if step:
+            row[:, :nb] = torch.from_numpy(rng.uniform(1e-3, 0.5, (n, nb)).astype(np.float32))
+            ctx.update_history(hist, n_pushed, row)
+            n_pushed += 1
+        mode = ap.AP_PRED_ADVANCE if step else ap.AP_PRED_REBASE
+        ctx.predict_incremental(hist, n_pushed, nb, nb, mode, pstate, pred, ws)
+        window = hist[:, [(n_pushed - H + r) % R for r in range(H)], :nb].cpu()
+        ref, bound = _reference(window, blob, c, c)
+        off = (pred[:, :nb].cpu().double() - ref).abs() - bound * (2 if step else 1) - 1e-7
+        assert off.max() <= 0, f"step {step}: {(off > 0).sum()} columns, worst {off.max():.3g} at {np.unravel_index(int(off.argmax()), off.shape)}"
