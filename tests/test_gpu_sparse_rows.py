@@ -60,14 +60,20 @@ def _passes(n, nb):
 
 
 @pytest.mark.parametrize("c1,c2", [(8, 8), (16, 32)])
-@pytest.mark.parametrize("n,nb,H", [
-    (1040, 752, 8),      # more passes than the chip holds workgroups: two of 376 columns per instance
-    (1040, 377, 6),      # a column more than a pass
-    (9, 1130, 64),       # few instances: many short passes
-    (5, 5, 6), (5, 1, 7), (3, 30, 9), (3, 31, 9), (3, 33, 9), (3, 64, 9),
+@pytest.mark.parametrize("n,nb,H,cols,last", [
+    (1040, 752, 8, 251, 250),      # more passes than the chip holds workgroups
+    (1040, 377, 6, 189, 188),      # a column more than the longest pass
+    (512, 752, 6, 376, 376),       # two of the longest passes per instance, all workgroups at once
+    (1100, 376, 6, 188, 188), (1024, 376, 6, 376, 376),
+    (128, 2735, 6, 342, 341),      # passes that end in the last of the staged pieces of 64 columns
+    (9, 1130, 64, 103, 100),       # few instances: many short passes
+    (1, 12433, 6, 112, 1),         # the last pass is one column: the one before reaches beyond the tile
+    (2, 12434, 6, 112, 2), (1, 12435, 6, 112, 3), (1, 12436, 6, 112, 4),
+    (5, 5, 6, 5, 5), (5, 1, 7, 1, 1), (3, 30, 9, 30, 30), (3, 31, 9, 31, 31), (3, 33, 9, 33, 33), (3, 64, 9, 64, 64),
 ])
-def test_sparse_history_every_column(n, nb, H, c1, c2):
+def test_sparse_history_every_column(n, nb, H, cols, last, c1, c2):
     import paper_2502_04077_amd as ap
+    assert _passes(n, nb) == (cols, last)
     dev = torch.device("cuda:0")
     if c1 == 16 and n > 100:
         n = 130                                           # (its tiles do not depend on the number of instances)
