@@ -306,7 +306,7 @@ void calibrate_stream_kernel(CalibArgs a) {
       {
         const bool inside = ps + 1 < npass;              // (one load site: the rows have one source on the way round)
         const CalibUnit w = inside ? u : v;
-        load_k(w, inside ? place : place_v, inside ? ps + 1 : 0);
+        if (inside || more) load_k(w, inside ? place : place_v, inside ? ps + 1 : 0);
       }
       float4v lg = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
