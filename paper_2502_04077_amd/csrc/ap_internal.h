@@ -15,7 +15,8 @@ constexpr int kAttnWaves = kAttnThreads / kWave;
 constexpr int kNarrowPieceTokens = 512;       // tokens whose probabilities a two- or one-wave sparse-decode workgroup holds in LDS at a time
 constexpr int kMaxHist = 256;                 // longest history ap_create accepts
 constexpr int kGroupTokens = 16;              // tokens one wave covers per load group (4 x dwordx4 loads)
-constexpr int kCalibChunkTokens = 1024;       // tokens per calibration chunk, fp32 (bf16: Shape::calib_chunk_tokens)
+constexpr int kCalibChunkTokens = 1024;       // tokens per calibration chunk; bf16: at most (calib_chunk_tokens), and at least
+constexpr int kCalibMinChunkTokens = 256;     // (four blocks, one per wave)
 
 // Device-side layout of the predictor weights (all fp32), re-packed by ap_set_weights so that the
 // weights one inner loop iteration needs are contiguous:
@@ -29,7 +30,7 @@ constexpr int kCalibChunkTokens = 1024;       // tokens per calibration chunk, f
 // context; a Shape points at it, so that copies of a Shape (the offload calls make two) share the answers.
 struct Occupancy {
   int sparse_slots[3] = {-1, -1, -1};   // sparse-decode workgroups in the four-, two- and one-wave form
-  int calib_slots = -1;                 // calibration workgroups
+  int calib_slots[3] = {-1, -1, -1};    // calibration workgroups, chunks of 1024, 512 and 256 tokens
 };
 
 struct Shape {
@@ -37,7 +38,7 @@ struct Shape {
   int predictor_mfma; // incremental predictor on f16 MFMA (8/8 and 16/32 channels)
   int n_split;        // workgroups per instance in sparse decode
   Occupancy* occ;     // owned by the context, never null
-  int calib_chunk_tokens, calib_chunks;   // calibrate: tokens that leave one (maximum, sum); most such chunks per instance
+  int calib_chunks;   // calibrate: most chunks per instance, each of which leaves one (maximum, sum)
   const int32_t* table;  // device block table of a paged K/V cache [n_inst][nb_cap], or null (caller-owned)
   int n_phys;            // physical blocks in the pool
   bool k_on_host;        // launch_calibrate: K is pinned host memory

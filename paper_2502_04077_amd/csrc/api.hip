@@ -53,16 +53,13 @@ static int choose_split(const Shape& s) {
   return (s.k + per - 1) / per;
 }
 
-// Tokens of a calibration unit (and of the chunks the merge sees): 1024, or in bf16 512 or 256 where that leaves the chip
-// without a workgroup for every place it has (8 instances at 32K: 1032 units of 256 tokens instead of 264 of 1024), unless
-// the merge would have more than 60000 bytes of factors.  At least four blocks, one per wave.
-static int choose_calib_chunk(const Shape& s) {
-  int tokens = kCalibChunkTokens;
-  if (s.kv_dtype != AP_BF16) return tokens;
-  while (tokens > 256 && (size_t)s.n_inst * s.t_cap / tokens < 1024 &&
-         (2 * (size_t)s.t_cap / tokens + 2) * s.g * sizeof(float) <= 60000)
-    tokens /= 2;
-  return tokens;
+// Most chunks an instance can have in calibration (calib_chunk_tokens): t_cap in chunks of 1024 tokens, or in the bf16 form, whose
+// chunks are shorter where there are fewer than 1024 in all, up to 2048 of them over the instances.
+static int most_calib_chunks(const Shape& s) {
+  const int full = (s.t_cap + kCalibChunkTokens - 1) / kCalibChunkTokens;
+  if (s.kv_dtype != AP_BF16) return full;
+  const int least = (s.t_cap + kCalibMinChunkTokens - 1) / kCalibMinChunkTokens, filled = 2048 / s.n_inst + 1;
+  return full > filled ? full : (least < filled ? least : filled);
 }
 
 }  // namespace ap
@@ -117,8 +114,7 @@ int ap_create(const ap_config* c, ap_ctx** out) {
     const size_t chunks = (s.nb_cap + chunk_blocks - 1) / chunk_blocks;
     if (chunks * s.g * sizeof(float) > 60000) { delete ctx; return AP_ERR_UNSUPPORTED; }
   }
-  s.calib_chunk_tokens = ap::choose_calib_chunk(s);
-  s.calib_chunks = (s.nb_cap + s.calib_chunk_tokens / s.b - 1) / (s.calib_chunk_tokens / s.b);
+  s.calib_chunks = ap::most_calib_chunks(s);
   s.table = nullptr;
   s.n_phys = 0;
   s.k_on_host = false;

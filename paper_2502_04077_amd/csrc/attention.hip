@@ -506,13 +506,32 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   }
 }
 
+// Tokens of a calibration unit (and of the chunks the merge sees): 1024, or in bf16 512 or 256 where that leaves the chip
+// without a workgroup for every place it has (8 instances at 32K: 1032 units of 256 tokens instead of 264 of 1024; 8 at 8K with
+// room for 128K 13.2 -> 9.5 us), unless the merge would have more than 60000 bytes of factors.
+int calib_chunk_tokens(const Shape& s, int t_cur) {
+  int tokens = kCalibChunkTokens;
+  if (s.kv_dtype != AP_BF16) return tokens;
+  while (tokens > kCalibMinChunkTokens && (size_t)s.n_inst * t_cur / tokens < 1024 &&
+         (2 * (size_t)t_cur / tokens + 2) * s.g * sizeof(float) <= 60000 && (2 * t_cur + tokens - 1) / tokens <= s.calib_chunks)
+    tokens /= 2;
+  return tokens;
+}
+
 template <typename T, int D, int G>
 hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
   if constexpr (std::is_same<T, bf16_t>::value) {
     a.ml_unit = 1.f;
-    const size_t quads = (a.chunk_blocks * (a.b / 4) + 4 * kAttnWaves - 1) / kAttnWaves;
-    const size_t lds = (size_t)kAttnWaves * ((kGroupTokens + G) * (D * 2 + kStageRowPad) + sizeof(float) * G * quads);
-    if (s.occ->calib_slots < 0) s.occ->calib_slots = resident_workgroups(calibrate_stream_kernel<D, G>, kAttnThreads, lds);
+    auto lds_of = [&](int tokens) {
+      const size_t quads = (tokens / 4 + 4 * kAttnWaves - 1) / kAttnWaves;
+      return (size_t)kAttnWaves * ((kGroupTokens + G) * (D * 2 + kStageRowPad) + sizeof(float) * G * quads);
+    };
+    const int tokens = a.chunk_blocks * a.b;
+    const size_t lds = lds_of(tokens);
+    if (s.occ->calib_slots[0] < 0)
+      for (int i = 0; i < 3; ++i)
+        s.occ->calib_slots[i] = resident_workgroups(calibrate_stream_kernel<D, G>, kAttnThreads, lds_of(kCalibChunkTokens >> i));
+    const int slots = s.occ->calib_slots[tokens == kCalibChunkTokens ? 0 : tokens == kCalibChunkTokens / 2 ? 1 : 2];
     a.n_units = a.n_chunks * s.n_inst;
     // As many units as fit at once: one workgroup each, no counter.  More: two workgroups a CU take them off the counter.
     // Eight waves a CU keep memory busy, and more of them only spread the reads over more places (256 instances at
@@ -521,7 +540,7 @@ hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
     // Over PCIe 16 workgroups fill the link, and a thousand places at once cost it 15 % (8 instances at 32K, 67 MB, us: 16
     // workgroups 1178, 64 1190, 256 1272, 512 1358).
     const int most = s.k_on_host ? 16 : 512;
-    if (a.n_units <= (s.k_on_host ? most : s.occ->calib_slots)) {
+    if (a.n_units <= (s.k_on_host ? most : slots)) {
       a.counter = nullptr;
     } else {
       if (grid > most) grid = most;
@@ -530,8 +549,8 @@ hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
     calibrate_stream_kernel<D, G><<<dim3(grid), kAttnThreads, lds, st>>>(a);
   } else {
     const size_t lds = sizeof(float) * ((size_t)G * a.chunk_blocks * a.b + G * a.chunk_blocks + 2 * G + a.chunk_blocks);
-    if (s.occ->calib_slots < 0) s.occ->calib_slots = resident_workgroups(calibrate_f32_kernel<D, G>, kAttnThreads, lds);
-    const int slots = s.occ->calib_slots > 0 ? s.occ->calib_slots : 2048;
+    if (s.occ->calib_slots[0] < 0) s.occ->calib_slots[0] = resident_workgroups(calibrate_f32_kernel<D, G>, kAttnThreads, lds);
+    const int slots = s.occ->calib_slots[0] > 0 ? s.occ->calib_slots[0] : 2048;
     a.n_units = a.n_chunks * s.n_inst;
     zero_counter_kernel<<<1, 1, 0, st>>>(a.counter);
     calibrate_f32_kernel<D, G><<<dim3(a.n_units < slots ? a.n_units : slots), kAttnThreads, lds, st>>>(a);
@@ -610,7 +629,7 @@ hipError_t launch_calibrate(const Shape& s, const void* q, const void* K, int t_
   a.counter = reinterpret_cast<int*>(ws + wl.counters);
   a.t_cap = s.t_cap; a.nb_cap = s.nb_cap; a.b = s.b; a.log2b = ilog2(s.b); a.t_cur = t_cur;
   a.nb_cur = (t_cur + s.b - 1) / s.b;
-  a.chunk_blocks = s.calib_chunk_tokens / s.b;
+  a.chunk_blocks = calib_chunk_tokens(s, t_cur) / s.b;
   a.n_units = 0;
   a.ml_unit = kLog2E;
   a.n_chunks = (a.nb_cur + a.chunk_blocks - 1) / a.chunk_blocks;

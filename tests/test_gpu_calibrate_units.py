@@ -10,6 +10,36 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("n,g,d,b,cap,lengths", [
+    (8, 4, 128, 16, 131072, (1, 255, 256, 257, 8192, 32769, 131072)),      # units of 256 tokens, then 512, then 1024
+    (1, 8, 64, 8, 65536, (65536, 4096, 65535)), (300, 2, 64, 32, 8192, (700, 8192, 2048)), (2, 1, 128, 64, 300000, (299999, 20000)),
+])
+def test_lengths_in_one_cache(n, g, d, b, cap, lengths):
+    """The unit goes by the length of the call, not by the room there is: one context and workspace through several lengths, the
+    last one first again.  Against float64, tolerance as below (a third more for 300000 terms)."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    cap = -(-cap // b) * b
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=b, hist_len=8, t_cap=cap, k_blocks=1, n_sink=0, n_local=0, c1=4, c2=4,
+                     kv_dtype="bf16")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(cap)
+    K = torch.empty((n, cap, d), dtype=torch.bfloat16, device=dev).normal_(generator=gen)
+    q = (2 * torch.randn((n, g, d), generator=gen, device=dev)).to(torch.bfloat16)
+    size = max(16, ctx.workspace_bytes())
+    ws = torch.full((size + 4096,), 255, dtype=torch.uint8, device=dev)
+    for t in lengths + lengths[:1]:
+        row = torch.full((n, cap // b), 7.0, device=dev)
+        ctx.calibrate(q, K, t, row, ws)
+        for i in sorted({0, n // 2, n - 1}):
+            p = torch.softmax(q[i].double() @ K[i, :t].double().T.contiguous() / math.sqrt(d), dim=1)
+            ref = torch.zeros((g, cap), dtype=torch.float64, device=dev)
+            ref[:, :t] = p
+            ref = ref.view(g, cap // b, b).amax(dim=(0, 2))
+            assert (row[i].double() - ref).abs().max() <= 2.7e-5 * ref.max(), (t, i)
+    assert (ws[size:] == 255).all()                       # nothing is written beyond the workspace
+
+
 @pytest.mark.parametrize("n,g,d,b,t,paged", [
     (1, 4, 128, 16, 1, False), (1, 4, 128, 8, 15, False), (2, 1, 64, 8, 257, True), (3, 8, 128, 32, 255, False),
     (2, 2, 64, 64, 1025, True), (1, 4, 128, 16, 4097, False), (33, 4, 128, 16, 32001, False), (70, 2, 128, 8, 16385, True),
