@@ -422,7 +422,7 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 // Workgroups per instance the streaming form uses, of the a.n_split that the workspace has room for: the number with the least
 // time by this reckoning.  The fullest of 256 CUs has r = ceil(workgroups / 256) of them and takes r shares of a list, at 32 KB
 // a us where it has one workgroup (20 at d = 64, whose workgroups have half the bytes on their way), 29 with two and 22.5
-// with more, when all of memory is busy; a merge costs 3.6 us and 0.03 a split.  So few instances are split until every
+// with more, when all of memory is busy; a merge costs 3 us, 0.03 a split and 0.006 an instance.  So few instances are split until every
 // CU has work, and 280 are not left with two lists on 24 CUs and one on the others.  No split is shorter than two passes a wave (128
 // tokens), 64 to merge at most unless LDS asks for more.  (Over 1 to 1000 instances, lists of 256 to 16384 tokens, g = 1 to 8,
 // both head sizes, wherever it takes 14 us or more, the choice is 1.3 % from the best one.  Decode + merge in us, d = 128, bf16,
@@ -437,7 +437,7 @@ template <int D> int stream_splits(const SparseArgs& a, int ninst, int g) {
   for (int u = best, first = best; u <= a.n_split && (u == first || (u <= 64 && tokens >= 128L * u)); ++u) {
     const long r = ((long)u * ninst + 255) / 256;
     const double kb_per_us = r == 1 ? (D == 128 ? 32.0 : 20.0) : r == 2 ? 29.0 : 22.5;
-    const double us = r * (4e-3 * D * tokens / u) / kb_per_us + (u > 1 ? 3.6 + 0.03 * u : 0.0);
+    const double us = r * (4e-3 * D * tokens / u) / kb_per_us + (u > 1 ? 3.0 + 0.03 * u + 0.006 * ninst : 0.0);
     if (u == first || us < best_us) { best = u; best_us = us; }
   }
   return best;
