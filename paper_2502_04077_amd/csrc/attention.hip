@@ -32,7 +32,7 @@ void sparse_stream_kernel(SparseArgs a) {
 // to factors scale[part * G + h] = exp2((m - M) unit) / L in LDS (0 for an empty part or an empty whole); unit is 1 where the
 // maxima are in units of log2, log2(e) for natural ones.  Every value is fetched by
 // a thread of its own, all at once: a thread that walks the parts of a head waits for memory once per part.  Calibration
-// merge: 33 -> 11 us for 128 instances of 129 chunks, 10 -> 4 us for 8 of 33; sparse decode: 6.4 -> 3.8 us for 8 instances
+// merge: 33 -> 10 us for 128 instances of 129 chunks, 10 -> 4 us for 8 of 33; sparse decode: 6.4 -> 3.8 us for 8 instances
 // of 16 splits, 12.7 -> 8.9 us for 128 of 17.  Called by every thread of the workgroup; ends with a barrier.
 template <int G>
 __device__ __forceinline__ void merge_scales(const float2* __restrict__ ml, int n_part, float unit, float* scale) {
@@ -200,9 +200,9 @@ __global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a
 // the block maxima).  The waves meet once per unit, to bring their maxima and sums together and to hear the id of the unit
 // after the next.  A launch with no more units than the chip holds workgroups gives each its own and needs no counter.
 // Measured with the merge, against the phased form (all logits of a unit, then softmax, barriers between; four workgroups
-// a CU, first units off the counter too): 8 instances at 32K 31.8 -> 17.2 us (units of 256 tokens instead of 1024, no
-// launch to clear the counter, the merge), 64 at 50K 157 -> 144, 256 at 50K 535 -> 520 (6.3 TB/s), 128 at 128K 723 -> 685,
-// 1024 at 32K 1379 -> 1352, 256 at 50K with g = 1 521 -> 500.
+// a CU, first units off the counter too), both in turn on one card: 8 instances at 32K 31.8 -> 16.6 us (units of 256 tokens
+// instead of 1024, no launch to clear the counter, the merge), 32 at 32K 70 -> 44-50, 256 at 50K 535 -> 521 (6.3 TB/s), 128 at 128K
+// 711 -> 682 (23 of it in the merge), 1024 at 32K 1379 -> 1352.
 struct CalibUnit { int inst, chunk, nblk, c0; };
 
 template <int D, int G>

@@ -635,8 +635,8 @@ constexpr int kChainPasses = 8;
 // present ones are staged, V rows as soon as the present ones are used, and a wave always has some 8 KiB on its way.
 // sparse_decode_body goes through phases instead - all logits, softmax, all V - with barriers between them and the
 // probabilities of the list in LDS.  With few instances, where nothing else fills the gaps, this form is the faster one
-// (decode + merge, 1024-token lists, d = 128, g = 4: 8 instances 13.5 -> 10.0 us, 256 instances 31.8 -> 28.5 us; 640 x 2048
-// tokens, g = 8: 142 -> 126 us).  With 1024 instances and more, g <= 4, the phases win (2048 instances: 177 against 190 us;
+// (decode + merge, both in turn on one card: 1024-token lists, d = 128, g = 4, 8 instances 13.2 -> 10.5 us, 300 instances 37 -> 33 us;
+// 640 x 2048 tokens, g = 8, 129 -> 121 us; over 1607 sizes of up to 1000 instances 27 % less).  With 1024 instances and more, g <= 4, the phases win (2048 instances: 177 against 190 us;
 // 4096, g = 1: 337 against 373): on scattered blocks a stream that alternates between K and V reaches 5.85 TB/s,
 // however many waves have loads on their way, and one that stays in one of the two for a while 6.25.
 //

@@ -1,4 +1,4 @@
-"""The streaming form of sparse decode (bf16 lists cut into splits, whole lists of 256 to 1023 instances, g = 8), at the sizes
+"""The streaming form of sparse decode (bf16 lists of fewer than 1024 instances, split or whole, and g = 8), at the sizes
 where it can go wrong, against the oracle: lists that end half way into a 16-token pass, one token, empty lists, contexts
 that end inside a block (with NaN rows behind), blocks of 8 to 64, paged caches.  Tolerance: fp32 sums of at most 2048
 bf16 products and exponentials good to 2 ulp, 2^-24 sqrt(2048) x a few: 2e-5 of the largest value."""
@@ -17,13 +17,15 @@ pytestmark = pytest.mark.gpu
     (3, 1, 64, 8, 17, 301, True),
     (5, 2, 128, 16, 64, 1600, False),      # two passes a wave
     (2, 8, 64, 64, 9, 1025, False),        # one token in the last block of 64
-    (256, 4, 128, 16, 8, 333, False),      # first size with one workgroup per instance
+    (256, 4, 128, 16, 8, 333, False),      # one workgroup per instance and CU
     (300, 2, 64, 32, 5, 257, True),
     (260, 8, 128, 8, 41, 999, False),
     (300, 1, 128, 16, 24, 401, False),
     (520, 8, 128, 16, 20, 777, True),
     (1030, 8, 64, 16, 7, 500, False),      # whole lists, g = 8
-    (2, 4, 128, 16, 600, 16001, False),    # a long list: splits longer than a piece
+    (2, 4, 128, 16, 600, 16001, False),    # a long list in many short splits
+    (128, 4, 128, 16, 600, 16001, False),  # ... and in two of 4800 tokens, several sets of sums a wave
+    (280, 2, 64, 32, 60, 2500, True),      # a second workgroup for some CUs unless the lists are split
     (40, 4, 128, 16, 2, 40, False),        # fewer tokens than a workgroup has lanes
 ])
 def test_stream_decode_vs_oracle(n, g, d, b, k, t, paged):
