@@ -37,7 +37,8 @@
 // Measured at 2048 instances x 2050 columns (0.20 GB to move: 31 us at the rate a plain read reaches), histories of 64
 // selected blocks in runs: 45.5 us, with all columns evaluated 67-69; an all-zero history 37 us (66), 128 instances x 8194
 // columns 14.2 us (22.9).  Where both halves have a value in every column of a pass (the first five steps after a prefill) nothing is
-// looked up and the pieces inside the tile take a loop of their own, without a test or an address of their own: 76 us, against 73
+// looked up and the pieces inside the tile take a loop of their own, without a test or an address of their own: 76 us (up to 90 in the
+// launches right after a prefill), against 73
 // for a kernel that only knows dense histories and reads the f16 words of row 2 in pairs (82-84 us with the lists made in any
 // case); there the SIMDs are full of vector instructions (62 a piece at four cycles) and MFMAs, which overlap in part
 // only.  A single pass per workgroup, 1 to 8 instances, takes 0.2 us longer than in that kernel: bits, barrier, list.
