@@ -4,13 +4,13 @@
 namespace ap {
 namespace {
 
-template <int KPT, int NT>
+template <int KPT, int NT, int GR>
 __global__ __launch_bounds__(NT) void select_topk_kernel(const float* __restrict__ pred, int nb_cap, int nb_cur, int k,
                                                          int n_sink, int n_local, int inst0,
                                                          int32_t* __restrict__ idx, int32_t* __restrict__ cnt) {
-  __shared__ uint32_t s_mem[sel_scratch_words<NT>()];
+  __shared__ __align__(16) uint32_t s_mem[sel_scratch_words<NT>()];
   const int inst = inst0 + blockIdx.x;
-  select_topk_body<KPT, NT>(pred + (size_t)inst * nb_cap, nb_cur, k, n_sink, n_local, idx + (size_t)inst * k,
+  select_topk_body<KPT, NT, GR>(pred + (size_t)inst * nb_cap, nb_cur, k, n_sink, n_local, idx + (size_t)inst * k,
                             cnt + inst, s_mem);
 }
 
@@ -75,31 +75,47 @@ hipError_t launch_refresh_selection(const Shape& s, int nb_prev, int nb_cur, int
 
 hipError_t launch_select(const Shape& s, int inst0, int ninst, const float* pred, int nb_cur, int32_t* idx,
                          int32_t* cnt, hipStream_t st) {
-  const int n_mid = nb_cur - s.n_sink - s.n_local;
+  const int n_mid = nb_cur - s.n_sink - s.n_local, k_mid = s.k - s.n_sink - s.n_local;
   const dim3 grid(ninst);
-#define AP_SELECT_NT(KPT, NT) \
-  select_topk_kernel<KPT, NT><<<grid, NT, 0, st>>>(pred, s.nb_cap, nb_cur, s.k, s.n_sink, s.n_local, inst0, idx, cnt)
-#define AP_SELECT(KPT) AP_SELECT_NT(KPT, kSelThreads)
-  // Few instances with long rows: 1024 threads per instance cut the serial chain of every pass (a 256-thread
-  // workgroup walks 32 keys per thread at 128K context while half of the chip has no workgroup at all).
-  if (ninst <= 512 && n_mid > 4 * kSelThreads) {
-    if (n_mid <= 4 * kSelThreadsWide) AP_SELECT_NT(4, kSelThreadsWide);
-    else if (n_mid <= 8 * kSelThreadsWide) AP_SELECT_NT(8, kSelThreadsWide);
-    else if (n_mid <= 9 * kSelThreadsWide) AP_SELECT_NT(9, kSelThreadsWide);     // (a 128K context that has grown a little)
-    else if (n_mid <= 12 * kSelThreadsWide) AP_SELECT_NT(12, kSelThreadsWide);
-    else if (n_mid <= 16 * kSelThreadsWide) AP_SELECT_NT(16, kSelThreadsWide);
-    else AP_SELECT_NT(0, kSelThreadsWide);
+#define AP_SELECT(KPT, NT, GR) \
+  select_topk_kernel<KPT, NT, GR><<<grid, NT, 0, st>>>(pred, s.nb_cap, nb_cur, s.k, s.n_sink, s.n_local, inst0, idx, cnt)
+  // By a bound, where its groups are at least twice the free places and the keys fit the registers: 128 groups up to 64 places (2048
+  // instances of 2041 candidates, 56 places: 8.1 us, 8.7 with 256 groups), 256 up to 128.  Threads: as many as leave the launch
+  // one round of workgroups and every thread some eight keys (us at 256 / 512 / 1024 threads: 8 instances x 2041 4.4 / 4.0 / 4.3,
+  // 128 x 8186 10.8 / 7.3 / 6.8, 640 x 3742 6.5 / 6.4 / 11.0, 2048 x 2041 8.1 / 10.4 / 17.6).
+#define AP_SELECT_BOUND(KPT, NT) \
+  if (n_mid <= KPT * NT) { \
+    if (k_mid <= 64) AP_SELECT(KPT, NT, 2); else AP_SELECT(KPT, NT, 4); \
+    return hipGetLastError(); \
   }
-  else if (n_mid <= 8 * kSelThreads) AP_SELECT(8);       // the variants differ only in unrolled trip count
-  else if (n_mid <= 9 * kSelThreads) AP_SELECT(9);
-  else if (n_mid <= 10 * kSelThreads) AP_SELECT(10);
-  else if (n_mid <= 12 * kSelThreads) AP_SELECT(12);
-  else if (n_mid <= 16 * kSelThreads) AP_SELECT(16);
-  else if (n_mid <= 24 * kSelThreads) AP_SELECT(24);
-  else if (n_mid <= 32 * kSelThreads) AP_SELECT(32);
-  else AP_SELECT(0);
+  if (k_mid >= 1 && k_mid <= kSelMaxMid) {
+    if (ninst > 1024 || n_mid <= 1024 || (ninst > 512 && n_mid <= 4096)) {
+      AP_SELECT_BOUND(4, 256) AP_SELECT_BOUND(8, 256) AP_SELECT_BOUND(9, 256) AP_SELECT_BOUND(12, 256)
+      AP_SELECT_BOUND(16, 256) AP_SELECT_BOUND(24, 256) AP_SELECT_BOUND(32, 256)
+    } else if (ninst > 512 || n_mid <= 4096) {
+      AP_SELECT_BOUND(4, 512) AP_SELECT_BOUND(6, 512) AP_SELECT_BOUND(8, 512) AP_SELECT_BOUND(12, 512) AP_SELECT_BOUND(16, 512)
+    } else {
+      AP_SELECT_BOUND(8, 1024) AP_SELECT_BOUND(9, 1024) AP_SELECT_BOUND(12, 1024) AP_SELECT_BOUND(16, 1024)
+    }
+  }
+#undef AP_SELECT_BOUND
+  // The radix select alone.  Few instances with long rows: 1024 threads per instance cut the serial chain of every pass (a
+  // 256-thread workgroup walks 32 keys per thread at 128K context while half of the chip has no workgroup at all).
+  if (ninst <= 512 && n_mid > 4 * kSelThreads) {
+    if (n_mid <= 4 * kSelThreadsWide) AP_SELECT(4, kSelThreadsWide, 0);
+    else if (n_mid <= 8 * kSelThreadsWide) AP_SELECT(8, kSelThreadsWide, 0);
+    else if (n_mid <= 9 * kSelThreadsWide) AP_SELECT(9, kSelThreadsWide, 0);     // (a 128K context that has grown a little)
+    else if (n_mid <= 12 * kSelThreadsWide) AP_SELECT(12, kSelThreadsWide, 0);
+    else if (n_mid <= 16 * kSelThreadsWide) AP_SELECT(16, kSelThreadsWide, 0);
+    else AP_SELECT(0, kSelThreadsWide, 0);
+  }
+  else if (n_mid <= 8 * kSelThreads) AP_SELECT(8, kSelThreads, 0);       // the variants differ only in unrolled trip count
+  else if (n_mid <= 12 * kSelThreads) AP_SELECT(12, kSelThreads, 0);
+  else if (n_mid <= 16 * kSelThreads) AP_SELECT(16, kSelThreads, 0);
+  else if (n_mid <= 24 * kSelThreads) AP_SELECT(24, kSelThreads, 0);
+  else if (n_mid <= 32 * kSelThreads) AP_SELECT(32, kSelThreads, 0);
+  else AP_SELECT(0, kSelThreads, 0);
 #undef AP_SELECT
-#undef AP_SELECT_NT
   return hipGetLastError();
 }
 

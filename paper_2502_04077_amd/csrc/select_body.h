@@ -1,6 +1,8 @@
 // Top-K block selection (Algorithm 1 step 5) with forced sink / local blocks (Sec. 4.1).
 //
-// One workgroup per instance.  Scores are mapped to order-preserving 32-bit keys; a 4-pass
+// One workgroup per instance.  Scores are mapped to order-preserving 32-bit keys.  With up to 128 free places the few keys
+// that reach a lower bound of the last one are ranked against each other (select_by_bound).  With more, or where too many keys
+// reach the bound (scores that all but coincide), a 4-pass
 // radix select (8 bits per pass, histogram in LDS) finds the key T of the k_mid-th largest score
 // and how many scores equal to T are still needed.  A final ordered sweep keeps every block with
 // key > T and the first `need` blocks with key == T, compacting in index order, so the output is
@@ -17,7 +19,12 @@ namespace {
 constexpr int kSelThreads = 256;           // workgroup size of the common variant
 constexpr int kSelThreadsWide = 1024;      // few instances, long rows: more threads per instance
 constexpr int kSelBins = 256;              // radix of one pass; the first kSelBins threads own one bin each
-template <int NT> constexpr int sel_scratch_words() { return kSelBins + 3 * (NT / kWave) + 8; }
+constexpr int kSelRanked = 256;            // select_by_bound: most keys it ranks against each other
+constexpr int kSelMaxMid = 128;            // ... and most free places it fills
+template <int NT> constexpr int sel_scratch_words() {
+  constexpr int radix = kSelBins + 3 * (NT / kWave) + 8, bound = 2 * (kSelRanked + 16) + 8 * kWave + kSelMaxMid + 17;
+  return radix > bound ? radix : bound;
+}
 
 __device__ __forceinline__ uint32_t score_key(float x) {
   uint32_t u = __float_as_uint(x);
@@ -59,11 +66,121 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
+// The k_mid largest of the keys that the threads hold (0 where a thread has none; ties to the lower block), written to out in
+// ascending order of blocks - or false, and nothing written, if more than kSelRanked keys would have to be ranked.
+//   A lower bound of the k_mid-th largest key is the k_mid-th largest of the maxima of 64 GR groups of keys, GR of them in
+//   every lane: each wave finds one for itself by trying the key's bits from the top, until hardly more than k_mid maxima reach
+//   it.  With the large keys spread over the groups few more keys than that do (74 of 2041 for k_mid = 56 and 128
+//   groups); these are ranked by counting, for each, how many come before it, and the same again by block.
+// Three barriers and no histogram, where the radix select has three a pass and an LDS atomic per key (the scores of a decode run, us,
+// radix select -> this: 2048 instances of 2041 candidates 14.9 -> 8.1, 4096 25.6 -> 13.6, 128 of 8186 12.6 -> 6.8, 8 of
+// 2041 5.8 -> 4.0, one of 126 3.5 -> 2.6).  What is left is the chain: scores, 15-20 tried bits, one LDS atomic, two rounds of counting.
+template <int KPT, int NT, int GR>
+__device__ __forceinline__ bool select_by_bound(const uint32_t (&keys)[KPT], int first, uint32_t k_mid,
+                                                int32_t* __restrict__ out, uint32_t* s_mem) {
+  constexpr int kWaves = NT / kWave;
+  constexpr int kHolders = GR * kWave / kWaves;         // lanes of a wave that hold the maximum of a group
+  static_assert(kHolders == 64 || kHolders == 32 || kHolders == 16 || kHolders == 8, "groups are lanes, or lanes 32, 16, 8 apart");
+  // (what is read in fours reads past the end of a list into zeros, which count as nothing)
+  unsigned long long* s_cand = reinterpret_cast<unsigned long long*>(s_mem);   // [kSelRanked + 16] key | ~block: larger comes first
+  uint32_t* s_max = s_mem + 2 * (kSelRanked + 16);      // [64 GR]
+  uint32_t* s_sel = s_max + 8 * kWave;                  // [k_mid] ~block by rank
+  uint32_t* s_count = s_sel + kSelMaxMid + 16;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+
+  uint32_t gm = keys[0];
+#pragma unroll
+  for (int i = 1; i < KPT; ++i) gm = max(gm, keys[i]);
+  if constexpr (kHolders <= 32) {
+    const auto s = __builtin_amdgcn_permlane32_swap(gm, gm, false, false);
+    gm = max(s[0], s[1]);
+  }
+  if constexpr (kHolders <= 16) {
+    const auto s = __builtin_amdgcn_permlane16_swap(gm, gm, false, false);
+    gm = max(s[0], s[1]);
+  }
+  if constexpr (kHolders <= 8) gm = max(gm, dpp_u32<0x128, 0xF>(gm));          // row_ror:8
+  if (lane < kHolders) s_max[wave * kHolders + lane] = gm;
+  for (int i = tid; i < kSelRanked + 16; i += NT) s_cand[i] = 0ull;
+  for (int i = tid; i < kSelMaxMid + 17; i += NT) s_sel[i] = 0u;               // (and the count)
+  __syncthreads();
+  uint32_t g[GR];
+#pragma unroll
+  for (int r = 0; r < GR; ++r) g[r] = s_max[r * kWave + lane];
+  uint32_t T = 0;
+  const uint32_t enough = k_mid + (k_mid >> 3);
+#pragma unroll 1
+  for (uint32_t bit = 0x80000000u; bit != 0u; bit >>= 1) {
+    const uint32_t t = T | bit;
+    uint32_t c = 0;
+#pragma unroll
+    for (int r = 0; r < GR; ++r) c += (uint32_t)__popcll(__ballot(g[r] >= t));
+    if (c >= k_mid) {
+      T = t;
+      if (c <= enough) break;
+    }
+  }
+  T = max(T, 1u);                                       // (a thread without a key holds 0)
+
+  uint32_t mine = 0;                                    // keys of this wave that reach the bound
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) mine += (uint32_t)__popcll(__ballot(keys[i] >= T));
+  uint32_t at = 0;
+  if (mine != 0u) {
+    if (lane == 0) at = atomicAdd(s_count, mine);
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (at + mine <= (uint32_t)kSelRanked) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        const bool take = keys[i] >= T;
+        const unsigned long long m = __ballot(take);
+        if (take) s_cand[__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, at))] =
+            ((unsigned long long)keys[i] << 32) | (uint32_t)~(first + i * NT);
+        at += (uint32_t)__popcll(m);
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t n = *s_count;
+  if (n > (uint32_t)kSelRanked || n < k_mid) return false;   // (the same for every thread; too few: scores that are NaN)
+  // Four lanes a key, each counting a quarter of the others.
+  const uint32_t part = tid & 3;
+#pragma unroll 1
+  for (uint32_t c = tid >> 2; c < n; c += NT / 4) {
+    const unsigned long long x = s_cand[c];
+    uint32_t rank = 0;
+#pragma unroll 1
+    for (uint32_t o = 0; o < n; o += 16) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rank += s_cand[o + 4 * i + part] > x ? 1u : 0u;
+    }
+    rank += dpp_u32<0xB1, 0xF>(rank);                   // quad_perm [1,0,3,2]
+    rank += dpp_u32<0x4E, 0xF>(rank);                   // quad_perm [2,3,0,1]
+    if (part == 0 && rank < k_mid) s_sel[rank] = (uint32_t)x;
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (uint32_t c = tid >> 2; c < k_mid; c += NT / 4) {
+    const uint32_t x = s_sel[c];
+    uint32_t before = 0;
+#pragma unroll 1
+    for (uint32_t o = 0; o < k_mid; o += 16) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) before += s_sel[o + 4 * i + part] > x ? 1u : 0u;
+    }
+    before += dpp_u32<0xB1, 0xF>(before);
+    before += dpp_u32<0x4E, 0xF>(before);
+    if (part == 0) out[before] = (int32_t)~x;
+  }
+  return true;
+}
+
 // Selection for one instance by one workgroup of NT threads (a multiple of kSelBins).
 //   p        the instance's scores (nb_cur valid entries)
 //   out      the instance's k index slots, cnt_out its count
 //   s_mem    sel_scratch_words<NT>() words of LDS, free for this call (the caller synchronises before)
-template <int KPT, int NT>   // KPT: keys per thread held in registers; 0 = re-read the scores in every pass
+// KPT: keys per thread held in registers; 0 = re-read the scores in every pass.  GR > 0: by a bound first, k_mid in 1 .. 32 GR.
+template <int KPT, int NT, int GR>
 __device__ __forceinline__ void select_topk_body(const float* __restrict__ p, int nb_cur, int k, int n_sink, int n_local,
                                         int32_t* __restrict__ out, int32_t* __restrict__ cnt_out, uint32_t* s_mem) {
   constexpr int kSelThreads = NT, kSelWaves = NT / kWave;
@@ -93,6 +210,17 @@ __device__ __forceinline__ void select_topk_body(const float* __restrict__ p, in
       const int j = lo + i * kSelThreads + tid;
       keys[i] = score_key(p[min(j, hi - 1)]);
     }
+  }
+  auto forced = [&]() __attribute__((always_inline)) {
+    for (int j = tid; j < n_sink; j += kSelThreads) out[j] = j;
+    for (int j = tid; j < n_local; j += kSelThreads) out[k - n_local + j] = nb_cur - n_local + j;
+    if (tid == 0) *cnt_out = k;
+  };
+  if constexpr (GR > 0) {
+    uint32_t own[NK];
+#pragma unroll
+    for (int i = 0; i < NK; ++i) own[i] = lo + i * NT + tid < hi ? keys[i] : 0u;
+    if (select_by_bound<NK, NT, GR>(own, lo + tid, (uint32_t)k_mid, out + n_sink, s_mem)) { forced(); return; }
   }
   auto key_at = [&](int i, int j) __attribute__((always_inline)) -> uint32_t {
     if constexpr (KPT > 0) return keys[i]; else return score_key(p[min(j, hi - 1)]);
@@ -170,11 +298,8 @@ __device__ __forceinline__ void select_topk_body(const float* __restrict__ p, in
     eq_seen += eq_total;
     __syncthreads();
   }
-  for (int j = tid; j < n_sink; j += kSelThreads) out[j] = j;
-  for (int j = tid; j < n_local; j += kSelThreads) out[k - n_local + j] = nb_cur - n_local + j;
-  if (tid == 0) *cnt_out = k;
+  forced();
 }
-
 
 }  // namespace
 }  // namespace ap
