@@ -99,9 +99,11 @@ __host__ __device__ constexpr int ri_slot_row(int h, int e) { return e < 6 ? (h 
 __host__ __device__ constexpr int ri_slot_kw(int h, int e) { return e < 6 ? e / 2 : (h ? 2 : e - 6); }
 constexpr int kMfmaTableFloatOffset = 676;
 constexpr int kMfmaTableHalfs = 2 * 6 * 64 * 8 + 2 * 64 * 8;
-// ... and by the tables of the interior-state kernel (predict_interior.h): layer 2 [step 8][lane 64][8 f16],
-// layer 1 [lane 64][8 f16].
-constexpr int kMfmaInteriorTableHalfs = 8 * 64 * 8 + 64 * 8;
+// ... followed by the tables of the full-tile kernel (predict_rebase8.h): layer 2 [order 2][kw 3][lane 64][8 f16], lane (m = 8 o + c2,
+// g): entries 0..3 (order 0; 4..7 in order 1) belong to y1 row q = g / 2 of the strip's four, the others to q = 2 + g / 2, input
+// channel 4 (g % 2) + e % 4, kernel row q - o; layer 1 [lane 64][4 f16], lane (m = 8 q + c1, g): entry e is x row
+// 2 (g / 2) + e % 2 of the pair's four and tap e / 2 (g even), or 2 for e < 2 and none (g odd); kernel row = x row - q, scaled 2^-4.
+constexpr int kMfmaRebaseTableHalfs = 2 * 3 * 64 * 8 + 64 * 4;
 // The same for 16/32 channels (fp32 section: 10*16 + 9*16*32 + 2*32 + 1 = 4833 floats):
 // layer 2 [half 2][pair 8][kw 3][lane 64][8 f16], lane (m = lane % 32, h = lane / 32) holding input channels
 // 8h..8h+7 of output channel m for the kernel row that pair (q, o) stands for; then layer 1
@@ -116,7 +118,7 @@ constexpr int kMfma16PairO[8] = {0, 0, 1, 2, 0, 2, 1, 2};
 __host__ __device__ constexpr int mfma16_phys(int half, int i) { return (half == 1 && (i == 1 || i == 2)) ? 3 - i : i; }
 
 __host__ __device__ constexpr int delta_const_offset(int c1, int c2) {
-  return (c1 == 8 && c2 == 8)     ? kMfmaTableFloatOffset + (kMfmaTableHalfs + kMfmaInteriorTableHalfs) / 2
+  return (c1 == 8 && c2 == 8)     ? kMfmaTableFloatOffset + (kMfmaTableHalfs + kMfmaRebaseTableHalfs) / 2
          : (c1 == 16 && c2 == 32) ? kMfma16TableFloatOffset + (kMfma16TableHalfs + kMfma16InteriorTableHalfs) / 2
                                   : (10 * c1 + 9 * c1 * c2 + 2 * c2 + 1 + 3) / 4 * 4;
 }
@@ -126,7 +128,10 @@ __host__ __device__ constexpr int delta_const_offset(int c1, int c2) {
 // Launchers that take (inst0, ninst) work on instances [inst0, inst0 + ninst) of the same buffers.
 hipError_t launch_predict(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
                           int newest_slot, int nb_cur, int col_begin, float* pstate, float* pred, hipStream_t st);
-// Interior state (rows 2..H-3) of every column from scratch on MFMA (8/8 or 16/32 channels, H >= 6); the incremental
+// Interior state and pred of every column from scratch on MFMA (8/8 channels, H >= 6).
+hipError_t launch_predict_rebase8(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
+                                  int newest_slot, int nb_cur, float* pstate, float* pred, hipStream_t st);
+// Interior state (rows 2..H-3) of every column from scratch on MFMA (16/32 channels, H >= 6); the incremental
 // kernel without an advance then adds the border rows and writes pred.
 hipError_t launch_predict_interior(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
                                    int newest_slot, int nb_cur, float* pstate, hipStream_t st);

@@ -228,29 +228,26 @@ int ap_set_weights(ap_ctx* ctx, const float* blob, size_t n_floats, void* stream
         }
   }
   if (mfma_table) {
-    // Interior-state kernel: strips of three output rows o from five y1 rows q (kernel row q - o), and three y1
-    // rows q from five x rows (kernel row xrow - q); no row of it touches the zero padding in time.
+    // Full-tile kernel: strips of two output rows from two pairs of y1 rows, and a pair of y1 rows from two pairs of x rows.
     _Float16* t = reinterpret_cast<_Float16*>(packed.data() + ap::kMfmaTableFloatOffset) + ap::kMfmaTableHalfs;
-    for (int step = 0; step < 8; ++step)
-      for (int lane = 0; lane < 64; ++lane) {
-        const int m = lane % 32, chunk = 2 * step + lane / 32, q = chunk / 3, kw = chunk % 3;
-        const int kh = q - m / 8;
-        for (int ci = 0; ci < 8; ++ci) {
-          float v = 0.f;
-          if (m < 24 && chunk < 15 && kh >= 0 && kh < 3) v = w2[(((size_t)(m % 8) * c1 + ci) * 3 + kh) * 3 + kw];
-          t[(step * 64 + lane) * 8 + ci] = (_Float16)v;
-        }
-      }
-    _Float16* t1 = t + 8 * 64 * 8;
+    for (int order = 0; order < 2; ++order)
+      for (int kw = 0; kw < 3; ++kw)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int e = 0; e < 8; ++e) {
+            const int m = lane % 16, g = lane / 16, later = (e / 4) ^ order;
+            const int kh = 2 * later + g / 2 - m / 8, ci = 4 * (g % 2) + e % 4;
+            float v = 0.f;
+            if (kh >= 0 && kh < 3) v = w2[(((size_t)(m % 8) * c1 + ci) * 3 + kh) * 3 + kw];
+            t[((order * 3 + kw) * 64 + lane) * 8 + e] = (_Float16)v;
+          }
+    _Float16* t1 = t + 2 * 3 * 64 * 8;
     for (int lane = 0; lane < 64; ++lane)
-      for (int e = 0; e < 8; ++e) {
-        const int m = lane % 32, k = 8 * (lane / 32) + e;
+      for (int e = 0; e < 4; ++e) {
+        const int m = lane % 16, g = lane / 16;
+        const int kh = 2 * (g / 2) + e % 2 - m / 8, kw = g % 2 == 0 ? e / 2 : e < 2 ? 2 : -1;
         float v = 0.f;
-        if (m < 24 && k < 15) {
-          const int kh = k / 3 - m / 8, kw = k % 3;
-          if (kh >= 0 && kh < 3) v = w1[((m % 8) * 3 + kh) * 3 + kw] * (1.f / 16.f);
-        }
-        t1[lane * 8 + e] = (_Float16)v;
+        if (kw >= 0 && kh >= 0 && kh < 3) v = w1[((m % 8) * 3 + kh) * 3 + kw] * (1.f / 16.f);
+        t1[lane * 4 + e] = (_Float16)v;
       }
   }
   if (mfma16_table) {
@@ -365,9 +362,12 @@ static int run_predictor(const ap_ctx* ctx, const float* hist, int64_t n_pushed,
   const int newest = newest_slot_of(s, n_pushed);
   if (pstate == nullptr || mode == AP_PRED_REBASE || s.H < 6) {
     if (s.H >= 6 && s.predictor_mfma) {
-      // Full tile on MFMA: the interior state from scratch (into the caller's pstate, or into the workspace when
-      // the caller keeps none), then the borders and the head as in a HOLD call.
+      // Full tile on MFMA: the interior state from scratch (into the caller's pstate, or into the workspace when the caller
+      // keeps none) and pred in one launch; for 16/32 channels the state, then the borders and the head as in a HOLD call.
       float* state = pstate != nullptr ? pstate : ws + ap::ws_layout(s).pred_state;
+      if (s.c1 == 8)
+        return ap::launch_predict_rebase8(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, state, pred, st) == hipSuccess
+                   ? AP_OK : AP_ERR_HIP;
       if (ap::launch_predict_interior(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, state, st) != hipSuccess ||
           ap::launch_predict_inc(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, 0, state, pred, st) != hipSuccess)
         return AP_ERR_HIP;

@@ -30,6 +30,7 @@
 #include "predict_body16.h"
 #include "predict_inc8.h"
 #include "predict_interior.h"
+#include "predict_rebase8.h"
 
 namespace ap {
 namespace {
@@ -285,13 +286,14 @@ __global__ __launch_bounds__(256) void predict_inc_mfma16_kernel(const float* __
                           gridDim.x, advance, pstate, pred, smem);
 }
 
-__global__ __launch_bounds__(256) void predict_interior_mfma_kernel(const float* __restrict__ hist,
-                                                                    const float* __restrict__ wts_global, int R, int H,
-                                                                    int newest_slot, int nb_cur, int nb_cap, int inst0,
-                                                                    float* __restrict__ pstate) {
-  extern __shared__ __align__(16) float smem[];
-  predict_interior_mfma_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0 + blockIdx.y, blockIdx.x,
-                             gridDim.x, pstate, smem);
+template <int SW>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))   // four workgroups per CU, as LDS has room for
+void predict_rebase8_kernel(const float* __restrict__ hist, const float* __restrict__ wts_global, int R, int H, int newest_slot,
+                            int nb_cur, int nb_cap, int inst0, RebasePlan plan, float* __restrict__ pstate,
+                            float* __restrict__ pred) {
+  extern __shared__ __align__(16) uint32_t smem_u[];
+  predict_rebase8_body<SW>(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0 + blockIdx.y, blockIdx.x, plan, pstate, pred,
+                       smem_u);
 }
 
 __global__ __launch_bounds__(256) void predict_interior_mfma16_kernel(const float* __restrict__ hist,
@@ -462,17 +464,35 @@ hipError_t launch_predict(const Shape& s, int inst0, int ninst, const float* dwe
 
 hipError_t launch_predict_interior(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
                                    int newest_slot, int nb_cur, float* pstate, hipStream_t st) {
-  const bool c8 = s.c1 == 8 && s.c2 == 8, c16 = s.c1 == 16 && s.c2 == 32;
-  if (!(c8 || c16) || s.H < 6) return hipErrorInvalidValue;
+  if (s.c1 != 16 || s.c2 != 32 || s.H < 6) return hipErrorInvalidValue;
   const int groups = (nb_cur + 4 * kPiOut - 1) / (4 * kPiOut);
   int chunks = (2048 + s.n_inst - 1) / s.n_inst;         // about eight workgroups per CU when instances are few
   if (chunks > groups) chunks = groups;
-  if (c8)
-    predict_interior_mfma_kernel<<<dim3(chunks, ninst), 256, sizeof(float) * kPredInteriorLdsFloats, st>>>(
-        hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, pstate);
-  else
-    predict_interior_mfma16_kernel<<<dim3(chunks, ninst), 256, sizeof(float) * kPredInterior16LdsFloats, st>>>(
-        hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, pstate);
+  predict_interior_mfma16_kernel<<<dim3(chunks, ninst), 256, sizeof(float) * kPredInterior16LdsFloats, st>>>(
+      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, pstate);
+  return hipGetLastError();
+}
+
+hipError_t launch_predict_rebase8(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
+                                  int newest_slot, int nb_cur, float* pstate, float* pred, hipStream_t st) {
+  if (s.c1 != 8 || s.c2 != 8 || s.H < 6) return hipErrorInvalidValue;
+  // Tiles: as wide as they may be (a tile stages eight columns beside its own), narrower where there would be fewer than the
+  // 1024 workgroups that the chip holds.
+  RebasePlan plan;
+  int tiles = (nb_cur + kRbCols - 1) / kRbCols;
+  const int filled = (1024 + ninst - 1) / ninst, most = (nb_cur + 55) / 56;
+  if (tiles < filled) tiles = filled < most ? filled : most;
+  plan.cols = (nb_cur + tiles - 1) / tiles;
+  tiles = (nb_cur + plan.cols - 1) / plan.cols;
+  const int strips = (s.H + 1) / 2, segs = (strips + kRbStrips - 1) / kRbStrips;
+  plan.seg_strips = (strips + segs - 1) / segs;
+#define AP_REBASE(SW) \
+  predict_rebase8_kernel<SW><<<dim3(tiles, ninst), 256, sizeof(uint32_t) * rebase_lds_words(SW, plan.seg_strips), st>>>( \
+      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan, pstate, pred)
+  if (plan.cols <= 64 - 2 * kRbHalo) AP_REBASE(64);
+  else if (plan.cols <= 128 - 2 * kRbHalo) AP_REBASE(128);
+  else AP_REBASE(256);
+#undef AP_REBASE
   return hipGetLastError();
 }
 
