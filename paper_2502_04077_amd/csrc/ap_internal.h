@@ -124,17 +124,11 @@ __host__ __device__ constexpr int delta_const_offset(int c1, int c2) {
 }
 
 // Launchers.  Each returns hipSuccess or the launch error.
-// Full-tile predictor over columns [col_begin, nb_cur); also writes the interior state if pstate != null.
+// Full-tile predictor over columns [col_begin, nb_cur); also writes the interior state if pstate != null.  With s.predictor_mfma and
+// H >= 6 on MFMA, where col_begin is 0 and pstate is given.
 // Launchers that take (inst0, ninst) work on instances [inst0, inst0 + ninst) of the same buffers.
 hipError_t launch_predict(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
                           int newest_slot, int nb_cur, int col_begin, float* pstate, float* pred, hipStream_t st);
-// Interior state and pred of every column from scratch on MFMA (8/8 channels, H >= 6).
-hipError_t launch_predict_rebase8(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
-                                  int newest_slot, int nb_cur, float* pstate, float* pred, hipStream_t st);
-// Interior state (rows 2..H-3) of every column from scratch on MFMA (16/32 channels, H >= 6); the incremental
-// kernel without an advance then adds the border rows and writes pred.
-hipError_t launch_predict_interior(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
-                                   int newest_slot, int nb_cur, float* pstate, hipStream_t st);
 // The same evaluation for a handful of columns [col_begin, nb_cur): one wave per (instance, column).
 hipError_t launch_predict_columns(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
                                   int newest_slot, int nb_cur, int col_begin, float* pstate, float* pred,

@@ -361,19 +361,9 @@ static int run_predictor(const ap_ctx* ctx, const float* hist, int64_t n_pushed,
   const Shape& s = ctx->s;
   const int newest = newest_slot_of(s, n_pushed);
   if (pstate == nullptr || mode == AP_PRED_REBASE || s.H < 6) {
-    if (s.H >= 6 && s.predictor_mfma) {
-      // Full tile on MFMA: the interior state from scratch (into the caller's pstate, or into the workspace when the caller
-      // keeps none) and pred in one launch; for 16/32 channels the state, then the borders and the head as in a HOLD call.
-      float* state = pstate != nullptr ? pstate : ws + ap::ws_layout(s).pred_state;
-      if (s.c1 == 8)
-        return ap::launch_predict_rebase8(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, state, pred, st) == hipSuccess
-                   ? AP_OK : AP_ERR_HIP;
-      if (ap::launch_predict_interior(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, state, st) != hipSuccess ||
-          ap::launch_predict_inc(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, 0, state, pred, st) != hipSuccess)
-        return AP_ERR_HIP;
-      return AP_OK;
-    }
-    return ap::launch_predict(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, 0, pstate, pred, st) == hipSuccess
+    // (on MFMA the state is made in any case: in the workspace where the caller keeps none)
+    float* state = pstate == nullptr && s.H >= 6 && s.predictor_mfma ? ws + ap::ws_layout(s).pred_state : pstate;
+    return ap::launch_predict(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, 0, state, pred, st) == hipSuccess
                ? AP_OK : AP_ERR_HIP;
   }
   if (ap::launch_predict_inc(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, mode == AP_PRED_ADVANCE, pstate,
@@ -383,10 +373,12 @@ static int run_predictor(const ap_ctx* ctx, const float* hist, int64_t n_pushed,
     // The tile grew: column nb_prev - 1 gained a right neighbour inside the tile and the new columns
     // have no state yet; evaluate those columns in full.
     const int col_begin = nb_prev > 1 ? nb_prev - 1 : 0;
+    Shape fp32 = s;                      // (in fp32, also where that means every column)
+    fp32.predictor_mfma = 0;
     const hipError_t e =
         nb_cur - col_begin <= 8
             ? ap::launch_predict_columns(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, col_begin, pstate, pred, st)
-            : ap::launch_predict(s, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, col_begin, pstate, pred, st);
+            : ap::launch_predict(fp32, 0, s.n_inst, ctx->dweights, hist, newest, nb_cur, col_begin, pstate, pred, st);
     if (e != hipSuccess) return AP_ERR_HIP;
   }
   return AP_OK;

@@ -449,33 +449,22 @@ hipError_t run_inc(const Shape& s, int inst0, int ninst, const float* dweights, 
   return hipGetLastError();
 }
 
-}  // namespace
-
-hipError_t launch_predict(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
-                          int newest_slot, int nb_cur, int col_begin, float* pstate, float* pred, hipStream_t st) {
-  if (s.c1 == 4 && s.c2 == 4)
-    return run_full<4, 4>(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, col_begin, pstate, pred, st);
-  if (s.c1 == 8 && s.c2 == 8)
-    return run_full<8, 8>(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, col_begin, pstate, pred, st);
-  if (s.c1 == 16 && s.c2 == 32)
-    return run_full<16, 32>(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, col_begin, pstate, pred, st);
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_predict_interior(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
-                                   int newest_slot, int nb_cur, float* pstate, hipStream_t st) {
-  if (s.c1 != 16 || s.c2 != 32 || s.H < 6) return hipErrorInvalidValue;
+// Interior state (rows 2..H-3) of every column from scratch, then the border rows and the head as in an incremental call without an
+// advance.
+hipError_t run_rebase16(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist, int newest_slot,
+                        int nb_cur, float* pstate, float* pred, hipStream_t st) {
   const int groups = (nb_cur + 4 * kPiOut - 1) / (4 * kPiOut);
   int chunks = (2048 + s.n_inst - 1) / s.n_inst;         // about eight workgroups per CU when instances are few
   if (chunks > groups) chunks = groups;
   predict_interior_mfma16_kernel<<<dim3(chunks, ninst), 256, sizeof(float) * kPredInterior16LdsFloats, st>>>(
       hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, pstate);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return run_inc<16, 32>(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, 0, pstate, pred, st);
 }
 
-hipError_t launch_predict_rebase8(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
-                                  int newest_slot, int nb_cur, float* pstate, float* pred, hipStream_t st) {
-  if (s.c1 != 8 || s.c2 != 8 || s.H < 6) return hipErrorInvalidValue;
+hipError_t run_rebase8(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist, int newest_slot,
+                       int nb_cur, float* pstate, float* pred, hipStream_t st) {
   // Tiles: as wide as they may be (a tile stages eight columns beside its own), narrower where there would be fewer than the
   // 1024 workgroups that the chip holds.
   RebasePlan plan;
@@ -494,6 +483,22 @@ hipError_t launch_predict_rebase8(const Shape& s, int inst0, int ninst, const fl
   else AP_REBASE(256);
 #undef AP_REBASE
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_predict(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
+                          int newest_slot, int nb_cur, int col_begin, float* pstate, float* pred, hipStream_t st) {
+  if (s.predictor_mfma && s.H >= 6 && col_begin == 0 && pstate != nullptr)
+    return s.c1 == 8 ? run_rebase8(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, pstate, pred, st)
+                     : run_rebase16(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, pstate, pred, st);
+  if (s.c1 == 4 && s.c2 == 4)
+    return run_full<4, 4>(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, col_begin, pstate, pred, st);
+  if (s.c1 == 8 && s.c2 == 8)
+    return run_full<8, 8>(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, col_begin, pstate, pred, st);
+  if (s.c1 == 16 && s.c2 == 32)
+    return run_full<16, 32>(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, col_begin, pstate, pred, st);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_predict_columns(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist,
