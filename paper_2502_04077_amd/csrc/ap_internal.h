@@ -42,6 +42,9 @@ struct Shape {
   const int32_t* table;  // device block table of a paged K/V cache [n_inst][nb_cap], or null (caller-owned)
   int n_phys;            // physical blocks in the pool
   bool k_on_host;        // launch_calibrate: K is pinned host memory
+  int* clear;            // counters of a decode's merges, one per instance: launches that have it (of the predictor, of an appended
+                         // row) set them to zero for the decode launch behind them; null: nothing to clear
+  bool cleared;          // launch_sparse_decode: a launch before it has done so
 };
 
 // Difference form of the predictor.  With an all-zero history the first layer gives c[ci] = relu(b1[ci]) at every
@@ -66,6 +69,7 @@ struct WsLayout {
   size_t part_ml;     // [n_inst][n_split][g][2]        split max / sum
   size_t part_acc;    // [n_inst][n_split][g][d]        split un-normalised output
   size_t part_bmp;    // [n_inst][g][k]                 per selected block: max prob relative to split max
+  size_t merge_count; // [n_inst] ints                  splits of an instance that have left their partials
   size_t cal_ml;      // [n_inst][calib_chunks][g][2]
   size_t cal_bmp;     // [n_inst][g][nb_cap]
   size_t pred_state;  // [n_inst][nb_cap]               interior state of a full-tile prediction without a caller state
@@ -162,7 +166,7 @@ hipError_t launch_stream_read(const void* src, size_t bytes, void* sink, int n_w
 hipError_t launch_stream_copy(const void* src, size_t bytes, void* dst, int n_wg, hipStream_t st);
 hipError_t launch_push_row(const Shape& s, float* hist, int slot, const float* row, hipStream_t st);
 
-// Floats of workspace that launch_sparse_decode touches (the split partials, which lead the layout).
+// Floats of workspace that launch_sparse_decode touches (the split partials and counters, which lead the layout).
 size_t sparse_ws_floats(const Shape& s);
 // The current device's copy of the library's static scratch array (for callers that may not allocate) and its
 // size in bytes; looked up once per device.  Returns hipSuccess or the lookup error.

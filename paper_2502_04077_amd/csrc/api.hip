@@ -25,6 +25,7 @@ WsLayout ws_layout(const Shape& s) {
   w.part_ml = o;  o = align4(o + (size_t)s.n_inst * s.n_split * s.g * 2);
   w.part_acc = o; o = align4(o + (size_t)s.n_inst * s.n_split * s.g * s.d);
   w.part_bmp = o; o = align4(o + (size_t)s.n_inst * s.g * s.k);
+  w.merge_count = o; o = align4(o + (size_t)s.n_inst);
   w.cal_ml = o;   o = align4(o + (size_t)s.n_inst * s.calib_chunks * s.g * 2);
   w.cal_bmp = o;  o = align4(o + (size_t)s.n_inst * s.g * s.nb_cap);
   w.pred_state = o; o = align4(o + (size_t)s.n_inst * s.nb_cap);
@@ -33,7 +34,7 @@ WsLayout ws_layout(const Shape& s) {
   return w;
 }
 
-// The split partials lead the layout; a context with one workgroup per instance has none.
+// The split partials and their counters lead the layout; a context with one workgroup per instance has none.
 size_t sparse_ws_floats(const Shape& s) { return s.n_split > 1 ? ws_layout(s).cal_ml : 0; }
 
 static bool pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -100,6 +101,7 @@ int ap_create(const ap_config* c, ap_ctx** out) {
   s.n_sink = c->n_sink; s.n_local = c->n_local; s.c1 = c->c1; s.c2 = c->c2; s.kv_dtype = c->kv_dtype;
   s.predictor_mfma = (((c->c1 == 8 && c->c2 == 8) || (c->c1 == 16 && c->c2 == 32)) &&
                       !(c->flags & AP_FLAG_PREDICTOR_FP32)) ? 1 : 0;
+  s.clear = nullptr; s.cleared = false;
   s.n_split = ap::choose_split(s);
   {
     // Dynamic LDS of the attention workgroup (sparse_lds_floats) and of the combine kernel must fit 64 KiB.
@@ -357,8 +359,9 @@ static int newest_slot_of(const Shape& s, int64_t n_pushed) {
 
 // Runs the predictor in the requested mode; shared by ap_predict_incremental and ap_step.
 static int run_predictor(const ap_ctx* ctx, const float* hist, int64_t n_pushed, int nb_cur, int nb_prev, int mode,
-                         float* pstate, float* pred, float* ws, hipStream_t st) {
-  const Shape& s = ctx->s;
+                         float* pstate, float* pred, float* ws, hipStream_t st, int* clear = nullptr) {
+  Shape s = ctx->s;
+  s.clear = clear;
   const int newest = newest_slot_of(s, n_pushed);
   if (pstate == nullptr || mode == AP_PRED_REBASE || s.H < 6) {
     // (on MFMA the state is made in any case: in the workspace where the caller keeps none)
@@ -446,7 +449,7 @@ int ap_sparse_decode_noalloc(ap_ctx* ctx, const void* q, const void* K, const vo
   AP_REQUIRE_PTR(out); AP_REQUIRE_PTR(row);
   const Shape& s = ctx->s;
   if (t_cur < 1 || t_cur > s.t_cap) return AP_ERR_RANGE;
-  if (ap::sparse_ws_floats(s) * sizeof(float) > AP_NOALLOC_SCRATCH_BYTES) return AP_ERR_RANGE;
+  if (s.n_split > 1 && ap::ws_layout(s).merge_count * sizeof(float) > AP_NOALLOC_SCRATCH_BYTES) return AP_ERR_RANGE;   // (the partials; the counters have room of their own)
   float* ws = nullptr;
   size_t bytes = 0;
   if (ap::static_scratch(&ws, &bytes) != hipSuccess) {
@@ -512,8 +515,11 @@ int ap_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, const voi
   const int nb_cur = (t_cur + s.b - 1) / s.b;
   const int nb_prev = t_cur > 1 ? (t_cur - 1 + s.b - 1) / s.b : 1;   // one token is appended per step
   hipStream_t st = static_cast<hipStream_t>(stream);
+  Shape decode = s;
   if (pred_mode != AP_PRED_SKIP) {
-    int rc = run_predictor(ctx, hist, n_pushed, nb_cur, nb_prev, pred_mode, pstate, pred, static_cast<float*>(ws), st);
+    int* counts = s.n_split > 1 ? reinterpret_cast<int*>(static_cast<float*>(ws) + ap::ws_layout(s).merge_count) : nullptr;
+    decode.cleared = counts != nullptr;
+    int rc = run_predictor(ctx, hist, n_pushed, nb_cur, nb_prev, pred_mode, pstate, pred, static_cast<float*>(ws), st, counts);
     if (rc != AP_OK) return rc;
   }
   if (reuse) {
@@ -524,7 +530,7 @@ int ap_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, const voi
   }
   const int slot = (int)(n_pushed % s.R);
   float* slot_row = hist + (size_t)slot * s.nb_cap;
-  if (ap::launch_sparse_decode(s, 0, s.n_inst, q, K, V, t_cur, idx, cnt, out, slot_row, (size_t)s.R * s.nb_cap,
+  if (ap::launch_sparse_decode(decode, 0, s.n_inst, q, K, V, t_cur, idx, cnt, out, slot_row, (size_t)s.R * s.nb_cap,
                                static_cast<float*>(ws), st) != hipSuccess)
     return AP_ERR_HIP;
   return AP_OK;
@@ -631,9 +637,11 @@ int ap_offload_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, c
   if (check_device_readable(K_src, &on_host) != AP_OK || check_device_readable(V_src) != AP_OK) return AP_ERR_ARG;
   hipStream_t cs = static_cast<hipStream_t>(compute_stream), ps = static_cast<hipStream_t>(copy_stream);
   if (hipStreamWaitEvent(cs, ctx->ev_staged, 0) != hipSuccess) return AP_ERR_HIP;
-  if (ap::launch_append_row(s, k_new, v_new, t_cur - 1, block_table, state, pool_K, pool_V, cs) != hipSuccess)
-    return AP_ERR_HIP;
   Shape paged = s;                       // the staged pools are a paged cache of n_inst * k blocks
+  if (s.n_split > 1) paged.clear = reinterpret_cast<int*>(static_cast<float*>(ws) + ap::ws_layout(s).merge_count);
+  if (ap::launch_append_row(paged, k_new, v_new, t_cur - 1, block_table, state, pool_K, pool_V, cs) != hipSuccess)
+    return AP_ERR_HIP;
+  paged.cleared = paged.clear != nullptr;
   paged.table = block_table;
   paged.n_phys = s.n_inst * s.k;
   float* slot_row = hist + (size_t)(n_pushed % s.R) * s.nb_cap;

@@ -6,26 +6,26 @@
 // Scratch for the entry point that must not allocate (ap_sparse_decode_noalloc): the split partials of one
 // sparse-decode call.  Every device the library runs on holds its own copy until the process ends.  In host code
 // this name is only a handle for hipGetSymbolAddress; kernels get the address that call returned.
-constexpr size_t kStaticScratchBytes = AP_NOALLOC_SCRATCH_BYTES;
+constexpr size_t kStaticScratchBytes = AP_NOALLOC_SCRATCH_BYTES + (65536 + 4) * sizeof(int);    // (a counter per instance beside them)
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace ap {
 namespace {
 
 // (the narrow forms are only worth launching if many of their workgroups fit a CU: four waves per SIMD, 128 VGPRs)
-template <typename T, int D, int G, int NW, bool PIECED>
+template <typename T, int D, int G, int NW, bool PIECED, bool MERGE = false>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW < kAttnWaves ? 4 : 1)))
 void sparse_decode_kernel(SparseArgs a) {
   extern __shared__ __align__(16) float smem[];
-  sparse_decode_body<T, D, G, NW, PIECED>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
+  sparse_decode_body<T, D, G, NW, PIECED, MERGE>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
 }
 
 // Waves per SIMD the registers are to leave room for: g d / 16 accumulators beside 16 of K and V rows each.
-template <int D, int G>
+template <int D, int G, bool MERGE>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(G <= 4 ? 4 : 3)))
 void sparse_stream_kernel(SparseArgs a) {
   extern __shared__ __align__(16) float smem[];
-  sparse_stream_body<D, G>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
+  sparse_stream_body<D, G, MERGE>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
 }
 
 // Brings the partial softmax statistics of one instance - ml[part * G + h] = (maximum, sum relative to it), part < n_part -
@@ -419,6 +419,12 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
   return hipGetLastError();
 }
 
+// Are the splits merged by the last workgroup of an instance to finish, or by a launch of their own?  By the last one where a
+// launch before has cleared the counters (one more launch for that would cost as much as the merge's own) and all
+// workgroups are resident at once: in further rounds every workgroup holds its place until its partials have reached memory.  (Step of 8 instances
+// 18.9 -> 18.4 us and three launches instead of four, of 128 at 128K 75.3 -> 73.8; 640 instances of two splits, counters cleared by a launch, 121 -> 132.)
+bool merge_inside(const Shape& s, int ninst, int n_split) { return s.cleared && n_split > 1 && (long)ninst * n_split <= 1024; }
+
 // Workgroups per instance the streaming form uses, of the a.n_split that the workspace has room for: the number with the least
 // time by this reckoning.  The fullest of 256 CUs has r = ceil(workgroups / 256) of them and takes r shares of a list, at 32 KB
 // a us where it has one workgroup (20 at d = 64, whose workgroups have half the bytes on their way), 29 with two and 22.5
@@ -444,7 +450,7 @@ template <int D> int stream_splits(const SparseArgs& a, int ninst, int g) {
 }
 
 template <int D, int G>
-hipError_t run_stream(int ninst, SparseArgs a, hipStream_t st) {
+hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   a.ml_unit = 1.f;
   int want = a.n_split > 1 ? stream_splits<D>(a, ninst, G) : 1;
   // (Lists of so many blocks, or rows with so many, that their entries beside the logits exceed 64 KiB take more splits; with
@@ -455,8 +461,13 @@ hipError_t run_stream(int ninst, SparseArgs a, hipStream_t st) {
   while (want < a.n_split && lds_of(want) > 65536) ++want;
   a.blk_per_split = (a.k + want - 1) / want;
   a.n_split = (a.k + a.blk_per_split - 1) / a.blk_per_split;
-  const size_t lds = lds_of(want);
-  sparse_stream_kernel<D, G><<<dim3(a.n_split, ninst), kAttnThreads, lds, st>>>(a);
+  const dim3 grid(a.n_split, ninst);
+  if (merge_inside(s, ninst, a.n_split)) {
+    const size_t merge = merge_lds_bytes(a.n_split, G), lds = lds_of(want) > merge ? lds_of(want) : merge;
+    sparse_stream_kernel<D, G, true><<<grid, kAttnThreads, lds, st>>>(a);
+    return hipGetLastError();
+  }
+  sparse_stream_kernel<D, G, false><<<grid, kAttnThreads, lds_of(want), st>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_split == 1) return e;
   return run_combine<D, G>(ninst, a, st);
@@ -466,10 +477,10 @@ template <typename T, int D, int G>
 hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   // The streaming form: bf16 lists cut into splits, and whole lists with g = 8 (1024 instances 120 -> 99 us, 1700
   // 172 -> 162; the phased form has no narrow variants for it).
-  if constexpr (std::is_same<T, bf16_t>::value && G == 8) return run_stream<D, G>(ninst, a, st);
+  if constexpr (std::is_same<T, bf16_t>::value && G == 8) return run_stream<D, G>(s, ninst, a, st);
   else {
   if constexpr (std::is_same<T, bf16_t>::value)
-    if (a.n_split > 1) return run_stream<D, G>(ninst, a, st);
+    if (a.n_split > 1) return run_stream<D, G>(s, ninst, a, st);
   const int nblk_cap = (a.n_split == 1) ? a.k : a.blk_per_split;
   a.piece_blocks = nblk_cap;
   const size_t lds = sizeof(float) * sparse_lds_floats<D, G, kAttnWaves>(nblk_cap, nblk_cap, a.b, a.nb_cap);
@@ -499,6 +510,12 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
       return hipGetLastError();
     }
   }
+  if constexpr (std::is_same<T, float>::value)
+    if (merge_inside(s, ninst, a.n_split)) {
+      const size_t merge = merge_lds_bytes(a.n_split, G);
+      sparse_decode_kernel<T, D, G, kAttnWaves, false, true><<<dim3(a.n_split, ninst), kAttnThreads, lds > merge ? lds : merge, st>>>(a);
+      return hipGetLastError();
+    }
   sparse_decode_kernel<T, D, G, kAttnWaves, false><<<dim3(a.n_split, ninst), kAttnThreads, lds, st>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_split == 1) return e;
@@ -588,6 +605,7 @@ hipError_t launch_sparse_decode(const Shape& s, int inst0, int ninst, const void
   const WsLayout wl = ws_layout(s);
   SparseArgs a;
   a.q = q; a.K = K; a.V = V; a.idx = idx; a.cnt = cnt; a.out = out; a.row = row; a.row_stride = row_stride;
+  a.merge_count = reinterpret_cast<int*>(ws + wl.merge_count);
   a.part_ml = ws + wl.part_ml; a.part_acc = ws + wl.part_acc; a.part_bmp = ws + wl.part_bmp;
   a.t_cap = s.t_cap; a.nb_cap = s.nb_cap; a.k = s.k; a.b = s.b; a.log2b = ilog2(s.b); a.t_cur = t_cur;
   a.nb_cur = (t_cur + s.b - 1) / s.b;

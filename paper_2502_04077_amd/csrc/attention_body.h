@@ -6,7 +6,8 @@
 //      accumulate, written to LDS (tokens at or beyond t_cur get -inf);
 //   2. per head: M = max l, p = exp(l - M) in place, L = sum p; per (head, block) the max p.
 // Sparse decode continues with  3. acc[h][:] = sum_tok p[h][tok] * V_tok  and either finishes
-// (one workgroup per instance) or leaves (M, L, acc, block maxima) for the combine kernel.
+// (one workgroup per instance) or leaves (M, L, acc, block maxima) for the merge: by the last workgroup of the instance to finish or
+// by the combine kernel (merge_inside in attention.hip).
 // Softmax definition: Sec. 3.1; block max-pooling of the probabilities: Algorithm 1 steps 1-2
 // (softmax is monotone, so the pooled probability of a block is exp(max logit - M) / L).
 //
@@ -90,6 +91,9 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_fill<0x143, 0xC>(0.f, v);
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
 }
+
+constexpr float kLog2E = 1.44269504088896340736f;
+__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
 template <typename T, int D, int G> struct Geom {
   static constexpr int E = KvT<T>::E;           // elements per 16-byte load
@@ -343,7 +347,125 @@ struct SparseArgs {
   int n_phys;                     // blocks in the pool (table entries are clamped into it)
   int piece_blocks;               // list positions whose probabilities are in LDS at a time
   float ml_unit;                  // the splits' maxima times this are exponents of 2
+  int* merge_count;               // [n_inst] splits that have left their partials, zero at launch (where they are merged inside)
 };
+
+// Data that one workgroup leaves for another of the same launch, which may run on another XCD with an L2 of its own: stores that are
+// written through to memory, loads that are answered from there (agent scope).  A release of ordinary stores would write back the
+// XCD's whole L2 instead, which costs four times a decode's time.
+// (SHARED = false: an ordinary store, for a launch behind this one.)
+template <bool SHARED> __device__ __forceinline__ void st_shared_out(float* p, float v) {
+  if constexpr (SHARED) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); else *p = v;
+}
+__device__ __forceinline__ float ld_shared_out(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Called by every thread of a workgroup that has left its partials of an instance: true in the last of n_split to get here.
+// s_last: an int of LDS that nothing else uses.
+__device__ __forceinline__ bool last_to_finish(int* count, int n_split, int* s_last) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's partials have reached memory
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *s_last = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_split - 1;
+  __syncthreads();
+  return *s_last != 0;
+}
+
+// The pooled row of an instance in splits is zero but for the listed blocks: every split clears its share of the columns,
+// before its partials are complete, and the last one fills in the values.
+__device__ __forceinline__ void clear_row_share(const SparseArgs& a, int inst, int split) {
+  const int per = ((a.nb_cap + a.n_split - 1) / a.n_split + 31) & ~31;
+  float* row = a.row + (size_t)inst * a.row_stride;
+  for (int j = split * per + threadIdx.x; j < min(a.nb_cap, (split + 1) * per); j += kAttnThreads) st_shared_out<true>(row + j, 0.f);
+}
+
+// LDS of the merge, which overlays what the decode had: factors, and a word for last_to_finish.
+inline size_t merge_lds_bytes(int n_split, int g) { return n_split > 1 ? sizeof(float) * ((size_t)n_split * g + 1) : 0; }
+
+// Merges the splits of one instance, by one workgroup of kAttnThreads that has found itself the last: global (M, L) per head, normalised
+// output, pooled row.  smem: merge_lds_bytes(..).  The chain of loads is what it costs, so whatever does not depend on anything is asked
+// for first.  (As a launch of its own: sparse_combine_kernel.)
+template <int D, int G>
+__device__ __forceinline__ void merge_splits(const SparseArgs& a, int inst, float* s_scale) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const float* ml = a.part_ml + (size_t)inst * a.n_split * G * 2;        // [split][head] (maximum, sum relative to it)
+  const float* acc = a.part_acc + (size_t)inst * a.n_split * G * D;
+  const float* bmp = a.part_bmp + (size_t)inst * G * a.k;
+  const int cnt = min(max(a.cnt[inst], 0), a.k);
+  auto block_of = [&](int jb) __attribute__((always_inline)) {
+    return min(max(a.idx[(size_t)inst * a.k + jb], 0), a.nb_cur - 1);
+  };
+  // This thread's first list position, with its block maxima, and its first outputs of the first splits.
+  int blk = -1;
+  float bm[G];
+  if ((int)threadIdx.x < cnt) {
+    blk = block_of(threadIdx.x);
+#pragma unroll
+    for (int h = 0; h < G; ++h) bm[h] = ld_shared_out(bmp + (size_t)h * a.k + threadIdx.x);
+  }
+  constexpr int kAhead = 8, PER = G * D > kAttnThreads ? 2 : 1;
+  float x[PER][kAhead];
+#pragma unroll
+  for (int i = 0; i < PER; ++i)
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s)
+      x[i][s] = s < a.n_split && i * kAttnThreads + (int)threadIdx.x < G * D ? ld_shared_out(acc + (size_t)s * G * D + i * kAttnThreads + threadIdx.x) : 0.f;
+  // Scales exp2((m - M) unit) / L of every split and head (0 for an empty part or an empty whole): wave h / .. of head h, lane l
+  // holds parts l, l + 64, ..
+  for (int h = wave; h < G; h += kAttnWaves) {
+    float M = -INFINITY, m0 = -INFINITY, l0 = 0.f;
+    if (lane < a.n_split) {
+      m0 = ld_shared_out(ml + 2 * (lane * G + h));
+      l0 = ld_shared_out(ml + 2 * (lane * G + h) + 1);
+    }
+    M = m0;
+    for (int p = lane + kWave; p < a.n_split; p += kWave) M = fmaxf(M, ld_shared_out(ml + 2 * (p * G + h)));
+    M = wave_max(M);
+    float L = m0 == -INFINITY ? 0.f : l0 * exp2_fast((m0 - M) * a.ml_unit);
+    for (int p = lane + kWave; p < a.n_split; p += kWave) {
+      const float m = ld_shared_out(ml + 2 * (p * G + h));
+      L += m == -INFINITY ? 0.f : ld_shared_out(ml + 2 * (p * G + h) + 1) * exp2_fast((m - M) * a.ml_unit);
+    }
+    L = wave_sum(L);
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    if (lane < a.n_split) s_scale[lane * G + h] = m0 == -INFINITY ? 0.f : exp2_fast((m0 - M) * a.ml_unit) * inv;
+    for (int p = lane + kWave; p < a.n_split; p += kWave) {
+      const float m = ld_shared_out(ml + 2 * (p * G + h));
+      s_scale[p * G + h] = m == -INFINITY ? 0.f : exp2_fast((m - M) * a.ml_unit) * inv;
+    }
+  }
+  __syncthreads();
+  // (added up in the order of the splits)
+  for (int i = 0, o = threadIdx.x; o < G * D; ++i, o += kAttnThreads) {
+    const int h = o / D;
+    float v = 0.f;
+    for (int s0 = 0; s0 < a.n_split; s0 += kAhead) {
+      if (s0 > 0 || i >= PER) {
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s) x[0][s] = s0 + s < a.n_split ? ld_shared_out(acc + (size_t)(s0 + s) * G * D + o) : 0.f;
+      }
+#pragma unroll
+      for (int s = 0; s < kAhead; ++s) {
+        const float y = s0 > 0 || i >= PER ? x[0][s] : i == 0 ? x[0][s] : x[PER - 1][s];
+        if (s0 + s < a.n_split) v = fmaf(y, s_scale[(s0 + s) * G + h], v);
+      }
+    }
+    a.out[(size_t)inst * G * D + o] = v;
+  }
+  // pooled probability of list position jb: max over heads of (block max relative to its split) * split scale
+  float* row = a.row + (size_t)inst * a.row_stride;
+  for (int jb = threadIdx.x; jb < cnt; jb += kAttnThreads) {
+    if (jb != (int)threadIdx.x) {
+      blk = block_of(jb);
+#pragma unroll
+      for (int h = 0; h < G; ++h) bm[h] = ld_shared_out(bmp + (size_t)h * a.k + jb);
+    }
+    const int s = jb / a.blk_per_split;
+    float mx = 0.f;
+#pragma unroll
+    for (int h = 0; h < G; ++h) mx = fmaxf(mx, bm[h] * s_scale[s * G + h]);
+    row[blk] = mx;                                       // (a block listed twice: either of two equal values)
+  }
+}
 
 // Sparse decode of instance `inst`, split `split`, by one workgroup of NW waves.
 // The list is worked off in pieces of a.piece_blocks positions - logits, softmax statistics, acc += p * V per
@@ -351,7 +473,7 @@ struct SparseArgs {
 // probabilities of one piece only.  PIECED = false: a.piece_blocks covers the list, one piece, no rescaling
 // (and the accumulators are not live during phase 1).
 // smem: sparse_lds_floats(...) floats of LDS, 16-byte aligned.
-template <typename T, int D, int G, int NW, bool PIECED>
+template <typename T, int D, int G, int NW, bool PIECED, bool MERGE>
 __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst, int split, float* smem) {
   using Ge = Geom<T, D, G>;
   constexpr int E = Ge::E, LPT = Ge::LPT, NL = Ge::NL, NT = NW * kWave;
@@ -389,6 +511,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
     for (int w = threadIdx.x; w < nwords; w += NT) s_listed[w] = 0u;
   }
   if (threadIdx.x < G) { s_m[threadIdx.x] = -INFINITY; s_l[threadIdx.x] = 0.f; }
+  if constexpr (MERGE) clear_row_share(a, inst, split);
   __syncthreads();
   for (int j = threadIdx.x; j < nblk; j += NT) {
     const int blk = min(max(a.idx[(size_t)inst * a.k + j0 + j], 0), a.nb_cur - 1);
@@ -561,16 +684,18 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
       float v = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) v += s_acc[w * G * D + o];
-      a.part_acc[ps * G * D + o] = v;
+      st_shared_out<MERGE>(a.part_acc + ps * G * D + o, v);
     }
     if (threadIdx.x < G) {
-      a.part_ml[(ps * G + threadIdx.x) * 2 + 0] = s_m[threadIdx.x];
-      a.part_ml[(ps * G + threadIdx.x) * 2 + 1] = s_l[threadIdx.x];
+      st_shared_out<MERGE>(a.part_ml + (ps * G + threadIdx.x) * 2 + 0, s_m[threadIdx.x]);
+      st_shared_out<MERGE>(a.part_ml + (ps * G + threadIdx.x) * 2 + 1, s_l[threadIdx.x]);
     }
     for (int pair = threadIdx.x; pair < G * nblk; pair += NT) {
       const int h = pair / nblk, jb = pair - h * nblk;
-      a.part_bmp[((size_t)inst * G + h) * a.k + j0 + jb] = s_bmp[pair];
+      st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, s_bmp[pair]);
     }
+    if constexpr (MERGE)
+      if (last_to_finish(a.merge_count + inst, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, smem);
   }
 }
 
@@ -612,8 +737,6 @@ template <int D, int G> constexpr int query_floats() { return G * (D * 2 + kStag
 // The streaming forms keep logits as they come out of the contraction and refer probabilities to whole numbers m, in units of
 // log2: with c = log2(e) / sqrt(d) a probability is exp2(fma(logit, c, -m)), whose exponent is rounded once instead of three
 // times, and the factors that bring sums from one reference to another are powers of two, which round nothing.
-constexpr float kLog2E = 1.44269504088896340736f;
-__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 template <int D> struct LogitUnit {
   static_assert(D == 64 || D == 128, "log2(e) / sqrt(d) for the compiled head sizes");
   static constexpr float kC = D == 64 ? 1.4426950408889634 / 8.0 : 1.4426950408889634 / 11.313708498984761;
@@ -646,7 +769,7 @@ constexpr int kChainPasses = 8;
 // (head = l % 16, tokens 4 (l / 16) + v), v = 0..3: a row of 16 lanes holds the logits of four tokens, which are, for
 // d = 128, the tokens whose V rows the row reads, and the probability of a head is a DPP broadcast away.
 // smem: sparse_stream_lds_floats(...) floats of LDS, 16-byte aligned.
-template <int D, int G>
+template <int D, int G, bool MERGE>
 __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst, int split, float* smem) {
   using T = bf16_t;
   using Ge = Geom<T, D, G>;
@@ -684,6 +807,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     for (int w = threadIdx.x; w < nwords; w += NT) s_listed[w] = 0u;
     __syncthreads();
   }
+  if constexpr (MERGE) clear_row_share(a, inst, split);
   for (int j = threadIdx.x; j < nblk; j += NT) {
     const int blk = min(max(a.idx[(size_t)inst * a.k + j0 + j], 0), a.nb_cur - 1);
     s_idx[j] = blk;
@@ -947,13 +1071,15 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
       float v = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) v = fmaf(smem[w * TILE + o], s_m[w * G + h], v);
-      a.part_acc[ps * G * D + o] = v;
+      st_shared_out<MERGE>(a.part_acc + ps * G * D + o, v);
     }
-    if (threadIdx.x < 2 * G) a.part_ml[ps * G * 2 + threadIdx.x] = s_ml[threadIdx.x];
+    if (threadIdx.x < 2 * G) st_shared_out<MERGE>(a.part_ml + ps * G * 2 + threadIdx.x, s_ml[threadIdx.x]);
     for (int pair = threadIdx.x; pair < G * nblk; pair += NT) {
       const int h = pair / nblk, jb = pair - h * nblk;
-      a.part_bmp[((size_t)inst * G + h) * a.k + j0 + jb] = block_max(h, jb);
+      st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, block_max(h, jb));
     }
+    if constexpr (MERGE)
+      if (last_to_finish(a.merge_count + inst, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, smem);
   }
 }
 

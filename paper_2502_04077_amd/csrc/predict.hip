@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kPredThreads) void predict_full_kernel(const float*
                                                                     int H, int newest_slot, int nb_cur, int nb_cap,
                                                                     int inst0, int col_begin,
                                                                     float* __restrict__ pstate,
-                                                                    float* __restrict__ pred) {
+                                                                    float* __restrict__ pred, int* __restrict__ clear) {
   extern __shared__ __align__(16) float smem[];
   float* s_x = smem;                        // [kXR][kXW]
   float* s_y1 = s_x + kXR * kXW;            // [C1][kYR][kYW]
@@ -49,6 +49,7 @@ __global__ __launch_bounds__(kPredThreads) void predict_full_kernel(const float*
   const Weights<C1, C2> W(wts_global);
 
   const int inst = inst0 + blockIdx.y;
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clear[inst] = 0;
   const int c0 = col_begin + blockIdx.x * kTW;   // first output column of this tile
   const int tid = threadIdx.x;
   const int col = tid & (kTW - 1);
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(2 * IW) void predict_inc_kernel(const float* __rest
                                                              const float* __restrict__ wts_global, int R, int H,
                                                              int newest_slot, int nb_cur, int nb_cap, int inst0,
                                                              int advance, float* __restrict__ pstate,
-                                                             float* __restrict__ pred) {
+                                                             float* __restrict__ pred, int* __restrict__ clear) {
   constexpr int XW = IW + 4, YW = IW + 2, NT = 2 * IW;
   extern __shared__ __align__(16) float smem[];
   float* s_y1 = smem;                       // [2][4][C1][YW]
@@ -221,6 +222,7 @@ __global__ __launch_bounds__(2 * IW) void predict_inc_kernel(const float* __rest
   const Weights<C1, C2> W(wts_global);
 
   const int inst = inst0 + blockIdx.y;
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clear[inst] = 0;
   const int c0 = blockIdx.x * IW;
   const int tid = threadIdx.x;
   stage_x_rows<XW, NT / kWave>(s_x, hist + (size_t)inst * R * nb_cap, newest_slot, H, R, nb_cap, nb_cur, c0);
@@ -270,8 +272,10 @@ __global__ __launch_bounds__(2 * IW) void predict_inc_kernel(const float* __rest
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))   // four workgroups per CU: 128 VGPRs
 void predict_inc_mfma_kernel(const float* __restrict__ hist, const float* __restrict__ wts_global, int R, int H,
                              int newest_slot, int nb_cur, int nb_cap, int inst0, PassPlan plan, int advance,
-                             float* __restrict__ pstate, float* __restrict__ pred) {
+                             float* __restrict__ pstate, float* __restrict__ pred, int* __restrict__ clear, int ninst) {
   extern __shared__ __align__(16) float smem[];
+  if (clear != nullptr)                                  // (a workgroup may have a part of an instance, or several)
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < ninst; i += gridDim.x * 256) clear[inst0 + i] = 0;
   predict_inc_reg_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0, plan, advance, pstate, pred,
                        smem);
 }
@@ -280,8 +284,9 @@ __global__ __launch_bounds__(256) void predict_inc_mfma16_kernel(const float* __
                                                                  const float* __restrict__ wts_global, int R, int H,
                                                                  int newest_slot, int nb_cur, int nb_cap, int inst0,
                                                                  int advance, float* __restrict__ pstate,
-                                                                 float* __restrict__ pred) {
+                                                                 float* __restrict__ pred, int* __restrict__ clear) {
   extern __shared__ __align__(16) float smem[];
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clear[inst0 + blockIdx.y] = 0;
   predict_inc_mfma16_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0 + blockIdx.y, blockIdx.x,
                           gridDim.x, advance, pstate, pred, smem);
 }
@@ -290,8 +295,9 @@ template <int SW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))   // four workgroups per CU, as LDS has room for
 void predict_rebase8_kernel(const float* __restrict__ hist, const float* __restrict__ wts_global, int R, int H, int newest_slot,
                             int nb_cur, int nb_cap, int inst0, RebasePlan plan, float* __restrict__ pstate,
-                            float* __restrict__ pred) {
+                            float* __restrict__ pred, int* __restrict__ clear) {
   extern __shared__ __align__(16) uint32_t smem_u[];
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clear[inst0 + blockIdx.y] = 0;
   predict_rebase8_body<SW>(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0 + blockIdx.y, blockIdx.x, plan, pstate, pred,
                        smem_u);
 }
@@ -398,7 +404,7 @@ hipError_t run_full(const Shape& s, int inst0, int ninst, const float* dweights,
   const size_t lds = sizeof(float) * (kXR * kXW + (size_t)C1 * kYR * kYW);
   const dim3 grid((nb_cur - col_begin + kTW - 1) / kTW, ninst);
   predict_full_kernel<C1, C2><<<grid, kPredThreads, lds, st>>>(hist, dweights, s.R, s.H, newest_slot, nb_cur,
-                                                              s.nb_cap, inst0, col_begin, pstate, pred);
+                                                              s.nb_cap, inst0, col_begin, pstate, pred, s.clear);
   return hipGetLastError();
 }
 
@@ -430,7 +436,7 @@ hipError_t run_inc(const Shape& s, int inst0, int ninst, const float* dweights, 
     plan.per_wg = (plan.total + grid - 1) / grid;
     plan.inv_pass = (uint32_t)((0x100000000ull + n_pass - 1) / n_pass);
     predict_inc_mfma_kernel<<<dim3(grid), 256, lds, st>>>(hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan,
-                                                          advance, pstate, pred);
+                                                          advance, pstate, pred, s.clear, ninst);
     return hipGetLastError();
   }
   if (C1 == 16 && C2 == 32 && s.predictor_mfma) {
@@ -439,13 +445,13 @@ hipError_t run_inc(const Shape& s, int inst0, int ninst, const float* dweights, 
     int chunks = (1024 + s.n_inst - 1) / s.n_inst;       // two workgroups fit a CU
     if (chunks > tiles) chunks = tiles;
     predict_inc_mfma16_kernel<<<dim3(chunks, ninst), 256, lds, st>>>(
-        hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, advance, pstate, pred);
+        hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, advance, pstate, pred, s.clear);
     return hipGetLastError();
   }
   constexpr int IW = C1 <= 8 ? 128 : 64;
   const size_t lds = sizeof(float) * (2 * 4 * (size_t)C1 * (IW + 2) + 2 * 5 * (IW + 4) + 4 * IW);
   predict_inc_kernel<C1, C2, IW><<<dim3((nb_cur + IW - 1) / IW, ninst), 2 * IW, lds, st>>>(
-      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, advance, pstate, pred);
+      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, advance, pstate, pred, s.clear);
   return hipGetLastError();
 }
 
@@ -477,7 +483,7 @@ hipError_t run_rebase8(const Shape& s, int inst0, int ninst, const float* dweigh
   plan.seg_strips = (strips + segs - 1) / segs;
 #define AP_REBASE(SW) \
   predict_rebase8_kernel<SW><<<dim3(tiles, ninst), 256, sizeof(uint32_t) * rebase_lds_words(SW, plan.seg_strips), st>>>( \
-      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan, pstate, pred)
+      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan, pstate, pred, s.clear)
   if (plan.cols <= 64 - 2 * kRbHalo) AP_REBASE(64);
   else if (plan.cols <= 128 - 2 * kRbHalo) AP_REBASE(128);
   else AP_REBASE(256);
