@@ -45,6 +45,7 @@ struct Shape {
   int* clear;            // counters of a decode's merges, one per instance: launches that have it (of the predictor, of an appended
                          // row) set them to zero for the decode launch behind them; null: nothing to clear
   bool cleared;          // launch_sparse_decode: a launch before it has done so
+  const float* select_by;   // launch_sparse_decode: scores to make the selection from first, into idx and cnt; null: it is there
 };
 
 // Difference form of the predictor.  With an all-zero history the first layer gives c[ci] = relu(b1[ci]) at every

@@ -101,7 +101,7 @@ int ap_create(const ap_config* c, ap_ctx** out) {
   s.n_sink = c->n_sink; s.n_local = c->n_local; s.c1 = c->c1; s.c2 = c->c2; s.kv_dtype = c->kv_dtype;
   s.predictor_mfma = (((c->c1 == 8 && c->c2 == 8) || (c->c1 == 16 && c->c2 == 32)) &&
                       !(c->flags & AP_FLAG_PREDICTOR_FP32)) ? 1 : 0;
-  s.clear = nullptr; s.cleared = false;
+  s.clear = nullptr; s.cleared = false; s.select_by = nullptr;
   s.n_split = ap::choose_split(s);
   {
     // Dynamic LDS of the attention workgroup (sparse_lds_floats) and of the combine kernel must fit 64 KiB.
@@ -525,8 +525,8 @@ int ap_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, const voi
   if (reuse) {
     if (nb_cur != nb_prev && ap::launch_refresh_selection(s, nb_prev, nb_cur, idx, cnt, st) != hipSuccess)
       return AP_ERR_HIP;
-  } else if (ap::launch_select(s, 0, s.n_inst, pred, nb_cur, idx, cnt, st) != hipSuccess) {
-    return AP_ERR_HIP;
+  } else {
+    decode.select_by = pred;
   }
   const int slot = (int)(n_pushed % s.R);
   float* slot_row = hist + (size_t)slot * s.nb_cap;

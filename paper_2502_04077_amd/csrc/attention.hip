@@ -13,19 +13,19 @@ namespace ap {
 namespace {
 
 // (the narrow forms are only worth launching if many of their workgroups fit a CU: four waves per SIMD, 128 VGPRs)
-template <typename T, int D, int G, int NW, bool PIECED, bool MERGE = false>
+template <typename T, int D, int G, int NW, bool PIECED, int HOW = kSplitsOnly>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW < kAttnWaves ? 4 : 1)))
 void sparse_decode_kernel(SparseArgs a) {
   extern __shared__ __align__(16) float smem[];
-  sparse_decode_body<T, D, G, NW, PIECED, MERGE>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
+  sparse_decode_body<T, D, G, NW, PIECED, HOW>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
 }
 
 // Waves per SIMD the registers are to leave room for: g d / 16 accumulators beside 16 of K and V rows each.
-template <int D, int G, bool MERGE>
+template <int D, int G, int HOW>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(G <= 4 ? 4 : 3)))
 void sparse_stream_kernel(SparseArgs a) {
   extern __shared__ __align__(16) float smem[];
-  sparse_stream_body<D, G, MERGE>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
+  sparse_stream_body<D, G, HOW>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
 }
 
 // Brings the partial softmax statistics of one instance - ml[part * G + h] = (maximum, sum relative to it), part < n_part -
@@ -425,6 +425,31 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 // 18.9 -> 18.4 us and three launches instead of four, of 128 at 128K 75.3 -> 73.8; 640 instances of two splits, counters cleared by a launch, 121 -> 132.)
 bool merge_inside(const Shape& s, int ninst, int n_split) { return s.cleared && n_split > 1 && (long)ninst * n_split <= 1024; }
 
+// Does the decode launch make the selection too?  Every workgroup of an instance makes all of it, which is no loss where they would
+// otherwise wait for the launch that does, and hardly any CU has two of them.  (Whole steps, 2041 candidates, us: 8 instances 17.6 -> 16.6,
+// 32 19.7 -> 18.4, 128 29.3 -> 28.0, one of fp32 with 126 candidates 16.8 -> 15.3, two launches instead of three; at 3742 candidates, with 16 keys
+// a thread, 8 instances 22.7 and 128 45.6 -> 46.1: no gain.)
+bool select_here(const Shape& s, int ninst, int n_split, int nb_cur) {
+  const int n_mid = nb_cur - s.n_sink - s.n_local, k_mid = s.k - s.n_sink - s.n_local;
+  return merge_inside(s, ninst, n_split) && (long)ninst * n_split <= 512 && n_mid <= kSelectInsideKeys * kSelThreads && k_mid >= 1 && k_mid <= kSelMaxMid;
+}
+
+// LDS bytes of a launch that merges, and selects if HOW says so, on top of lds for the decode; sets a.sel_at.
+size_t lds_of_form(SparseArgs& a, size_t lds, int g, int how) {
+  const size_t merge = merge_lds_bytes(a.n_split, g), scratch = sizeof(uint32_t) * sel_scratch_words<kSelThreads>();
+  if (lds < merge) lds = merge;
+  if (how != kSelectInside) return lds;
+  if (lds < scratch) lds = scratch;
+  a.sel_at = (int)(lds / sizeof(float));
+  return lds + sizeof(int32_t) * (a.k + 1);
+}
+
+// The selection that a decode launch leaves to one of its own.
+hipError_t select_first(const Shape& s, int ninst, const SparseArgs& a, hipStream_t st) {
+  if (a.pred == nullptr) return hipSuccess;
+  return launch_select(s, a.inst0, ninst, a.pred, a.nb_cur, const_cast<int32_t*>(a.idx), const_cast<int32_t*>(a.cnt), st);
+}
+
 // Workgroups per instance the streaming form uses, of the a.n_split that the workspace has room for: the number with the least
 // time by this reckoning.  The fullest of 256 CUs has r = ceil(workgroups / 256) of them and takes r shares of a list, at 32 KB
 // a us where it has one workgroup (20 at d = 64, whose workgroups have half the bytes on their way), 29 with two and 22.5
@@ -462,13 +487,22 @@ hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   a.blk_per_split = (a.k + want - 1) / want;
   a.n_split = (a.k + a.blk_per_split - 1) / a.blk_per_split;
   const dim3 grid(a.n_split, ninst);
+  if (a.pred != nullptr && select_here(s, ninst, a.n_split, a.nb_cur)) {
+    const size_t lds = lds_of_form(a, lds_of(want), G, kSelectInside);
+    if (lds <= 65536) {
+      sparse_stream_kernel<D, G, kSelectInside><<<grid, kAttnThreads, lds, st>>>(a);
+      return hipGetLastError();
+    }
+  }
+  hipError_t e = select_first(s, ninst, a, st);
+  if (e != hipSuccess) return e;
   if (merge_inside(s, ninst, a.n_split)) {
-    const size_t merge = merge_lds_bytes(a.n_split, G), lds = lds_of(want) > merge ? lds_of(want) : merge;
-    sparse_stream_kernel<D, G, true><<<grid, kAttnThreads, lds, st>>>(a);
+    const size_t lds = lds_of_form(a, lds_of(want), G, kMergeInside);
+    sparse_stream_kernel<D, G, kMergeInside><<<grid, kAttnThreads, lds, st>>>(a);
     return hipGetLastError();
   }
-  sparse_stream_kernel<D, G, false><<<grid, kAttnThreads, lds_of(want), st>>>(a);
-  hipError_t e = hipGetLastError();
+  sparse_stream_kernel<D, G, kSplitsOnly><<<grid, kAttnThreads, lds_of(want), st>>>(a);
+  e = hipGetLastError();
   if (e != hipSuccess || a.n_split == 1) return e;
   return run_combine<D, G>(ninst, a, st);
 }
@@ -484,6 +518,11 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   const int nblk_cap = (a.n_split == 1) ? a.k : a.blk_per_split;
   a.piece_blocks = nblk_cap;
   const size_t lds = sizeof(float) * sparse_lds_floats<D, G, kAttnWaves>(nblk_cap, nblk_cap, a.b, a.nb_cap);
+  size_t lds_inside = 0;
+  if (std::is_same<T, float>::value && a.pred != nullptr && select_here(s, ninst, a.n_split, a.nb_cur)) lds_inside = lds_of_form(a, lds, G, kSelectInside);
+  const bool inside = lds_inside != 0 && lds_inside <= 65536;
+  hipError_t e = inside ? hipSuccess : select_first(s, ninst, a, st);
+  if (e != hipSuccess) return e;
   // More instances than the chip holds four-wave workgroups: the launch runs in rounds, the last one part
   // empty, and every round pays its start-up and drain.  Workgroups of two waves or one that keep the
   // probabilities of kNarrowPieceTokens tokens at a time are small enough for more of them to be resident; the
@@ -512,12 +551,12 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   }
   if constexpr (std::is_same<T, float>::value)
     if (merge_inside(s, ninst, a.n_split)) {
-      const size_t merge = merge_lds_bytes(a.n_split, G);
-      sparse_decode_kernel<T, D, G, kAttnWaves, false, true><<<dim3(a.n_split, ninst), kAttnThreads, lds > merge ? lds : merge, st>>>(a);
+      if (inside) sparse_decode_kernel<T, D, G, kAttnWaves, false, kSelectInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_inside, st>>>(a);
+      else sparse_decode_kernel<T, D, G, kAttnWaves, false, kMergeInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_of_form(a, lds, G, kMergeInside), st>>>(a);
       return hipGetLastError();
     }
   sparse_decode_kernel<T, D, G, kAttnWaves, false><<<dim3(a.n_split, ninst), kAttnThreads, lds, st>>>(a);
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e != hipSuccess || a.n_split == 1) return e;
   return run_combine<D, G>(ninst, a, st);
   }
@@ -615,6 +654,7 @@ hipError_t launch_sparse_decode(const Shape& s, int inst0, int ninst, const void
   a.piece_blocks = s.k;
   a.ml_unit = kLog2E;
   a.table = s.table; a.n_phys = s.n_phys;
+  a.pred = s.select_by; a.n_sink = s.n_sink; a.n_local = s.n_local; a.sel_at = 0;
   AP_DISPATCH(run_sparse, s, ninst, a, st)
 }
 

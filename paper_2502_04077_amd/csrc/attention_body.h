@@ -18,7 +18,7 @@
 
 #include <type_traits>
 
-#include "ap_internal.h"
+#include "select_body.h"
 
 namespace ap {
 namespace {
@@ -347,8 +347,32 @@ struct SparseArgs {
   int n_phys;                     // blocks in the pool (table entries are clamped into it)
   int piece_blocks;               // list positions whose probabilities are in LDS at a time
   float ml_unit;                  // the splits' maxima times this are exponents of 2
+  const float* pred;              // scores [n_inst][nb_cap] that the decode selects by itself (kSelectInside), writing idx and cnt
+  int n_sink, n_local, sel_at;    // forced blocks; where in LDS (floats) the list goes: k blocks and their number
   int* merge_count;               // [n_inst] splits that have left their partials, zero at launch (where they are merged inside)
 };
+
+// What a decode launch of an instance in splits does beside its own share: nothing; merging, by the last workgroup to finish;
+// before that also the selection, by every workgroup for itself (see run_stream).
+constexpr int kSplitsOnly = 0, kMergeInside = 1, kSelectInside = 2;
+constexpr int kSelectInsideKeys = 9;                    // scores a thread holds: up to 2304 candidates
+
+// The instance's selection by this workgroup of 256 threads, into LDS at a.sel_at; that of the first split writes idx and cnt too.
+// Returns the number of listed blocks.  smem: sel_scratch_words<256>() words that are free until it returns.
+__device__ __forceinline__ int select_inside(const SparseArgs& a, int inst, int split, float* smem) {
+  static_assert(kAttnThreads == kSelThreads, "one workgroup does both");
+  int32_t* s_list = reinterpret_cast<int32_t*>(smem + a.sel_at);
+  select_topk_body<kSelectInsideKeys, kSelThreads, 4>(a.pred + (size_t)inst * a.nb_cap, a.nb_cur, a.k, a.n_sink, a.n_local, s_list,
+                                                      s_list + a.k, reinterpret_cast<uint32_t*>(smem));
+  __syncthreads();
+  const int cnt = __builtin_amdgcn_readfirstlane(s_list[a.k]);
+  if (split == 0) {
+    int32_t* idx = const_cast<int32_t*>(a.idx) + (size_t)inst * a.k;
+    for (int j = threadIdx.x; j < cnt; j += kAttnThreads) idx[j] = s_list[j];
+    if (threadIdx.x == 0) const_cast<int32_t*>(a.cnt)[inst] = cnt;
+  }
+  return cnt;
+}
 
 // Data that one workgroup leaves for another of the same launch, which may run on another XCD with an L2 of its own: stores that are
 // written through to memory, loads that are answered from there (agent scope).  A release of ordinary stores would write back the
@@ -382,18 +406,14 @@ __device__ __forceinline__ void clear_row_share(const SparseArgs& a, int inst, i
 inline size_t merge_lds_bytes(int n_split, int g) { return n_split > 1 ? sizeof(float) * ((size_t)n_split * g + 1) : 0; }
 
 // Merges the splits of one instance, by one workgroup of kAttnThreads that has found itself the last: global (M, L) per head, normalised
-// output, pooled row.  smem: merge_lds_bytes(..).  The chain of loads is what it costs, so whatever does not depend on anything is asked
+// output, pooled row.  `block_of(jb)`: block at list position jb < cnt.  smem: merge_lds_bytes(..).  The chain of loads is what it costs, so whatever does not depend on anything is asked
 // for first.  (As a launch of its own: sparse_combine_kernel.)
-template <int D, int G>
-__device__ __forceinline__ void merge_splits(const SparseArgs& a, int inst, float* s_scale) {
+template <int D, int G, class BlockOf>
+__device__ __forceinline__ void merge_splits(const SparseArgs& a, int inst, int cnt, BlockOf block_of, float* s_scale) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const float* ml = a.part_ml + (size_t)inst * a.n_split * G * 2;        // [split][head] (maximum, sum relative to it)
   const float* acc = a.part_acc + (size_t)inst * a.n_split * G * D;
   const float* bmp = a.part_bmp + (size_t)inst * G * a.k;
-  const int cnt = min(max(a.cnt[inst], 0), a.k);
-  auto block_of = [&](int jb) __attribute__((always_inline)) {
-    return min(max(a.idx[(size_t)inst * a.k + jb], 0), a.nb_cur - 1);
-  };
   // This thread's first list position, with its block maxima, and its first outputs of the first splits.
   int blk = -1;
   float bm[G];
@@ -473,14 +493,18 @@ __device__ __forceinline__ void merge_splits(const SparseArgs& a, int inst, floa
 // probabilities of one piece only.  PIECED = false: a.piece_blocks covers the list, one piece, no rescaling
 // (and the accumulators are not live during phase 1).
 // smem: sparse_lds_floats(...) floats of LDS, 16-byte aligned.
-template <typename T, int D, int G, int NW, bool PIECED, bool MERGE>
+template <typename T, int D, int G, int NW, bool PIECED, int HOW>
 __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst, int split, float* smem) {
   using Ge = Geom<T, D, G>;
   constexpr int E = Ge::E, LPT = Ge::LPT, NL = Ge::NL, NT = NW * kWave;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int dpart = lane % LPT, tslot = lane / LPT;
 
-  const int cnt = min(max(a.cnt[inst], 0), a.k);
+  constexpr bool MERGE = HOW != kSplitsOnly;
+  int cnt;
+  if constexpr (HOW == kSelectInside) cnt = select_inside(a, inst, split, smem); else cnt = min(max(a.cnt[inst], 0), a.k);
+  const int32_t* list = HOW == kSelectInside ? reinterpret_cast<const int32_t*>(smem + a.sel_at) : a.idx + (size_t)inst * a.k;
+  auto listed = [&](int jb) __attribute__((always_inline)) { return min(max(list[jb], 0), a.nb_cur - 1); };
   // With one workgroup per instance the whole list is local; otherwise this split's slice.
   const int j0 = (a.n_split == 1) ? 0 : min(cnt, split * a.blk_per_split);
   const int j1 = (a.n_split == 1) ? cnt : min(cnt, j0 + a.blk_per_split);
@@ -514,7 +538,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
   if constexpr (MERGE) clear_row_share(a, inst, split);
   __syncthreads();
   for (int j = threadIdx.x; j < nblk; j += NT) {
-    const int blk = min(max(a.idx[(size_t)inst * a.k + j0 + j], 0), a.nb_cur - 1);
+    const int blk = listed(j0 + j);
     s_idx[j] = blk;
     s_phys[j] = a.table ? min(max(a.table[(size_t)inst * a.nb_cap + blk], 0), a.n_phys - 1) : blk;
     if (whole_row) atomicOr(&s_listed[blk >> 5], 1u << (blk & 31));
@@ -695,7 +719,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
       st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, s_bmp[pair]);
     }
     if constexpr (MERGE)
-      if (last_to_finish(a.merge_count + inst, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, smem);
+      if (last_to_finish(a.merge_count + inst, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
   }
 }
 
@@ -769,7 +793,7 @@ constexpr int kChainPasses = 8;
 // (head = l % 16, tokens 4 (l / 16) + v), v = 0..3: a row of 16 lanes holds the logits of four tokens, which are, for
 // d = 128, the tokens whose V rows the row reads, and the probability of a head is a DPP broadcast away.
 // smem: sparse_stream_lds_floats(...) floats of LDS, 16-byte aligned.
-template <int D, int G, bool MERGE>
+template <int D, int G, int HOW>
 __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst, int split, float* smem) {
   using T = bf16_t;
   using Ge = Geom<T, D, G>;
@@ -782,7 +806,11 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
   const int dpart = lane % LPT, tslot = lane / LPT;
   const int head = lane & 15, row16 = lane >> 4;         // what this lane's logits are of
 
-  const int cnt = min(max(a.cnt[inst], 0), a.k);
+  constexpr bool MERGE = HOW != kSplitsOnly;
+  int cnt;
+  if constexpr (HOW == kSelectInside) cnt = select_inside(a, inst, split, smem); else cnt = min(max(a.cnt[inst], 0), a.k);
+  const int32_t* list = HOW == kSelectInside ? reinterpret_cast<const int32_t*>(smem + a.sel_at) : a.idx + (size_t)inst * a.k;
+  auto listed = [&](int jb) __attribute__((always_inline)) { return min(max(list[jb], 0), a.nb_cur - 1); };
   // With one workgroup per instance the whole list is local; otherwise this split's slice.
   const bool whole_row = a.n_split == 1;
   const int j0 = whole_row ? 0 : min(cnt, split * a.blk_per_split);
@@ -809,7 +837,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
   }
   if constexpr (MERGE) clear_row_share(a, inst, split);
   for (int j = threadIdx.x; j < nblk; j += NT) {
-    const int blk = min(max(a.idx[(size_t)inst * a.k + j0 + j], 0), a.nb_cur - 1);
+    const int blk = listed(j0 + j);
     s_idx[j] = blk;
     s_phys[j] = a.table ? min(max(a.table[(size_t)inst * a.nb_cap + blk], 0), a.n_phys - 1) : blk;
     if (whole_row) atomicOr(&s_listed[blk >> 5], 1u << (blk & 31));
@@ -1079,7 +1107,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
       st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, block_max(h, jb));
     }
     if constexpr (MERGE)
-      if (last_to_finish(a.merge_count + inst, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, smem);
+      if (last_to_finish(a.merge_count + inst, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
   }
 }
 

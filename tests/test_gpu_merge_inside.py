@@ -1,5 +1,6 @@
-"""Splits merged by the last workgroup of an instance to finish (inside a fused step) against the merge in a launch of its own
-(the single call): the same bytes, call after call with new queries, whichever workgroup happens to be the last."""
+"""A fused step of few instances - the selection made by every split for itself, the splits merged by the last workgroup to finish -
+against the single calls, which have a launch for each: the same bytes, call after call with new queries, whichever workgroup
+happens to be the last."""
 import numpy as np
 import pytest
 import torch
@@ -15,6 +16,8 @@ pytestmark = pytest.mark.gpu
     (2, 1, 128, 8, 1024, 1100, "f32", 8),     # more splits than a wave has lanes
     (8, 4, 128, 16, 64, 2050, "bf16", 64), (1, 1, 128, 16, 300, 700, "bf16", 16), (128, 2, 64, 16, 64, 500, "bf16", 16),
     (5, 8, 128, 32, 64, 131, "bf16", 16), (1, 4, 128, 64, 256, 300, "bf16", 16), (2, 8, 64, 8, 4096, 4099, "bf16", 8),
+    (4, 4, 128, 8, 64, 2307, "bf16", 8), (4, 4, 128, 8, 64, 2308, "bf16", 8),         # most candidates the decode selects from, and one more
+    (3, 2, 128, 16, 131, 400, "bf16", 8), (3, 2, 128, 16, 132, 400, "bf16", 8),       # most free places, and one more
     (300, 4, 128, 16, 64, 200, "bf16", 16), (3, 4, 128, 16, 64, 40, "bf16", 16),      # (the last: lists shorter than the budget)
 ])
 def test_same_bytes(n, g, d, block, k, nb, dtype, hist):
@@ -24,7 +27,7 @@ def test_same_bytes(n, g, d, block, k, nb, dtype, hist):
     ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=block, hist_len=hist, t_cap=cap * block, k_blocks=k, n_sink=1, n_local=2, c1=4, c2=4,
                      kv_dtype=dtype)
     rng = np.random.default_rng([n, k, nb])
-    ctx.set_weights((0.2 * rng.standard_normal(n_weight_floats(4, 4))).astype(np.float32))
+    blob = (0.2 * rng.standard_normal(n_weight_floats(4, 4))).astype(np.float32)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     gen = torch.Generator(device=dev)
     gen.manual_seed(n * 1000 + k)
@@ -32,8 +35,8 @@ def test_same_bytes(n, g, d, block, k, nb, dtype, hist):
     ring = torch.rand((n, hist + 1, cap), generator=gen, device=dev)
     pred, pstate, row = (torch.zeros((n, cap), device=dev) for _ in range(3))
     out, out2 = (torch.zeros((n, g, d), device=dev) for _ in range(2))
-    idx = torch.zeros((n, k), dtype=torch.int32, device=dev)
-    cnt = torch.zeros((n,), dtype=torch.int32, device=dev)
+    idx, idx2 = (torch.full((n, k), -7, dtype=torch.int32, device=dev) for _ in range(2))
+    cnt, cnt2 = (torch.zeros((n,), dtype=torch.int32, device=dev) for _ in range(2))
     ws = torch.zeros((ctx.workspace_bytes(),), dtype=torch.uint8, device=dev)
     t, pushed = nb * block - 3, 4 * hist
     for i in range(12):
@@ -41,7 +44,10 @@ def test_same_bytes(n, g, d, block, k, nb, dtype, hist):
         ws.random_(0, 256, generator=gen)                # whatever an earlier call left there
         ring[:, pushed % (hist + 1)] = 9.0
         out.fill_(7.0)
+        ctx.set_weights(blob * (i != 5))                 # (all weights zero: scores that are all the same)
         ctx.step(ring, pushed, q, K, V, t, out, idx, cnt, pred, pstate, ap.AP_PRED_REBASE, ws)
+        ctx.select_topk(pred, nb, idx2, cnt2, ws)
+        assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2), i
         ctx.sparse_decode(q, K, V, t, idx, cnt, out2, row, ws)
         assert torch.equal(out, out2), i
         assert torch.equal(ring[:, pushed % (hist + 1)], row), i
