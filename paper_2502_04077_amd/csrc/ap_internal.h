@@ -15,7 +15,7 @@ constexpr int kAttnWaves = kAttnThreads / kWave;
 constexpr int kNarrowPieceTokens = 512;       // tokens whose probabilities a two- or one-wave sparse-decode workgroup holds in LDS at a time
 constexpr int kMaxHist = 256;                 // longest history ap_create accepts
 constexpr int kGroupTokens = 16;              // tokens one wave covers per load group (4 x dwordx4 loads)
-constexpr int kCalibChunkTokens = 1024;       // tokens per calibration chunk; bf16: at most (calib_chunk_tokens), and at least
+constexpr int kCalibChunkTokens = 1024;       // tokens per calibration chunk: at most (calib_chunk_tokens), and at least
 constexpr int kCalibMinChunkTokens = 256;     // (four blocks, one per wave)
 
 // Device-side layout of the predictor weights (all fp32), re-packed by ap_set_weights so that the

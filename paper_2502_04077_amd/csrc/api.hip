@@ -54,11 +54,10 @@ static int choose_split(const Shape& s) {
   return (s.k + per - 1) / per;
 }
 
-// Most chunks an instance can have in calibration (calib_chunk_tokens): t_cap in chunks of 1024 tokens, or in the bf16 form, whose
-// chunks are shorter where there are fewer than 1024 in all, up to 2048 of them over the instances.
+// Most chunks an instance can have in calibration (calib_chunk_tokens): t_cap in chunks of 1024 tokens, or, as they are shorter where
+// there are fewer than 1024 in all, up to 2048 of them over the instances.
 static int most_calib_chunks(const Shape& s) {
   const int full = (s.t_cap + kCalibChunkTokens - 1) / kCalibChunkTokens;
-  if (s.kv_dtype != AP_BF16) return full;
   const int least = (s.t_cap + kCalibMinChunkTokens - 1) / kCalibMinChunkTokens, filled = 2048 / s.n_inst + 1;
   return full > filled ? full : (least < filled ? least : filled);
 }

@@ -156,10 +156,13 @@ __global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a
   extern __shared__ __align__(16) float smem[];
   __shared__ int s_unit;
   for (;;) {
-    if (threadIdx.x == 0) s_unit = atomicAdd(a.counter, 1);
-    __syncthreads();
-    const int unit = s_unit;
-    if (unit >= a.n_units) break;                        // (the same for every thread; every workgroup gets here)
+    int unit = blockIdx.x;
+    if (a.counter != nullptr) {
+      if (threadIdx.x == 0) s_unit = atomicAdd(a.counter, 1);
+      __syncthreads();
+      unit = s_unit;
+      if (unit >= a.n_units) break;                      // (the same for every thread; every workgroup gets here)
+    }
     const int inst = unit / a.n_chunks, chunk = unit - inst * a.n_chunks;
     const int c0 = chunk * a.chunk_blocks;
     const int nblk = min(a.chunk_blocks, a.nb_cur - c0);
@@ -189,6 +192,7 @@ __global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a
       ml[0] = s_m[threadIdx.x];
       ml[1] = s_l[threadIdx.x];
     }
+    if (a.counter == nullptr) break;                     // (a workgroup has one unit)
     __syncthreads();                                     // the next unit overwrites s_unit and the tiles
   }
 }
@@ -562,12 +566,12 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   }
 }
 
-// Tokens of a calibration unit (and of the chunks the merge sees): 1024, or in bf16 512 or 256 where that leaves the chip
+// Tokens of a calibration unit (and of the chunks the merge sees): 1024, or 512 or 256 where that leaves the chip
 // without a workgroup for every place it has (8 instances at 32K: 1032 units of 256 tokens instead of 264 of 1024; 8 at 8K with
 // room for 128K 13.2 -> 9.5 us), unless the merge would have more than 60000 bytes of factors.
 int calib_chunk_tokens(const Shape& s, int t_cur) {
   int tokens = kCalibChunkTokens;
-  if (s.kv_dtype != AP_BF16) return tokens;
+  if (s.kv_dtype != AP_BF16 && s.k_on_host) return tokens;   // (the fp32 form has no small grid for the link)
   while (tokens > kCalibMinChunkTokens && (size_t)s.n_inst * t_cur / tokens < 1024 &&
          (2 * (size_t)t_cur / tokens + 2) * s.g * sizeof(float) <= 60000 && (2 * t_cur + tokens - 1) / tokens <= s.calib_chunks)
     tokens /= 2;
@@ -604,12 +608,14 @@ hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
     }
     calibrate_stream_kernel<D, G><<<dim3(grid), kAttnThreads, lds, st>>>(a);
   } else {
-    const size_t lds = sizeof(float) * ((size_t)G * a.chunk_blocks * a.b + G * a.chunk_blocks + 2 * G + a.chunk_blocks);
-    if (s.occ->calib_slots[0] < 0) s.occ->calib_slots[0] = resident_workgroups(calibrate_f32_kernel<D, G>, kAttnThreads, lds);
+    auto lds_of = [&](int blocks) { return sizeof(float) * ((size_t)G * blocks * a.b + G * blocks + 2 * G + blocks); };
+    if (s.occ->calib_slots[0] < 0)       // (for the longest units: no more than the chip holds of any)
+      s.occ->calib_slots[0] = resident_workgroups(calibrate_f32_kernel<D, G>, kAttnThreads, lds_of(kCalibChunkTokens / a.b));
     const int slots = s.occ->calib_slots[0] > 0 ? s.occ->calib_slots[0] : 2048;
     a.n_units = a.n_chunks * s.n_inst;
-    zero_counter_kernel<<<1, 1, 0, st>>>(a.counter);
-    calibrate_f32_kernel<D, G><<<dim3(a.n_units < slots ? a.n_units : slots), kAttnThreads, lds, st>>>(a);
+    if (a.n_units <= slots) a.counter = nullptr;         // (a workgroup each)
+    else zero_counter_kernel<<<1, 1, 0, st>>>(a.counter);
+    calibrate_f32_kernel<D, G><<<dim3(a.n_units < slots ? a.n_units : slots), kAttnThreads, lds_of(a.chunk_blocks), st>>>(a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -73,3 +73,28 @@ def test_calibrate_vs_float64(n, g, d, b, t, paged):
             ref[:, :t] = p
             ref = ref.view(g, cap, b).amax(dim=(0, 2))
             assert (row[i].double() - ref).abs().max() <= 2e-5 * ref.max(), (i, again)
+
+
+@pytest.mark.parametrize("n,g,d,b,lengths", [(1, 4, 64, 16, (2051, 255, 257, 1)), (3, 8, 128, 8, (5003, 513)), (700, 2, 64, 32, (1100, 2000))])
+def test_fp32_units(n, g, d, b, lengths):
+    """fp32 caches: units of 256 or 512 tokens, one a workgroup, and 1024 handed out by the counter, as the length of the call goes."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    cap = -(-max(lengths) // b) * b + b
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=b, hist_len=8, t_cap=cap, k_blocks=1, n_sink=0, n_local=0, c1=4, c2=4, kv_dtype="f32")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(cap)
+    K = torch.randn((n, cap, d), generator=gen, device=dev)
+    q = 2 * torch.randn((n, g, d), generator=gen, device=dev)
+    size = max(16, ctx.workspace_bytes())
+    ws = torch.full((size + 4096,), 255, dtype=torch.uint8, device=dev)
+    for t in lengths + lengths[:1]:
+        row = torch.full((n, cap // b), 7.0, device=dev)
+        ctx.calibrate(q, K, t, row, ws)
+        for i in sorted({0, n // 2, n - 1}):
+            p = torch.softmax(q[i].double() @ K[i, :t].double().T.contiguous() / math.sqrt(d), dim=1)
+            ref = torch.zeros((g, cap), dtype=torch.float64, device=dev)
+            ref[:, :t] = p
+            ref = ref.view(g, cap // b, b).amax(dim=(0, 2))
+            assert (row[i].double() - ref).abs().max() <= 2e-5 * ref.max(), (t, i)
+    assert (ws[size:] == 255).all()
