@@ -280,15 +280,14 @@ void predict_inc_mfma_kernel(const float* __restrict__ hist, const float* __rest
                        smem);
 }
 
-__global__ __launch_bounds__(256) void predict_inc_mfma16_kernel(const float* __restrict__ hist,
-                                                                 const float* __restrict__ wts_global, int R, int H,
-                                                                 int newest_slot, int nb_cur, int nb_cap, int inst0,
-                                                                 int advance, float* __restrict__ pstate,
-                                                                 float* __restrict__ pred, int* __restrict__ clear) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))   // two workgroups per CU: 256 VGPRs
+void predict_inc_mfma16_kernel(const float* __restrict__ hist, const float* __restrict__ wts_global, int R, int H,
+                               int newest_slot, int nb_cur, int nb_cap, int inst0, PassPlan plan, int advance,
+                               float* __restrict__ pstate, float* __restrict__ pred, int* __restrict__ clear, int ninst) {
   extern __shared__ __align__(16) float smem[];
-  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clear[inst0 + blockIdx.y] = 0;
-  predict_inc_mfma16_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0 + blockIdx.y, blockIdx.x,
-                          gridDim.x, advance, pstate, pred, smem);
+  if (clear != nullptr)                                  // (a workgroup may have a part of an instance, or several)
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < ninst; i += gridDim.x * 256) clear[inst0 + i] = 0;
+  predict_inc_mfma16_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0, plan, advance, pstate, pred, smem);
 }
 
 template <int SW>
@@ -408,44 +407,58 @@ hipError_t run_full(const Shape& s, int inst0, int ninst, const float* dweights,
   return hipGetLastError();
 }
 
+PassPlan pass_plan(int ninst, int n_pass, int cols, int slots) {
+  PassPlan plan;
+  plan.n_pass = n_pass;
+  plan.cols = cols;
+  plan.total = ninst * n_pass;
+  const int grid = plan.total < slots ? plan.total : slots;
+  plan.per_wg = (plan.total + grid - 1) / grid;
+  plan.inv_pass = (uint32_t)((0x100000000ull + n_pass - 1) / n_pass);
+  return plan;
+}
+
+// Passes per instance, of at most `widest` columns and hardly fewer than `narrowest`: what makes the rounds of the `slots` workgroups that the
+// chip holds at once shortest, a pass costing as much as some 100 columns besides its own.  Of the numbers that make as many
+// rounds the largest is the best one: the others need not be looked at.
+PassPlan plan_passes(int ninst, int nb_cur, int widest, int narrowest, int slots) {
+  constexpr int kPassCost = 100;
+  int n_pass = 1;
+  long best = -1;
+  const int least = (nb_cur + widest - 1) / widest, most = (nb_cur + narrowest - 1) / narrowest;
+  for (int p = least; p <= most; ++p) {
+    const long same = ((long)ninst * p + slots - 1) / slots * slots / ninst;
+    p = same < most ? (int)same : most;
+    const int cols = (nb_cur + p - 1) / p, used = (nb_cur + cols - 1) / cols;     // (no pass without columns)
+    const long rounds = ((long)ninst * used + slots - 1) / slots, cost = rounds * (cols + kPassCost);
+    if (best < 0 || cost < best) { best = cost; n_pass = used; }
+  }
+  return pass_plan(ninst, n_pass, (nb_cur + n_pass - 1) / n_pass, slots);
+}
+
 template <int C1, int C2>
 hipError_t run_inc(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist, int newest_slot,
                    int nb_cur, int advance, float* pstate, float* pred, hipStream_t st) {
   if (C1 == 8 && C2 == 8 && s.predictor_mfma) {
     const size_t lds = sizeof(float) * kPredRegLdsFloats;
-    // Workgroups the chip holds at once: four a CU (LDS and registers), 256 CUs.  Passes per instance: what makes the
-    // rounds of them shortest, a pass costing as much as some 100 columns besides its own, down to 112 columns (two
-    // pieces of a dense list for either wave of a half; down to 60 the same: 7.6 us at 8 instances, 14.1 at 128 x 8194).  Of the
-    // numbers that make as many rounds the largest is the best one: the others need not be looked at.
-    constexpr int kSlots = 1024, kPassCost = 100;
-    int n_pass = 1;
-    long best = -1;
-    const int least = (nb_cur + kRiPassCols - 1) / kRiPassCols, most = (nb_cur + 111) / 112;
-    for (int p = least; p <= most; ++p) {
-      const long same = ((long)ninst * p + kSlots - 1) / kSlots * kSlots / ninst;
-      p = same < most ? (int)same : most;
-      const int cols = (nb_cur + p - 1) / p, used = (nb_cur + cols - 1) / cols;     // (no pass without columns)
-      const long rounds = ((long)ninst * used + kSlots - 1) / kSlots, cost = rounds * (cols + kPassCost);
-      if (best < 0 || cost < best) { best = cost; n_pass = used; }
-    }
-    PassPlan plan;
-    plan.n_pass = n_pass;
-    plan.cols = (nb_cur + n_pass - 1) / n_pass;
-    plan.total = ninst * n_pass;
-    const int grid = plan.total < kSlots ? plan.total : kSlots;
-    plan.per_wg = (plan.total + grid - 1) / grid;
-    plan.inv_pass = (uint32_t)((0x100000000ull + n_pass - 1) / n_pass);
+    // Down to 112 columns a pass: two pieces of a dense list for either wave of a half (down to 60 the same: 7.6 us at 8
+    // instances, 14.1 at 128 x 8194).  1024 workgroups at once: four a CU (LDS and registers), 256 CUs.
+    const PassPlan plan = plan_passes(ninst, nb_cur, kRiPassCols, 112, 1024);
+    const int grid = plan.total < 1024 ? plan.total : 1024;
     predict_inc_mfma_kernel<<<dim3(grid), 256, lds, st>>>(hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan,
                                                           advance, pstate, pred, s.clear, ninst);
     return hipGetLastError();
   }
   if (C1 == 16 && C2 == 32 && s.predictor_mfma) {
     const size_t lds = sizeof(float) * kPred16LdsFloats;
-    const int tiles = (nb_cur + kP16IW - 1) / kP16IW;
-    int chunks = (1024 + s.n_inst - 1) / s.n_inst;       // two workgroups fit a CU
-    if (chunks > tiles) chunks = tiles;
-    predict_inc_mfma16_kernel<<<dim3(chunks, ninst), 256, lds, st>>>(
-        hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, advance, pstate, pred, s.clear);
+    // (down to 62 columns a pass: a block of 32 entries of a dense list for either wave of a half; two workgroups a CU)
+    PassPlan plan = plan_passes(ninst, nb_cur, kP16Cols, 62, 512);
+    if (plan.per_wg >= 8) {              // many passes a workgroup: whole chunks and a rest, instead of passes alike (dense rows 344 -> 327 us)
+      plan = pass_plan(ninst, (nb_cur + kP16Cols - 1) / kP16Cols, kP16Cols, 512);
+    }
+    const int grid = plan.total < 512 ? plan.total : 512;
+    predict_inc_mfma16_kernel<<<dim3(grid), 256, lds, st>>>(hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan, advance,
+                                                            pstate, pred, s.clear, ninst);
     return hipGetLastError();
   }
   constexpr int IW = C1 <= 8 ? 128 : 64;

@@ -1,5 +1,5 @@
-// Shared device code of the predictor kernels: weight access, ring addressing, operand types and the tile
-// geometry of the LDS-staged MFMA kernels (see predict.hip for the method).
+// Shared device code of the predictor kernels: weight access, ring addressing and operand types (see predict.hip for the
+// method).
 #pragma once
 
 #include "ap_internal.h"
@@ -83,16 +83,6 @@ __device__ __forceinline__ uint32_t split_hi_lo(float xv) {
   const half2v pr = {hi, (_Float16)(xv - (float)hi)};
   return __builtin_bit_cast(uint32_t, pr);
 }
-
-// Tile geometry of the incremental MFMA kernel for 16/32 channels: 124 output columns per tile; x columns c0-2 .. c0+125 (128) and y1
-// columns c0-1 .. c0+126 (128) are staged, of which outputs 0..123 use x columns 0..127 and y1 columns 0..125.
-// The two surplus columns of each MFMA block read past their row into finite values and feed only outputs
-// that are dropped.
-constexpr int kPmIW = 124;
-constexpr int kPmXW = 128;
-constexpr int kPmYW = 130;                        // y1 columns per plane (layer-2 reads run 2 past the 128 written)
-constexpr int kPmLD = 128;
-constexpr int kPmXBuf = 10 * kPmXW + 4;           // words per x buffer (layer-1 reads run 2 past the last row)
 
 }  // namespace
 }  // namespace ap

@@ -1,14 +1,24 @@
 // MFMA form of the incremental predictor for the paper's own network (16 and 32 hidden channels; architecture
 // table of the appendix "Implement Details").  Same method as predict_inc_mfma_body (see predict.hip): per
 // column, the state of the interior rows moves by (row entering) - (row leaving) and the four border rows are
-// evaluated afresh; 124 output columns per tile, waves 0,1 = top half, waves 2,3 = bottom half, each wave
-// owning two 32-column blocks.
+// evaluated afresh; waves 0,1 = top half, waves 2,3 = bottom half.
+//
+// Only columns that can contribute are evaluated, as in predict_inc8.h: an instance's columns are cut into passes of up to 252, a
+// thread stages one column (all ten rows) and says for either half whether one of the five values is other than zero, and the list a half
+// works off holds the outputs with such a value within two columns, the tile's ends, and their direct neighbours, ascending.
+// The list goes in chunks of 128 entries, of which the first and the last are neighbours: 126 outputs; its blocks of 32 are dealt to the two
+// waves of a half, and blocks beyond the list's end are left out.  With dense rows the list is every column.
+// Measured (us; before: every column, tiles of 124), histories of 64 selected blocks in runs: 2048 instances x 2050 columns 128 (295), 256 x 1251 17
+// (32), 8 x 2050 8.7 (9.1); all rows dense 327 (301), 31 (32.5), 8.8 (7.9); all zero 64 (293).  With a dense row every 32 steps one half
+// is dense in ten of 32.  With dense rows it is bound by issue: as many MFMAs as before and 8 % more vector instructions (stages,
+// lists and addresses); with sparse ones by the passes' serial part.  Two waves per SIMD, 242 VGPRs: 261 of them, and one workgroup a CU,
+// cost 70 %; without a straight path through both blocks of a wave, or with the lists made by scalar instructions, 30-100 % more on sparse rows.
 //
 // v_mfma_f32_32x32x16_f16: D[32 x 32] += A[32 x 16] * B[16 x 32]; lane l supplies row/column l % 32 and K
 // entries 8 (l / 32) .. + 7, and receives D rows 8 (v / 4) + 4 (l / 32) + v % 4 (v = 0..15) of column l % 32.
 //   layer 1: rows = (y1 row q, c1): two row blocks (q = 0,1 and q = 2,3); K = 16 = (x row 0..4, kw 0..2) + one
 //            unused slot; columns = 32 y1 columns.  x is scaled by 2^12 and split into f16 hi + lo (two MFMAs; the
-//            split is done once, when a tile's rows are staged),
+//            split is done once, when a pass's rows are staged),
 //            the weights are f16 scaled by 2^-4, the accumulator starts at 2^8 b1: the result is 2^8 y1 before
 //            the ReLU.  It is rounded to f16 (the scale keeps y1 up to 255 inside the f16 range), clamped at 0
 //            and stored as [half][q][channel half][column] x 8 channels, so a layer-2 operand is one 16-byte read.
@@ -24,31 +34,40 @@
 // that leaves the state is the one that entered only up to fp32 rounding; callers re-base now and then anyway.
 #pragma once
 
-#include "predict_body.h"
+#include "predict_inc8.h"
 
 namespace ap {
 namespace {
 
-constexpr int kP16IW = kPmIW, kP16XW = kPmXW, kP16YW = kPmYW, kP16LD = kPmLD, kP16XBuf = kPmXBuf;   // same tile geometry
+constexpr int kP16Staged = 256;                   // staged columns of a pass, one a thread: kP16Halo more than outputs on either side
+constexpr int kP16Halo = 2, kP16Cols = kP16Staged - 2 * kP16Halo;   // most output columns per pass
+constexpr int kP16Outs = 126;                     // outputs of a chunk of 128 list entries
+constexpr int kP16YW = 130;                       // y1 entries per plane (layer-2 reads run 2 past the 128 written)
+constexpr int kP16BitWords = 20;                  // read by the sixteen lanes of a row, and one further on either side
+constexpr int kP16XBuf = 10 * kP16Staged + 4;
 constexpr int kP16Y1Floats = 2 * 4 * 2 * kP16YW * 4;
 // A1 | 2^8 init1 | 2^-8 w3 | x offsets | 2^8 init2 of (half, row type all / border) | 2^8 lo2 of the same | 2^8 lo1 (f16)
 constexpr int kP16ConstFloats = 2 * 2 * kWave * 4 + 2 * 16 + 2 * 16 + 2 * 8 + 2 * 2 * 2 * 16 + 2 * 2 * 2 * 16 + 2 * 4;
-constexpr int kPred16LdsFloats = kP16Y1Floats + 2 * kP16XBuf + 8 * kP16LD + kP16ConstFloats;
+// y1 | two passes' x | partial sums [half][staged column] (moving, border) | lists | two passes' bits [half] | constants
+constexpr int kPred16LdsFloats = kP16Y1Floats + 2 * kP16XBuf + 4 * kP16Staged + kP16Staged + 4 * kP16BitWords + kP16ConstFloats;
+static_assert(kPred16LdsFloats * sizeof(float) <= 65536, "LDS of a workgroup");
 
-// Workgroup `chunk` of `n_chunks` of instance `inst` (256 threads); smem: kPred16LdsFloats floats, 16-byte aligned.
+// A workgroup of 256 threads takes a run of consecutive passes of all instances (PassPlan); smem: kPred16LdsFloats floats, 16-byte aligned.
 __device__ __forceinline__ void predict_inc_mfma16_body(const float* __restrict__ hist,
                                                         const float* __restrict__ wts_global, int R, int H,
-                                                        int newest_slot, int nb_cur, int nb_cap, int inst, int chunk,
-                                                        int n_chunks, int advance, float* __restrict__ pstate,
+                                                        int newest_slot, int nb_cur, int nb_cap, int inst0,
+                                                        const PassPlan& plan, int advance, float* __restrict__ pstate,
                                                         float* __restrict__ pred, float* smem) {
-  constexpr int C1 = 16, C2 = 32, IW = kP16IW, XW = kP16XW, YW = kP16YW, LD = kP16LD, XBUF = kP16XBuf;
+  constexpr int C1 = 16, C2 = 32, XW = kP16Staged, YW = kP16YW, XBUF = kP16XBuf;
   constexpr float kXScale = 4096.f, kAccScale = 256.f;
   half8* s_y1 = reinterpret_cast<half8*>(smem);          // [half 2][q 4][channel half 2][YW] x 8 f16
   uint32_t* s_xb = reinterpret_cast<uint32_t*>(smem + kP16Y1Floats);   // 2 buffers of [10][XW] (+4) hi|lo words
-  float* s_red = reinterpret_cast<float*>(s_xb + 2 * XBUF);                        // [half 2][moving | border][lane half 2][LD]
-  // Per-lane operands that only one phase of a tile needs live here and are re-read in that phase, which
+  float* s_part = reinterpret_cast<float*>(s_xb + 2 * XBUF);           // [half 2][XW][moving | border]
+  uint16_t* s_lists = reinterpret_cast<uint16_t*>(s_part + 4 * XW);    // [half 2][XW] staged column | kRiIsOutput
+  uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_lists + 2 * XW);    // [buffer 2][half 2][a zero word | column / 32 | zero words]
+  // Per-lane operands that only one phase of a chunk needs live here and are re-read in that phase, which
   // keeps the kernel at two waves per SIMD next to the 96 registers of layer-2 weights:
-  half8* s_a1 = reinterpret_cast<half8*>(s_red + 8 * LD);   // [half 2][row block 2][lane 64]
+  half8* s_a1 = reinterpret_cast<half8*>(s_bits + 4 * kP16BitWords);      // [half 2][row block 2][lane 64]
   float* s_b1 = reinterpret_cast<float*>(s_a1 + 2 * 2 * kWave);   // [lane half 2][16] accumulator start of layer 1
   float* s_w3 = s_b1 + 2 * 16;                           // [lane half 2][16] head weight of accumulator entry v
   int* s_xoff = reinterpret_cast<int*>(s_w3 + 2 * 16);   // [lane half 2][8]  x offset of layer-1 K slot e
@@ -58,19 +77,20 @@ __device__ __forceinline__ void predict_inc_mfma16_body(const float* __restrict_
   float* s_l2 = s_i2 + 2 * 2 * 2 * 16;                      // the same layout
   half4* s_l1 = reinterpret_cast<half4*>(s_l2 + 2 * 2 * 2 * 16);   // [channel half pl 2][lane half 2] clamp of the first layer
 
-  const int tiles = (nb_cur + IW - 1) / IW;
-  const int per_wg = (tiles + n_chunks - 1) / n_chunks;
-  const int t_begin = chunk * per_wg;
-  const int t_end = min(tiles, t_begin + per_wg);
-  if (t_begin >= t_end) return;
+  const int g_begin = blockIdx.x * plan.per_wg, g_end = min(plan.total, g_begin + plan.per_wg);
+  if (g_begin >= g_end) return;                          // (the whole workgroup)
+  int at_inst = g_begin, at_pass = 0;
+  if (plan.n_pass > 1) {
+    at_inst = __umulhi((uint32_t)g_begin, plan.inv_pass);
+    at_pass = g_begin - at_inst * plan.n_pass;
+    if (at_pass < 0) { --at_inst; at_pass += plan.n_pass; }
+  }
+  int inst = inst0 + at_inst, c0 = at_pass * plan.cols;
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int hf = wave >> 1;
+  const int hf = wave >> 1, wsub = wave & 1;
   const int n = lane & 31, hsel = lane >> 5;
-  const float* hist_inst = hist + (size_t)inst * R * nb_cap;
-  float* pstate_inst = pstate + (size_t)inst * nb_cap;
-  float* pred_inst = pred + (size_t)inst * nb_cap;
 
   // Operand tables and constants.
   const half8* tab = reinterpret_cast<const half8*>(wts_global + kMfma16TableFloatOffset);
@@ -106,44 +126,107 @@ __device__ __forceinline__ void predict_inc_mfma16_body(const float* __restrict_
   }
   if (tid < 4) s_xb[XBUF - 4 + tid] = s_xb[2 * XBUF - 4 + tid] = 0u;
 
-  // x staging: thread tid fetches column tid % 128 of staged rows hf, hf + 2, .., hf + 8; staged rows 0..4 are
-  // history rows -1..3, staged rows 5..9 are rows H-5..H-1.
-  const int xcol = (tid & (XW - 1)) - 2;
-  int xrow_off[5];
+  // Staging: thread tid fetches staged column tid (tile column c0 - kP16Halo + tid) of all ten rows, a pass ahead into registers; staged rows
+  // 0..4 are history rows -1..3, staged rows 5..9 are rows H-5..H-1.
+  uint32_t row_off[10];                                  // (wave-uniform, byte offsets into an instance's ring)
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    const int rr = hf + 2 * i;
-    xrow_off[i] = ring_slot(newest_slot, H, R, rr < 5 ? rr - 1 : H - 10 + rr) * nb_cap;
-  }
-  float xpre[5], pst_cur = 0.f, pst_next = 0.f;
+  for (int r = 0; r < 10; ++r)
+    row_off[r] = (uint32_t)__builtin_amdgcn_readfirstlane(ring_slot(newest_slot, H, R, r < 5 ? r - 1 : H - 10 + r)) * (uint32_t)nb_cap * 4u;
+  float xpre[10], pst_cur = 0.f, pst_next = 0.f;
   // Loads are unconditional on clamped addresses; the raw values stay untouched in registers until `stash`
-  // masks them, so nothing waits on them while the current tile is computed.
-  auto fetch = [&](int tile, float& pst) __attribute__((always_inline)) {
-    const int c0 = tile * IW;
-    const int j = min(max(c0 + xcol, 0), nb_cur - 1);
+  // masks them, so nothing waits on them while the current pass is computed.
+  auto fetch = [&](int in, int at, float& pst) __attribute__((always_inline)) {
+    const char* src = reinterpret_cast<const char*>(hist + (size_t)in * R * nb_cap);
+    const uint32_t j = (uint32_t)min(max(at - kP16Halo + tid, 0), nb_cur - 1);
 #pragma unroll
-    for (int i = 0; i < 5; ++i) xpre[i] = hist_inst[xrow_off[i] + j];
-    pst = pstate_inst[min(c0 + tid, nb_cur - 1)];
+    for (int i = 0; i < 10; ++i) xpre[i] = *reinterpret_cast<const float*>(src + (row_off[i] + j * 4u));
+    pst = (pstate + (size_t)in * nb_cap)[j];
   };
-  auto stash = [&](int tile, uint32_t* s_x) __attribute__((always_inline)) {
-    const int j = tile * IW + xcol;
-    const float scale = (j >= 0 && j < nb_cur) ? kXScale : 0.f;
+  // The words of a pass, and a bit per column and half: is one of its five values other than zero.
+  auto stash = [&](int at, int buf) __attribute__((always_inline)) {
+    const int j = at - kP16Halo + tid;
+    const bool inside = j >= 0 && j < nb_cur;
+    uint32_t* s_x = s_xb + buf * XBUF + tid;
 #pragma unroll
-    for (int i = 0; i < 5; ++i) s_x[(hf + 2 * i) * XW + (tid & (XW - 1))] = split_hi_lo(xpre[i] * scale);
+    for (int h2 = 0; h2 < 2; ++h2) {
+      uint32_t any = 0u;
+#pragma unroll
+      for (int r = 0; r < 5; ++r) {
+        const uint32_t w = split_hi_lo(inside ? xpre[h2 * 5 + r] * kXScale : 0.f);
+        any |= w;
+        s_x[(h2 * 5 + r) * XW] = w;
+      }
+      const unsigned long long m = __ballot((any & 0x7fff7fffu) != 0u);
+      if (lane < 2) s_bits[(buf * 2 + h2) * kP16BitWords + 1 + 2 * wave + lane] = (uint32_t)(m >> (32 * lane));
+    }
   };
   float inf = INFINITY;                 // opaque, so that med3(a, 0, inf) stays one instruction
   asm volatile("" : "+v"(inf));
-  fetch(t_begin, pst_cur);
-  stash(t_begin, s_xb);
+  for (int i = tid; i < 4 * kP16BitWords; i += 256) s_bits[i] = 0u;     // (the words around a row stay zero)
+  fetch(inst, c0, pst_cur);
+  __syncthreads();
+  stash(c0, 0);
   __syncthreads();
 
+  int buf = 0;
 #pragma unroll 1
-  for (int tile = t_begin; tile < t_end; ++tile) {
-    const int c0 = tile * IW;
-    const uint32_t* s_x = s_xb + ((tile - t_begin) & 1) * XBUF;
-    const bool more = tile + 1 < t_end;
-    if (more) fetch(tile + 1, pst_next);
-    int fresh = 0;                      // opaque zero: the phase operands are read again in every tile
+  for (int left = g_end - g_begin; left > 0; --left, buf ^= 1) {
+    const int len = min(nb_cur - c0, plan.cols);         // output columns, from staged column kP16Halo on
+    const uint32_t* s_x = s_xb + buf * XBUF;
+    const bool more = left > 1;
+    int inst_next = inst, c0_next = c0 + plan.cols;
+    if (c0_next >= nb_cur) { ++inst_next; c0_next = 0; }
+    if (more) fetch(inst_next, c0_next, pst_next);
+
+    // The halves' lists, as in predict_inc8.h: lane w of a row of 16 works on columns 32 w .. 32 w + 31, the even rows on the top half,
+    // the odd ones on the bottom half; then wave w writes the entries of columns 64 w .. 64 w + 63 of both.
+    int count[2];
+    bool output[2];                                      // is this thread's column an output of the half
+    {
+      const int w = lane & 15;
+      const uint32_t* bits = s_bits + (buf * 2 + ((lane >> 4) & 1)) * kP16BitWords + 1 + w;
+      const uint32_t a0 = bits[0], whole = bit_range(kP16Halo, kP16Halo + len, w);
+      count[0] = count[1] = len + 2;
+      output[0] = output[1] = true;                      // (in the columns of the pass)
+      if ((uint32_t)__ballot((a0 & whole) == whole) != ~0u) {          // has not every column of the pass a value in either half?
+        const uint32_t am = bits[-1], ap = bits[1];
+        // column i takes the bits of columns i - 2 .. i + 2
+        uint32_t out = a0 | __builtin_amdgcn_alignbit(a0, am, 31) | __builtin_amdgcn_alignbit(a0, am, 30) |
+                       __builtin_amdgcn_alignbit(ap, a0, 1) | __builtin_amdgcn_alignbit(ap, a0, 2);
+        out &= whole;
+        if (c0 == 0) out |= bit_range(kP16Halo, kP16Halo + 1, w);      // (beside the tile y1 = 0 stands for d1 = lo1)
+        if (c0 + len == nb_cur) out |= bit_range(kP16Halo + len - 1, kP16Halo + len, w);
+        const uint32_t prev = dpp_all<0x111>(out), next = dpp_all<0x101>(out);      // row_shr:1: word w - 1; row_shl:1: word w + 1
+        const uint32_t listed = out | __builtin_amdgcn_alignbit(out, prev, 31) | __builtin_amdgcn_alignbit(next, out, 1);
+        const uint32_t own = (uint32_t)__builtin_popcount(listed);
+        uint32_t incl = own;                               // inclusive sums over each row of 16 lanes
+        incl += dpp_all<0x111>(incl);
+        incl += dpp_all<0x112>(incl);
+        incl += dpp_all<0x114>(incl);
+        incl += dpp_all<0x118>(incl);
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) {
+          const int at = h2 * 16 + 2 * wave;
+          count[h2] = __builtin_amdgcn_readlane(incl, h2 * 16 + 15);
+          const uint32_t lo = __builtin_amdgcn_readlane(listed, at), hi = __builtin_amdgcn_readlane(listed, at + 1);
+          const uint32_t olo = __builtin_amdgcn_readlane(out, at), ohi = __builtin_amdgcn_readlane(out, at + 1);
+          output[h2] = __builtin_amdgcn_inverse_ballot_w64(((unsigned long long)ohi << 32) | olo);
+          const uint32_t rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, __builtin_amdgcn_readlane(incl - own, at)));
+          if (__builtin_amdgcn_inverse_ballot_w64(((unsigned long long)hi << 32) | lo))
+            s_lists[h2 * XW + rank] = (uint16_t)(tid | (output[h2] ? kRiIsOutput : 0u));
+        }
+      }
+    }
+    if (count[0] != len + 2 || count[1] != len + 2) __syncthreads();   // (dense lists are not looked at; the same for every wave)
+    const uint16_t* s_list = s_lists + hf * XW;
+    const int cnt = hf ? count[1] : count[0], longest = max(count[0], count[1]);
+    const bool dense = cnt == len + 2;                   // every column: entry e is column kP16Halo - 1 + e, an output but for
+                                                         // the ends (and what is read beyond them is staged, too)
+    auto entry_at = [&](int e) __attribute__((always_inline)) { return (uint32_t)s_list[min(e, cnt - 1)]; };
+
+#pragma unroll 1
+    for (int e_chunk = 0; e_chunk + 2 < longest; e_chunk += kP16Outs) {       // (the same for every wave)
+    int fresh = 0;                      // opaque zero: the phase operands are read again in every chunk
     asm volatile("" : "+v"(fresh));
 
     // Layer 1.
@@ -157,18 +240,17 @@ __device__ __forceinline__ void predict_inc_mfma16_body(const float* __restrict_
 #pragma unroll
       for (int e = 0; e < 8; ++e) xoff[e] = s_xoff[fresh + hsel * 8 + e];
       const half4 lo1a = s_l1[fresh + 0 * 2 + hsel], lo1b = s_l1[fresh + 1 * 2 + hsel];
-#pragma unroll
-      for (int blk = 0; blk < 2; ++blk) {
-        const int yc = ((wave & 1) * 2 + blk) * 32 + n;  // y1 column 0..127  <->  tile column c0 - 1 + yc
+      auto block = [&](int blk, int col) __attribute__((always_inline)) {
+        const int yc = (blk * 2 + wsub) * 32 + n;        // entry 0..127 of the chunk
         uint4v whi, wlo;
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
-          const uint32_t wa = xs[yc + xoff[e]], wb = xs[yc + xoff[e + 1]];
+          const uint32_t wa = xs[col - 1 + xoff[e]], wb = xs[col - 1 + xoff[e + 1]];
           whi[e / 2] = __builtin_amdgcn_perm(wb, wa, 0x05040100u);
           wlo[e / 2] = __builtin_amdgcn_perm(wb, wa, 0x07060302u);
         }
         const half8 Bhi = __builtin_bit_cast(half8, whi), Blo = __builtin_bit_cast(half8, wlo);
-        const int j = c0 - 1 + yc;
+        const int j = c0 - kP16Halo + col;
         const bool outside = j < 0 || j >= nb_cur;
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
@@ -193,6 +275,20 @@ __device__ __forceinline__ void predict_inc_mfma16_body(const float* __restrict_
             for (int p = 0; p < 2; ++p)
               reinterpret_cast<half4*>(s_y1 + ((hf * 4 + q) * 2 + p) * YW + yc)[hsel] = p ? lo1b : lo1a;
         }
+      };
+      // (both blocks without a branch between them, where the list is long enough: their chains hide each other's latency)
+      const int e = e_chunk + wsub * 32 + n;
+      if (e_chunk + (2 + wsub) * 32 < cnt) {
+        if (dense) {
+          block(0, kP16Halo - 1 + e);
+          block(1, kP16Halo - 1 + e + 64);
+        } else {
+          const int col0 = entry_at(e) & ~kRiIsOutput, col1 = entry_at(e + 64) & ~kRiIsOutput;
+          block(0, col0);
+          block(1, col1);
+        }
+      } else if (e_chunk + wsub * 32 < cnt) {
+        block(0, dense ? kP16Halo - 1 + e : entry_at(e) & ~kRiIsOutput);
       }
     }
     __syncthreads();
@@ -204,9 +300,8 @@ __device__ __forceinline__ void predict_inc_mfma16_body(const float* __restrict_
       b2acc[v] = s_i2[fresh + ((hf * 2 + 0) * 2 + hsel) * 16 + v];
       b2bor[v] = s_i2[fresh + ((hf * 2 + 1) * 2 + hsel) * 16 + v];
     }
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      const int cb = ((wave & 1) * 2 + blk) * 32;
+    auto block = [&](int blk) __attribute__((always_inline)) {
+      const int cb = (blk * 2 + wsub) * 32;              // outputs cb .. cb + 31: entries cb + 1 ..
       const half8* yq = s_y1 + ((size_t)hf * 4 * 2 + hsel) * YW + cb + n;   // + q * 2 * YW + kw
       float16v acc0, acc1, acc2;
 #pragma unroll
@@ -242,24 +337,36 @@ __device__ __forceinline__ void predict_inc_mfma16_body(const float* __restrict_
         t1 = fmaf(w, __builtin_amdgcn_fmed3f(acc1[v], lb, inf), t1);
         t2 = fmaf(w, __builtin_amdgcn_fmed3f(acc2[v], la, inf), t2);
       }
-      s_red[((hf * 2 + 0) * 2 + hsel) * LD + cb + n] = t0;
-      s_red[((hf * 2 + 1) * 2 + hsel) * LD + cb + n] = t1 + t2;
+      // Sum the two channel halves: afterwards lanes 0..31 hold the moving row, lanes 32..63 the two border rows.
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t0), __float_as_uint(t1 + t2), false, false);
+      const int e = e_chunk + cb + n + 1;
+      const uint32_t entry = dense ? (uint32_t)(kP16Halo - 1 + e) | kRiIsOutput : entry_at(e);
+      if (cb + n < kP16Outs && e < cnt - 1 && (entry & kRiIsOutput))
+        s_part[(hf * XW + (entry & ~kRiIsOutput)) * 2 + hsel] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    };
+    if (e_chunk + (2 + wsub) * 32 + 2 < cnt) { block(0); block(1); }
+    else if (e_chunk + wsub * 32 + 2 < cnt) block(0);
+    if (e_chunk + kP16Outs + 2 < longest) __syncthreads();               // (the next chunk overwrites what was read)
     }
+    // The next pass's words go to the other buffer; this barrier is also the one before its lists and y1 overwrite this pass's.
+    if (more) stash(c0_next, buf ^ 1);
     __syncthreads();
-    if (tid < IW && c0 + tid < nb_cur) {
-      auto part = [&](int half, int kind) __attribute__((always_inline)) {
-        return s_red[((half * 2 + kind) * 2 + 0) * LD + tid] + s_red[((half * 2 + kind) * 2 + 1) * LD + tid];
-      };
+    if (tid >= kP16Halo && tid < kP16Halo + len) {
+      const float2* part = reinterpret_cast<const float2*>(s_part);
+      float2 top = make_float2(0.f, 0.f), bot = make_float2(0.f, 0.f);       // (a column that is no output has no partial sums)
+      if (output[0]) top = part[tid];
+      if (output[1]) bot = part[XW + tid];
+      const size_t o = (size_t)inst * nb_cap + (c0 - kP16Halo + tid);
       float st = pst_cur;
-      if (advance) {
-        st = (st - part(0, 0)) + part(1, 0);
-        pstate_inst[c0 + tid] = st;
+      if (advance && (output[0] || output[1])) {
+        st = (st - top.x) + bot.x;
+        pstate[o] = st;
       }
-      pred_inst[c0 + tid] = (st + (part(0, 1) + part(1, 1))) / (float)H;
+      pred[o] = (st + (top.y + bot.y)) / (float)H;
     }
-    if (more) stash(tile + 1, s_xb + (((tile - t_begin) & 1) ^ 1) * XBUF);
     pst_cur = pst_next;
-    __syncthreads();
+    inst = inst_next;
+    c0 = c0_next;
   }
 }
 
