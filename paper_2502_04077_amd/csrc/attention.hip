@@ -429,13 +429,13 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 // 18.9 -> 18.4 us and three launches instead of four, of 128 at 128K 75.3 -> 73.8; 640 instances of two splits, counters cleared by a launch, 121 -> 132.)
 bool merge_inside(const Shape& s, int ninst, int n_split) { return s.cleared && n_split > 1 && (long)ninst * n_split <= 1024; }
 
-// Does the decode launch make the selection too?  Every workgroup of an instance makes all of it, which is no loss where they would
-// otherwise wait for the launch that does, and hardly any CU has two of them.  (Whole steps, 2041 candidates, us: 8 instances 17.6 -> 16.6,
-// 32 19.7 -> 18.4, 128 29.3 -> 28.0, one of fp32 with 126 candidates 16.8 -> 15.3, two launches instead of three; at 3742 candidates, with 16 keys
+// Does the streaming decode (and the fp32 one in splits) make the selection too?  Every workgroup of an instance makes all of it, which is
+// no loss where they would otherwise wait for the launch that does, and hardly any CU has two of them.  (Whole steps, 2041 candidates, us: 8 instances 17.6 -> 16.6,
+// 32 19.7 -> 18.4, 128 29.3 -> 28.0, one of fp32 with 126 candidates 16.8 -> 15.3, two launches instead of three; whole lists, 256 of 1243 candidates, 57.5 -> 55.1; at 3742 candidates, with 16 keys
 // a thread, 8 instances 22.7 and 128 45.6 -> 46.1: no gain.)
 bool select_here(const Shape& s, int ninst, int n_split, int nb_cur) {
   const int n_mid = nb_cur - s.n_sink - s.n_local, k_mid = s.k - s.n_sink - s.n_local;
-  return merge_inside(s, ninst, n_split) && (long)ninst * n_split <= 512 && n_mid <= kSelectInsideKeys * kSelThreads && k_mid >= 1 && k_mid <= kSelMaxMid;
+  return (n_split == 1 || merge_inside(s, ninst, n_split)) && (long)ninst * n_split <= 512 && n_mid <= kSelectInsideKeys * kSelThreads && k_mid >= 1 && k_mid <= kSelMaxMid;
 }
 
 // LDS bytes of a launch that merges, and selects if HOW says so, on top of lds for the decode; sets a.sel_at.
@@ -523,7 +523,7 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   a.piece_blocks = nblk_cap;
   const size_t lds = sizeof(float) * sparse_lds_floats<D, G, kAttnWaves>(nblk_cap, nblk_cap, a.b, a.nb_cap);
   size_t lds_inside = 0;
-  if (std::is_same<T, float>::value && a.pred != nullptr && select_here(s, ninst, a.n_split, a.nb_cur)) lds_inside = lds_of_form(a, lds, G, kSelectInside);
+  if (std::is_same<T, float>::value && a.n_split > 1 && a.pred != nullptr && select_here(s, ninst, a.n_split, a.nb_cur)) lds_inside = lds_of_form(a, lds, G, kSelectInside);
   const bool inside = lds_inside != 0 && lds_inside <= 65536;
   hipError_t e = inside ? hipSuccess : select_first(s, ninst, a, st);
   if (e != hipSuccess) return e;

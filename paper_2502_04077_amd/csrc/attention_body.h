@@ -352,8 +352,8 @@ struct SparseArgs {
   int* merge_count;               // [n_inst] splits that have left their partials, zero at launch (where they are merged inside)
 };
 
-// What a decode launch of an instance in splits does beside its own share: nothing; merging, by the last workgroup to finish;
-// before that also the selection, by every workgroup for itself (see run_stream).
+// What a decode launch does beside its own share: nothing; merging, by the last workgroup of an instance to finish;
+// before that also the selection, by every workgroup for itself (whole lists too; see select_here).
 constexpr int kSplitsOnly = 0, kMergeInside = 1, kSelectInside = 2;
 constexpr int kSelectInsideKeys = 9;                    // scores a thread holds: up to 2304 candidates
 
@@ -835,7 +835,8 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     for (int w = threadIdx.x; w < nwords; w += NT) s_listed[w] = 0u;
     __syncthreads();
   }
-  if constexpr (MERGE) clear_row_share(a, inst, split);
+  if constexpr (MERGE)
+    if (!whole_row) clear_row_share(a, inst, split);
   for (int j = threadIdx.x; j < nblk; j += NT) {
     const int blk = listed(j0 + j);
     s_idx[j] = blk;
