@@ -245,7 +245,7 @@ int ap_set_weights(ap_ctx* ctx, const float* blob, size_t n_floats, void* stream
     for (int lane = 0; lane < 64; ++lane)
       for (int e = 0; e < 4; ++e) {
         const int m = lane % 16, g = lane / 16;
-        const int kh = 2 * (g / 2) + e % 2 - m / 8, kw = g % 2 == 0 ? e / 2 : e < 2 ? 2 : -1;
+        const int kh = 2 * (g / 2) + e % 2 - m / 8, kw = g % 2 == 0 ? e / 2 : e >= 2 ? 2 : -1;
         float v = 0.f;
         if (kw >= 0 && kh >= 0 && kh < 3) v = w1[((m % 8) * 3 + kh) * 3 + kw] * (1.f / 16.f);
         t1[lane * 4 + e] = (_Float16)v;

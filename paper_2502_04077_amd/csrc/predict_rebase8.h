@@ -9,7 +9,7 @@
 // column, zeros outside the window).  v_mfma_f32_16x16x16_f16 and _16x16x32_f16: D[16 x 16] += A[16 x K] * B[K x 16], lane l
 // supplies row / column l % 16 and K entries K/4 (l / 16) .. and receives D rows 4 (l / 16) + v of column l % 16.
 //   layer 1  rows = (y1 row of the pair, channel), K = 16 = 4 lane groups x 2 words: x pair t-1 (groups 0, 1) or t (2, 3) of
-//            columns j-1, j (groups 0, 2) or j+1, j+2 (1, 3; the last with weight 0)
+//            columns j-1, j (groups 0, 2) or j, j+1 (1, 3; the first with weight 0)
 //   layer 2  rows = (output row, channel), K = 32 = two y1 pairs x 2 rows x 8 channels for one column tap: the result of
 //            layer 1 is, per lane, four channels of one y1 row of its own column, which is what its lane group supplies.  The
 //            centre tap takes those registers as they are, the outer taps the same moved by one lane with DPP moves; a
@@ -265,7 +265,7 @@ __device__ __forceinline__ void predict_rebase8_body(const float* __restrict__ h
       // Where this lane's two words of x pair t0 - 1 (or t0) begin.
       const uint32_t* xa[2];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) xa[b] = s_x + at[b] - 1 + 2 * (g & 1) + (g >> 1) * SW;
+      for (int b = 0; b < 2; ++b) xa[b] = s_x + at[b] - 1 + (g & 1) + (g >> 1) * SW;
 
       typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
       auto words = [&](int b, int j) __attribute__((always_inline)) { return u32x2{xa[b][j * SW], xa[b][j * SW + 1]}; };

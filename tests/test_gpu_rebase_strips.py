@@ -70,3 +70,25 @@ def test_full_tile(n, nb, H, mode):
     assert off(x[:, 1:], 2 * _reference(torch.from_numpy(x[check, :H]), blob, c1, c2)[1]) <= 0
     ctx.predict(hist, n_pushed + 1, nb, pred, ws)        # without a state of the caller's
     assert off(x[:, 1:]) <= 0
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 1e4])
+def test_what_is_not_finite_stays_where_it_is(bad):
+    """A value that is not finite (or leaves f16's range: 2^12 x) reaches the columns within two of it and no others."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    n, nb, H, b, c1, c2 = 3, 300, 64, 8, 8, 8
+    ctx = ap.Context(n_inst=n, g=1, head_dim=64, block=b, hist_len=H, t_cap=nb * b, k_blocks=2, n_sink=1, n_local=1, c1=c1, c2=c2, kv_dtype="bf16")
+    rng = np.random.default_rng(5)
+    ctx.set_weights((rng.standard_normal(n_weight_floats(c1, c2)) * 0.2).astype(np.float32))
+    x = _rows("dense", rng, n, H + 1, nb)
+    hist = torch.from_numpy(x).to(dev)                   # (H rows pushed after H + 1 others fill the ring in order)
+    pred, pstate, ref = (torch.zeros((n, nb), device=dev) for _ in range(3))
+    ws = torch.zeros((max(16, ctx.workspace_bytes()),), dtype=torch.uint8, device=dev)
+    ctx.predict_incremental(hist, H, nb, nb, ap.AP_PRED_REBASE, pstate, ref, ws)
+    for i, col in enumerate((0, 29, 173)):
+        hist[i, 30 + i, col] = bad
+    ctx.predict_incremental(hist, H, nb, nb, ap.AP_PRED_REBASE, pstate, pred, ws)
+    for i, col in enumerate((0, 29, 173)):
+        far = (torch.arange(nb, device=dev) - col).abs() > 2
+        assert torch.equal(pred[i][far], ref[i][far]), i
