@@ -34,8 +34,8 @@ WsLayout ws_layout(const Shape& s) {
   return w;
 }
 
-// The split partials and their counters lead the layout; a context with one workgroup per instance has none.
-size_t sparse_ws_floats(const Shape& s) { return s.n_split > 1 ? ws_layout(s).cal_ml : 0; }
+// The split partials lead the layout; a context with one workgroup per instance has none.
+size_t sparse_ws_floats(const Shape& s) { return s.n_split > 1 ? ws_layout(s).merge_count : 0; }
 
 static bool pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
 
@@ -448,7 +448,7 @@ int ap_sparse_decode_noalloc(ap_ctx* ctx, const void* q, const void* K, const vo
   AP_REQUIRE_PTR(out); AP_REQUIRE_PTR(row);
   const Shape& s = ctx->s;
   if (t_cur < 1 || t_cur > s.t_cap) return AP_ERR_RANGE;
-  if (s.n_split > 1 && ap::ws_layout(s).merge_count * sizeof(float) > AP_NOALLOC_SCRATCH_BYTES) return AP_ERR_RANGE;   // (the partials; the counters have room of their own)
+  if (ap::sparse_ws_floats(s) * sizeof(float) > AP_NOALLOC_SCRATCH_BYTES) return AP_ERR_RANGE;
   float* ws = nullptr;
   size_t bytes = 0;
   if (ap::static_scratch(&ws, &bytes) != hipSuccess) {

@@ -6,7 +6,7 @@
 // Scratch for the entry point that must not allocate (ap_sparse_decode_noalloc): the split partials of one
 // sparse-decode call.  Every device the library runs on holds its own copy until the process ends.  In host code
 // this name is only a handle for hipGetSymbolAddress; kernels get the address that call returned.
-constexpr size_t kStaticScratchBytes = AP_NOALLOC_SCRATCH_BYTES + (65536 + 4) * sizeof(int);    // (a counter per instance beside them)
+constexpr size_t kStaticScratchBytes = AP_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace ap {
