@@ -104,11 +104,10 @@ __host__ __device__ constexpr int ri_slot_row(int h, int e) { return e < 6 ? (h 
 __host__ __device__ constexpr int ri_slot_kw(int h, int e) { return e < 6 ? e / 2 : (h ? 2 : e - 6); }
 constexpr int kMfmaTableFloatOffset = 676;
 constexpr int kMfmaTableHalfs = 2 * 6 * 64 * 8 + 2 * 64 * 8;
-// ... followed by the tables of the full-tile kernel (predict_rebase8.h): layer 2 [order 2][kw 3][lane 64][8 f16], lane (m = 8 o + c2,
-// g): entries 0..3 (order 0; 4..7 in order 1) belong to y1 row q = g / 2 of the strip's four, the others to q = 2 + g / 2, input
-// channel 4 (g % 2) + e % 4, kernel row q - o; layer 1 [lane 64][4 f16], lane (m = 8 q + c1, g): entry e is x row
-// 2 (g / 2) + e % 2 of the pair's four and tap e / 2 (g even), or none for e < 2 and 2 (g odd); kernel row = x row - q, scaled 2^-4.
-constexpr int kMfmaRebaseTableHalfs = 2 * 3 * 64 * 8 + 64 * 4;
+// ... followed by the tables of the interior-state kernel (predict_rebase8.h): layer 2 [step 8][lane 64][8 f16], lane (m = 8 o + c2, h):
+// chunk 2 step + h = 3 q + kw of y1 row q, kernel row q - o, entry e is input channel e; layer 1 [lane 64][8 f16], lane (m = 8 q + c1, h):
+// entry e is K slot (h, e) = (x row ri_slot_row, tap ri_slot_kw) but for the constant, kernel row = x row - q, scaled 2^-4.
+constexpr int kMfmaRebaseTableHalfs = 8 * 64 * 8 + 64 * 8;
 // The same for 16/32 channels (fp32 section: 10*16 + 9*16*32 + 2*32 + 1 = 4833 floats):
 // layer 2 [half 2][pair 8][kw 3][lane 64][8 f16], lane (m = lane % 32, h = lane / 32) holding input channels
 // 8h..8h+7 of output channel m for the kernel row that pair (q, o) stands for; then layer 1

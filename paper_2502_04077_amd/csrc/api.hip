@@ -229,26 +229,25 @@ int ap_set_weights(ap_ctx* ctx, const float* blob, size_t n_floats, void* stream
         }
   }
   if (mfma_table) {
-    // Full-tile kernel: strips of two output rows from two pairs of y1 rows, and a pair of y1 rows from two pairs of x rows.
+    // Interior-state kernel: strips of three output rows o from five y1 rows q, and three y1 rows from five x rows; no row of it
+    // touches the zero padding in time.
     _Float16* t = reinterpret_cast<_Float16*>(packed.data() + ap::kMfmaTableFloatOffset) + ap::kMfmaTableHalfs;
-    for (int order = 0; order < 2; ++order)
-      for (int kw = 0; kw < 3; ++kw)
-        for (int lane = 0; lane < 64; ++lane)
-          for (int e = 0; e < 8; ++e) {
-            const int m = lane % 16, g = lane / 16, later = (e / 4) ^ order;
-            const int kh = 2 * later + g / 2 - m / 8, ci = 4 * (g % 2) + e % 4;
-            float v = 0.f;
-            if (kh >= 0 && kh < 3) v = w2[(((size_t)(m % 8) * c1 + ci) * 3 + kh) * 3 + kw];
-            t[((order * 3 + kw) * 64 + lane) * 8 + e] = (_Float16)v;
-          }
-    _Float16* t1 = t + 2 * 3 * 64 * 8;
+    for (int step = 0; step < 8; ++step)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int m = lane % 32, chunk = 2 * step + lane / 32, kh = chunk / 3 - m / 8;
+        for (int ci = 0; ci < 8; ++ci) {
+          float v = 0.f;
+          if (m < 24 && chunk < 15 && kh >= 0 && kh < 3) v = w2[(((size_t)(m % 8) * c1 + ci) * 3 + kh) * 3 + chunk % 3];
+          t[(step * 64 + lane) * 8 + ci] = (_Float16)v;
+        }
+      }
+    _Float16* t1 = t + 8 * 64 * 8;
     for (int lane = 0; lane < 64; ++lane)
-      for (int e = 0; e < 4; ++e) {
-        const int m = lane % 16, g = lane / 16;
-        const int kh = 2 * (g / 2) + e % 2 - m / 8, kw = g % 2 == 0 ? e / 2 : e >= 2 ? 2 : -1;
+      for (int e = 0; e < 8; ++e) {
+        const int m = lane % 32, xrow = ap::ri_slot_row(lane / 32, e), kh = xrow - m / 8;
         float v = 0.f;
-        if (kw >= 0 && kh >= 0 && kh < 3) v = w1[((m % 8) * 3 + kh) * 3 + kw] * (1.f / 16.f);
-        t1[lane * 4 + e] = (_Float16)v;
+        if (m < 24 && xrow >= 0 && kh >= 0 && kh < 3) v = w1[((m % 8) * 3 + kh) * 3 + ap::ri_slot_kw(lane / 32, e)] * (1.f / 16.f);
+        t1[lane * 8 + e] = (_Float16)v;
       }
   }
   if (mfma16_table) {

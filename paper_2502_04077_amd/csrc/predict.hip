@@ -291,14 +291,11 @@ void predict_inc_mfma16_kernel(const float* __restrict__ hist, const float* __re
 }
 
 template <int SW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))   // four workgroups per CU, as LDS has room for
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))   // three workgroups per CU, as LDS has room for
 void predict_rebase8_kernel(const float* __restrict__ hist, const float* __restrict__ wts_global, int R, int H, int newest_slot,
-                            int nb_cur, int nb_cap, int inst0, RebasePlan plan, float* __restrict__ pstate,
-                            float* __restrict__ pred, int* __restrict__ clear) {
+                            int nb_cur, int nb_cap, int inst0, RebasePlan plan, float* __restrict__ pstate) {
   extern __shared__ __align__(16) uint32_t smem_u[];
-  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clear[inst0 + blockIdx.y] = 0;
-  predict_rebase8_body<SW>(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0 + blockIdx.y, blockIdx.x, plan, pstate, pred,
-                       smem_u);
+  predict_rebase8_body<SW>(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0 + blockIdx.y, blockIdx.x, plan, pstate, smem_u);
 }
 
 __global__ __launch_bounds__(256) void predict_interior_mfma16_kernel(const float* __restrict__ hist,
@@ -485,23 +482,25 @@ hipError_t run_rebase16(const Shape& s, int inst0, int ninst, const float* dweig
 hipError_t run_rebase8(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist, int newest_slot,
                        int nb_cur, float* pstate, float* pred, hipStream_t st) {
   // Tiles: as wide as they may be (a tile stages eight columns beside its own), narrower where there would be fewer than the
-  // 1024 workgroups that the chip holds.
+  // 768 workgroups that the chip holds.
   RebasePlan plan;
   int tiles = (nb_cur + kRbCols - 1) / kRbCols;
-  const int filled = (1024 + ninst - 1) / ninst, most = (nb_cur + 55) / 56;
+  const int filled = (768 + ninst - 1) / ninst, most = (nb_cur + 55) / 56;
   if (tiles < filled) tiles = filled < most ? filled : most;
   plan.cols = (nb_cur + tiles - 1) / tiles;
   tiles = (nb_cur + plan.cols - 1) / plan.cols;
-  const int strips = (s.H + 1) / 2, segs = (strips + kRbStrips - 1) / kRbStrips;
+  const int strips = (s.H - 2) / 3, segs = (strips + kRbStrips - 1) / kRbStrips;
   plan.seg_strips = (strips + segs - 1) / segs;
 #define AP_REBASE(SW) \
   predict_rebase8_kernel<SW><<<dim3(tiles, ninst), 256, sizeof(uint32_t) * rebase_lds_words(SW, plan.seg_strips), st>>>( \
-      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan, pstate, pred, s.clear)
+      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan, pstate)
   if (plan.cols <= 64 - 2 * kRbHalo) AP_REBASE(64);
   else if (plan.cols <= 128 - 2 * kRbHalo) AP_REBASE(128);
   else AP_REBASE(256);
 #undef AP_REBASE
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return run_inc<8, 8>(s, inst0, ninst, dweights, hist, newest_slot, nb_cur, 0, pstate, pred, st);
 }
 
 }  // namespace

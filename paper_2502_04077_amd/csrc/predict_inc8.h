@@ -118,13 +118,14 @@ __device__ __forceinline__ void predict_inc_reg_body(const float* __restrict__ h
   const int n = lane & 31, hsel = lane >> 5;
 
   // Ring rows of the ten staged x rows, as byte offsets into an instance's ring: staged rows 0..4 of the top half are history
-  // rows -1..3, of the bottom half H-5..H-1.  (Wave-uniform: they live in scalar registers.)
+  // rows -1..3, of the bottom half H-5..H-1.  (Wave-uniform: they live in scalar registers.)  Without an advance no row leaves, and row -1 is
+  // not looked at, whatever it may hold: row 0 stands in for it.
   uint32_t row_off[2][5];
 #pragma unroll
   for (int h2 = 0; h2 < 2; ++h2)
 #pragma unroll
     for (int r = 0; r < 5; ++r)
-      row_off[h2][r] = (uint32_t)__builtin_amdgcn_readfirstlane(ring_slot(newest_slot, H, R, h2 ? H - 5 + r : r - 1)) * (uint32_t)nb_cap * 4u;
+      row_off[h2][r] = (uint32_t)__builtin_amdgcn_readfirstlane(ring_slot(newest_slot, H, R, h2 ? H - 5 + r : max(r - 1, advance ? -1 : 0))) * (uint32_t)nb_cap * 4u;
   // The raw rows of a pass are asked for a whole pass ahead and go straight to LDS: of the six pieces of 64 columns
   // wave w brings piece w of all ten rows and piece 4 + w / 2 of one half's rows (every address is clamped into the
   // tile; what lies outside only reaches lanes that mask it).  Staged column i is history column c0 - 4 + i.

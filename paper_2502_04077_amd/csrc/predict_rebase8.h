@@ -1,37 +1,37 @@
-// The predictor over the full history tile for 8/8 channels on MFMA: what a re-base or a first prediction needs.  Writes the
-// interior state of the incremental form,
-//   state[j] = sum_{r=2}^{H-3} sum_c w3[c] * (relu(y2[c][r][j]) - relu(B2[c]))      (difference form, ap_internal.h),
-// and pred, which adds the border rows 0, 1, H-2, H-1.  Same arithmetic as the incremental kernel (x as one f16 of 2^12 x,
-// fp32 accumulation, y1 kept as f16 of 2^8 d1), so a re-based state continues the advanced one without a step.
+// The interior state of the incremental predictor from scratch, 8/8 channels on MFMA: what a re-base or a first prediction needs,
+//   state[j] = sum_{r=2}^{H-3} sum_c w3[c] * (relu(y2[c][r][j]) - relu(B2[c]))      (difference form, ap_internal.h).
+// The border rows 0, 1, H-2, H-1 and pred are then added by the incremental kernel run without an advance.  Same operands as there (x as one
+// f16 of 2^12 x, fp32 accumulation, y1 kept as f16 of 2^8 d1), so a re-based state continues the advanced one without a step.
 //
-// The time axis is walked in strips of two output rows: strip t is rows 2t, 2t+1, which meet y1 rows 2t-1 .. 2t+2, i.e. the
-// y1 pairs t and t+1 (pair t: rows 2t-1, 2t), and pair t meets the x pairs t-1 and t (x pair p: rows 2p, 2p+1; one word of LDS a
-// column, zeros outside the window).  v_mfma_f32_16x16x16_f16 and _16x16x32_f16: D[16 x 16] += A[16 x K] * B[K x 16], lane l
-// supplies row / column l % 16 and K entries K/4 (l / 16) .. and receives D rows 4 (l / 16) + v of column l % 16.
-//   layer 1  rows = (y1 row of the pair, channel), K = 16 = 4 lane groups x 2 words: x pair t-1 (groups 0, 1) or t (2, 3) of
-//            columns j-1, j (groups 0, 2) or j, j+1 (1, 3; the first with weight 0)
-//   layer 2  rows = (output row, channel), K = 32 = two y1 pairs x 2 rows x 8 channels for one column tap: the result of
-//            layer 1 is, per lane, four channels of one y1 row of its own column, which is what its lane group supplies.  The
-//            centre tap takes those registers as they are, the outer taps the same moved by one lane with DPP moves; a
-//            pair is used twice, as the later and as the earlier one.  Three MFMAs a strip.
-//   head     fp32: clamp, weight, into a running sum per lane; lane groups are added up once per item.
-// An item is 32 columns (two blocks of 16, the inner lanes at the seam exchanged), whose first and last have wrong neighbours: 30
-// outputs.  (Blocks of 32 columns with three output rows of 32 D rows, as before, fill 42 % of their MFMAs, these 75 %.)
+// The time axis is walked in strips of three output rows, with v_mfma_f32_32x32x16_f16: D[32 x 32] += A[32 x 16] * B[16 x 32]; lane l
+// supplies row / column l % 32 and K entries 8 (l / 32) .. + 7 and receives D rows 8 (v / 4) + 4 (l / 32) + v % 4 of column l % 32.
+//   pass p    layer 1 for y1 rows 1+3p .. 3+3p from x rows 3p .. 3p+4: rows = (y1 row, channel), 8 of 32 idle; K = 15 (x row, tap) pairs.
+//             A column's x rows lie in LDS as f16 in threes: a word with rows 3p, 3p+1 and a half word with row 3p+2
+//   strip s   layer 2 for output rows 2+3s .. 4+3s from the y1 rows of passes s and s+1, of which the wave keeps six in LDS:
+//             rows = (output row, channel), K = 15 (y1 row, tap) chunks of 8 channels in 8 steps, each operand one 16-byte read
+//   head      fp32: clamp, weight, the four channels of a lane, into a running sum; the two channel halves meet at the end
+// Order is part of the result: an MFMA adds its K entries in two groups of eight, the second onto what the first gave (the order inside a
+// group does not matter), so a y2 value is nine groups of 8 channels in the order of the taps, and a column's sum goes row by row.  A column is
+// evaluated by one item, from its first strip to its last, whatever its neighbours in the tile need: equal windows
+// have equal states, bit for bit, wherever they lie, and blocks whose scores coincide are told apart by their order alone.  (Sums taken in another order - two
+// rows at a time, dense and sparse strips apart - are no further from the exact ones, but decide near ties another way now and then.)
 //
-// Only what can contribute is evaluated: where the five columns around an output are zero in the six rows around a strip, its
-// terms are exactly zero.  Every column has a bit per x pair, so a word per column says which strips matter.  A row that a sparse step pushed
+// Only what can contribute is evaluated: where the five columns around an output are zero in the seven rows around a strip, its
+// terms are exactly zero.  Every column has a bit per three x rows, so a word per column says which strips matter.  A row that a sparse step pushed
 // is zero outside the selection, a row of a prefill or a calibration nowhere: strips that matter in more than half of a tile's columns
-// are evaluated in all of them, and for the other strips the columns in which one matters are listed with
-// their neighbours, as in predict_inc8.h, and an item walks those strips that matter in one of its columns.
-// A tile's rows are read once, straight into f16 words; four workgroups a CU, so that some read while others compute.
+// are dense.  The columns in which another strip matters are listed with their neighbours, as in predict_inc8.h, and an item
+// of 32 entries, 30 outputs, walks the dense strips and those that matter in one of its columns; items of consecutive columns walk the
+// dense strips for the others (or all that matter in one of theirs, where most columns would be listed).
+// A tile's rows are read once, straight into f16 words.
 //
-// Measured at 2048 instances x 2050 columns, H = 64, state and pred (before: three output rows to 32 D rows, every strip of every
-// column, the border rows and pred by a second launch over ten rows): histories of 64 selected blocks in runs with a dense row every 32 steps 381 us
-// (913), without dense rows 302 (972), all rows dense 695 (991), all zero 233 (965); 8 instances 10 us (15.8).  The 1.09 GB of rows are 155 us
-// at a plain read's rate, and 205 us with the masks and lists and no arithmetic; dense strips are bound by issue: 160 cycles of vector instructions
-// (twelve DPP moves, sixteen of the head, eight of the first layer's results) and 128 of MFMAs a strip and item, 240 together.
-// Measured and not kept: strips with border rows inside the runs (381 -> 415: branches in every strip), all 64 rows of a column on their
-// way at once (255 -> 360 on zeros: registers), an instance's tiles on one XCD (no difference).
+// Measured at 2048 instances x 2050 columns, H = 64, state and pred, 33 to 77 us of it the border rows and pred (before: every strip of every
+// column, rows staged by every wave for itself): histories of 64 selected blocks in runs with a dense row every 32 steps 539 us (866),
+// without dense rows 444 (955), all rows dense 884 (1012), all zero 305 (950); 8 instances 18 us (18).  Reading the 1.09 GB of rows and
+// listing take 213 us without arithmetic (155 at a plain read's rate); then it is bound by a strip's chain: nine MFMAs of which eight
+// build on each other, y1 into LDS and back, the head, some 540 cycles with three waves a SIMD and 800 where one wave of a workgroup has the listed columns.
+// Measured and not kept: operands asked for a strip ahead but their addresses kept in a register each (spills: 588 us instead of 539), 66
+// rows on their way at a time (no difference), the same sums by 16x16x32 MFMAs, two output rows at a time and half the
+// MFMA cycles (533, all dense 911).  Strips of two rows summed in an order of their own, dense and listed ones apart, take 369 us.
 #pragma once
 
 #include "predict_body.h"
@@ -41,166 +41,160 @@ namespace {
 
 constexpr int kRbOut = 30;                              // outputs per item
 constexpr int kRbCols = 8 * kRbOut;                     // most output columns per tile (two items a wave)
-constexpr int kRbStrips = 32;                           // most strips per segment of the time axis (one bit each)
-constexpr int kRbBatch = 16;                            // x pairs of a column on their way at a time
+constexpr int kRbStrips = 21;                           // most strips per segment of the time axis
 constexpr int kRbHalo = 4;                              // staged columns on either side of a tile's outputs
+constexpr int kRbYW = 34;                               // y1 columns of a row (32 written, reads run 2 further)
 
-// Tiles of cols columns (staged: 64, 128 or 256, at least cols + 8), the time axis in segments.
+// Tiles of cols columns (staged: 64, 128 or 256, at least cols + 8), the time axis in segments of at most kRbStrips strips.
 struct RebasePlan { int cols, seg_strips; };
 
-// LDS words: x pairs | sums [dense, listed][column] (interior, border), before that a mask of x pairs per thread |
-// strips per column | list (bytes), before that active columns per wave and strip |
-// outputs per wave | where the second layer starts and is clamped, per row type
-constexpr int rebase_sum_words(int staged) { return 4 * staged > 512 ? 4 * staged : 512; }
+// LDS words: y1 [wave][6 rows][kRbYW] x 8 f16 | x rows in threes: two in a word, the third in a half word |
+// sums [channel half][column], before that masks of x rows per thread | strips per column | active columns per wave and strip, then
+// the list (bytes) | listed columns per wave | next item
+constexpr int kRbY1Words = 4 * 6 * kRbYW * 4;
 constexpr int rebase_lds_words(int staged, int seg_strips) {
-  return (seg_strips + 2) * staged + rebase_sum_words(staged) + staged + 4 * kRbStrips + 8 + 8 * 8;
+  return kRbY1Words + (seg_strips + 2) * staged * 3 / 2 + 512 + staged + 4 * 32 + 8 + 4;
 }
+static_assert(rebase_lds_words(256, kRbStrips) * 4 * 3 <= 160 * 1024, "three workgroups a CU");
 
-typedef float rb_float4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float add_lane_groups(float v) {      // sum over the four rows of 16 lanes, in every lane
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
-// Moved by a lane within rows of 16: lane n gets lane n - 1 / n + 1; at the row's end what `other` has at its far end (a block's
-// neighbour), or, without one, anything.
-template <int CTRL> __device__ __forceinline__ uint32_t dpp_row(uint32_t old, uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, 0xF, 0xF, false);
-}
-constexpr int kRowShl1 = 0x101, kRowShr1 = 0x111, kRowRor1 = 0x121, kRowRor15 = 0x12F;
-
-// Workgroup of 256 threads, SW staged columns; smem: rebase_lds_words(..) words.
+// Workgroup of 256 threads, SW staged columns; smem: rebase_lds_words(..) words, 16-byte aligned.
 template <int SW>
 __device__ __forceinline__ void predict_rebase8_body(const float* __restrict__ hist, const float* __restrict__ wts_global, int R,
                                                      int H, int newest_slot, int nb_cur, int nb_cap, int inst, int tile,
-                                                     const RebasePlan& plan, float* __restrict__ pstate,
-                                                     float* __restrict__ pred, uint32_t* smem) {
+                                                     const RebasePlan& plan, float* __restrict__ pstate, uint32_t* smem) {
   constexpr int C = 8;
   constexpr float kXScale = 4096.f, kAccScale = 256.f;
   typedef _Float16 half2v __attribute__((ext_vector_type(2)));
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int n = lane & 15, g = lane >> 4;
+  const int n = lane & 31, h = lane >> 5;
   constexpr int kParts = 256 / SW;                       // threads per staged column
+  constexpr int kBatch = SW == 64 ? 6 : 11;              // threes of x rows of a column on their way at a time
   const int c0 = tile * plan.cols, len = min(nb_cur - c0, plan.cols);
   const float* hist_inst = hist + (size_t)inst * R * nb_cap;
 
-  uint32_t* s_x = smem;                                                        // [seg_strips + 2][SW]
-  float2* s_sum = reinterpret_cast<float2*>(smem + (plan.seg_strips + 2) * SW);   // [2][SW]
-  unsigned long long* s_mask = reinterpret_cast<unsigned long long*>(s_sum);   // [256]
-  uint32_t* s_act = smem + (plan.seg_strips + 2) * SW + rebase_sum_words(SW);  // [SW]
-  uint32_t* s_cnt = s_act + SW;                                                // [wave 4][kRbStrips]
+  half8* s_y1 = reinterpret_cast<half8*>(smem) + wave * 6 * kRbYW;             // [6][kRbYW]
+  const int n_threes = plan.seg_strips + 2;
+  uint32_t* s_x01 = smem + kRbY1Words;                                         // [n_threes][SW]
+  _Float16* s_x2 = reinterpret_cast<_Float16*>(s_x01 + n_threes * SW);         // [n_threes][SW]
+  uint32_t* s_rest = s_x01 + n_threes * SW * 3 / 2;
+  float* s_sum = reinterpret_cast<float*>(s_rest);                             // [2][SW]
+  unsigned long long* s_mask = reinterpret_cast<unsigned long long*>(s_rest);  // [256]
+  uint32_t* s_act = s_rest + 512;                                              // [SW]
+  uint32_t* s_cnt = s_act + SW;                                                // [wave 4][32]
   uint8_t* s_list = reinterpret_cast<uint8_t*>(s_cnt);                         // [SW]
-  unsigned long long* s_out = reinterpret_cast<unsigned long long*>(s_cnt + 4 * kRbStrips);   // [wave 4]
+  unsigned long long* s_out = reinterpret_cast<unsigned long long*>(s_cnt + 4 * 32);   // [wave 4]
+  int* s_next = reinterpret_cast<int*>(s_out + 4);       // next item
 
-  const rb_float4* s_dc = reinterpret_cast<rb_float4*>(s_out + 4) + (g & 1);   // [start, clamp][row type 4][channel half 2]
-
-  // Operand tables and per-lane constants.
-  const half8* tab2 = reinterpret_cast<const half8*>(wts_global + kMfmaTableFloatOffset) + kMfmaTableHalfs / 8;
-  half8 A2[2][3];                                        // [which half of B holds the earlier pair][tap]
-#pragma unroll
-  for (int o = 0; o < 2; ++o)
-#pragma unroll
-    for (int kw = 0; kw < 3; ++kw) A2[o][kw] = tab2[(o * 3 + kw) * kWave + lane];
-  const half4 A1 = reinterpret_cast<const half4*>(tab2 + 6 * kWave)[lane];
-  const rb_float4* dc = reinterpret_cast<const rb_float4*>(wts_global + delta_const_offset(C, C)) + (g & 1);   // channels 4 (g % 2) ..
-  const rb_float4 b1acc = kAccScale * dc[0], b2all = kAccScale * dc[(2 * C + kRowAll * C) / 4];
-  const rb_float4 lo2all = kAccScale * dc[(2 * C + (4 + kRowAll) * C) / 4];
-  const rb_float4 w3v = (1.f / kAccScale) * reinterpret_cast<const rb_float4*>(wts_global + 10 * C + 9 * C * C + C)[g & 1];
-  half4 lo1h;
-  {
-    const rb_float4 lo1 = kAccScale * dc[C / 4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) lo1h[c] = (_Float16)lo1[c];
-  }
-  if (tid < 8 * C) reinterpret_cast<float*>(s_out + 4)[tid] = kAccScale * wts_global[delta_const_offset(C, C) + 2 * C + tid];
-  float inf = INFINITY;                                  // opaque, so that med3(a, lo, inf) stays one instruction
-  asm volatile("" : "+v"(inf));
-
-  const int n_strips = (H + 1) / 2;
-  const int col = tid & (SW - 1), part = __builtin_amdgcn_readfirstlane(tid / SW);   // staged column, and which of its x pairs
+  const int n_rows = H - 4, n_strips = (n_rows + 2) / 3; // interior rows 2 .. H-3
+  const int col = tid & (SW - 1), part = __builtin_amdgcn_readfirstlane(tid / SW);   // staged column, and which of its x rows
   const int j_col = c0 - kRbHalo + col;                  // its column of the tile
   const bool is_out = part == 0 && col >= kRbHalo && col < kRbHalo + len;
-  float total_int = 0.f, total_bor = 0.f;                // of this thread's column
+  float total[2] = {0.f, 0.f};                           // of this thread's column, by channel halves
 
 #pragma unroll 1
   for (int t0 = 0; t0 < n_strips; t0 += plan.seg_strips) {
     const int n_seg = min(plan.seg_strips, n_strips - t0);
-    const uint32_t seg_mask = n_seg == 32 ? ~0u : (1u << n_seg) - 1u;
-    // x pairs t0 - 1 .. t0 + n_seg: f16 of 2^12 x, zero outside the window and the tile, and a bit for each that is not zero.
-    // A thread takes a run of its column's pairs, sixteen rows on their way at a time.
+    const uint32_t seg_mask = (1u << n_seg) - 1u;
+    // x rows 3 t0 .. 3 (t0 + n_seg) + 5: f16 of 2^12 x, zero outside the window and the tile, and two bits for every three: is one of
+    // them other than zero, and is the first.  A thread takes a run of its column's rows, up to 33 on their way at a time.
     {
-      const bool last_seg = t0 + n_seg == n_strips;
-      const int lo = t0 == 0 ? 1 : 0, hi = n_seg + 2 - (last_seg ? 1 : 0), per = (hi - lo + kParts - 1) / kParts;
-      const int i_begin = lo + part * per, i_end = min(hi, i_begin + per);
-      const uint32_t keep = j_col >= 0 && j_col < nb_cur ? ~0u : 0u;
+      const int per = (n_seg + 2 + kParts - 1) / kParts, i_begin = part * per, i_end = min(n_seg + 2, i_begin + per);
+      const bool inside = j_col >= 0 && j_col < nb_cur;
       // (rows as scalar byte offsets into the instance's ring, walked from slot to slot)
       const uint32_t j_load = (uint32_t)min(max(j_col, 0), nb_cur - 1) * 4u, row_bytes = (uint32_t)nb_cap * 4u;
-      int row = 2 * (t0 - 1 + i_begin), slot = ring_slot(newest_slot, H, R, min(row, H - 1));
-      if (part == 0 && t0 == 0) s_x[col] = 0u;
-      if (part == 0 && last_seg) s_x[(n_seg + 1) * SW + col] = 0u;
+      int row = 3 * (t0 + i_begin), slot = ring_slot(newest_slot, H, R, min(row, H - 1));
       unsigned long long mask = 0;
 #pragma unroll 1
-      for (int i0 = i_begin; i0 < i_end; i0 += kRbBatch) {
-        float x[kRbBatch][2];
+      for (int i0 = i_begin; i0 < i_end; i0 += kBatch) {
+        float x[kBatch][3];
 #pragma unroll
-        for (int u = 0; u < kRbBatch; ++u) {
+        for (int u = 0; u < kBatch; ++u) {
 #pragma unroll
-          for (int r = 0; r < 2; ++r) {                  // (past the last row the last one again)
+          for (int r = 0; r < 3; ++r) {                  // (past the last row the last one again)
             x[u][r] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(hist_inst) + (j_load + (uint32_t)slot * row_bytes));
             if (++row < H && ++slot == R) slot = 0;
           }
         }
 #pragma unroll
-        for (int u = 0; u < kRbBatch; ++u)               // (all on their way before the first is used)
-          asm volatile("" : "+v"(x[u][0]), "+v"(x[u][1]));
-        uint32_t bits = 0u;
+        for (int u = 0; u < kBatch; ++u)               // (all on their way before the first is used)
+          asm volatile("" : "+v"(x[u][0]), "+v"(x[u][1]), "+v"(x[u][2]));
+        uint32_t some = 0u, first = 0u;
 #pragma unroll
-        for (int u = 0; u < kRbBatch; ++u) {
+        for (int u = 0; u < kBatch; ++u) {
           if (i0 + u >= i_end) break;
-          const int i = i0 + u;
-          const half2v h = {(_Float16)(x[u][0] * kXScale), (_Float16)(x[u][1] * kXScale)};
-          const uint32_t rows = 2 * (t0 + i) > H ? 0xffffu : ~0u;      // (the second row is row H)
-          const uint32_t w = __builtin_bit_cast(uint32_t, h) & (keep & rows);
-          s_x[i * SW + col] = w;
-          bits |= (w & 0x7fff7fffu) != 0u ? 1u << u : 0u;
+          const int i = i0 + u, left = H - 3 * (t0 + i);      // rows of the three that exist
+          const half2v x01 = {(_Float16)(x[u][0] * kXScale), (_Float16)(x[u][1] * kXScale)};
+          const _Float16 x2 = (_Float16)(x[u][2] * kXScale);
+          const uint32_t keep = left >= 2 ? ~0u : left == 1 ? 0xffffu : 0u;
+          const uint32_t w = inside ? __builtin_bit_cast(uint32_t, x01) & keep : 0u;
+          const uint16_t w2 = inside && left >= 3 ? __builtin_bit_cast(uint16_t, x2) : (uint16_t)0;
+          s_x01[i * SW + col] = w;
+          s_x2[i * SW + col] = __builtin_bit_cast(_Float16, w2);
+          some |= ((w & 0x7fff7fffu) | (w2 & 0x7fffu)) != 0u ? 1u << u : 0u;
+          first |= (w & 0x7fffu) != 0u ? 1u << u : 0u;
         }
-        mask |= (unsigned long long)bits << i0;
+        mask |= (unsigned long long)(some << i0) | ((unsigned long long)(first << i0) << 32);
       }
       s_mask[tid] = mask;
     }
     __syncthreads();
-    // The strips that matter to an output column: those that a value within two columns reaches.
+    // Operand tables and per-lane constants (asked for here, where the staged rows have left the registers).
+    const float* wts = wts_global;
+    asm volatile("" : "+s"(wts));
+    const half8* tab = reinterpret_cast<const half8*>(wts + kMfmaTableFloatOffset) + kMfmaTableHalfs / 8;
+    half8 A2[8];
+#pragma unroll
+    for (int st = 0; st < 8; ++st) A2[st] = tab[st * kWave + lane];
+    const half8 A1 = tab[8 * kWave + lane];
+    const float* dc = wts + delta_const_offset(C, C);
+    float16v b1acc, b2acc;                                 // entry v is D row 8 (v / 4) + c, c = 4 h + v % 4
+    float w3v[4], lo2v[4];
+    half4 lo1h;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      b1acc[v] = v < 12 ? kAccScale * dc[4 * h + v % 4] : 0.f;
+      b2acc[v] = v < 12 ? kAccScale * dc[2 * C + kRowAll * C + 4 * h + v % 4] : 0.f;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      w3v[c] = wts[10 * C + 9 * C * C + C + 4 * h + c] * (1.f / kAccScale);
+      lo2v[c] = kAccScale * dc[2 * C + (4 + kRowAll) * C + 4 * h + c];
+      lo1h[c] = (_Float16)(kAccScale * dc[C + 4 * h + c]);
+    }
+    float inf = INFINITY;                                  // opaque, so that med3(a, lo, inf) stays one instruction
+    asm volatile("" : "+v"(inf));
+    // The strips that matter to an output column: those that a value within two columns reaches (strip s: x rows 3s .. 3s+6).
     uint32_t act = 0u;
     if (is_out) {
       unsigned long long m = 0;
       for (int p = 0; p < kParts; ++p)
 #pragma unroll
         for (int d = -2; d <= 2; ++d) m |= s_mask[p * SW + col + d];
-      act = (uint32_t)(m | (m >> 1) | (m >> 2)) & seg_mask;
+      const uint32_t some = (uint32_t)m, first = (uint32_t)(m >> 32);
+      act = (some | (some >> 1) | (first >> 2)) & seg_mask;
       if (j_col == 0 || j_col == nb_cur - 1) act = seg_mask;       // (beside the tile y1 = 0 stands for d1 = lo1)
     }
     uint32_t active = 0u;                                // lane t: columns of this wave to which strip t matters
 #pragma unroll
     for (int t = 0; t < kRbStrips; ++t) {
-      const uint32_t c = (uint32_t)__popcll(__ballot((int)(act << (kRbStrips - 1 - t)) < 0));
+      const uint32_t c = (uint32_t)__popcll(__ballot((int)(act << (31 - t)) < 0));
       asm("v_writelane_b32 %0, %1, %2" : "+v"(active) : "s"(c), "n"(t));
     }
-    if (lane < kRbStrips) s_cnt[wave * kRbStrips + lane] = active;
+    if (lane < 32) s_cnt[wave * 32 + lane] = active;
     __syncthreads();
     uint32_t in_all = 0u;
-    if (lane < kRbStrips) in_all = (s_cnt[lane] + s_cnt[kRbStrips + lane]) + (s_cnt[2 * kRbStrips + lane] + s_cnt[3 * kRbStrips + lane]);
-    const uint32_t dense = (uint32_t)__ballot(2 * (int)in_all > len) & seg_mask;        // strips evaluated in every column
+    if (lane < 32) in_all = (s_cnt[lane] + s_cnt[32 + lane]) + (s_cnt[2 * 32 + lane] + s_cnt[3 * 32 + lane]);
+    const uint32_t dense = (uint32_t)__ballot(2 * (int)in_all > len) & seg_mask;
     if (part == 0) {
-      s_sum[col] = s_sum[SW + col] = make_float2(0.f, 0.f);        // (the masks have been read)
+      s_sum[col] = total[0];                             // (the masks have been read)
+      s_sum[SW + col] = total[1];
       s_act[col] = act & ~dense;
     }
     {
       const unsigned long long o = __ballot((act & ~dense) != 0u);
       if (lane == 0) s_out[wave] = o;
+      if (tid == 0) *s_next = 0;
     }
     __syncthreads();
     int n_list = 0;
@@ -221,183 +215,166 @@ __device__ __forceinline__ void predict_rebase8_body(const float* __restrict__ h
     }
     __syncthreads();
 
-    const int n_dense = dense ? (len + kRbOut - 1) / kRbOut : 0;
-    // Few listed columns: two waves take an item's strips by halves (their two sums are added in either order with the same result).
-    const int n_listed = n_list > 2 ? (n_list - 2 + kRbOut - 1) / kRbOut : 0, halves = n_listed <= 2 ? 1 : 0;
-    const int n_items = n_dense + (n_listed << halves);
+    // Most columns listed: items of consecutive columns take their strips along.
+    const bool together = 4 * n_list > 3 * len;
+    const int n_row = dense != 0u || together ? (len + kRbOut - 1) / kRbOut : 0;       // items of consecutive columns
+    const int n_listed = !together && n_list > 2 ? (n_list - 2 + kRbOut - 1) / kRbOut : 0;
+    // (the listed ones first: they are the longer ones; a wave takes the next one when it is done with one)
 #pragma unroll 1
-    for (int item = wave; item < n_items; item += 4) {
-      const bool listed = item >= n_dense;
-      const int e0 = (listed ? (item - n_dense) >> halves : item) * kRbOut;
-      int at[2];                                         // this lane's staged columns
-      bool output[2], outside[2];
+    for (;;) {
+      int item = 0;
+      if (lane == 0) item = atomicAdd(s_next, 1);
+      item = __builtin_amdgcn_readfirstlane(item);
+      if (item >= n_listed + n_row) break;
+      const bool listed = item < n_listed;
+      const int e0 = (listed ? item : item - n_listed) * kRbOut;
+      // Entry n is this lane's column of the first layer, entry n + 1 that of its output (lanes 0 .. 29).
+      int at, at_out;
+      bool output = n < kRbOut;
       uint32_t S = 0u;
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int p = 16 * b + n, e = e0 + p;
-        output[b] = p >= 1 && p <= kRbOut;
-        if (listed) {
-          at[b] = s_list[min(e, n_list - 1)];
-          const uint32_t a = s_act[at[b]];
-          output[b] = output[b] && e < n_list - 1 && a != 0u;
-          S |= output[b] ? a : 0u;
-        } else {
-          at[b] = min(kRbHalo - 1 + e, SW - 3);
-          output[b] = output[b] && at[b] < kRbHalo + len;
-        }
-        const int j = c0 - kRbHalo + at[b];
-        outside[b] = j < 0 || j >= nb_cur;
-      }
       if (listed) {
-        S |= dpp_row<0xB1>(0u, S);                       // quad_perm [1,0,3,2]
-        S |= dpp_row<0x4E>(0u, S);                       // quad_perm [2,3,0,1]
-        S |= dpp_row<0x141>(0u, S);                      // row_half_mirror
-        S |= dpp_row<0x140>(0u, S);                      // row_mirror
-        S = __builtin_amdgcn_readfirstlane(S);           // (the rows of 16 lanes hold the same columns)
-        if (halves) {
-          const uint32_t early = (1u << (n_seg / 2)) - 1u;
-          S &= ((item - n_dense) & 1) ? ~early : early;
-        }
+        at = s_list[min(e0 + n, n_list - 1)];
+        at_out = s_list[min(e0 + n + 1, n_list - 1)];
+        const uint32_t a = s_act[at_out];
+        output = output && e0 + n + 1 < n_list - 1 && a != 0u;
+        S = output ? a : 0u;
       } else {
-        S = dense;
+        at = min(kRbHalo - 1 + e0 + n, SW - 2);
+        at_out = min(kRbHalo + e0 + n, SW - 2);
+        const uint32_t a = s_act[at_out];
+        output = output && e0 + n < len && (together || a == 0u);
+        S = output && together ? a : 0u;
+        if (!__any(output)) continue;
       }
-      const bool border = __any(outside[0] || outside[1]);
-      // Where this lane's two words of x pair t0 - 1 (or t0) begin.
-      const uint32_t* xa[2];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) xa[b] = s_x + at[b] - 1 + (g & 1) + (g >> 1) * SW;
+      for (int i = 16; i > 0; i >>= 1) S |= __shfl_xor(S, i, kWave);
+      S = __builtin_amdgcn_readfirstlane(S) | dense;     // (both halves of the wave hold the same columns)
+      const int j_y1 = c0 - kRbHalo + at;
+      const bool outside = j_y1 < 0 || j_y1 >= nb_cur, border = __any(outside);
+      float sum = s_sum[h * SW + at_out];
 
-      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-      auto words = [&](int b, int j) __attribute__((always_inline)) { return u32x2{xa[b][j * SW], xa[b][j * SW + 1]}; };
-      auto first_layer = [&](u32x2 w) __attribute__((always_inline)) {
-        return __builtin_amdgcn_mfma_f32_16x16x16f16(A1, __builtin_bit_cast(half4, w), b1acc, 0, 0, 0);
+      // Layer-1 operand of pass p: K entries of half h = (rows 3h, 3h+1) x three taps, and row 2's outer taps by halves
+      // (the last one of half 1 has no weight and is the tap beside it once more).
+      const uint32_t* x01 = s_x01 + h * SW + at - 1;
+      const uint16_t* x2a = reinterpret_cast<const uint16_t*>(s_x2) + at - 1 + 2 * h;
+      const uint16_t* x2b = reinterpret_cast<const uint16_t*>(s_x2) + at + h;
+      auto x_of = [&](int p) __attribute__((always_inline)) {
+        uint4v w;
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw) w[kw] = x01[p * SW + kw];
+        w[3] = (uint32_t)x2a[p * SW] | ((uint32_t)x2b[p * SW] << 16);
+        return w;
       };
-      // y1 pair from its result: this lane's four channels of one of the two rows, in two registers.
-      auto clamped = [&](int b, rb_float4 acc, auto border_tag) __attribute__((always_inline)) {
-        half4 h;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) h[c] = (_Float16)acc[c];
-        h = __builtin_elementwise_max(h, lo1h);
-        if (decltype(border_tag)::value) h = outside[b] ? lo1h : h;    // layer-2 padding: y1 = 0 beside the tile, d1 = lo1
-        return __builtin_bit_cast(u32x2, h);
+      auto first_layer = [&](uint4v w) __attribute__((always_inline)) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(A1, __builtin_bit_cast(half8, w), b1acc, 0, 0, 0);
       };
-      // Layer-2 operands of the two blocks, per tap: the pair in half `half` of the K entries.
-      uint4v centre[2], left[2], right[2];
-      auto put = [&](const u32x2 (&y)[2], auto half_tag) __attribute__((always_inline)) {
-        constexpr int o = 2 * decltype(half_tag)::value;
+      auto put = [&](const float16v& acc, auto parity_tag) __attribute__((always_inline)) {
+        half4 y[3];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
+        for (int q = 0; q < 3; ++q) {
 #pragma unroll
-          for (int b = 0; b < 2; ++b) centre[b][o + r] = y[b][r];
-          left[0][o + r] = dpp_all<kRowRor1>(y[0][r]);                 // (lane 0: its own column 15, wanted by block 1)
-          left[1][o + r] = dpp_row<kRowShr1>(left[0][o + r], y[1][r]);
-          right[1][o + r] = dpp_all<kRowRor15>(y[1][r]);               // (lane 15: its own column 0)
-          right[0][o + r] = dpp_row<kRowShl1>(right[1][o + r], y[0][r]);
+          for (int c = 0; c < 4; ++c) y[q][c] = (_Float16)acc[4 * q + c];
+          y[q] = __builtin_elementwise_max(y[q], lo1h);
         }
-      };
-      // Layer 2 and the head: four weighted channels of one output row of each block.
-      auto second_layer = [&](rb_float4 start, rb_float4 lo, float (&sum)[2], auto order_tag) __attribute__((always_inline)) {
-        constexpr int o = decltype(order_tag)::value;
-        rb_float4 acc[2];
+        if (border) {                                    // layer-2 padding: y1 = 0 beside the tile, d1 = lo1
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2[o][1], __builtin_bit_cast(half8, centre[b]), start, 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2[o][0], __builtin_bit_cast(half8, left[b]), acc[b], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2[o][2], __builtin_bit_cast(half8, right[b]), acc[b], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) sum[b] = fmaf(w3v[c], __builtin_amdgcn_fmed3f(acc[b][c], lo[c], inf), sum[b]);
-      };
-      constexpr std::integral_constant<int, 0> kFirst{};
-      constexpr std::integral_constant<int, 1> kSecond{};
-      float sum_int[2] = {0.f, 0.f}, sum_bor[2] = {0.f, 0.f};
-
-      // Strips that hold a border row: y1 rows outside the window are no terms at all, rows 0 and H-1 have constants of their own.
-      uint32_t edges = 0u;
-      if (t0 == 0) edges |= 1u;
-      for (int t = max((H - 2) / 2, t0); t < t0 + n_seg; ++t) edges |= 1u << (t - t0);
-      uint32_t E = S & edges;
-      S &= ~edges;
-#pragma unroll 1
-      while (E != 0u) {
-        const int j = __builtin_ctz(E);
-        E &= E - 1u;
-        const int t = t0 + j, row = 2 * t + (g >> 1);    // this lane's output row
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int row1 = 2 * (t + k) - 1 + (g >> 1);   // its y1 row of pair t + k
-          u32x2 y[2];
-#pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            y[b] = clamped(b, first_layer(words(b, j + k)), std::true_type{});
-            if (row1 < 0 || row1 >= H) y[b] = u32x2{0u, 0u};
-          }
-          if (k == 0) put(y, kFirst); else put(y, kSecond);
+          for (int q = 0; q < 3; ++q) y[q] = outside ? lo1h : y[q];
         }
-        const int type = row == 0 ? kRowTop : row == H - 1 ? kRowBot : kRowAll;
-        float s[2] = {0.f, 0.f};
-        second_layer(s_dc[type * 2], s_dc[(4 + type) * 2], s, kFirst);
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          if (row >= 2 && row <= H - 3) sum_int[b] += s[b];
-          else if (row < H) sum_bor[b] += s[b];
+        for (int q = 0; q < 3; ++q) reinterpret_cast<half4*>(s_y1 + (3 * decltype(parity_tag)::value + q) * kRbYW + n)[h] = y[q];
+      };
+      // Operand of step st of a strip whose first pass is of parity P: y1 row q < 3 is of that pass, the others of the next one
+      // (chunk 15 has no weight).  The second half of the wave reads the next chunk: a tap or a row further, or from the ring's start.
+      const half8 *y_tap = s_y1 + n + h, *y_row = s_y1 + n + h * (kRbYW - 2), *y_turn = s_y1 + n - h * (5 * kRbYW + 2), *y_same = s_y1 + n;
+      auto operand = [&](int st, auto parity_tag) __attribute__((always_inline)) {
+        constexpr int P = decltype(parity_tag)::value;
+        const int q = 2 * st / 3, kw = 2 * st % 3, slot = q < 3 ? 3 * P + q : 3 * (1 - P) + q - 3;
+        const half8* y = st == 7 ? y_same : kw < 2 ? y_tap : slot == 5 ? y_turn : y_row;
+        return y[slot * kRbYW + kw];
+      };
+      // Strip t, whose two passes are in LDS and the first four operands (B) on their way; w: the x words of the pass after those, which is
+      // made meanwhile (at a run's end for nothing).  One wave reads what it has just written: the LDS keeps a wave's accesses in
+      // order, the compiler has to as well.
+      uint4v w;
+      half8 B[8];
+      auto strip = [&](int t, auto parity_tag, auto other_tag) __attribute__((always_inline)) {
+#pragma unroll
+        for (int st = 4; st < 6; ++st) B[st] = operand(st, parity_tag);
+        const float16v d = first_layer(w);
+        w = x_of(min(t + 3, n_seg));
+        float16v acc;
+#pragma unroll
+        for (int st = 0; st < 4; ++st) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[st], B[st], st == 0 ? b2acc : acc, 0, 0, 0);
+        asm volatile("" ::: "memory");
+        put(d, parity_tag);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int st = 6; st < 8; ++st) B[st] = operand(st, parity_tag);
+#pragma unroll
+        for (int st = 4; st < 8; ++st) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[st], B[st], acc, 0, 0, 0);
+#pragma unroll
+        for (int st = 0; st < 4; ++st) B[st] = operand(st, other_tag);
+        const int left = n_rows - 3 * (t0 + t);          // output rows of this strip that exist
+        float v[3];
+#pragma unroll
+        for (int o = 0; o < 3; ++o) {
+          v[o] = 0.f;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[o] = fmaf(w3v[c], __builtin_amdgcn_fmed3f(acc[4 * o + c], lo2v[c], inf), v[o]);
         }
-      }
-      // The others, in runs of consecutive strips; the pair a strip and the next one share is evaluated once.  The first layer of
-      // the pair after the next and its words are under way while a strip is worked on (at a run's end for nothing).
-      auto runs = [&](auto border_tag) __attribute__((always_inline)) {
+        if (left < 3) {
+          v[2] = 0.f;                                    // (adds nothing)
+          if (left < 2) v[1] = 0.f;
+        }
+        sum = ((sum + v[0]) + v[1]) + v[2];
+      };
+      constexpr std::integral_constant<int, 0> kEven{};
+      constexpr std::integral_constant<int, 1> kOdd{};
 #pragma unroll 1
-        while (S != 0u) {
-          int j = __builtin_ctz(S);
-          rb_float4 d1[2];
-          u32x2 y[2], w[2];
+      while (S != 0u) {                                  // a run of consecutive strips
+        int t = __builtin_ctz(S);
+        {
+          const float16v d0 = first_layer(x_of(t)), d1 = first_layer(x_of(t + 1));
+          w = x_of(min(t + 2, n_seg));
+          if (t & 1) {
+            put(d0, kOdd);
+            put(d1, kEven);
+            asm volatile("" ::: "memory");
 #pragma unroll
-          for (int b = 0; b < 2; ++b) { y[b] = clamped(b, first_layer(words(b, j)), border_tag); d1[b] = first_layer(words(b, j + 1)); w[b] = words(b, j + 2); }
-          put(y, kFirst);
-          auto strip = [&](auto half_tag, auto order_tag) __attribute__((always_inline)) {
+            for (int st = 0; st < 4; ++st) B[st] = operand(st, kOdd);
+          } else {
+            put(d0, kEven);
+            put(d1, kOdd);
+            asm volatile("" ::: "memory");
 #pragma unroll
-            for (int b = 0; b < 2; ++b) y[b] = clamped(b, d1[b], border_tag);
-            put(y, half_tag);
-#pragma unroll
-            for (int b = 0; b < 2; ++b) { d1[b] = first_layer(w[b]); w[b] = words(b, j + 3); }
-            second_layer(b2all, lo2all, sum_int, order_tag);
-            S &= S - 1u;
-            ++j;
-            return S != 0u && (int)__builtin_ctz(S) == j;
-          };
-#pragma unroll 1
-          for (;;) {
-            if (!strip(kSecond, kFirst)) break;
-            if (!strip(kFirst, kSecond)) break;
+            for (int st = 0; st < 4; ++st) B[st] = operand(st, kEven);
           }
         }
-      };
-      if (border) runs(std::true_type{}); else runs(std::false_type{});
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const float si = add_lane_groups(sum_int[b]), sb = add_lane_groups(sum_bor[b]);
-        if (g == 0 && output[b]) {
-          float2* to = s_sum + (listed ? SW : 0) + at[b];
-          atomicAdd(&to->x, si);                         // (onto zero: the same as a store, but for an item in halves)
-          atomicAdd(&to->y, sb);
+        auto more = [&]() __attribute__((always_inline)) {
+          S &= S - 1u;
+          ++t;
+          return S != 0u && (int)__builtin_ctz(S) == t;
+        };
+#pragma unroll 1
+        for (;;) {
+          if (!(t & 1)) {
+            strip(t, kEven, kOdd);
+            if (!more()) break;
+          }
+          strip(t, kOdd, kEven);
+          if (!more()) break;
         }
       }
+      if (output) s_sum[h * SW + at_out] = sum;
     }
     __syncthreads();
     if (part == 0) {
-      const float2 d = s_sum[col], l = s_sum[SW + col];
-      total_int += d.x + l.x;
-      total_bor += d.y + l.y;
+      total[0] = s_sum[col];
+      total[1] = s_sum[SW + col];
     }
     if (t0 + n_seg < n_strips) __syncthreads();          // (the next segment's masks lie where the sums are)
   }
-  if (is_out) {
-    const size_t o = (size_t)inst * nb_cap + j_col;
-    pstate[o] = total_int;
-    pred[o] = (total_int + total_bor) * (1.f / (float)H);
-  }
+  if (is_out) pstate[(size_t)inst * nb_cap + j_col] = total[0] + total[1];
 }
 
 }  // namespace

@@ -1,4 +1,4 @@
-"""The full tile in one launch (8/8 channels): strips of two rows, segments of the time axis, tiles and items of columns, dense
+"""The full tile (8/8 channels): strips of rows, segments of the time axis, tiles and items of columns, dense
 strips and listed columns, each at its edges, every column against float64 - and one more row pushed on the state it leaves."""
 import numpy as np
 import pytest
