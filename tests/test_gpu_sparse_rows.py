@@ -59,6 +59,27 @@ def _passes(n, nb):
     return cols, nb - (used - 1) * cols
 
 
+def _passes16(n, nb):
+    """The same for the 16/32 step predictor, and the passes of a workgroup."""
+    best = None
+    for p in range(-(-nb // 252), -(-nb // 62) + 1):
+        cols = -(-nb // p)
+        cost = -(-n * -(-nb // cols) // 512) * (cols + 100)
+        if best is None or cost < best[0]:
+            best = (cost, cols)
+    used = -(-nb // best[1])
+    if -(-n * used // 512) >= 8:                          # many passes a workgroup: the longest ones, and a rest
+        used, cols = -(-nb // 252), 252
+    else:
+        cols = -(-nb // used)
+    return cols, nb - (used - 1) * cols, -(-n * used // min(512, n * used))
+
+
+def _sample(n, c1):
+    """Instances that are compared: for 16/32 channels, whose float64 evaluation takes long, 130 of them, the first and the last among them."""
+    return list(range(n)) if c1 == 8 or n <= 130 else sorted(set(np.linspace(0, n - 1, 130).astype(int).tolist()))
+
+
 @pytest.mark.parametrize("c1,c2", [(8, 8), (16, 32)])
 @pytest.mark.parametrize("n,nb,H,cols,last", [
     (1040, 752, 8, 251, 250),      # more passes than the chip holds workgroups
@@ -75,8 +96,7 @@ def test_sparse_history_every_column(n, nb, H, cols, last, c1, c2):
     import paper_2502_04077_amd as ap
     assert _passes(n, nb) == (cols, last)
     dev = torch.device("cuda:0")
-    if c1 == 16 and n > 100:
-        n = 130                                           # (its tiles do not depend on the number of instances)
+    check = _sample(n, c1)
     b = 8
     ctx = ap.Context(n_inst=n, g=1, head_dim=64, block=b, hist_len=H, t_cap=(nb + 3) * b, k_blocks=2, n_sink=1, n_local=1,
                      c1=c1, c2=c2, kv_dtype="bf16")
@@ -101,10 +121,10 @@ def test_sparse_history_every_column(n, nb, H, cols, last, c1, c2):
         modes = [ap.AP_PRED_ADVANCE] if step > 0 else [ap.AP_PRED_REBASE]
         if step in (1, H // 2, H + 8):
             modes.append(ap.AP_PRED_REBASE)
-        ref, bound = _reference(torch.from_numpy(window), blob, c1, c2)
+        ref, bound = _reference(torch.from_numpy(window[check]), blob, c1, c2)
         for mode in modes:
             ctx.predict_incremental(hist, n_pushed, nb, nb, mode, pstate, pred, ws)
-            got = pred[:, :nb].cpu().double()
+            got = pred[check, :nb].cpu().double()
             off = (got - ref).abs() - bound * (2 if mode == ap.AP_PRED_ADVANCE else 1) - 1e-7
             assert off.max() <= 0, f"step {step} mode {mode}: {(off > 0).sum()} columns, worst {off.max():.3g} at {np.unravel_index(int(off.argmax()), off.shape)}"
 
@@ -136,18 +156,27 @@ def test_tile_end_beside_a_short_last_pass(n, nb, last):
     assert bound.max() < 0.1
 
 
-@pytest.mark.parametrize("n,nb,H", [(1024, 376, 6), (128, 2735, 6), (1040, 377, 7), (6, 12433, 6), (3, 31, 9), (2, 33, 6), (1, 1, 6),
-                                    (9, 500, 64)])
-def test_dense_history_every_column(n, nb, H):
+@pytest.mark.parametrize("n,nb,H,c1,c2,plan", [(*c, 8, 8, None) for c in (
+    (1024, 376, 6), (128, 2735, 6), (1040, 377, 7), (6, 12433, 6), (3, 31, 9), (2, 33, 6), (1, 1, 6), (9, 500, 64))] + [
+    # 16/32 channels: (columns of a pass, of the last one, passes of a workgroup); a chunk of a list yields 126 outputs
+    (512, 126, 6, 16, 32, (126, 126, 1)), (512, 127, 7, 16, 32, (127, 127, 1)), (512, 252, 6, 16, 32, (252, 252, 1)), (700, 505, 6, 16, 32, (169, 167, 5)),
+    (3, 1251, 9, 16, 32, (60, 51, 1)), (2, 5, 6, 16, 32, (5, 5, 1)),
+    # ... many passes a workgroup: the longest ones, and a rest of any length
+    (3600, 252, 6, 16, 32, (252, 252, 8)), (2100, 253, 6, 16, 32, (252, 1, 9)), (2048, 254, 7, 16, 32, (252, 2, 8)), (3600, 128, 6, 16, 32, (252, 128, 8)),
+    (2100, 505, 6, 16, 32, (252, 1, 13)), (2050, 379, 64, 16, 32, (252, 127, 9)),
+])
+def test_dense_history_every_column(n, nb, H, c1, c2, plan):
     """Passes in which every column has a value look nothing up: all of them, all but one column in one half, all but a run in
     both, changing as the rows move on; every column against float64."""
     import paper_2502_04077_amd as ap
+    assert plan is None or _passes16(n, nb) == plan
+    check = _sample(n, c1)
     dev = torch.device("cuda:0")
-    c, b = 8, 8
+    b = 8
     ctx = ap.Context(n_inst=n, g=1, head_dim=64, block=b, hist_len=H, t_cap=(nb + 3) * b, k_blocks=2, n_sink=1, n_local=1,
-                     c1=c, c2=c, kv_dtype="bf16")
+                     c1=c1, c2=c2, kv_dtype="bf16")
     rng = np.random.default_rng(nb + H)
-    blob = (rng.standard_normal(n_weight_floats(c, c)) * 0.2).astype(np.float32)
+    blob = (rng.standard_normal(n_weight_floats(c1, c2)) * 0.2).astype(np.float32)
     ctx.set_weights(blob)
     R, cap = ctx.hist_slots(), ctx.nb_cap()
     hist = torch.zeros((n, R, cap), device=dev)
@@ -155,6 +184,9 @@ def test_dense_history_every_column(n, nb, H):
     n_pushed = 3 * R
     hist[0, [(n_pushed + i) % R for i in range(5)], nb // 2] = 0.0          # the top half's rows, or most of them
     hist[n - 1, :, nb // 3:nb // 3 + 40] = 0.0
+    if c1 == 16 and n > 100:                              # (lists that are neither empty nor every column, most of them longer than a chunk)
+        for i in check[1:-1:3]:
+            hist[i, :, (7 * i) % nb:(7 * i) % nb + 6 + i % 50] = 0.0
     row, pred, pstate = (torch.zeros((n, cap), device=dev) for _ in range(3))
     ws = torch.zeros((max(16, ctx.workspace_bytes()),), dtype=torch.uint8, device=dev)
     for step in range(4):
@@ -164,7 +196,7 @@ def test_dense_history_every_column(n, nb, H):
             n_pushed += 1
         mode = ap.AP_PRED_ADVANCE if step else ap.AP_PRED_REBASE
         ctx.predict_incremental(hist, n_pushed, nb, nb, mode, pstate, pred, ws)
-        window = hist[:, [(n_pushed - H + r) % R for r in range(H)], :nb].cpu()
-        ref, bound = _reference(window, blob, c, c)
-        off = (pred[:, :nb].cpu().double() - ref).abs() - bound * (2 if step else 1) - 1e-7
+        window = hist[check][:, [(n_pushed - H + r) % R for r in range(H)], :nb].cpu()
+        ref, bound = _reference(window, blob, c1, c2)
+        off = (pred[check, :nb].cpu().double() - ref).abs() - bound * (2 if step else 1) - 1e-7
         assert off.max() <= 0, f"step {step}: {(off > 0).sum()} columns, worst {off.max():.3g} at {np.unravel_index(int(off.argmax()), off.shape)}"
