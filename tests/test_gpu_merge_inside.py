@@ -53,3 +53,80 @@ def test_same_bytes(n, g, d, block, k, nb, dtype, hist):
         assert torch.equal(out, out2), i
         assert torch.equal(ring[:, pushed % (hist + 1)], row), i
         pushed += 1
+
+
+@pytest.mark.parametrize("c1,c2,fp32", [(4, 4, False), (8, 8, False), (16, 32, False), (8, 8, True), (16, 32, True)])
+@pytest.mark.parametrize("hist", [16, 4])                # (below 6 every call evaluates the full tile)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_every_predictor_clears_the_counters(c1, c2, fp32, hist, dtype):
+    """The counters of the merge lie in the workspace, and whichever predictor runs sets them to zero: all of its forms over a
+    workspace of garbage - re-base with and without a state of the caller's, advance, hold, a tile that grows - with selections made and reused."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    n, g, d, block, k, nb = 5, 4, 128, 16, 64, 300
+    cap = nb + 4
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=block, hist_len=hist, t_cap=cap * block, k_blocks=k, n_sink=1, n_local=2, c1=c1, c2=c2,
+                     kv_dtype=dtype, flags=ap.AP_FLAG_PREDICTOR_FP32 if fp32 else 0)
+    rng = np.random.default_rng(c1 + hist)
+    ctx.set_weights((0.2 * rng.standard_normal(n_weight_floats(c1, c2))).astype(np.float32))
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(c1 * 100 + hist)
+    K, V = (torch.randn((n, cap * block, d), generator=gen, device=dev).to(dt) for _ in range(2))
+    ring = torch.rand((n, hist + 1, cap), generator=gen, device=dev) * 0.01
+    pred, pstate, row = (torch.zeros((n, cap), device=dev) for _ in range(3))
+    out, out2 = (torch.zeros((n, g, d), device=dev) for _ in range(2))
+    idx, idx2 = (torch.full((n, k), -7, dtype=torch.int32, device=dev) for _ in range(2))
+    cnt, cnt2 = (torch.zeros((n,), dtype=torch.int32, device=dev) for _ in range(2))
+    ws = torch.zeros((ctx.workspace_bytes(),), dtype=torch.uint8, device=dev)
+    pushed, end = 4 * hist, nb * block
+    reuse = ap.AP_STEP_REUSE_SELECTION
+    for i, (mode, t, state) in enumerate([
+            (ap.AP_PRED_REBASE, end - 3, pstate), (ap.AP_PRED_ADVANCE, end - 2, pstate), (ap.AP_PRED_HOLD, end - 2, pstate), (ap.AP_PRED_ADVANCE, end, pstate),
+            (ap.AP_PRED_ADVANCE, end + 1, pstate), (ap.AP_PRED_ADVANCE | reuse, end + 2, pstate), (ap.AP_PRED_HOLD | reuse, end + 2, pstate),
+            (ap.AP_PRED_SKIP | reuse, end + 3, pstate), (ap.AP_PRED_REBASE, end + 4, None), (ap.AP_PRED_REBASE, end + 5, pstate)]):
+        q = torch.randn((n, g, d), generator=gen, device=dev).to(dt)
+        ws.random_(0, 256, generator=gen)
+        ring[:, pushed % (hist + 1)] = 9.0
+        out.fill_(7.0)
+        ctx.step(ring, pushed, q, K, V, t, out, idx, cnt, pred, state, mode, ws)
+        if not mode & reuse:
+            ctx.select_topk(pred, -(-t // block), idx2, cnt2, ws)
+            assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2), i
+        ctx.sparse_decode(q, K, V, t, idx, cnt, out2, row, ws)
+        assert torch.equal(out, out2), i
+        assert torch.equal(ring[:, pushed % (hist + 1)], row), i
+        pushed += 1
+
+
+def test_offload_step_clears_the_counters():
+    """The same where the launch of the appended row does it: offload steps over a workspace of garbage against the single calls."""
+    from paper_2502_04077_amd.offload import OffloadRun
+    from test_gpu_parity import small
+    from workloads import kv_cache, predictor_weights, queries
+    dev = torch.device("cuda:0")
+    w = small("offload", layers=2, batch=1, kv_heads=3, g=4, head_dim=128, t0=1010, budget_tokens=512, hist_len=16, steps=12, calib_every=5)
+    K, V = kv_cache(w, dev)
+    hosts = []
+    for x in (K, V):
+        hosts.append(torch.empty(x.shape, dtype=x.dtype, pin_memory=True))
+        hosts[-1].copy_(x)
+    runs = [OffloadRun(w, *hosts, dev, rebase_every=4, single_calls=single) for single in (False, True)]
+    for run in runs:
+        run.set_weights(predictor_weights(w))
+        for j in range(w.hist_len):
+            run.warmup_calibrate(queries(w, j - w.hist_len, dev), w.t0 - w.hist_len + 1 + j)
+        run.start(w.t_at(0))
+    for s in range(w.steps):
+        t, q = w.t_at(s), queries(w, s, dev)
+        for run in runs:
+            for L in run.layers:
+                L.ws.random_(0, 256)
+                L.out.fill_(7.0)
+            run.step(q, K[:, t - 1, :].contiguous(), V[:, t - 1, :].contiguous(), t, calibrate=w.is_calibration_step(s))
+        assert torch.equal(runs[0].out(), runs[1].out()), s
+        assert torch.equal(runs[0].logical_history(), runs[1].logical_history()), s
+        for a, b in zip(runs[0].staged_selection(), runs[1].staged_selection()):
+            assert torch.equal(a, b), s
+    for run in runs:
+        run.finish()
