@@ -31,7 +31,7 @@ def _scores(mode, n_inst, nb, k, rng):
     (3, 131, 16, 1, 2), (2, 130, 128, 0, 0), (3, 1024 + 6, 68, 2, 4), (3, 1024 + 7, 69, 1, 4), (2, 2048 + 8, 64, 4, 4),
     (2, 3072 + 4, 132, 4, 0), (2, 3072 + 5, 132, 3, 0), (1, 4096, 129, 0, 0), (2, 4097, 5, 2, 2), (1, 8194, 128, 4, 4),
     (1, 16384 + 8, 128, 4, 4), (1, 16384 + 9, 128, 4, 4), (520, 4096, 72, 4, 4), (520, 4200, 72, 4, 4), (1030, 2304, 65, 0, 1),
-    (1030, 2313, 64, 4, 4),
+    (1030, 2313, 64, 4, 4), (600, 2300, 200, 1, 1), (600, 2500, 200, 0, 1),          # (the last two: 9 and 10 keys a thread, radix select alone)
 ])
 @pytest.mark.parametrize("mode", ["normal", "few_groups", "runs", "zeros", "close", "extreme"])
 def test_bit_exact(n_inst, nb, k, n_sink, n_local, mode):
