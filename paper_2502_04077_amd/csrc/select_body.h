@@ -22,7 +22,7 @@ constexpr int kSelBins = 256;              // radix of one pass; the first kSelB
 constexpr int kSelRanked = 256;            // select_by_bound: most keys it ranks against each other
 constexpr int kSelMaxMid = 128;            // ... and most free places it fills
 template <int NT> constexpr int sel_scratch_words() {
-  constexpr int radix = kSelBins + 3 * (NT / kWave) + 8, bound = 2 * (kSelRanked + 16) + 8 * kWave + kSelMaxMid + 17;
+  constexpr int radix = kSelBins + 3 * (NT / kWave) + 8, bound = 2 * (kSelRanked + 16) + 8 * kWave + kSelMaxMid + 18;
   return radix > bound ? radix : bound;
 }
 
@@ -67,17 +67,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
 }
 
 // The k_mid largest of the keys that the threads hold (0 where a thread has none; ties to the lower block), written to out in
-// ascending order of blocks - or false, and nothing written, if more than kSelRanked keys would have to be ranked.
+// ascending order of blocks - or false, and nothing written, if more than kSelRanked keys would have to be ranked.  Then T and need say, where
+// need is not 0, that all keys above T are wanted and the first `need` equal to T.
 //   A lower bound of the k_mid-th largest key is the k_mid-th largest of the maxima of 64 GR groups of keys, GR of them in
 //   every lane: each wave finds one for itself by trying the key's bits from the top, until hardly more than k_mid maxima reach
 //   it.  With the large keys spread over the groups few more keys than that do (74 of 2041 for k_mid = 56 and 128
 //   groups); these are ranked by counting, for each, how many come before it, and the same again by block.
+// Where the bound lets too many keys through because they coincide with it, the radix passes are left out (2048 instances of 2041 candidates, all
+// scores equal: 13.6 us by the radix select alone, 21.9 with a bound in front of it, 14.3 so; eight different scores 18.2, 23.8, 21.9).
 // Three barriers and no histogram, where the radix select has three a pass and an LDS atomic per key (the scores of a decode run, us,
 // radix select -> this: 2048 instances of 2041 candidates 14.9 -> 8.1, 4096 25.6 -> 13.6, 128 of 8186 12.6 -> 6.8, 8 of
 // 2041 5.8 -> 4.0, one of 126 3.5 -> 2.6).  What is left is the chain: scores, 15-20 tried bits, one LDS atomic, two rounds of counting.
 template <int KPT, int NT, int GR>
 __device__ __forceinline__ bool select_by_bound(const uint32_t (&keys)[KPT], int first, uint32_t k_mid,
-                                                int32_t* __restrict__ out, uint32_t* s_mem) {
+                                                int32_t* __restrict__ out, uint32_t* s_mem, uint32_t& T, uint32_t& need) {
   constexpr int kWaves = NT / kWave;
   constexpr int kHolders = GR * kWave / kWaves;         // lanes of a wave that hold the maximum of a group
   static_assert(kHolders == 64 || kHolders == 32 || kHolders == 16 || kHolders == 8, "groups are lanes, or lanes 32, 16, 8 apart");
@@ -102,12 +105,12 @@ __device__ __forceinline__ bool select_by_bound(const uint32_t (&keys)[KPT], int
   if constexpr (kHolders <= 8) gm = max(gm, dpp_u32<0x128, 0xF>(gm));          // row_ror:8
   if (lane < kHolders) s_max[wave * kHolders + lane] = gm;
   for (int i = tid; i < kSelRanked + 16; i += NT) s_cand[i] = 0ull;
-  for (int i = tid; i < kSelMaxMid + 17; i += NT) s_sel[i] = 0u;               // (and the count)
+  for (int i = tid; i < kSelMaxMid + 18; i += NT) s_sel[i] = 0u;               // (and the counts)
   __syncthreads();
   uint32_t g[GR];
 #pragma unroll
   for (int r = 0; r < GR; ++r) g[r] = s_max[r * kWave + lane];
-  uint32_t T = 0;
+  T = 0;
   const uint32_t enough = k_mid + (k_mid >> 3);
 #pragma unroll 1
   for (uint32_t bit = 0x80000000u; bit != 0u; bit >>= 1) {
@@ -142,7 +145,21 @@ __device__ __forceinline__ bool select_by_bound(const uint32_t (&keys)[KPT], int
   }
   __syncthreads();
   const uint32_t n = *s_count;
-  if (n > (uint32_t)kSelRanked || n < k_mid) return false;   // (the same for every thread; too few: scores that are NaN)
+  need = 0;
+  if (n < k_mid) return false;                          // (the same for every thread; scores that are NaN)
+  if (n > (uint32_t)kSelRanked) {
+    // Scores of which many coincide - blocks without a history all have the same - make the bound the last wanted key itself: fewer than
+    // k_mid keys are larger.
+    uint32_t above = 0;
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) above += (uint32_t)__popcll(__ballot(keys[i] > T));
+    if (lane == 0 && above != 0u) atomicAdd(s_count + 1, above);
+    __syncthreads();
+    above = s_count[1];
+    if (above < k_mid) need = k_mid - above;
+    __syncthreads();                                    // (the caller uses this LDS)
+    return false;
+  }
   // Four lanes a key, each counting a quarter of the others.
   const uint32_t part = tid & 3;
 #pragma unroll 1
@@ -216,20 +233,22 @@ __device__ __forceinline__ void select_topk_body(const float* __restrict__ p, in
     for (int j = tid; j < n_local; j += kSelThreads) out[k - n_local + j] = nb_cur - n_local + j;
     if (tid == 0) *cnt_out = k;
   };
+  uint32_t prefix = 0;                                  // high bits of T found so far
+  uint32_t need = 0;                                    // still to take among keys matching prefix
   if constexpr (GR > 0) {
     uint32_t own[NK];
 #pragma unroll
     for (int i = 0; i < NK; ++i) own[i] = lo + i * NT + tid < hi ? keys[i] : 0u;
-    if (select_by_bound<NK, NT, GR>(own, lo + tid, (uint32_t)k_mid, out + n_sink, s_mem)) { forced(); return; }
+    if (select_by_bound<NK, NT, GR>(own, lo + tid, (uint32_t)k_mid, out + n_sink, s_mem, prefix, need)) { forced(); return; }
   }
   auto key_at = [&](int i, int j) __attribute__((always_inline)) -> uint32_t {
     if constexpr (KPT > 0) return keys[i]; else return score_key(p[min(j, hi - 1)]);
   };
   const int n_iter = KPT > 0 ? KPT : (hi - lo + kSelThreads - 1) / kSelThreads;
 
-  uint32_t prefix = 0;                                  // high bits of T found so far
-  uint32_t need = (uint32_t)k_mid;                      // still to take among keys matching prefix
-  if (k_mid > 0) {
+  if (need == 0u && k_mid > 0) {
+    prefix = 0;
+    need = (uint32_t)k_mid;
     if (tid < kSelBins) s_hist[tid] = 0;
     __syncthreads();
     for (int shift = 24, pass = 0; shift >= 0; shift -= 8, ++pass) {

@@ -20,6 +20,13 @@ def _scores(mode, n_inst, nb, k, rng):
         p = np.where(rng.random((n_inst, nb)) < 0.5 * k / nb, p, np.where(rng.random((n_inst, nb)) < 0.5, 0.0, -0.0)).astype(np.float32)
     elif mode == "close":                        # scores that differ in their last digits
         p = (1.0 + 2.0 ** -22 * rng.integers(0, 64, size=(n_inst, nb))).astype(np.float32)
+    elif mode == "equal":                        # nothing but one score; the places go to the first blocks
+        p[:] = 0.25
+    elif mode == "few_values":                   # far more blocks on the last wanted score than there are places
+        p = rng.integers(0, 8, size=(n_inst, nb)).astype(np.float32)
+    elif mode == "ties_below":                   # fewer distinct large scores than places, the rest a tie
+        p = np.zeros((n_inst, nb), np.float32)
+        p[:, 1::max(1, nb // max(1, k // 2))] = rng.standard_normal((n_inst, nb))[:, 1::max(1, nb // max(1, k // 2))]
     elif mode == "extreme":
         p[:, ::5] = np.inf
         p[:, 1::5] = -np.inf
@@ -33,7 +40,7 @@ def _scores(mode, n_inst, nb, k, rng):
     (1, 16384 + 8, 128, 4, 4), (1, 16384 + 9, 128, 4, 4), (520, 4096, 72, 4, 4), (520, 4200, 72, 4, 4), (1030, 2304, 65, 0, 1),
     (1030, 2313, 64, 4, 4), (600, 2300, 200, 1, 1), (600, 2500, 200, 0, 1),          # (the last two: 9 and 10 keys a thread, radix select alone)
 ])
-@pytest.mark.parametrize("mode", ["normal", "few_groups", "runs", "zeros", "close", "extreme"])
+@pytest.mark.parametrize("mode", ["normal", "few_groups", "runs", "zeros", "close", "equal", "few_values", "ties_below", "extreme"])
 def test_bit_exact(n_inst, nb, k, n_sink, n_local, mode):
     import paper_2502_04077_amd as ap
     dev = torch.device("cuda:0")
