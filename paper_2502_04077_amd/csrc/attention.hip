@@ -424,10 +424,19 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 }
 
 // Are the splits merged by the last workgroup of an instance to finish, or by a launch of their own?  By the last one where a
-// launch before has cleared the counters (one more launch for that would cost as much as the merge's own) and all
-// workgroups are resident at once: in further rounds every workgroup holds its place until its partials have reached memory.  (Step of 8 instances
-// 18.9 -> 18.4 us and three launches instead of four, of 128 at 128K 75.3 -> 73.8; 640 instances of two splits, counters cleared by a launch, 121 -> 132.)
-bool merge_inside(const Shape& s, int ninst, int n_split) { return s.cleared && n_split > 1 && (long)ninst * n_split <= 1024; }
+// launch before has cleared the counters (one more launch for that would cost as much as the merge's own), and
+//   - there are no more than two workgroups a CU, which are resident at once whatever LDS they have: in further rounds every workgroup holds its
+//     place until its partials have reached memory.  (513 to 1024 workgroups, steps in us, merged inside / by a launch: fp32, 1024 tokens, g = 8,
+//     d = 128, 60 instances 42.0 / 35.9, g = 4, 40 instances 26.0 / 24.5; bf16, g = 8, d = 64, 510 x 8192 tokens 231 / 214, g = 4, d = 128,
+//     350 x 8192 250 / 246, 510 x 16384 699 / 705.  640 instances of two splits, counters cleared by a launch, 121 -> 132.)
+//   - one workgroup has little to merge: few splits, and few sums in all.  (8 instances, fp32, g = 4, d = 128: 16 splits 19.4 / 21.9, 24 22.9 /
+//     22.2, 64 36.1 / 25.8; g = 1, 64 splits 29.0 / 22.1; bf16, d = 128, g = 4: 8 splits 16.2 / 20.1, 16 20.5 / 21.3, 20 23.1 / 22.0; 4 instances,
+//     g = 8, 12 splits 22.0 / 25.8, 16 24.3 / 23.5, 64 51.6 / 29.0.)
+constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288;
+bool merge_inside(const Shape& s, int ninst, int n_split) {
+  return s.cleared && n_split > 1 && n_split <= kMergeInsideSplits && n_split * s.g * s.d <= kMergeInsideSums &&
+         (long)ninst * n_split <= kMergeInsideWorkgroups;
+}
 
 // Does the streaming decode (and the fp32 one in splits) make the selection too?  Every workgroup of an instance makes all of it, which is
 // no loss where they would otherwise wait for the launch that does, and hardly any CU has two of them.  (Whole steps, 2041 candidates, us: 8 instances 17.6 -> 16.6,

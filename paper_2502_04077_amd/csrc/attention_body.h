@@ -402,6 +402,7 @@ __device__ __forceinline__ void clear_row_share(const SparseArgs& a, int inst, i
   for (int j = split * per + threadIdx.x; j < min(a.nb_cap, (split + 1) * per); j += kAttnThreads) st_shared_out<true>(row + j, 0.f);
 }
 
+constexpr int kMergeInsideSplits = 16;                  // most splits that are merged so (merge_inside in attention.hip)
 // LDS of the merge, which overlays what the decode had: factors, and a word for last_to_finish.
 inline size_t merge_lds_bytes(int n_split, int g) { return n_split > 1 ? sizeof(float) * ((size_t)n_split * g + 1) : 0; }
 
@@ -429,29 +430,19 @@ __device__ __forceinline__ void merge_splits(const SparseArgs& a, int inst, int 
 #pragma unroll
     for (int s = 0; s < kAhead; ++s)
       x[i][s] = s < a.n_split && i * kAttnThreads + (int)threadIdx.x < G * D ? ld_shared_out(acc + (size_t)s * G * D + i * kAttnThreads + threadIdx.x) : 0.f;
-  // Scales exp2((m - M) unit) / L of every split and head (0 for an empty part or an empty whole): wave h / .. of head h, lane l
-  // holds parts l, l + 64, ..
+  // Scales exp2((m - M) unit) / L of every split and head (0 for an empty part or an empty whole): wave h / .. of head h, a lane per
+  // split.
+  static_assert(kMergeInsideSplits <= kWave, "a lane per split");
   for (int h = wave; h < G; h += kAttnWaves) {
-    float M = -INFINITY, m0 = -INFINITY, l0 = 0.f;
+    float m0 = -INFINITY, l0 = 0.f;
     if (lane < a.n_split) {
       m0 = ld_shared_out(ml + 2 * (lane * G + h));
       l0 = ld_shared_out(ml + 2 * (lane * G + h) + 1);
     }
-    M = m0;
-    for (int p = lane + kWave; p < a.n_split; p += kWave) M = fmaxf(M, ld_shared_out(ml + 2 * (p * G + h)));
-    M = wave_max(M);
-    float L = m0 == -INFINITY ? 0.f : l0 * exp2_fast((m0 - M) * a.ml_unit);
-    for (int p = lane + kWave; p < a.n_split; p += kWave) {
-      const float m = ld_shared_out(ml + 2 * (p * G + h));
-      L += m == -INFINITY ? 0.f : ld_shared_out(ml + 2 * (p * G + h) + 1) * exp2_fast((m - M) * a.ml_unit);
-    }
-    L = wave_sum(L);
+    const float M = wave_max(m0);
+    const float L = wave_sum(m0 == -INFINITY ? 0.f : l0 * exp2_fast((m0 - M) * a.ml_unit));
     const float inv = L > 0.f ? 1.f / L : 0.f;
     if (lane < a.n_split) s_scale[lane * G + h] = m0 == -INFINITY ? 0.f : exp2_fast((m0 - M) * a.ml_unit) * inv;
-    for (int p = lane + kWave; p < a.n_split; p += kWave) {
-      const float m = ld_shared_out(ml + 2 * (p * G + h));
-      s_scale[p * G + h] = m == -INFINITY ? 0.f : exp2_fast((m - M) * a.ml_unit) * inv;
-    }
   }
   __syncthreads();
   // (added up in the order of the splits)

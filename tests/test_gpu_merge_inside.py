@@ -14,6 +14,10 @@ pytestmark = pytest.mark.gpu
     (1, 4, 64, 16, 16, 130, "f32", 16),       # fp32 form
     (3, 8, 128, 16, 130, 300, "f32", 16),
     (2, 1, 128, 8, 1024, 1100, "f32", 8),     # more splits than a wave has lanes
+    (8, 4, 128, 16, 64, 130, "f32", 8), (8, 4, 128, 16, 68, 130, "f32", 8),           # most splits merged inside, and one more
+    (8, 8, 128, 16, 48, 130, "f32", 8), (8, 8, 128, 16, 52, 130, "f32", 8),           # most sums, and more
+    (32, 2, 64, 16, 64, 90, "f32", 8), (33, 2, 64, 16, 64, 90, "f32", 8),             # most workgroups, and more
+    (4, 8, 128, 16, 96, 200, "bf16", 8), (4, 4, 128, 16, 128, 200, "bf16", 8),
     (8, 4, 128, 16, 64, 2050, "bf16", 64), (1, 1, 128, 16, 300, 700, "bf16", 16), (128, 2, 64, 16, 64, 500, "bf16", 16),
     (5, 8, 128, 32, 64, 131, "bf16", 16), (1, 4, 128, 64, 256, 300, "bf16", 16), (2, 8, 64, 8, 4096, 4099, "bf16", 8),
     (4, 4, 128, 8, 64, 2307, "bf16", 8), (4, 4, 128, 8, 64, 2308, "bf16", 8),         # most candidates the decode selects from, and one more
