@@ -432,19 +432,23 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 //   - one workgroup has little to merge: few splits, and few sums in all.  (8 instances, fp32, g = 4, d = 128: 16 splits 19.4 / 21.9, 24 22.9 /
 //     22.2, 64 36.1 / 25.8; g = 1, 64 splits 29.0 / 22.1; bf16, d = 128, g = 4: 8 splits 16.2 / 20.1, 16 20.5 / 21.3, 20 23.1 / 22.0; 4 instances,
 //     g = 8, 12 splits 22.0 / 25.8, 16 24.3 / 23.5, 64 51.6 / 29.0.)
-constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288;
-bool merge_inside(const Shape& s, int ninst, int n_split) {
-  return s.cleared && n_split > 1 && n_split <= kMergeInsideSplits && n_split * s.g * s.d <= kMergeInsideSums &&
+// Fewer splits behind a selection that is a launch of its own, where the merge's launch finds the host ahead (16 splits, 126 places, 16
+// instances 23.5 / 20.6, 8 instances 21.6 / 20.6; 4 splits, 128 instances, 35.5 / 36.5; without a selection 16 splits, 8 instances 15.1 / 16.5).
+constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288, kMergeBehindSelect = 8;
+bool merge_inside(const Shape& s, int ninst, int n_split, int most = kMergeInsideSplits) {
+  return s.cleared && n_split > 1 && n_split <= most && n_split * s.g * s.d <= kMergeInsideSums &&
          (long)ninst * n_split <= kMergeInsideWorkgroups;
 }
 
 // Does the streaming decode (and the fp32 one in splits) make the selection too?  Every workgroup of an instance makes all of it, which is
-// no loss where they would otherwise wait for the launch that does, and hardly any CU has two of them.  (Whole steps, 2041 candidates, us: 8 instances 17.6 -> 16.6,
-// 32 19.7 -> 18.4, 128 29.3 -> 28.0, one of fp32 with 126 candidates 16.8 -> 15.3, two launches instead of three; whole lists, 256 of 1243 candidates, 57.5 -> 55.1; at 3742 candidates, with 16 keys
-// a thread, 8 instances 22.7 and 128 45.6 -> 46.1: no gain.)
+// no loss where they would otherwise wait for the launch that does, and hardly any CU has two of them.  (Whole steps, 2041 candidates, us:
+// 8 instances 17.6 -> 16.6, 32 19.7 -> 18.4, 128 29.3 -> 28.0, one of fp32 with 126 candidates 16.8 -> 15.3, two launches instead of three; whole
+// lists, 256 of 1243 candidates, 57.5 -> 55.1.)  Many places for one workgroup to rank (97 to 128 of them) only where there are few splits: 8 instances,
+// 16 splits, 126 places 20.6 with three launches or four, 16 instances 21.9 and 20.6, 128 instances of four splits 34.4 and 36.7.
 bool select_here(const Shape& s, int ninst, int n_split, int nb_cur) {
   const int n_mid = nb_cur - s.n_sink - s.n_local, k_mid = s.k - s.n_sink - s.n_local;
-  return (n_split == 1 || merge_inside(s, ninst, n_split)) && (long)ninst * n_split <= 512 && n_mid <= kSelectInsideKeys * kSelThreads && k_mid >= 1 && k_mid <= kSelMaxMid;
+  return (n_split == 1 || merge_inside(s, ninst, n_split)) && (long)ninst * n_split <= kMergeInsideWorkgroups &&
+         n_mid <= kSelectInsideKeys * kSelThreads && k_mid >= 1 && k_mid <= (n_split <= kMergeBehindSelect ? kSelMaxMid : kSelFewMid);
 }
 
 // LDS bytes of a launch that merges, and selects if HOW says so, on top of lds for the decode; sets a.sel_at.
@@ -509,7 +513,7 @@ hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   }
   hipError_t e = select_first(s, ninst, a, st);
   if (e != hipSuccess) return e;
-  if (merge_inside(s, ninst, a.n_split)) {
+  if (merge_inside(s, ninst, a.n_split, a.pred ? kMergeBehindSelect : kMergeInsideSplits)) {
     const size_t lds = lds_of_form(a, lds_of(want), G, kMergeInside);
     sparse_stream_kernel<D, G, kMergeInside><<<grid, kAttnThreads, lds, st>>>(a);
     return hipGetLastError();
@@ -563,7 +567,7 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
     }
   }
   if constexpr (std::is_same<T, float>::value)
-    if (merge_inside(s, ninst, a.n_split)) {
+    if (merge_inside(s, ninst, a.n_split, a.pred && !inside ? kMergeBehindSelect : kMergeInsideSplits)) {
       if (inside) sparse_decode_kernel<T, D, G, kAttnWaves, false, kSelectInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_inside, st>>>(a);
       else sparse_decode_kernel<T, D, G, kAttnWaves, false, kMergeInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_of_form(a, lds, G, kMergeInside), st>>>(a);
       return hipGetLastError();

@@ -80,7 +80,10 @@ hipError_t launch_select(const Shape& s, int inst0, int ninst, const float* pred
 #define AP_SELECT(KPT, NT, GR) \
   select_topk_kernel<KPT, NT, GR><<<grid, NT, 0, st>>>(pred, s.nb_cap, nb_cur, s.k, s.n_sink, s.n_local, inst0, idx, cnt)
   // By a bound, where its groups are at least twice the free places and the keys fit the registers: 128 groups up to 64 places (2048
-  // instances of 2041 candidates, 56 places: 8.1 us, 8.7 with 256 groups), 256 up to 128.  Threads: as many as leave the launch
+  // instances of 2041 candidates, 56 places: 8.1 us, 8.7 with 256 groups), 256 up to 96, and to 128 where the radix select has long rows to
+  // go through: what is ranked grows with the square of the places.  (By a bound / radix select alone, us, 96 places: 8 instances x 700 candidates
+  // 5.6 / 6.4, 2048 x 700 10.9 / 11.2; 126 places: 8 x 160 6.6 / 5.9, 8 x 1300 6.4 / 6.8, 640 x 2050 10.5 / 9.8, x 4000 12.7 / 16.5, 2048 x 700
+  // 15.0 / 11.1, x 4000 24.1 / 29.2.)  Threads: as many as leave the launch
   // one round of workgroups and every thread some eight keys (us at 256 / 512 / 1024 threads: 8 instances x 2041 4.4 / 4.0 / 4.3,
   // 128 x 8186 10.8 / 7.3 / 6.8, 640 x 3742 6.5 / 6.4 / 11.0, 2048 x 2041 8.1 / 10.4 / 17.6).
 #define AP_SELECT_BOUND(KPT, NT) \
@@ -88,7 +91,7 @@ hipError_t launch_select(const Shape& s, int inst0, int ninst, const float* pred
     if (k_mid <= 64) AP_SELECT(KPT, NT, 2); else AP_SELECT(KPT, NT, 4); \
     return hipGetLastError(); \
   }
-  if (k_mid >= 1 && k_mid <= kSelMaxMid) {
+  if (k_mid >= 1 && (k_mid <= kSelFewMid || (k_mid <= kSelMaxMid && n_mid > (ninst <= 512 ? 1024 : 3072)))) {
     if (ninst > 1024 || n_mid <= 1024 || (ninst > 512 && n_mid <= 4096)) {
       AP_SELECT_BOUND(4, 256) AP_SELECT_BOUND(8, 256) AP_SELECT_BOUND(9, 256) AP_SELECT_BOUND(12, 256)
       AP_SELECT_BOUND(16, 256) AP_SELECT_BOUND(24, 256) AP_SELECT_BOUND(32, 256)

@@ -21,6 +21,7 @@ constexpr int kSelThreadsWide = 1024;      // few instances, long rows: more thr
 constexpr int kSelBins = 256;              // radix of one pass; the first kSelBins threads own one bin each
 constexpr int kSelRanked = 256;            // select_by_bound: most keys it ranks against each other
 constexpr int kSelMaxMid = 128;            // ... and most free places it fills
+constexpr int kSelFewMid = 96;             // places up to which it wins whatever the number of candidates (launch_select)
 template <int NT> constexpr int sel_scratch_words() {
   constexpr int radix = kSelBins + 3 * (NT / kWave) + 8, bound = 2 * (kSelRanked + 16) + 8 * kWave + kSelMaxMid + 18;
   return radix > bound ? radix : bound;

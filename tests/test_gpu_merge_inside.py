@@ -21,7 +21,8 @@ pytestmark = pytest.mark.gpu
     (8, 4, 128, 16, 64, 2050, "bf16", 64), (1, 1, 128, 16, 300, 700, "bf16", 16), (128, 2, 64, 16, 64, 500, "bf16", 16),
     (5, 8, 128, 32, 64, 131, "bf16", 16), (1, 4, 128, 64, 256, 300, "bf16", 16), (2, 8, 64, 8, 4096, 4099, "bf16", 8),
     (4, 4, 128, 8, 64, 2307, "bf16", 8), (4, 4, 128, 8, 64, 2308, "bf16", 8),         # most candidates the decode selects from, and one more
-    (3, 2, 128, 16, 131, 400, "bf16", 8), (3, 2, 128, 16, 132, 400, "bf16", 8),       # most free places, and one more
+    (3, 2, 128, 16, 99, 400, "bf16", 8), (3, 2, 128, 16, 100, 400, "bf16", 8),        # most free places of a selection inside, and one more
+    (3, 2, 128, 16, 131, 400, "bf16", 8), (3, 2, 128, 16, 132, 400, "bf16", 8),
     (256, 4, 128, 16, 64, 700, "bf16", 8), (500, 8, 64, 16, 64, 90, "bf16", 8), (513, 8, 64, 16, 16, 90, "bf16", 8),   # whole lists, and a workgroup too many
     (300, 4, 128, 16, 64, 200, "bf16", 16), (3, 4, 128, 16, 64, 40, "bf16", 16),      # (the last: lists shorter than the budget)
 ])

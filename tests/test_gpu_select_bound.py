@@ -1,5 +1,5 @@
 """The selection that ranks the few keys above a lower bound, where it can go wrong: each workgroup size and number of keys
-per thread at its edges, 1, 64, 65, 128 and 129 free places (128 groups, 256 groups, radix select), and scores that put the
+per thread at its edges, 1, 64, 65, 96, 97, 128 and 129 free places (128 groups, 256 groups, radix select), and scores that put the
 largest keys into few groups, let too many keys reach the bound, or leave fewer groups with a key than there are places."""
 import numpy as np
 import pytest
@@ -39,6 +39,7 @@ def _scores(mode, n_inst, nb, k, rng):
     (2, 3072 + 4, 132, 4, 0), (2, 3072 + 5, 132, 3, 0), (1, 4096, 129, 0, 0), (2, 4097, 5, 2, 2), (1, 8194, 128, 4, 4),
     (1, 16384 + 8, 128, 4, 4), (1, 16384 + 9, 128, 4, 4), (520, 4096, 72, 4, 4), (520, 4200, 72, 4, 4), (1030, 2304, 65, 0, 1),
     (1030, 2313, 64, 4, 4), (600, 2300, 200, 1, 1), (600, 2500, 200, 0, 1),          # (the last two: 9 and 10 keys a thread, radix select alone)
+    (3, 300, 98, 1, 1), (3, 300, 99, 1, 1), (3, 1126, 126, 1, 1), (3, 1027, 126, 1, 1), (520, 3074, 126, 1, 1), (520, 3075, 126, 1, 1),
 ])
 @pytest.mark.parametrize("mode", ["normal", "few_groups", "runs", "zeros", "close", "equal", "few_values", "ties_below", "extreme"])
 def test_bit_exact(n_inst, nb, k, n_sink, n_local, mode):
