@@ -147,9 +147,10 @@ struct CalibArgs {
 __global__ void zero_counter_kernel(int* counter) { *counter = 0; }
 
 // Workgroups are dealt to the XCDs in turn, and the XCDs do not stream equally fast (in the sparse-decode kernel the
-// slowest ends 12 % after the mean): a launch of one workgroup per chunk ends with its slowest XCD.  So the
-// grid is what the chip holds at once, and every workgroup takes (instance, chunk) units off a counter until
-// none is left; a unit is 1024 tokens, 30-40 us of streaming.  (fp32)
+// slowest ends 12 % after the mean): a launch of many rounds of workgroups, one per unit, ends with its slowest XCD.  So where there are
+// more (instance, chunk) units than the chip holds workgroups, the grid is what it holds, and every workgroup takes units off a
+// counter until none is left; 1024 tokens are 30-40 us of streaming.  As many units as fit or fewer, down to 256 tokens long
+// (calib_chunk_tokens): a workgroup each, no counter and no launch that clears it.  (fp32)
 template <int D, int G>
 __global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a) {
   using T = float;
@@ -581,11 +582,14 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
 
 // Tokens of a calibration unit (and of the chunks the merge sees): 1024, or 512 or 256 where that leaves the chip
 // without a workgroup for every place it has (8 instances at 32K: 1032 units of 256 tokens instead of 264 of 1024; 8 at 8K with
-// room for 128K 13.2 -> 9.5 us), unless the merge would have more than 60000 bytes of factors.
+// room for 128K 13.2 -> 9.5 us), unless the merge would have more than 60000 bytes of factors.  fp32 at d = 128 has half as many places, and a
+// last round of few units costs more than long units (us with 256 / 512 / 1024 tokens: 32 instances x 8000 tokens 26.7 / 29.8 / 42.2, 50 x 8000
+// 58.3 / 42.0 / 46.3, 8 x 131000 116 / 117 / 98, 400 x 2000 95 / 95 / 90; d = 64, 200 x 2000 23.6 / 24.0 / 25.7).
 int calib_chunk_tokens(const Shape& s, int t_cur) {
   int tokens = kCalibChunkTokens;
   if (s.kv_dtype != AP_BF16 && s.k_on_host) return tokens;   // (the fp32 form has no small grid for the link)
-  while (tokens > kCalibMinChunkTokens && (size_t)s.n_inst * t_cur / tokens < 1024 &&
+  const size_t places = s.kv_dtype != AP_BF16 && s.d == 128 ? 512 : 1024;
+  while (tokens > kCalibMinChunkTokens && (size_t)s.n_inst * t_cur / tokens < places &&
          (2 * (size_t)t_cur / tokens + 2) * s.g * sizeof(float) <= 60000 && (2 * t_cur + tokens - 1) / tokens <= s.calib_chunks)
     tokens /= 2;
   return tokens;

@@ -75,9 +75,13 @@ def test_calibrate_vs_float64(n, g, d, b, t, paged):
             assert (row[i].double() - ref).abs().max() <= 2e-5 * ref.max(), (i, again)
 
 
-@pytest.mark.parametrize("n,g,d,b,lengths", [(1, 4, 64, 16, (2051, 255, 257, 1)), (3, 8, 128, 8, (5003, 513)), (700, 2, 64, 32, (1100, 2000))])
+@pytest.mark.parametrize("n,g,d,b,lengths", [
+    (1, 4, 64, 16, (2051, 255, 257, 1)), (3, 8, 128, 8, (5003, 513)),      # units of 256 tokens, one a workgroup
+    (700, 2, 64, 32, (1100, 2000)), (200, 4, 128, 16, (2000, 2700, 1000)),            # of 512 and 1024; d = 128: 512, 1024 and 256
+    (2100, 1, 64, 16, (1025, 300, 2000)), (1100, 2, 128, 64, (1900,)),     # more units than the chip can hold workgroups (2048): off the counter
+])
 def test_fp32_units(n, g, d, b, lengths):
-    """fp32 caches: units of 256 or 512 tokens, one a workgroup, and 1024 handed out by the counter, as the length of the call goes."""
+    """fp32 caches: units of 256, 512 or 1024 tokens, as the length of the call goes, one a workgroup or handed out by the counter."""
     import paper_2502_04077_amd as ap
     dev = torch.device("cuda:0")
     cap = -(-max(lengths) // b) * b + b
