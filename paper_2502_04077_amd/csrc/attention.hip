@@ -425,7 +425,7 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 }
 
 // Are the splits merged by the last workgroup of an instance to finish, or by a launch of their own?  By the last one where a
-// launch before has cleared the counters (one more launch for that would cost as much as the merge's own), and
+// launch before has cleared the counters, which lie in the caller's workspace (one more launch for that would cost as much as the merge's own), and
 //   - there are no more than two workgroups a CU, which are resident at once whatever LDS they have: in further rounds every workgroup holds its
 //     place until its partials have reached memory.  (513 to 1024 workgroups, steps in us, merged inside / by a launch: fp32, 1024 tokens, g = 8,
 //     d = 128, 60 instances 42.0 / 35.9, g = 4, 40 instances 26.0 / 24.5; bf16, g = 8, d = 64, 510 x 8192 tokens 231 / 214, g = 4, d = 128,
@@ -433,11 +433,12 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 //   - one workgroup has little to merge: few splits, and few sums in all.  (8 instances, fp32, g = 4, d = 128: 16 splits 19.4 / 21.9, 24 22.9 /
 //     22.2, 64 36.1 / 25.8; g = 1, 64 splits 29.0 / 22.1; bf16, d = 128, g = 4: 8 splits 16.2 / 20.1, 16 20.5 / 21.3, 20 23.1 / 22.0; 4 instances,
 //     g = 8, 12 splits 22.0 / 25.8, 16 24.3 / 23.5, 64 51.6 / 29.0.)
-// Fewer splits behind a selection that is a launch of its own, where the merge's launch finds the host ahead (16 splits, 126 places, 16
-// instances 23.5 / 20.6, 8 instances 21.6 / 20.6; 4 splits, 128 instances, 35.5 / 36.5; without a selection 16 splits, 8 instances 15.1 / 16.5).
-constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288, kMergeBehindSelect = 8;
-bool merge_inside(const Shape& s, int ninst, int n_split, int most = kMergeInsideSplits) {
-  return s.cleared && n_split > 1 && n_split <= most && n_split * s.g * s.d <= kMergeInsideSums &&
+// Fewer sums behind a selection that is a launch of its own, where the merge's launch finds the host ahead (g = 4, d = 128: 16 splits, 126
+// places, 16 instances 23.5 / 20.6, 8 instances 21.6 / 20.6, 4 splits, 128 instances, 35.5 / 36.5; g = 1, d = 64: 15 splits, 7 instances 22.0 / 23.2;
+// without a selection 16 splits, 8 instances 15.1 / 16.5).
+constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288, kMergeBehindSelectSums = 4096;
+bool merge_inside(const Shape& s, int ninst, int n_split, int most_sums = kMergeInsideSums) {
+  return s.cleared && n_split > 1 && n_split <= kMergeInsideSplits && n_split * s.g * s.d <= most_sums &&
          (long)ninst * n_split <= kMergeInsideWorkgroups;
 }
 
@@ -446,10 +447,11 @@ bool merge_inside(const Shape& s, int ninst, int n_split, int most = kMergeInsid
 // 8 instances 17.6 -> 16.6, 32 19.7 -> 18.4, 128 29.3 -> 28.0, one of fp32 with 126 candidates 16.8 -> 15.3, two launches instead of three; whole
 // lists, 256 of 1243 candidates, 57.5 -> 55.1.)  Many places for one workgroup to rank (97 to 128 of them) only where there are few splits: 8 instances,
 // 16 splits, 126 places 20.6 with three launches or four, 16 instances 21.9 and 20.6, 128 instances of four splits 34.4 and 36.7.
+constexpr int kRankedSplits = 8;
 bool select_here(const Shape& s, int ninst, int n_split, int nb_cur) {
   const int n_mid = nb_cur - s.n_sink - s.n_local, k_mid = s.k - s.n_sink - s.n_local;
   return (n_split == 1 || merge_inside(s, ninst, n_split)) && (long)ninst * n_split <= kMergeInsideWorkgroups &&
-         n_mid <= kSelectInsideKeys * kSelThreads && k_mid >= 1 && k_mid <= (n_split <= kMergeBehindSelect ? kSelMaxMid : kSelFewMid);
+         n_mid <= kSelectInsideKeys * kSelThreads && k_mid >= 1 && k_mid <= (n_split <= kRankedSplits ? kSelMaxMid : kSelFewMid);
 }
 
 // LDS bytes of a launch that merges, and selects if HOW says so, on top of lds for the decode; sets a.sel_at.
@@ -514,7 +516,7 @@ hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   }
   hipError_t e = select_first(s, ninst, a, st);
   if (e != hipSuccess) return e;
-  if (merge_inside(s, ninst, a.n_split, a.pred ? kMergeBehindSelect : kMergeInsideSplits)) {
+  if (merge_inside(s, ninst, a.n_split, a.pred ? kMergeBehindSelectSums : kMergeInsideSums)) {
     const size_t lds = lds_of_form(a, lds_of(want), G, kMergeInside);
     sparse_stream_kernel<D, G, kMergeInside><<<grid, kAttnThreads, lds, st>>>(a);
     return hipGetLastError();
@@ -568,7 +570,7 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
     }
   }
   if constexpr (std::is_same<T, float>::value)
-    if (merge_inside(s, ninst, a.n_split, a.pred && !inside ? kMergeBehindSelect : kMergeInsideSplits)) {
+    if (merge_inside(s, ninst, a.n_split, a.pred && !inside ? kMergeBehindSelectSums : kMergeInsideSums)) {
       if (inside) sparse_decode_kernel<T, D, G, kAttnWaves, false, kSelectInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_inside, st>>>(a);
       else sparse_decode_kernel<T, D, G, kAttnWaves, false, kMergeInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_of_form(a, lds, G, kMergeInside), st>>>(a);
       return hipGetLastError();

@@ -355,10 +355,11 @@ struct SparseArgs {
 // What a decode launch does beside its own share: nothing; merging, by the last workgroup of an instance to finish;
 // before that also the selection, by every workgroup for itself (whole lists too; see select_here).
 constexpr int kSplitsOnly = 0, kMergeInside = 1, kSelectInside = 2;
-// Scores a thread holds: up to 3072 candidates.  (Steps of 8 / 32 / 128 instances, us, with 9, 12 and 15 scores a thread: 2042 candidates
-// 16.6 16.7 17.2 / 18.5 18.8 19.0 / 28.6 28.4 28.8, 2442, for nine too many, 18.1 17.0 17.3 / 20.6 19.1 19.2 / 30.2 29.0 29.7, 2992 18.4 17.2 17.3 / 21.1
-// 19.9 19.9 / 31.3 30.4 30.5; 15 would take 3692 from 18.6 21.2 34.4 to 18.0 20.2 33.5, and 0.4 us from the common 2042.)
-constexpr int kSelectInsideKeys = 12;
+// Scores a thread holds: up to 2304 candidates.  (Steps of 8 / 32 / 128 instances, us, with 9, 12 and 15 scores a thread: 2042 candidates
+// 16.6 16.8 17.2 / 18.5 18.8 19.0 / 28.6 28.6 28.8, one of fp32 with 126 candidates 16.9 and 17.4; 2442, for nine too many, 18.2 17.0 17.3 / 20.4 19.1
+// 19.2 / 30.2 29.4 29.7, 2992 18.4 17.1 17.3 / 21.0 19.7 19.9 / 31.7 30.4 30.5, 3692 19.0 18.7 18.0 / 21.4 21.2 20.2 / 34.9 34.2 33.5.  More scores
+// a thread win some 1.2 us where they are needed and cost 0.2 to 0.5 where they are not.)
+constexpr int kSelectInsideKeys = 9;
 
 // The instance's selection by this workgroup of 256 threads, into LDS at a.sel_at; that of the first split writes idx and cnt too.
 // Returns the number of listed blocks.  smem: sel_scratch_words<256>() words that are free until it returns.

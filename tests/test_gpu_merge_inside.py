@@ -20,9 +20,9 @@ pytestmark = pytest.mark.gpu
     (4, 8, 128, 16, 96, 200, "bf16", 8), (4, 4, 128, 16, 128, 200, "bf16", 8),
     (8, 4, 128, 16, 64, 2050, "bf16", 64), (1, 1, 128, 16, 300, 700, "bf16", 16), (128, 2, 64, 16, 64, 500, "bf16", 16),
     (5, 8, 128, 32, 64, 131, "bf16", 16), (1, 4, 128, 64, 256, 300, "bf16", 16), (2, 8, 64, 8, 4096, 4099, "bf16", 8),
-    (4, 4, 128, 8, 64, 2307, "bf16", 8), (4, 4, 128, 8, 64, 2308, "bf16", 8),
-    (4, 4, 128, 8, 64, 3075, "bf16", 8), (4, 4, 128, 8, 64, 3076, "bf16", 8),         # most candidates the decode selects from, and one more
-    (4, 4, 64, 8, 64, 3075, "f32", 8), (4, 4, 64, 8, 64, 3076, "f32", 8),
+    (4, 4, 128, 8, 64, 2307, "bf16", 8), (4, 4, 128, 8, 64, 2308, "bf16", 8),         # most candidates the decode selects from, and one more
+    (4, 4, 64, 8, 64, 2307, "f32", 8), (4, 4, 64, 8, 64, 2308, "f32", 8),
+    (7, 1, 64, 16, 121, 3841, "bf16", 8), (7, 2, 128, 16, 128, 3841, "bf16", 8), (7, 4, 128, 16, 128, 3841, "bf16", 8),   # 15 and 16 splits behind a selection's launch
     (3, 2, 128, 16, 99, 400, "bf16", 8), (3, 2, 128, 16, 100, 400, "bf16", 8),        # most free places of a selection inside, and one more
     (3, 2, 128, 16, 131, 400, "bf16", 8), (3, 2, 128, 16, 132, 400, "bf16", 8),
     (256, 4, 128, 16, 64, 700, "bf16", 8), (500, 8, 64, 16, 64, 90, "bf16", 8), (513, 8, 64, 16, 16, 90, "bf16", 8),   # whole lists, and a workgroup too many
