@@ -411,11 +411,11 @@ int ilog2(int x) { int l = 0; while ((1 << l) < x) ++l; return l; }
 // Workgroups of kernel `fn` (NT threads, lds bytes of LDS) the device holds at once; 0 if it cannot be asked.
 template <class Fn> int resident_workgroups(Fn fn, int nt, size_t lds) {
   int per_cu = 0, dev = 0;
-  hipDeviceProp_t prop;
+  int n_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, nt, lds) != hipSuccess ||
-      hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
+      hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
-  return per_cu * prop.multiProcessorCount;
+  return per_cu * n_cu;
 }
 
 template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, hipStream_t st) {
