@@ -1,5 +1,5 @@
 // MFMA form of the incremental predictor for the paper's own network (16 and 32 hidden channels; architecture
-// table of the appendix "Implement Details").  Same method as predict_inc_mfma_body (see predict.hip): per
+// table of the appendix "Implement Details").  Same method as predict_inc_reg_body (predict_inc8.h): per
 // column, the state of the interior rows moves by (row entering) - (row leaving) and the four border rows are
 // evaluated afresh; waves 0,1 = top half, waves 2,3 = bottom half.
 //
@@ -10,8 +10,9 @@
 // waves of a half, and blocks beyond the list's end are left out.  With dense rows the list is every column.
 // Measured (us; before: every column, tiles of 124), histories of 64 selected blocks in runs: 2048 instances x 2050 columns 128 (295), 256 x 1251 17
 // (32), 8 x 2050 8.7 (9.1); all rows dense 327 (301), 31 (32.5), 8.8 (7.9); all zero 64 (293).  With a dense row every 32 steps one half
-// is dense in ten of 32.  With dense rows it is bound by issue: as many MFMAs as before and 8 % more vector instructions (stages,
-// lists and addresses); with sparse ones by the passes' serial part.  Two waves per SIMD, 242 VGPRs: 261 of them, and one workgroup a CU,
+// is dense in ten of 32.  With rows 0..3 dense and the newest ones sparse, the steps after a prefill, 282 (275). Dense: as many MFMAs as before and
+// 8 % more vector instructions (stages, lists and addresses), neither unit full (38 and 44 % of the SIMDs' cycles): a chunk's layers wait for each other at
+// barriers; sparse: the passes' serial part.  Two waves per SIMD, 242 VGPRs: 261 of them, and one workgroup a CU,
 // cost 70 %; without a straight path through both blocks of a wave, or with the lists made by scalar instructions, 30-100 % more on sparse rows.
 //
 // v_mfma_f32_32x32x16_f16: D[32 x 32] += A[32 x 16] * B[16 x 32]; lane l supplies row/column l % 32 and K

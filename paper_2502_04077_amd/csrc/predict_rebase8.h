@@ -27,8 +27,9 @@
 // Measured at 2048 instances x 2050 columns, H = 64, state and pred, 33 to 77 us of it the border rows and pred (before: every strip of every
 // column, rows staged by every wave for itself): histories of 64 selected blocks in runs with a dense row every 32 steps 539 us (866),
 // without dense rows 444 (955), all rows dense 884 (1012), all zero 305 (950); 8 instances 18 us (18).  Reading the 1.09 GB of rows and
-// listing take 213 us without arithmetic (155 at a plain read's rate); then it is bound by a strip's chain: nine MFMAs of which eight
-// build on each other, y1 into LDS and back, the head, some 540 cycles with three waves a SIMD and 800 where one wave of a workgroup has the listed columns.
+// listing take 213 us without arithmetic (155 at a plain read's rate).  Dense strips are bound by issue (63 % of the SIMDs' cycles vector
+// instructions, 54 % MFMAs), selected columns by a strip's chain in the one wave that has the list: nine MFMAs of which eight build on each other, y1
+// into LDS and back, the head.
 // Measured and not kept: operands asked for a strip ahead but their addresses kept in a register each (spills: 588 us instead of 539), 66
 // rows on their way at a time (no difference), the same sums by 16x16x32 MFMAs, two output rows at a time and half the
 // MFMA cycles (533, all dense 911).  Strips of two rows summed in an order of their own, dense and listed ones apart, take 369 us.

@@ -11,7 +11,6 @@
 namespace ap {
 #define AP_STUB { return hipErrorUnknown; }
 hipError_t launch_predict(const Shape&, int, int, const float*, const float*, int, int, int, float*, float*, hipStream_t) AP_STUB
-hipError_t launch_predict_interior(const Shape&, int, int, const float*, const float*, int, int, float*, hipStream_t) AP_STUB
 hipError_t launch_predict_columns(const Shape&, int, int, const float*, const float*, int, int, int, float*, float*, hipStream_t) AP_STUB
 hipError_t launch_predict_inc(const Shape&, int, int, const float*, const float*, int, int, int, float*, float*, hipStream_t) AP_STUB
 hipError_t launch_select(const Shape&, int, int, const float*, int, int32_t*, int32_t*, hipStream_t) AP_STUB
