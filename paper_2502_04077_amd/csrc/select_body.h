@@ -1,6 +1,6 @@
 // Top-K block selection (Algorithm 1 step 5) with forced sink / local blocks (Sec. 4.1).
 //
-// One workgroup per instance.  Scores are mapped to order-preserving 32-bit keys.  With up to 128 free places the few keys
+// One workgroup per instance.  Scores are mapped to order-preserving 32-bit keys.  With few free places (launch_select) the few keys
 // that reach a lower bound of the last one are ranked against each other (select_by_bound).  With more, or where too many keys
 // reach the bound (scores that all but coincide), a 4-pass
 // radix select (8 bits per pass, histogram in LDS) finds the key T of the k_mid-th largest score
