@@ -481,12 +481,14 @@ hipError_t run_rebase16(const Shape& s, int inst0, int ninst, const float* dweig
 
 hipError_t run_rebase8(const Shape& s, int inst0, int ninst, const float* dweights, const float* hist, int newest_slot,
                        int nb_cur, float* pstate, float* pred, hipStream_t st) {
-  // Tiles: as wide as they may be (a tile stages eight columns beside its own), narrower where there would be fewer than the
-  // 768 workgroups that the chip holds.
+  // Tiles: as wide as they may be (a tile stages eight columns beside its own, and a workgroup's list, barriers and chains cost it
+  // whatever its width: 3000 instances x 250 columns, H = 96, two tiles 318 us, three 416; 2048 x 500, H = 64, three 182, five 215), narrower where there is
+  // room for more among the 768 workgroups that the chip holds, but not into a second round (710 x 118, H = 96, two tiles 56, one 42; 300 x 118
+  // three 43, two 32; 100 x 500 eight 32, seven 25).
   RebasePlan plan;
   int tiles = (nb_cur + kRbCols - 1) / kRbCols;
-  const int filled = (768 + ninst - 1) / ninst, most = (nb_cur + 55) / 56;
-  if (tiles < filled) tiles = filled < most ? filled : most;
+  const int room = 768 / ninst, most = (nb_cur + 55) / 56;
+  if (tiles < room) tiles = room < most ? room : most;
   plan.cols = (nb_cur + tiles - 1) / tiles;
   tiles = (nb_cur + plan.cols - 1) / plan.cols;
   const int strips = (s.H - 2) / 3, segs = (strips + kRbStrips - 1) / kRbStrips;
