@@ -74,7 +74,6 @@ struct WsLayout {
   size_t cal_ml;      // [n_inst][calib_chunks][g][2]
   size_t cal_bmp;     // [n_inst][g][nb_cap]
   size_t pred_state;  // [n_inst][nb_cap]               interior state of a full-tile prediction without a caller state
-  size_t counters;    // [4] ints                       work counters of persistent kernels (zeroed by the launch that uses them)
   size_t total;       // floats
 };
 

@@ -136,7 +136,6 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_combine_kernel(SparseArgs
 struct CalibArgs {
   const void* q; const void* K;
   float* row; float* cal_ml; float* cal_bmp;
-  int* counter;                   // next unit to hand out, zero at launch; null: every workgroup has one unit
   int n_units;                    // n_inst * n_chunks
   int t_cap, nb_cap, b, log2b, t_cur, nb_cur, chunk_blocks, n_chunks, chunk_slots;
   const int32_t* table;
@@ -144,70 +143,57 @@ struct CalibArgs {
   float ml_unit;                  // the chunks' maxima times this are exponents of 2
 };
 
-__global__ void zero_counter_kernel(int* counter) { *counter = 0; }
-
-// Workgroups are dealt to the XCDs in turn, and the XCDs do not stream equally fast (in the sparse-decode kernel the
-// slowest ends 12 % after the mean): a launch of many rounds of workgroups, one per unit, ends with its slowest XCD.  So where there are
-// more (instance, chunk) units than the chip holds workgroups, the grid is what it holds, and every workgroup takes units off a
-// counter until none is left; 1024 tokens are 30-40 us of streaming.  As many units as fit or fewer, down to 256 tokens long
-// (calib_chunk_tokens): a workgroup each, no counter and no launch that clears it.  (fp32)
+// A workgroup for every unit (a chunk of an instance).  (fp32.  With units off a counter, cleared by a launch before, 100 instances at 32K took 321 us
+// instead of 304; 16 55.8, 54.4.)
 template <int D, int G>
 __global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a) {
   using T = float;
   extern __shared__ __align__(16) float smem[];
-  __shared__ int s_unit;
-  for (;;) {
-    int unit = blockIdx.x;
-    if (a.counter != nullptr) {
-      if (threadIdx.x == 0) s_unit = atomicAdd(a.counter, 1);
-      __syncthreads();
-      unit = s_unit;
-      if (unit >= a.n_units) break;                      // (the same for every thread; every workgroup gets here)
-    }
-    const int inst = unit / a.n_chunks, chunk = unit - inst * a.n_chunks;
-    const int c0 = chunk * a.chunk_blocks;
-    const int nblk = min(a.chunk_blocks, a.nb_cur - c0);
-    const int ld = a.chunk_blocks * a.b;
-    const int ntok = nblk * a.b;
-    float* s_p = smem;                    // [G][ld]
-    float* s_bmp = s_p + G * ld;          // [G][chunk_blocks]
-    float* s_m = s_bmp + G * a.chunk_blocks;
-    float* s_l = s_m + G;
-    int* s_phys = reinterpret_cast<int*>(s_l + G);   // [chunk_blocks] place of each block of the chunk in K
+  const int unit = blockIdx.x;
+  const int inst = unit / a.n_chunks, chunk = unit - inst * a.n_chunks;
+  const int c0 = chunk * a.chunk_blocks;
+  const int nblk = min(a.chunk_blocks, a.nb_cur - c0);
+  const int ld = a.chunk_blocks * a.b;
+  const int ntok = nblk * a.b;
+  float* s_p = smem;                    // [G][ld]
+  float* s_bmp = s_p + G * ld;          // [G][chunk_blocks]
+  float* s_m = s_bmp + G * a.chunk_blocks;
+  float* s_l = s_m + G;
+  int* s_phys = reinterpret_cast<int*>(s_l + G);   // [chunk_blocks] place of each block of the chunk in K
 
-    for (int j = threadIdx.x; j < nblk; j += kAttnThreads)
-      s_phys[j] = a.table ? min(max(a.table[(size_t)inst * a.nb_cap + c0 + j], 0), a.n_phys - 1) : c0 + j;
-    __syncthreads();
-    const T* q_inst = static_cast<const T*>(a.q) + (size_t)inst * G * D;
-    const T* K_inst = static_cast<const T*>(a.K) + (a.table ? 0 : (size_t)inst * a.t_cap * D);
-    qk_logits<T, D, G, 0>(q_inst, K_inst, a.b, a.log2b, a.t_cur, ntok, [&](int jb) { return c0 + jb; },
-                         [&](int jb) { return s_phys[jb]; }, s_p, ld, nullptr);
-    __syncthreads();
-    softmax_stats<G>(s_p, ld, ntok, a.b, nblk, s_m, s_l, s_bmp);
-    for (int pair = threadIdx.x; pair < G * nblk; pair += kAttnThreads) {
-      const int h = pair / nblk, jb = pair - h * nblk;
-      a.cal_bmp[((size_t)inst * G + h) * a.nb_cap + c0 + jb] = s_bmp[pair];
-    }
-    if (threadIdx.x < G) {
-      float* ml = a.cal_ml + (((size_t)inst * a.chunk_slots + chunk) * G + threadIdx.x) * 2;
-      ml[0] = s_m[threadIdx.x];
-      ml[1] = s_l[threadIdx.x];
-    }
-    if (a.counter == nullptr) break;                     // (a workgroup has one unit)
-    __syncthreads();                                     // the next unit overwrites s_unit and the tiles
+  for (int j = threadIdx.x; j < nblk; j += kAttnThreads)
+    s_phys[j] = a.table ? min(max(a.table[(size_t)inst * a.nb_cap + c0 + j], 0), a.n_phys - 1) : c0 + j;
+  __syncthreads();
+  const T* q_inst = static_cast<const T*>(a.q) + (size_t)inst * G * D;
+  const T* K_inst = static_cast<const T*>(a.K) + (a.table ? 0 : (size_t)inst * a.t_cap * D);
+  qk_logits<T, D, G, 0>(q_inst, K_inst, a.b, a.log2b, a.t_cur, ntok, [&](int jb) { return c0 + jb; },
+                       [&](int jb) { return s_phys[jb]; }, s_p, ld, nullptr);
+  __syncthreads();
+  softmax_stats<G>(s_p, ld, ntok, a.b, nblk, s_m, s_l, s_bmp);
+  for (int pair = threadIdx.x; pair < G * nblk; pair += kAttnThreads) {
+    const int h = pair / nblk, jb = pair - h * nblk;
+    a.cal_bmp[((size_t)inst * G + h) * a.nb_cap + c0 + jb] = s_bmp[pair];
+  }
+  if (threadIdx.x < G) {
+    float* ml = a.cal_ml + (((size_t)inst * a.chunk_slots + chunk) * G + threadIdx.x) * 2;
+    ml[0] = s_m[threadIdx.x];
+    ml[1] = s_l[threadIdx.x];
   }
 }
 
 // The same for bf16, streaming: the four waves of a workgroup take 16-token passes of a unit in turn (whole blocks, where a
 // block is longer) - so that together they read consecutive memory, which streams better than four places at once -
-// with the K rows of a wave's next pass, of the next unit's first one too, on their way while it works on the present one
+// with the K rows of a wave's next pass on their way while it works on the present one
 // (logits on MFMA as in sparse_stream_body; no probabilities are kept, one largest logit per four tokens goes to LDS for
-// the block maxima).  The waves meet once per unit, to bring their maxima and sums together and to hear the id of the unit
-// after the next.  A launch with no more units than the chip holds workgroups gives each its own and needs no counter.
-// Measured with the merge, against the phased form (all logits of a unit, then softmax, barriers between; four workgroups
-// a CU, first units off the counter too), both in turn on one card: 8 instances at 32K 31.8 -> 16.6 us (units of 256 tokens
-// instead of 1024, no launch to clear the counter, the merge), 32 at 32K 70 -> 44-50, 256 at 50K 535 -> 521 (6.3 TB/s), 128 at 128K
-// 711 -> 682 (23 of it in the merge), 1024 at 32K 1379 -> 1352.
+// the block maxima).  The waves meet once per unit, to bring their maxima and sums together, and write the block maxima.
+// A workgroup each for the units of K in device memory; over PCIe a few workgroups, each taking every gridDim.x-th, with the rows of the next unit's first pass
+// on their way as well.  run_calib says how many workgroups a CU has.
+// What bounds it: reads of K, and what little is written.  The block maxima are 0.4 % of the bytes, but of 519 us of 256 instances at 50K they cost 20
+// where every wave writes every fourth float to its XCD's L2, 14 where neighbouring lanes write neighbouring columns through to memory.  Measured, launch
+// and merge, us, before (512 workgroups, units off a counter, a wave's own blocks written by it) and now: 256 instances at 50K 519, 482 (6.8 TB/s); 2048 at 32K
+// 2678, 2488; 4096, g = 1, 5083, 4768; 62 95, 85; 24 48, 40; 300 at 30K, d = 64, 245, 185; 8 17.0, 16.7.  No difference: two or four
+// passes of rows on their way per wave, units of 63 or 65 blocks.  Merging by the last workgroup of an instance: 8 instances 17.6, 256 a wave's merge
+// holds up its workgroup's stream, 558.
 struct CalibUnit { int inst, chunk, nblk, c0; };
 
 template <int D, int G>
@@ -218,7 +204,6 @@ void calibrate_stream_kernel(CalibArgs a) {
   constexpr int NW = kAttnWaves, E = Ge::E, LPT = Ge::LPT, TPI = Ge::TPI, NL = Ge::NL, KS = D / 32;
   constexpr int RS = D * 2 + kStageRowPad, TILE = kGroupTokens * RS, QROWS = G * RS;
   extern __shared__ __align__(16) char smem_c[];
-  __shared__ int s_next[2];
   __shared__ float s_ml[2][NW][2 * G];                           // [unit parity][wave][maxima | sums]
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -227,7 +212,7 @@ void calibrate_stream_kernel(CalibArgs a) {
   const int qpb = a.b >> 2, quads = (a.chunk_blocks * qpb + 4 * NW - 1) / NW;   // groups of four tokens: per block, per wave (at most)
   char* stage = smem_c + wave * TILE;
   char* s_q = smem_c + NW * TILE + wave * QROWS;                 // (a wave may be a unit ahead, in another instance)
-  float* s_qmax = reinterpret_cast<float*>(smem_c + NW * (TILE + QROWS)) + wave * G * quads;   // [G][quads]
+  float* s_qmax = reinterpret_cast<float*>(smem_c + NW * (TILE + QROWS));       // [unit parity][wave][G][quads]
 
   auto unit_of = [&](int unit) __attribute__((always_inline)) {
     CalibUnit u;
@@ -270,12 +255,7 @@ void calibrate_stream_kernel(CalibArgs a) {
     }
   };
 
-  // The first two units of a workgroup are fixed, the others come off the counter: a thousand workgroups that all ask for
-  // their first unit wait 13 us for the last answer (and 40 us where each asks for three).
-  const bool handed_out = a.counter != nullptr;
-  const int unit = blockIdx.x;
-  if (threadIdx.x == 0) { s_next[0] = unit; s_next[1] = unit + (int)gridDim.x; }
-  __syncthreads();
+  int unit = blockIdx.x;
   if (unit >= a.n_units) return;                         // (the whole workgroup)
   CalibUnit u = unit_of(unit);
   int place = places(u);
@@ -285,13 +265,9 @@ void calibrate_stream_kernel(CalibArgs a) {
 
 #pragma unroll 1
   for (int round = 0;; ++round) {
-    // The next unit's id was written before the last barrier; the one after it is asked for now.
-    int next = a.n_units;
-    if (handed_out) next = __builtin_amdgcn_readfirstlane(s_next[(round + 1) & 1]);
-    int asked = 0;
-    if (handed_out && threadIdx.x == 0) asked = 2 * (int)gridDim.x + atomicAdd(a.counter, 1);
-    const bool more = next < a.n_units;
-    const CalibUnit v = more ? unit_of(next) : u;
+    unit += gridDim.x;
+    const bool more = unit < a.n_units;
+    const CalibUnit v = more ? unit_of(unit) : u;
     const int place_v = more ? places(v) : place;
     if (u.inst != q_inst) {
       const T* q = static_cast<const T*>(a.q) + (size_t)u.inst * G * D;
@@ -302,6 +278,7 @@ void calibrate_stream_kernel(CalibArgs a) {
     }
     const int npass = passes(u), n_valid = min(a.t_cur - u.c0 * a.b, u.nblk * a.b);    // tokens of the unit inside the context
     float m = -INFINITY, l = 0.f;
+    float* qmax = s_qmax + ((round & 1) * NW + wave) * G * quads;
 #pragma unroll 1
     for (int ps = 0; ps < max(npass, 1); ++ps) {         // (a wave without a pass hands its loads on)
 #pragma unroll
@@ -326,7 +303,7 @@ void calibrate_stream_kernel(CalibArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) p[i] = i < n_in ? lg[i] : -INFINITY;
       const float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
-      if (head < G && ps < npass) s_qmax[head * quads + ps * 4 + row16] = mx;
+      if (head < G && ps < npass) qmax[head * quads + ps * 4 + row16] = mx;
       const float m_new = fmaxf(m, Unit::reference(mx)), m_ref = m_new == -INFINITY ? 0.f : m_new;      // (nothing but masked tokens so far)
       auto rel = [&](float x) __attribute__((always_inline)) { return Unit::exp_of(x, m_ref); };
       l = l * exp2_fast(m - m_ref) + ((rel(p[0]) + rel(p[1])) + (rel(p[2]) + rel(p[3])));
@@ -338,41 +315,46 @@ void calibrate_stream_kernel(CalibArgs a) {
     const float lw = across_32(across_16(m == -INFINITY ? 0.f : l * exp2_fast(m - mw), plus), plus);
     float (*ml)[2 * G] = s_ml[round & 1];
     if (lane < G) { ml[wave][lane] = mw; ml[wave][G + lane] = lw; }
-    if (threadIdx.x == 0) s_next[round & 1] = asked;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (not __syncthreads(): that would wait for the K rows on their way)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    // The unit's maximum and sum, of head lane % G; block maxima relative to that maximum.
+    // The unit's maximum and sum, of head lane % G; block maxima relative to that maximum, one head's columns by neighbouring lanes, written
+    // through to memory, where the merge's launch finds them.  (The next unit's maxima go to the other half of s_ml and s_qmax: a wave that gets to the one
+    // after it has met the others in between.)
     {
-      const int h = lane & (G - 1);
+      const int hl = lane & (G - 1);
       float M = -INFINITY, L = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) M = fmaxf(M, ml[w][h]);             // (a unit has a token inside the context)
+      for (int w = 0; w < NW; ++w) M = fmaxf(M, ml[w][hl]);            // (a unit has a token inside the context)
 #pragma unroll
-      for (int w = 0; w < NW; ++w) L += ml[w][G + h] * exp2_fast(ml[w][h] - M);
+      for (int w = 0; w < NW; ++w) L += ml[w][G + hl] * exp2_fast(ml[w][hl] - M);
       if (wave == 0 && lane < G) {
         float* to = a.cal_ml + (((size_t)u.inst * a.chunk_slots + u.chunk) * G + lane) * 2;
-        to[0] = M;
-        to[1] = L;
+        st_shared_out<true>(to, M);
+        st_shared_out<true>(to + 1, L);
       }
-      // This wave's blocks: head lane % G, block lane / G and on (one column of a head after the other by neighbouring lanes)
-      const int per_grain = 1 << (log2gran - a.log2b);
-      const int mine = (npass >> (log2gran - 4)) * per_grain;
-      for (int i = lane / G; i < mine; i += kWave / G) {
-        const int jb = ((i / per_grain) * NW + wave) * per_grain + i % per_grain;
-        const float* qm = s_qmax + h * quads + i * qpb;
-        float mx = qm[0];
+      const int per = log2gran - a.log2b;                // (log2) blocks of a grain; the grains are dealt to the waves in turn
+      const int log2blocks = 31 - __builtin_clz(a.chunk_blocks);
 #pragma unroll 1
-        for (int k = 1; k < qpb; ++k) mx = fmaxf(mx, qm[k]);
-        if (jb < u.nblk) a.cal_bmp[((size_t)u.inst * G + h) * a.nb_cap + u.c0 + jb] = Unit::exp_of(mx, M);
+      for (int p = threadIdx.x; p < G << log2blocks; p += kAttnThreads) {
+        const int h = p >> log2blocks, jb = p & (a.chunk_blocks - 1);
+        const float Mh = fmaxf(fmaxf(ml[0][h], ml[1][h]), fmaxf(ml[2][h], ml[3][h]));
+        const int grain = jb >> per, i = ((grain / NW) << per) + (jb & ((1 << per) - 1));
+        const float* qm = s_qmax + (((round & 1) * NW + grain % NW) * G + h) * quads + i * qpb;
+        if (jb < u.nblk) {
+          float mx = qm[0];
+#pragma unroll 1
+          for (int k = 1; k < qpb; ++k) mx = fmaxf(mx, qm[k]);
+          st_shared_out<true>(a.cal_bmp + ((size_t)u.inst * G + h) * a.nb_cap + u.c0 + jb, Unit::exp_of(mx, Mh));
+        }
       }
-      asm volatile("" ::: "memory");                     // the next unit overwrites what was read
     }
     if (!more) break;                                    // (the same for every wave)
     u = v;
     place = place_v;
   }
 }
+static_assert(kAttnWaves == 4, "four waves' maxima");
 
 // Merges the chunks of one instance into the dense row, kCombineCols columns per workgroup (blockIdx.x; blockIdx.y =
 // instance); the block maxima do not wait for the scales.
@@ -597,44 +579,33 @@ int calib_chunk_tokens(const Shape& s, int t_cur) {
   return tokens;
 }
 
+// LDS that leaves room for two workgroups a CU.  With d = 128 these keep memory busy, and more only spread the reads over more places (us with two / as
+// many as fit: 256 instances at 50K 482 / 501, 2048 at 32K 2488 / 2606, 62 85 / 91) - unless all fit at once and none has to wait (8 instances at 32K 19.2 /
+// 16.7).  d = 64, with half the bytes on their way per workgroup: as many as fit (300 at 30K, two 261, three 201, five 188).
+constexpr size_t kCalibPairLds = 65536;
+
 template <typename T, int D, int G>
 hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
   if constexpr (std::is_same<T, bf16_t>::value) {
     a.ml_unit = 1.f;
-    auto lds_of = [&](int tokens) {
+    auto lds_of = [&](int tokens, bool several) {          // (largest logits of two units, where a workgroup takes several)
       const size_t quads = (tokens / 4 + 4 * kAttnWaves - 1) / kAttnWaves;
-      return (size_t)kAttnWaves * ((kGroupTokens + G) * (D * 2 + kStageRowPad) + sizeof(float) * G * quads);
+      return (size_t)kAttnWaves * ((kGroupTokens + G) * (D * 2 + kStageRowPad) + (several ? 2 : 1) * sizeof(float) * G * quads);
     };
-    const int tokens = a.chunk_blocks * a.b;
-    const size_t lds = lds_of(tokens);
-    if (s.occ->calib_slots[0] < 0)
-      for (int i = 0; i < 3; ++i)
-        s.occ->calib_slots[i] = resident_workgroups(calibrate_stream_kernel<D, G>, kAttnThreads, lds_of(kCalibChunkTokens >> i));
-    const int slots = s.occ->calib_slots[tokens == kCalibChunkTokens ? 0 : tokens == kCalibChunkTokens / 2 ? 1 : 2];
-    a.n_units = a.n_chunks * s.n_inst;
-    // As many units as fit at once: one workgroup each, no counter.  More: two workgroups a CU take them off the counter.
-    // Eight waves a CU keep memory busy, and more of them only spread the reads over more places (256 instances at
-    // 50K, us: six workgroups a CU 547, four 534, three 528, two 520, one 697).
-    int grid = a.n_units;
     // Over PCIe 16 workgroups fill the link, and a thousand places at once cost it 15 % (8 instances at 32K, 67 MB, us: 16
     // workgroups 1178, 64 1190, 256 1272, 512 1358).
-    const int most = s.k_on_host ? 16 : 512;
-    if (a.n_units <= (s.k_on_host ? most : slots)) {
-      a.counter = nullptr;
-    } else {
-      if (grid > most) grid = most;
-      zero_counter_kernel<<<1, 1, 0, st>>>(a.counter);
+    const int grid = s.k_on_host && a.n_units > 16 ? 16 : a.n_units;
+    const int tokens = a.chunk_blocks * a.b;
+    size_t lds = lds_of(tokens, grid < a.n_units);
+    if (D == 128 && !s.k_on_host) {
+      const int kind = tokens == kCalibChunkTokens ? 0 : tokens == kCalibChunkTokens / 2 ? 1 : 2;
+      if (s.occ->calib_slots[kind] < 0) s.occ->calib_slots[kind] = resident_workgroups(calibrate_stream_kernel<D, G>, kAttnThreads, lds);
+      if (a.n_units > s.occ->calib_slots[kind] && lds < kCalibPairLds) lds = kCalibPairLds;
     }
     calibrate_stream_kernel<D, G><<<dim3(grid), kAttnThreads, lds, st>>>(a);
   } else {
-    auto lds_of = [&](int blocks) { return sizeof(float) * ((size_t)G * blocks * a.b + G * blocks + 2 * G + blocks); };
-    if (s.occ->calib_slots[0] < 0)       // (for the longest units: no more than the chip holds of any)
-      s.occ->calib_slots[0] = resident_workgroups(calibrate_f32_kernel<D, G>, kAttnThreads, lds_of(kCalibChunkTokens / a.b));
-    const int slots = s.occ->calib_slots[0] > 0 ? s.occ->calib_slots[0] : 2048;
-    a.n_units = a.n_chunks * s.n_inst;
-    if (a.n_units <= slots) a.counter = nullptr;         // (a workgroup each)
-    else zero_counter_kernel<<<1, 1, 0, st>>>(a.counter);
-    calibrate_f32_kernel<D, G><<<dim3(a.n_units < slots ? a.n_units : slots), kAttnThreads, lds_of(a.chunk_blocks), st>>>(a);
+    const size_t lds = sizeof(float) * ((size_t)G * a.chunk_blocks * a.b + G * a.chunk_blocks + 2 * G + a.chunk_blocks);
+    calibrate_f32_kernel<D, G><<<dim3(a.n_units), kAttnThreads, lds, st>>>(a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -709,13 +680,12 @@ hipError_t launch_calibrate(const Shape& s, const void* q, const void* K, int t_
   const WsLayout wl = ws_layout(s);
   CalibArgs a;
   a.q = q; a.K = K; a.row = row; a.cal_ml = ws + wl.cal_ml; a.cal_bmp = ws + wl.cal_bmp;
-  a.counter = reinterpret_cast<int*>(ws + wl.counters);
   a.t_cap = s.t_cap; a.nb_cap = s.nb_cap; a.b = s.b; a.log2b = ilog2(s.b); a.t_cur = t_cur;
   a.nb_cur = (t_cur + s.b - 1) / s.b;
   a.chunk_blocks = calib_chunk_tokens(s, t_cur) / s.b;
-  a.n_units = 0;
   a.ml_unit = kLog2E;
   a.n_chunks = (a.nb_cur + a.chunk_blocks - 1) / a.chunk_blocks;
+  a.n_units = a.n_chunks * s.n_inst;
   a.chunk_slots = s.calib_chunks;
   a.table = s.table; a.n_phys = s.n_phys;
   AP_DISPATCH(run_calib, s, a, st)

@@ -102,3 +102,32 @@ def test_fp32_units(n, g, d, b, lengths):
             ref = ref.view(g, cap // b, b).amax(dim=(0, 2))
             assert (row[i].double() - ref).abs().max() <= 2e-5 * ref.max(), (t, i)
     assert (ws[size:] == 255).all()
+
+
+@pytest.mark.parametrize("n,g,d,b,t", [
+    (5, 4, 128, 16, 20000), (17, 2, 64, 8, 257), (16, 1, 128, 64, 256), (9, 8, 128, 32, 4099), (70, 4, 128, 16, 17000),
+])
+def test_several_units_a_workgroup(n, g, d, b, t):
+    """K in pinned host memory: 16 workgroups go through several units each (25, two or three, one, ten, 75 of 1024 tokens), the largest logits in one
+    half of LDS or the other in turn.  Byte for byte what a workgroup per unit makes of the same K in device memory."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    cap = -(-t // b) * b + b
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=b, hist_len=8, t_cap=cap, k_blocks=1, n_sink=0, n_local=0, c1=4, c2=4, kv_dtype="bf16")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(t)
+    K = torch.randn((n, cap, d), generator=gen, device=dev).to(torch.bfloat16)
+    q = (2 * torch.randn((n, g, d), generator=gen, device=dev)).to(torch.bfloat16)
+    K_host = torch.empty(K.shape, dtype=K.dtype, pin_memory=True)
+    K_host.copy_(K)
+    ws = torch.full((max(16, ctx.workspace_bytes()),), 255, dtype=torch.uint8, device=dev)
+    rows = []
+    for k in (K_host, K):
+        rows.append(torch.full((n, cap // b), 7.0, device=dev))
+        ctx.calibrate(q, k, t, rows[-1], ws)
+    assert torch.equal(rows[0], rows[1])
+    p = torch.softmax(q[0].double() @ K[0, :t].double().T.contiguous() / math.sqrt(d), dim=1)
+    ref = torch.zeros((g, cap), dtype=torch.float64, device=dev)
+    ref[:, :t] = p
+    ref = ref.view(g, cap // b, b).amax(dim=(0, 2))
+    assert (rows[0][0].double() - ref).abs().max() <= 2e-5 * ref.max()
