@@ -42,9 +42,7 @@ struct Shape {
   const int32_t* table;  // device block table of a paged K/V cache [n_inst][nb_cap], or null (caller-owned)
   int n_phys;            // physical blocks in the pool
   bool k_on_host;        // launch_calibrate: K is pinned host memory
-  int* clear;            // counters of a decode's merges, one per instance: launches that have it (of the predictor, of an appended
-                         // row) set them to zero for the decode launch behind them; null: nothing to clear
-  bool cleared;          // launch_sparse_decode: a launch before it has done so
+  bool no_counters;      // launch_sparse_decode: the workspace ends with the split partials (the scratch of the no-allocation call)
   const float* select_by;   // launch_sparse_decode: scores to make the selection from first, into idx and cnt; null: it is there
 };
 
@@ -65,12 +63,17 @@ constexpr int kRowAll = 0, kRowTop = 1, kRowBot = 2, kRowOnly = 3;   // = (row =
 __host__ __device__ constexpr int delta_const_offset(int c1, int c2);
 __host__ __device__ constexpr int delta_const_floats(int c1, int c2) { return 2 * c1 + 8 * c2; }
 
+// Words that workgroups count in lie a cache line apart: additions to words of one line wait for each other (8 instances of 129 workgroups
+// each that count at the end of 10 us of work: in eight words of one line 36 us, in eight lines 18).  Only calls of few instances count.
+constexpr int kTicketStride = 16, kTicketInstances = 256;
+
 // Workspace carve-up (float offsets from ws).
 struct WsLayout {
   size_t part_ml;     // [n_inst][n_split][g][2]        split max / sum
   size_t part_acc;    // [n_inst][n_split][g][d]        split un-normalised output
   size_t part_bmp;    // [n_inst][g][k]                 per selected block: max prob relative to split max
-  size_t merge_count; // [n_inst] ints                  splits of an instance that have left their partials
+  size_t merge_count; // [n_inst][kTicketStride] 64-bit words, the first of each in use: splits of an instance that have
+                      //                                left their partials.  None with more than kTicketInstances instances
   size_t cal_ml;      // [n_inst][calib_chunks][g][2]
   size_t cal_bmp;     // [n_inst][g][nb_cap]
   size_t pred_state;  // [n_inst][nb_cap]               interior state of a full-tile prediction without a caller state
@@ -165,8 +168,11 @@ hipError_t launch_stream_read(const void* src, size_t bytes, void* sink, int n_w
 hipError_t launch_stream_copy(const void* src, size_t bytes, void* dst, int n_wg, hipStream_t st);
 hipError_t launch_push_row(const Shape& s, float* hist, int slot, const float* row, hipStream_t st);
 
+// A number for the upper bits of the counters of one launch, whose lower `bits` bits are zero; never zero, hardly ever the same twice.
+unsigned long long new_nonce(int bits);
+
 // Floats of workspace that launch_sparse_decode touches (the split partials, which lead the layout; the counters behind them only
-// where a launch before has cleared them).
+// where s.no_counters does not rule them out).
 size_t sparse_ws_floats(const Shape& s);
 // The current device's copy of the library's static scratch array (for callers that may not allocate) and its
 // size in bytes; looked up once per device.  Returns hipSuccess or the lookup error.

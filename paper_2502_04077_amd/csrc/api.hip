@@ -1,4 +1,6 @@
 // C ABI of the library: argument validation, context, workspace layout, launch sequencing.
+#include <atomic>
+#include <chrono>
 #include <new>
 #include <vector>
 
@@ -25,7 +27,7 @@ WsLayout ws_layout(const Shape& s) {
   w.part_ml = o;  o = align4(o + (size_t)s.n_inst * s.n_split * s.g * 2);
   w.part_acc = o; o = align4(o + (size_t)s.n_inst * s.n_split * s.g * s.d);
   w.part_bmp = o; o = align4(o + (size_t)s.n_inst * s.g * s.k);
-  w.merge_count = o; o = align4(o + (size_t)s.n_inst);
+  w.merge_count = o; o = align4(o + (s.n_inst <= kTicketInstances ? (size_t)s.n_inst * kTicketStride * 2 : 0));
   w.cal_ml = o;   o = align4(o + (size_t)s.n_inst * s.calib_chunks * s.g * 2);
   w.cal_bmp = o;  o = align4(o + (size_t)s.n_inst * s.g * s.nb_cap);
   w.pred_state = o; o = align4(o + (size_t)s.n_inst * s.nb_cap);
@@ -35,6 +37,17 @@ WsLayout ws_layout(const Shape& s) {
 
 // The split partials lead the layout; a context with one workgroup per instance has none.
 size_t sparse_ws_floats(const Shape& s) { return s.n_split > 1 ? ws_layout(s).merge_count : 0; }
+
+unsigned long long new_nonce(int bits) {
+  // (splitmix64 over a count of this process's launches, from a start that differs from process to process)
+  static std::atomic<unsigned long long> launches{(unsigned long long)std::chrono::system_clock::now().time_since_epoch().count() ^
+                                                  (unsigned long long)reinterpret_cast<uintptr_t>(&launches)};
+  unsigned long long z = launches.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  z = ((z ^ (z >> 31)) >> bits) << bits;
+  return z != 0 ? z : 1ull << bits;
+}
 
 static bool pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
 
@@ -99,7 +112,7 @@ int ap_create(const ap_config* c, ap_ctx** out) {
   s.n_sink = c->n_sink; s.n_local = c->n_local; s.c1 = c->c1; s.c2 = c->c2; s.kv_dtype = c->kv_dtype;
   s.predictor_mfma = (((c->c1 == 8 && c->c2 == 8) || (c->c1 == 16 && c->c2 == 32)) &&
                       !(c->flags & AP_FLAG_PREDICTOR_FP32)) ? 1 : 0;
-  s.clear = nullptr; s.cleared = false; s.select_by = nullptr;
+  s.no_counters = false; s.select_by = nullptr;
   s.n_split = ap::choose_split(s);
   {
     // Dynamic LDS of the attention workgroup (sparse_lds_floats) and of the combine kernel must fit 64 KiB.
@@ -356,9 +369,8 @@ static int newest_slot_of(const Shape& s, int64_t n_pushed) {
 
 // Runs the predictor in the requested mode; shared by ap_predict_incremental and ap_step.
 static int run_predictor(const ap_ctx* ctx, const float* hist, int64_t n_pushed, int nb_cur, int nb_prev, int mode,
-                         float* pstate, float* pred, float* ws, hipStream_t st, int* clear = nullptr) {
-  Shape s = ctx->s;
-  s.clear = clear;
+                         float* pstate, float* pred, float* ws, hipStream_t st) {
+  const Shape& s = ctx->s;
   const int newest = newest_slot_of(s, n_pushed);
   if (pstate == nullptr || mode == AP_PRED_REBASE || s.H < 6) {
     // (on MFMA the state is made in any case: in the workspace where the caller keeps none)
@@ -444,7 +456,8 @@ int ap_sparse_decode_noalloc(ap_ctx* ctx, const void* q, const void* K, const vo
   if (ctx == nullptr) return AP_ERR_ARG;
   AP_REQUIRE_PTR(q); AP_REQUIRE_PTR(K); AP_REQUIRE_PTR(V); AP_REQUIRE_PTR(idx); AP_REQUIRE_PTR(cnt);
   AP_REQUIRE_PTR(out); AP_REQUIRE_PTR(row);
-  const Shape& s = ctx->s;
+  Shape s = ctx->s;
+  s.no_counters = true;
   if (t_cur < 1 || t_cur > s.t_cap) return AP_ERR_RANGE;
   if (ap::sparse_ws_floats(s) * sizeof(float) > AP_NOALLOC_SCRATCH_BYTES) return AP_ERR_RANGE;
   float* ws = nullptr;
@@ -514,9 +527,7 @@ int ap_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, const voi
   hipStream_t st = static_cast<hipStream_t>(stream);
   Shape decode = s;
   if (pred_mode != AP_PRED_SKIP) {
-    int* counts = s.n_split > 1 ? reinterpret_cast<int*>(static_cast<float*>(ws) + ap::ws_layout(s).merge_count) : nullptr;
-    decode.cleared = counts != nullptr;
-    int rc = run_predictor(ctx, hist, n_pushed, nb_cur, nb_prev, pred_mode, pstate, pred, static_cast<float*>(ws), st, counts);
+    int rc = run_predictor(ctx, hist, n_pushed, nb_cur, nb_prev, pred_mode, pstate, pred, static_cast<float*>(ws), st);
     if (rc != AP_OK) return rc;
   }
   if (reuse) {
@@ -635,10 +646,8 @@ int ap_offload_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, c
   hipStream_t cs = static_cast<hipStream_t>(compute_stream), ps = static_cast<hipStream_t>(copy_stream);
   if (hipStreamWaitEvent(cs, ctx->ev_staged, 0) != hipSuccess) return AP_ERR_HIP;
   Shape paged = s;                       // the staged pools are a paged cache of n_inst * k blocks
-  if (s.n_split > 1) paged.clear = reinterpret_cast<int*>(static_cast<float*>(ws) + ap::ws_layout(s).merge_count);
   if (ap::launch_append_row(paged, k_new, v_new, t_cur - 1, block_table, state, pool_K, pool_V, cs) != hipSuccess)
     return AP_ERR_HIP;
-  paged.cleared = paged.clear != nullptr;
   paged.table = block_table;
   paged.n_phys = s.n_inst * s.k;
   float* slot_row = hist + (size_t)(n_pushed % s.R) * s.nb_cap;

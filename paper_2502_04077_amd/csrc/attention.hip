@@ -406,21 +406,24 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
   return hipGetLastError();
 }
 
-// Are the splits merged by the last workgroup of an instance to finish, or by a launch of their own?  By the last one where a
-// launch before has cleared the counters, which lie in the caller's workspace (one more launch for that would cost as much as the merge's own), and
+// Are the splits merged by the last workgroup of an instance to finish, or by a launch of their own?  By the last one where the workspace has counters, and
 //   - there are no more than two workgroups a CU, which are resident at once whatever LDS they have: in further rounds every workgroup holds its
 //     place until its partials have reached memory.  (513 to 1024 workgroups, steps in us, merged inside / by a launch: fp32, 1024 tokens, g = 8,
 //     d = 128, 60 instances 42.0 / 35.9, g = 4, 40 instances 26.0 / 24.5; bf16, g = 8, d = 64, 510 x 8192 tokens 231 / 214, g = 4, d = 128,
-//     350 x 8192 250 / 246, 510 x 16384 699 / 705.  640 instances of two splits, counters cleared by a launch, 121 -> 132.)
+//     350 x 8192 250 / 246, 510 x 16384 699 / 705.  fp32 without a selection inside, d = 128, one workgroup a CU: 1024 tokens, g = 4, 30 instances
+//     13.6 / 12.1, 3 instances 11.0 / 11.6.)
 //   - one workgroup has little to merge: few splits, and few sums in all.  (8 instances, fp32, g = 4, d = 128: 16 splits 19.4 / 21.9, 24 22.9 /
 //     22.2, 64 36.1 / 25.8; g = 1, 64 splits 29.0 / 22.1; bf16, d = 128, g = 4: 8 splits 16.2 / 20.1, 16 20.5 / 21.3, 20 23.1 / 22.0; 4 instances,
 //     g = 8, 12 splits 22.0 / 25.8, 16 24.3 / 23.5, 64 51.6 / 29.0.)
 // Fewer sums behind a selection that is a launch of its own, where the merge's launch finds the host ahead (g = 4, d = 128: 16 splits, 126
 // places, 16 instances 23.5 / 20.6, 8 instances 21.6 / 20.6, 4 splits, 128 instances, 35.5 / 36.5; g = 1, d = 64: 15 splits, 7 instances 22.0 / 23.2;
-// without a selection 16 splits, 8 instances 15.1 / 16.5).
+// without a selection 16 splits, 8 instances 15.1 / 16.5).  Single calls, us, by a launch / inside, bf16, d = 128: 8 instances x 1024 tokens, g = 4, 11.0 /
+// 8.7, 16 x 2048 14.3 / 10.4, 64 x 2048, g = 8, 22.6 / 19.3, 100 x 1024 16.6 / 14.4, 30 x 4096 15.7 / 15.4, 128 x 4096 49.6 / 48.6.
+static_assert(kMergeInsideSplits < 1 << kTicketBits, "a ticket each");
 constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288, kMergeBehindSelectSums = 4096;
+static_assert(2 * kTicketInstances >= kMergeInsideWorkgroups, "every instance in two splits or more has a word");
 bool merge_inside(const Shape& s, int ninst, int n_split, int most_sums = kMergeInsideSums) {
-  return s.cleared && n_split > 1 && n_split <= kMergeInsideSplits && n_split * s.g * s.d <= most_sums &&
+  return !s.no_counters && n_split > 1 && n_split <= kMergeInsideSplits && n_split * s.g * s.d <= most_sums &&
          (long)ninst * n_split <= kMergeInsideWorkgroups;
 }
 
@@ -552,7 +555,7 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
     }
   }
   if constexpr (std::is_same<T, float>::value)
-    if (merge_inside(s, ninst, a.n_split, a.pred && !inside ? kMergeBehindSelectSums : kMergeInsideSums)) {
+    if (merge_inside(s, ninst, a.n_split, a.pred && !inside ? kMergeBehindSelectSums : kMergeInsideSums) && (inside || D == 64 || ninst * a.n_split <= 256)) {
       if (inside) sparse_decode_kernel<T, D, G, kAttnWaves, false, kSelectInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_inside, st>>>(a);
       else sparse_decode_kernel<T, D, G, kAttnWaves, false, kMergeInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_of_form(a, lds, G, kMergeInside), st>>>(a);
       return hipGetLastError();
@@ -640,7 +643,8 @@ hipError_t launch_sparse_decode(const Shape& s, int inst0, int ninst, const void
   const WsLayout wl = ws_layout(s);
   SparseArgs a;
   a.q = q; a.K = K; a.V = V; a.idx = idx; a.cnt = cnt; a.out = out; a.row = row; a.row_stride = row_stride;
-  a.merge_count = reinterpret_cast<int*>(ws + wl.merge_count);
+  a.merge_count = reinterpret_cast<unsigned long long*>(ws + wl.merge_count);
+  a.merge_nonce = new_nonce(kTicketBits);
   a.part_ml = ws + wl.part_ml; a.part_acc = ws + wl.part_acc; a.part_bmp = ws + wl.part_bmp;
   a.t_cap = s.t_cap; a.nb_cap = s.nb_cap; a.k = s.k; a.b = s.b; a.log2b = ilog2(s.b); a.t_cur = t_cur;
   a.nb_cur = (t_cur + s.b - 1) / s.b;

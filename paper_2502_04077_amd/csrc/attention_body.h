@@ -349,7 +349,8 @@ struct SparseArgs {
   float ml_unit;                  // the splits' maxima times this are exponents of 2
   const float* pred;              // scores [n_inst][nb_cap] that the decode selects by itself (kSelectInside), writing idx and cnt
   int n_sink, n_local, sel_at;    // forced blocks; where in LDS (floats) the list goes: k blocks and their number
-  int* merge_count;               // [n_inst] splits that have left their partials, zero at launch (where they are merged inside)
+  unsigned long long* merge_count;  // [n_inst] splits that have left their partials (take_ticket), where they are merged inside
+  unsigned long long merge_nonce;
 };
 
 // What a decode launch does beside its own share: nothing; merging, by the last workgroup of an instance to finish;
@@ -387,13 +388,35 @@ template <bool SHARED> __device__ __forceinline__ void st_shared_out(float* p, f
 }
 __device__ __forceinline__ float ld_shared_out(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// Counting without a launch that clears the counter, in a word of the caller's workspace that may hold anything: its upper bits are a number
+// that the host draws anew for every launch (new_nonce), the lower kTicketBits the count.  Whoever is going to take a ticket first sees to it that the word carries the number
+// (begin_tickets, early, so that nobody waits for the answer: it is at zero where the last launch ended properly, and carries the number already where
+// another was faster); the one that gets the last ticket leaves it at zero (end_tickets), so that a captured launch, whose number stands still, starts afresh
+// on every replay.  What lies in a fresh workspace is taken for a count once in 2^52 words.  Called by one lane.
+constexpr int kTicketBits = 12;                         // (kMergeInsideSplits and more)
+__device__ __forceinline__ unsigned long long begin_tickets(unsigned long long* word, unsigned long long nonce) {
+  unsigned long long seen = 0ull;
+  __hip_atomic_compare_exchange_strong(word, &seen, nonce, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return seen;                                           // for take_ticket
+}
+__device__ __forceinline__ uint32_t take_ticket(unsigned long long* word, unsigned long long nonce, unsigned long long seen) {
+  // Neither zero nor this launch's: the word held something else.  It only ever changes from that to the number.
+  if (seen != 0ull && ((seen ^ nonce) >> kTicketBits) != 0ull)
+    __hip_atomic_compare_exchange_strong(word, &seen, nonce, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return (uint32_t)(__hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ((1ull << kTicketBits) - 1ull));
+}
+__device__ __forceinline__ void end_tickets(unsigned long long* word) { __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // Called by every thread of a workgroup that has left its partials of an instance: true in the last of n_split to get here.
 // s_last: an int of LDS that nothing else uses.
-__device__ __forceinline__ bool last_to_finish(int* count, int n_split, int* s_last) {
+__device__ __forceinline__ bool last_to_finish(unsigned long long* count, unsigned long long nonce, unsigned long long seen, int n_split, int* s_last) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's partials have reached memory
   __syncthreads();
-  if (threadIdx.x == 0)
-    *s_last = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_split - 1;
+  if (threadIdx.x == 0) {
+    const bool last = (int)take_ticket(count, nonce, seen) == n_split - 1;
+    if (last) end_tickets(count);
+    *s_last = last;
+  }
   __syncthreads();
   return *s_last != 0;
 }
@@ -569,6 +592,14 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
 #pragma unroll
     for (int e = 0; e < E; ++e) acc[h][e] = 0.f;
 
+  // (behind the first rows: answers come in order)
+  unsigned long long tickets = 0;
+  auto begin = [&]() __attribute__((always_inline)) {
+    if constexpr (MERGE)
+      if (threadIdx.x == 0 && !whole_row) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
+  };
+  if (nblk <= 0) begin();
+
   int p0 = 0, piece = 0;
   if (nblk > 0) do {
     const int nb_p = min(pb, nblk - p0);
@@ -599,6 +630,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
       }
     };
     if (kEarlyV && wave < ngroups) load_v(wave);
+    if (p0 == 0) begin();
     __syncthreads();
     softmax_stats<G, NW>(s_p, ld, ntok, a.b, nblk, s_m, s_l, s_bmp + p0, s_alpha);
     if (threadIdx.x < G) s_mpiece[piece * G + threadIdx.x] = s_m[threadIdx.x];
@@ -714,7 +746,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
       st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, s_bmp[pair]);
     }
     if constexpr (MERGE)
-      if (last_to_finish(a.merge_count + inst, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
+      if (last_to_finish(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
   }
 }
 
@@ -902,6 +934,9 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     load_k(next);
     load_v(next);
   }
+  unsigned long long tickets = 0;                        // (behind the rows: answers come in order)
+  if constexpr (MERGE)
+    if (threadIdx.x == 0 && !whole_row) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
 
   float m = -INFINITY, l = 0.f;                          // running statistics of this lane's head and row of 16 lanes
   float acc[G][E];
@@ -1103,7 +1138,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
       st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, block_max(h, jb));
     }
     if constexpr (MERGE)
-      if (last_to_finish(a.merge_count + inst, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
+      if (last_to_finish(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
   }
 }
 

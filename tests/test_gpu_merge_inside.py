@@ -137,3 +137,66 @@ def test_offload_step_clears_the_counters():
             assert torch.equal(a, b), s
     for run in runs:
         run.finish()
+
+
+@pytest.mark.parametrize("n,g,d,block,k,nb,dtype", [
+    (8, 4, 128, 16, 64, 300, "bf16"), (1, 8, 64, 8, 300, 400, "bf16"), (50, 8, 64, 16, 128, 130, "bf16"), (3, 4, 128, 16, 64, 90, "f32"),
+    (16, 2, 64, 16, 40, 90, "f32"), (4, 8, 128, 32, 200, 200, "bf16"), (256, 1, 128, 16, 512, 513, "bf16"),
+])
+def test_single_calls_count_in_any_workspace(n, g, d, block, k, nb, dtype):
+    """Single calls merge inside too, counting in words of the workspace that may hold anything - garbage, zeros, all ones, what the call before left -
+    and from a captured graph, whose launches count under the same number every time.  Against the call without counters, whose
+    merge is a launch of its own: the same bytes."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=block, hist_len=8, t_cap=nb * block, k_blocks=k, n_sink=0, n_local=0, c1=4, c2=4, kv_dtype=dtype)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n + k)
+    K, V = (torch.randn((n, nb * block, d), generator=gen, device=dev).to(dt) for _ in range(2))
+    q = torch.randn((n, g, d), generator=gen, device=dev).to(dt)
+    ref = torch.zeros((n, g, d), device=dev), torch.zeros((n, nb), device=dev)
+    got = torch.zeros((n, g, d), device=dev), torch.zeros((n, nb), device=dev)
+    size = ctx.workspace_bytes()
+    ws = torch.full((size + 4096,), 255, dtype=torch.uint8, device=dev)
+    idx = torch.zeros((n, k), dtype=torch.int32, device=dev)
+    cnt = torch.full((n,), k, dtype=torch.int32, device=dev)
+
+    def lists(i):
+        order = torch.rand((n, nb), generator=gen, device=dev).argsort(dim=1)[:, :k]
+        idx.copy_(order.sort(dim=1).values)
+        cnt.copy_(torch.tensor([k, 1, k // 2, 0][i % 4]).expand(n))
+
+    def fill(i):
+        for x in got:
+            x.fill_(7.0)
+        if i % 4 == 1:
+            ws[:size].random_(0, 256, generator=gen)
+        elif i % 4 == 2:
+            ws[:size].zero_()
+        elif i % 4 == 3:
+            ws[:size].fill_(255)
+
+    def check(what):
+        ctx.sparse_decode_noalloc(q, K, V, nb * block - 3, idx, cnt, *ref)
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), what
+
+    for i in range(9):
+        lists(i)
+        fill(i)
+        ctx.sparse_decode(q, K, V, nb * block - 3, idx, cnt, *got, ws)
+        check(i)
+    lists(0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.sparse_decode(q, K, V, nb * block - 3, idx, cnt, *got, ws)
+    for i in range(5):
+        lists(i)
+        fill(i)
+        if i == 2:
+            ctx.sparse_decode(q, K, V, nb * block - 3, idx, cnt, *got, ws)      # (a launch of the program's own in between)
+        graph.replay()
+        check(("replay", i))
+        torch.cuda.synchronize()
+    assert (ws[size:] == 255).all()
