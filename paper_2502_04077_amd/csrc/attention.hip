@@ -28,6 +28,22 @@ void sparse_stream_kernel(SparseArgs a) {
   sparse_stream_body<D, G, HOW>(a, a.inst0 + blockIdx.y, blockIdx.x, smem);
 }
 
+// The first n_whole instances by a workgroup each, those after them in a.n_split splits, whose workgroups come behind (mixed_splits).
+template <int D, int G>
+__global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(G <= 4 ? 4 : 3)))
+void sparse_mixed_kernel(SparseArgs a, int n_whole) {
+  extern __shared__ __align__(16) float smem[];
+  int inst = blockIdx.x, split = 0;
+  if (inst < n_whole) {
+    a.n_split = 1;
+  } else {
+    const int unit = inst - n_whole;
+    inst = n_whole + unit / a.n_split;
+    split = unit % a.n_split;
+  }
+  sparse_stream_body<D, G, kSplitsOnly>(a, a.inst0 + inst, split, smem);
+}
+
 // Brings the partial softmax statistics of one instance - ml[part * G + h] = (maximum, sum relative to it), part < n_part -
 // to factors scale[part * G + h] = exp2((m - M) unit) / L in LDS (0 for an empty part or an empty whole); unit is 1 where the
 // maxima are in units of log2, log2(e) for natural ones.  Every value is fetched by
@@ -76,10 +92,10 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_combine_kernel(SparseArgs
   extern __shared__ __align__(16) float smem[];
   const int inst = a.inst0 + blockIdx.y;
   float* s_scale = smem;                               // [n_split][G]  exp(m_s - M) / L
-  const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + (size_t)inst * a.n_split * G;
+  const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + (size_t)(inst - a.part_first) * a.n_split * G;
   if (blockIdx.x == 0) {
     merge_scales<G>(ml, a.n_split, a.ml_unit, s_scale);
-    const float* acc = a.part_acc + (size_t)inst * a.n_split * G * D;
+    const float* acc = a.part_acc + (size_t)(inst - a.part_first) * a.n_split * G * D;
     for (int o = threadIdx.x; o < G * D; o += kAttnThreads) {
       const int h = o / D;
       float v = 0.f;
@@ -479,6 +495,28 @@ template <int D> int stream_splits(const SparseArgs& a, int ninst, int g) {
   return best;
 }
 
+// Instances a little beyond a multiple of the CUs: that multiple goes a workgroup each, as many a CU, and only what is beyond it in splits, in one launch
+// with the long workgroups first.  Splitting every list alike leaves some CUs a share more than others, however short the shares, and merges all
+// instances.  Returns the splits of those beyond, 0 or 1 if all are to be treated alike.  They get one more workgroup a CU, two where they are a quarter of the CUs
+// or fewer, not more (600 instances x 2048 tokens, g = 8, 88 beyond: 111.2 us with two splits, 117.0 with three, 115.6 with five; 300 x 1024, g = 4, 44 beyond:
+// 32.3 with 11, 33.3 with five).  Not where half of the CUs would still be without one, or short lists make a merge of them cost more than the balance gives.
+// bf16, us, all alike / mixed: g = 8, d = 128, 2048 tokens, 264 instances 60.6 / 56.0, 320 67.9 / 63.3, 520 109.9 / 98.8, 640 123.3 / 117.3, 700 128.4 / 133.7 (not
+// taken), 800 162 / 144, 896 171 / 161; g = 4, 1024 tokens, 264 32.0 / 28.6, 540 55.6 / 52.1, 640 62.4 / 59.2, 350 36.1 / 39.4 (not taken); g = 2, 4096 tokens, 520
+// 186 / 173, 640 211 / 208; d = 64, g = 4, 4096 tokens, 520 108 / 91, 264 57.4 / 56.9, 2048 tokens, 280 33.0 / 35.4 (not taken); g = 1, 512 tokens, 560 27.2 / 28.1
+// (not taken).
+template <int D> int mixed_splits(const SparseArgs& a, int ninst, int g) {
+  constexpr int kCUs = 256;
+  const int n_whole = ninst / kCUs * kCUs, beyond = ninst - n_whole;
+  const long tokens = (long)a.k * a.b;
+  if (a.n_split < 2 || n_whole == 0 || beyond == 0 || beyond > (n_whole == kCUs ? kCUs / 4 : kCUs / 2) || (D == 64 && n_whole == kCUs)) return 0;
+  if (4 * D * tokens < 512 * 1024 || g * tokens > 40960) return 0;         // (the latter: a whole list's logits, as in stream_splits)
+  long splits = (beyond > kCUs / 4 ? kCUs : 2 * kCUs) / beyond;
+  if (splits > tokens / 128) splits = tokens / 128;                        // (two passes a wave)
+  if (splits > 64) splits = 64;
+  const long room = (long)a.n_split * ninst / beyond;                      // partials the workspace is laid out for
+  return (int)(splits < room ? splits : room);
+}
+
 template <int D, int G>
 hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   a.ml_unit = 1.f;
@@ -489,6 +527,23 @@ hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
     return sizeof(float) * sparse_stream_lds_floats<D, G>((a.k + splits - 1) / splits, a.b, splits == 1 ? a.nb_cap : 0);
   };
   while (want < a.n_split && lds_of(want) > 65536) ++want;
+  if (const int splits = mixed_splits<D>(a, ninst, G); splits > 1) {
+    SparseArgs m = a;
+    m.blk_per_split = (a.k + splits - 1) / splits;
+    m.n_split = (a.k + m.blk_per_split - 1) / m.blk_per_split;
+    const size_t lds_whole = lds_of(1), lds_split = lds_of(m.n_split), lds = lds_whole > lds_split ? lds_whole : lds_split;
+    if (m.n_split > 1 && lds <= 65536) {
+      const int beyond = ninst % 256, n_whole = ninst - beyond;
+      hipError_t e = select_first(s, ninst, m, st);
+      if (e != hipSuccess) return e;
+      m.part_first = m.inst0 + n_whole;
+      sparse_mixed_kernel<D, G><<<dim3(n_whole + beyond * m.n_split), kAttnThreads, lds, st>>>(m, n_whole);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      m.inst0 = m.part_first;
+      return run_combine<D, G>(beyond, m, st);
+    }
+  }
   a.blk_per_split = (a.k + want - 1) / want;
   a.n_split = (a.k + a.blk_per_split - 1) / a.blk_per_split;
   const dim3 grid(a.n_split, ninst);
@@ -651,6 +706,7 @@ hipError_t launch_sparse_decode(const Shape& s, int inst0, int ninst, const void
   a.n_split = s.n_split;
   a.blk_per_split = (s.k + s.n_split - 1) / s.n_split;
   a.inst0 = inst0;
+  a.part_first = 0;
   a.piece_blocks = s.k;
   a.ml_unit = kLog2E;
   a.table = s.table; a.n_phys = s.n_phys;
