@@ -28,7 +28,7 @@
  *     asks the runtime once how many of its workgroups the device holds at a time; it is a host query,
  *     nothing is enqueued for it, but make that first call outside a stream capture.
  *   - Calls that use one context or one workspace are issued in stream order on one stream: the workspace
- *     (partial results, the work counter of the calibration kernel) is shared by them.
+ *     (partial results, the counters of a merge) is shared by them.
  *   - All instances share one length t_cur per call.
  *   - Inputs must be finite; NaN scores give an unspecified (but in-range, duplicate-free) selection.
  */

@@ -66,7 +66,7 @@ def test_same_bytes(n, g, d, block, k, nb, dtype, hist):
 @pytest.mark.parametrize("hist", [16, 4])                # (below 6 every call evaluates the full tile)
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_every_predictor_clears_the_counters(c1, c2, fp32, hist, dtype):
-    """The counters of the merge lie in the workspace, and whichever predictor runs sets them to zero: all of its forms over a
+    """The counters of the merge lie in the workspace, and no predictor has to clear them: all of its forms over a
     workspace of garbage - re-base with and without a state of the caller's, advance, hold, a tile that grows - with selections made and reused."""
     import paper_2502_04077_amd as ap
     dev = torch.device("cuda:0")
@@ -107,7 +107,7 @@ def test_every_predictor_clears_the_counters(c1, c2, fp32, hist, dtype):
 
 
 def test_offload_step_clears_the_counters():
-    """The same where the launch of the appended row does it: offload steps over a workspace of garbage against the single calls."""
+    """The same behind an appended row: offload steps over a workspace of garbage against the single calls."""
     from paper_2502_04077_amd.offload import OffloadRun
     from test_gpu_parity import small
     from workloads import kv_cache, predictor_weights, queries
