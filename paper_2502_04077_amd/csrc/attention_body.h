@@ -521,6 +521,9 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
 
   constexpr bool MERGE = HOW != kSplitsOnly;
   int cnt;
+  unsigned long long tickets = 0;                        // (asked for before the selection, else behind the rows: answers come in order)
+  if constexpr (HOW == kSelectInside)
+    if (threadIdx.x == 0 && a.n_split > 1) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
   if constexpr (HOW == kSelectInside) cnt = select_inside(a, inst, split, smem); else cnt = min(max(a.cnt[inst], 0), a.k);
   const int32_t* list = HOW == kSelectInside ? reinterpret_cast<const int32_t*>(smem + a.sel_at) : a.idx + (size_t)inst * a.k;
   auto listed = [&](int jb) __attribute__((always_inline)) { return min(max(list[jb], 0), a.nb_cur - 1); };
@@ -594,9 +597,8 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
     for (int e = 0; e < E; ++e) acc[h][e] = 0.f;
 
   // (behind the first rows: answers come in order)
-  unsigned long long tickets = 0;
   auto begin = [&]() __attribute__((always_inline)) {
-    if constexpr (MERGE)
+    if constexpr (HOW == kMergeInside)
       if (threadIdx.x == 0 && !whole_row) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
   };
   if (nblk <= 0) begin();
@@ -836,6 +838,9 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
 
   constexpr bool MERGE = HOW != kSplitsOnly;
   int cnt;
+  unsigned long long tickets = 0;                        // (asked for before the selection, else behind the rows: answers come in order)
+  if constexpr (HOW == kSelectInside)
+    if (threadIdx.x == 0 && a.n_split > 1) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
   if constexpr (HOW == kSelectInside) cnt = select_inside(a, inst, split, smem); else cnt = min(max(a.cnt[inst], 0), a.k);
   const int32_t* list = HOW == kSelectInside ? reinterpret_cast<const int32_t*>(smem + a.sel_at) : a.idx + (size_t)inst * a.k;
   auto listed = [&](int jb) __attribute__((always_inline)) { return min(max(list[jb], 0), a.nb_cur - 1); };
@@ -935,8 +940,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     load_k(next);
     load_v(next);
   }
-  unsigned long long tickets = 0;                        // (behind the rows: answers come in order)
-  if constexpr (MERGE)
+  if constexpr (HOW == kMergeInside)
     if (threadIdx.x == 0 && !whole_row) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
 
   float m = -INFINITY, l = 0.f;                          // running statistics of this lane's head and row of 16 lanes
