@@ -42,6 +42,9 @@ struct Shape {
   const int32_t* table;  // device block table of a paged K/V cache [n_inst][nb_cap], or null (caller-owned)
   int n_phys;            // physical blocks in the pool
   bool k_on_host;        // launch_calibrate: K is pinned host memory
+  unsigned long long* clear;  // counters of a decode's merges (WsLayout::merge_count): launches that have it (of the predictor, of an appended
+                         // row) set them to zero for the decode launch behind them; null: nothing to clear
+  bool cleared;          // launch_sparse_decode: a launch before it has done so
   bool no_counters;      // launch_sparse_decode: the workspace ends with the split partials (the scratch of the no-allocation call)
   const float* select_by;   // launch_sparse_decode: scores to make the selection from first, into idx and cnt; null: it is there
 };

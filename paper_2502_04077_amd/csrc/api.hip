@@ -112,7 +112,7 @@ int ap_create(const ap_config* c, ap_ctx** out) {
   s.n_sink = c->n_sink; s.n_local = c->n_local; s.c1 = c->c1; s.c2 = c->c2; s.kv_dtype = c->kv_dtype;
   s.predictor_mfma = (((c->c1 == 8 && c->c2 == 8) || (c->c1 == 16 && c->c2 == 32)) &&
                       !(c->flags & AP_FLAG_PREDICTOR_FP32)) ? 1 : 0;
-  s.no_counters = false; s.select_by = nullptr;
+  s.clear = nullptr; s.cleared = false; s.no_counters = false; s.select_by = nullptr;
   s.n_split = ap::choose_split(s);
   {
     // Dynamic LDS of the attention workgroup (sparse_lds_floats) and of the combine kernel must fit 64 KiB.
@@ -367,10 +367,17 @@ static int newest_slot_of(const Shape& s, int64_t n_pushed) {
   return n_pushed <= 0 ? s.R - 1 : (int)((n_pushed - 1) % s.R);
 }
 
+// The counters of a decode's merges in the workspace, for the launch before it to clear; null where there are none.
+static unsigned long long* merge_counters(const Shape& s, void* ws) {
+  if (s.n_split < 2 || s.n_inst > ap::kTicketInstances) return nullptr;
+  return reinterpret_cast<unsigned long long*>(static_cast<float*>(ws) + ap::ws_layout(s).merge_count);
+}
+
 // Runs the predictor in the requested mode; shared by ap_predict_incremental and ap_step.
 static int run_predictor(const ap_ctx* ctx, const float* hist, int64_t n_pushed, int nb_cur, int nb_prev, int mode,
-                         float* pstate, float* pred, float* ws, hipStream_t st) {
-  const Shape& s = ctx->s;
+                         float* pstate, float* pred, float* ws, hipStream_t st, unsigned long long* clear = nullptr) {
+  Shape s = ctx->s;
+  s.clear = clear;
   const int newest = newest_slot_of(s, n_pushed);
   if (pstate == nullptr || mode == AP_PRED_REBASE || s.H < 6) {
     // (on MFMA the state is made in any case: in the workspace where the caller keeps none)
@@ -527,7 +534,9 @@ int ap_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, const voi
   hipStream_t st = static_cast<hipStream_t>(stream);
   Shape decode = s;
   if (pred_mode != AP_PRED_SKIP) {
-    int rc = run_predictor(ctx, hist, n_pushed, nb_cur, nb_prev, pred_mode, pstate, pred, static_cast<float*>(ws), st);
+    unsigned long long* counters = merge_counters(s, ws);
+    decode.cleared = counters != nullptr;
+    int rc = run_predictor(ctx, hist, n_pushed, nb_cur, nb_prev, pred_mode, pstate, pred, static_cast<float*>(ws), st, counters);
     if (rc != AP_OK) return rc;
   }
   if (reuse) {
@@ -646,8 +655,10 @@ int ap_offload_step(ap_ctx* ctx, float* hist, int64_t n_pushed, const void* q, c
   hipStream_t cs = static_cast<hipStream_t>(compute_stream), ps = static_cast<hipStream_t>(copy_stream);
   if (hipStreamWaitEvent(cs, ctx->ev_staged, 0) != hipSuccess) return AP_ERR_HIP;
   Shape paged = s;                       // the staged pools are a paged cache of n_inst * k blocks
+  paged.clear = merge_counters(s, ws);
   if (ap::launch_append_row(paged, k_new, v_new, t_cur - 1, block_table, state, pool_K, pool_V, cs) != hipSuccess)
     return AP_ERR_HIP;
+  paged.cleared = paged.clear != nullptr;
   paged.table = block_table;
   paged.n_phys = s.n_inst * s.k;
   float* slot_row = hist + (size_t)(n_pushed % s.R) * s.nb_cap;

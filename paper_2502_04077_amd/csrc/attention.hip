@@ -699,7 +699,7 @@ hipError_t launch_sparse_decode(const Shape& s, int inst0, int ninst, const void
   SparseArgs a;
   a.q = q; a.K = K; a.V = V; a.idx = idx; a.cnt = cnt; a.out = out; a.row = row; a.row_stride = row_stride;
   a.merge_count = reinterpret_cast<unsigned long long*>(ws + wl.merge_count);
-  a.merge_nonce = new_nonce(kTicketBits);
+  a.merge_nonce = s.cleared ? 0 : new_nonce(kTicketBits);
   a.part_ml = ws + wl.part_ml; a.part_acc = ws + wl.part_acc; a.part_bmp = ws + wl.part_bmp;
   a.t_cap = s.t_cap; a.nb_cap = s.nb_cap; a.k = s.k; a.b = s.b; a.log2b = ilog2(s.b); a.t_cur = t_cur;
   a.nb_cur = (t_cur + s.b - 1) / s.b;

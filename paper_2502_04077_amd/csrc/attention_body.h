@@ -351,7 +351,7 @@ struct SparseArgs {
   const float* pred;              // scores [n_inst][nb_cap] that the decode selects by itself (kSelectInside), writing idx and cnt
   int n_sink, n_local, sel_at;    // forced blocks; where in LDS (floats) the list goes: k blocks and their number
   unsigned long long* merge_count;  // [n_inst] splits that have left their partials (take_ticket), where they are merged inside
-  unsigned long long merge_nonce;
+  unsigned long long merge_nonce;   // number of this launch in them; 0: they are zero at launch
 };
 
 // What a decode launch does beside its own share: nothing; merging, by the last workgroup of an instance to finish;
@@ -394,6 +394,8 @@ __device__ __forceinline__ float ld_shared_out(const float* p) { return __hip_at
 // (begin_tickets, early, so that nobody waits for the answer: it is at zero where the last launch ended properly, and carries the number already where
 // another was faster); the one that gets the last ticket leaves it at zero (end_tickets), so that a captured launch, whose number stands still, starts afresh
 // on every replay.  What lies in a fresh workspace is taken for a count once in 2^52 words.  Called by one lane.
+// A launch behind one that has cleared the words (of the predictor, of an appended row) has the number zero and only counts; one that makes the selection
+// too always is, and has no code for more.
 constexpr int kTicketBits = 12;                         // (kMergeInsideSplits and more)
 __device__ __forceinline__ unsigned long long begin_tickets(unsigned long long* word, unsigned long long nonce) {
   unsigned long long seen = 0ull;
@@ -409,14 +411,19 @@ __device__ __forceinline__ uint32_t take_ticket(unsigned long long* word, unsign
 __device__ __forceinline__ void end_tickets(unsigned long long* word) { __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // Called by every thread of a workgroup that has left its partials of an instance: true in the last of n_split to get here.
-// s_last: an int of LDS that nothing else uses.
+// TICKETS: as above; without, the word is zero at launch in any case.  s_last: an int of LDS that nothing else uses.
+template <bool TICKETS>
 __device__ __forceinline__ bool last_to_finish(unsigned long long* count, unsigned long long nonce, unsigned long long seen, int n_split, int* s_last) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's partials have reached memory
   __syncthreads();
   if (threadIdx.x == 0) {
-    const bool last = (int)take_ticket(count, nonce, seen) == n_split - 1;
-    if (last) end_tickets(count);
-    *s_last = last;
+    if constexpr (TICKETS) {
+      const bool last = (int)take_ticket(count, nonce, seen) == n_split - 1;
+      if (last && nonce != 0) end_tickets(count);
+      *s_last = last;
+    } else {
+      *s_last = __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(count), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(n_split - 1);
+    }
   }
   __syncthreads();
   return *s_last != 0;
@@ -521,9 +528,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
 
   constexpr bool MERGE = HOW != kSplitsOnly;
   int cnt;
-  unsigned long long tickets = 0;                        // (asked for before the selection, else behind the rows: answers come in order)
-  if constexpr (HOW == kSelectInside)
-    if (threadIdx.x == 0 && a.n_split > 1) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
+  unsigned long long tickets = 0;                        // (asked for behind the first rows: answers come in order)
   if constexpr (HOW == kSelectInside) cnt = select_inside(a, inst, split, smem); else cnt = min(max(a.cnt[inst], 0), a.k);
   const int32_t* list = HOW == kSelectInside ? reinterpret_cast<const int32_t*>(smem + a.sel_at) : a.idx + (size_t)inst * a.k;
   auto listed = [&](int jb) __attribute__((always_inline)) { return min(max(list[jb], 0), a.nb_cur - 1); };
@@ -599,7 +604,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
   // (behind the first rows: answers come in order)
   auto begin = [&]() __attribute__((always_inline)) {
     if constexpr (HOW == kMergeInside)
-      if (threadIdx.x == 0 && !whole_row) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
+      if (threadIdx.x == 0 && !whole_row && a.merge_nonce != 0) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
   };
   if (nblk <= 0) begin();
 
@@ -749,7 +754,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
       st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, s_bmp[pair]);
     }
     if constexpr (MERGE)
-      if (last_to_finish(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
+      if (last_to_finish<HOW == kMergeInside>(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
   }
 }
 
@@ -838,9 +843,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
 
   constexpr bool MERGE = HOW != kSplitsOnly;
   int cnt;
-  unsigned long long tickets = 0;                        // (asked for before the selection, else behind the rows: answers come in order)
-  if constexpr (HOW == kSelectInside)
-    if (threadIdx.x == 0 && a.n_split > 1) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
+  unsigned long long tickets = 0;                        // (asked for behind the first rows: answers come in order)
   if constexpr (HOW == kSelectInside) cnt = select_inside(a, inst, split, smem); else cnt = min(max(a.cnt[inst], 0), a.k);
   const int32_t* list = HOW == kSelectInside ? reinterpret_cast<const int32_t*>(smem + a.sel_at) : a.idx + (size_t)inst * a.k;
   auto listed = [&](int jb) __attribute__((always_inline)) { return min(max(list[jb], 0), a.nb_cur - 1); };
@@ -941,7 +944,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     load_v(next);
   }
   if constexpr (HOW == kMergeInside)
-    if (threadIdx.x == 0 && !whole_row) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
+    if (threadIdx.x == 0 && !whole_row && a.merge_nonce != 0) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
 
   float m = -INFINITY, l = 0.f;                          // running statistics of this lane's head and row of 16 lanes
   float acc[G][E];
@@ -1143,7 +1146,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
       st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, block_max(h, jb));
     }
     if constexpr (MERGE)
-      if (last_to_finish(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
+      if (last_to_finish<HOW == kMergeInside>(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
   }
 }
 

@@ -41,7 +41,8 @@ __global__ __launch_bounds__(kPredThreads) void predict_full_kernel(const float*
                                                                     int H, int newest_slot, int nb_cur, int nb_cap,
                                                                     int inst0, int col_begin,
                                                                     float* __restrict__ pstate,
-                                                                    float* __restrict__ pred) {
+                                                                    float* __restrict__ pred,
+                                                                    unsigned long long* __restrict__ clear) {
   extern __shared__ __align__(16) float smem[];
   float* s_x = smem;                        // [kXR][kXW]
   float* s_y1 = s_x + kXR * kXW;            // [C1][kYR][kYW]
@@ -49,6 +50,7 @@ __global__ __launch_bounds__(kPredThreads) void predict_full_kernel(const float*
   const Weights<C1, C2> W(wts_global);
 
   const int inst = inst0 + blockIdx.y;
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clear[(size_t)inst * kTicketStride] = 0ull;
   const int c0 = col_begin + blockIdx.x * kTW;   // first output column of this tile
   const int tid = threadIdx.x;
   const int col = tid & (kTW - 1);
@@ -212,7 +214,7 @@ __global__ __launch_bounds__(2 * IW) void predict_inc_kernel(const float* __rest
                                                              const float* __restrict__ wts_global, int R, int H,
                                                              int newest_slot, int nb_cur, int nb_cap, int inst0,
                                                              int advance, float* __restrict__ pstate,
-                                                             float* __restrict__ pred) {
+                                                             float* __restrict__ pred, unsigned long long* __restrict__ clear) {
   constexpr int XW = IW + 4, YW = IW + 2, NT = 2 * IW;
   extern __shared__ __align__(16) float smem[];
   float* s_y1 = smem;                       // [2][4][C1][YW]
@@ -221,6 +223,7 @@ __global__ __launch_bounds__(2 * IW) void predict_inc_kernel(const float* __rest
   const Weights<C1, C2> W(wts_global);
 
   const int inst = inst0 + blockIdx.y;
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clear[(size_t)inst * kTicketStride] = 0ull;
   const int c0 = blockIdx.x * IW;
   const int tid = threadIdx.x;
   stage_x_rows<XW, NT / kWave>(s_x, hist + (size_t)inst * R * nb_cap, newest_slot, H, R, nb_cap, nb_cur, c0);
@@ -270,8 +273,10 @@ __global__ __launch_bounds__(2 * IW) void predict_inc_kernel(const float* __rest
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))   // four workgroups per CU: 128 VGPRs
 void predict_inc_mfma_kernel(const float* __restrict__ hist, const float* __restrict__ wts_global, int R, int H,
                              int newest_slot, int nb_cur, int nb_cap, int inst0, PassPlan plan, int advance,
-                             float* __restrict__ pstate, float* __restrict__ pred) {
+                             float* __restrict__ pstate, float* __restrict__ pred, unsigned long long* __restrict__ clear, int ninst) {
   extern __shared__ __align__(16) float smem[];
+  if (clear != nullptr)                                  // (a workgroup may have a part of an instance, or several)
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < ninst; i += gridDim.x * 256) clear[(size_t)(inst0 + i) * kTicketStride] = 0ull;
   predict_inc_reg_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0, plan, advance, pstate, pred,
                        smem);
 }
@@ -279,8 +284,10 @@ void predict_inc_mfma_kernel(const float* __restrict__ hist, const float* __rest
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))   // two workgroups per CU: 256 VGPRs
 void predict_inc_mfma16_kernel(const float* __restrict__ hist, const float* __restrict__ wts_global, int R, int H,
                                int newest_slot, int nb_cur, int nb_cap, int inst0, PassPlan plan, int advance,
-                               float* __restrict__ pstate, float* __restrict__ pred) {
+                               float* __restrict__ pstate, float* __restrict__ pred, unsigned long long* __restrict__ clear, int ninst) {
   extern __shared__ __align__(16) float smem[];
+  if (clear != nullptr)                                  // (a workgroup may have a part of an instance, or several)
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < ninst; i += gridDim.x * 256) clear[(size_t)(inst0 + i) * kTicketStride] = 0ull;
   predict_inc_mfma16_body(hist, wts_global, R, H, newest_slot, nb_cur, nb_cap, inst0, plan, advance, pstate, pred, smem);
 }
 
@@ -394,7 +401,7 @@ hipError_t run_full(const Shape& s, int inst0, int ninst, const float* dweights,
   const size_t lds = sizeof(float) * (kXR * kXW + (size_t)C1 * kYR * kYW);
   const dim3 grid((nb_cur - col_begin + kTW - 1) / kTW, ninst);
   predict_full_kernel<C1, C2><<<grid, kPredThreads, lds, st>>>(hist, dweights, s.R, s.H, newest_slot, nb_cur,
-                                                              s.nb_cap, inst0, col_begin, pstate, pred);
+                                                              s.nb_cap, inst0, col_begin, pstate, pred, s.clear);
   return hipGetLastError();
 }
 
@@ -437,7 +444,7 @@ hipError_t run_inc(const Shape& s, int inst0, int ninst, const float* dweights, 
     const PassPlan plan = plan_passes(ninst, nb_cur, kRiPassCols, 112, 1024);
     const int grid = plan.total < 1024 ? plan.total : 1024;
     predict_inc_mfma_kernel<<<dim3(grid), 256, lds, st>>>(hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan,
-                                                          advance, pstate, pred);
+                                                          advance, pstate, pred, s.clear, ninst);
     return hipGetLastError();
   }
   if (C1 == 16 && C2 == 32 && s.predictor_mfma) {
@@ -449,13 +456,13 @@ hipError_t run_inc(const Shape& s, int inst0, int ninst, const float* dweights, 
     }
     const int grid = plan.total < 512 ? plan.total : 512;
     predict_inc_mfma16_kernel<<<dim3(grid), 256, lds, st>>>(hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, plan, advance,
-                                                            pstate, pred);
+                                                            pstate, pred, s.clear, ninst);
     return hipGetLastError();
   }
   constexpr int IW = C1 <= 8 ? 128 : 64;
   const size_t lds = sizeof(float) * (2 * 4 * (size_t)C1 * (IW + 2) + 2 * 5 * (IW + 4) + 4 * IW);
   predict_inc_kernel<C1, C2, IW><<<dim3((nb_cur + IW - 1) / IW, ninst), 2 * IW, lds, st>>>(
-      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, advance, pstate, pred);
+      hist, dweights, s.R, s.H, newest_slot, nb_cur, s.nb_cap, inst0, advance, pstate, pred, s.clear);
   return hipGetLastError();
 }
 

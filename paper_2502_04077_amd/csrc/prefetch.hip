@@ -111,15 +111,17 @@ __global__ __launch_bounds__(kGatherThreads) void gather_blocks_kernel(
   }
 }
 
-// One new token row per instance, written into the staged copy of block t_pos / b if that block is staged.
+// One new token row per instance, written into the staged copy of block t_pos / b if that block is staged.  Also clears the
+// instance's counter of the decode launch that follows (clear may be null).
 __global__ __launch_bounds__(kWave) void append_row_kernel(const uint4* __restrict__ k_new,
                                                            const uint4* __restrict__ v_new,
                                                            const int32_t* __restrict__ table,
                                                            const int32_t* __restrict__ state,
                                                            uint4* __restrict__ pool_K, uint4* __restrict__ pool_V,
                                                            int k, int nb_cap, int state_stride, int b, int row_units,
-                                                           int t_pos) {
+                                                           int t_pos, unsigned long long* __restrict__ clear) {
   const int inst = blockIdx.x;
+  if (clear != nullptr && threadIdx.x == 0) clear[(size_t)inst * kTicketStride] = 0ull;
   const int blk = t_pos / b;
   const int sl = table[(size_t)inst * nb_cap + blk] - inst * k;
   if (sl < 0 || sl >= k || state[(size_t)inst * state_stride + sl] != blk + 1) return;
@@ -155,7 +157,7 @@ hipError_t launch_append_row(const Shape& s, const void* k_new, const void* v_ne
   append_row_kernel<<<dim3(s.n_inst), kWave, 0, st>>>(static_cast<const uint4*>(k_new), static_cast<const uint4*>(v_new),
                                                      table, state, static_cast<uint4*>(pool_K),
                                                      static_cast<uint4*>(pool_V), s.k, s.nb_cap,
-                                                     prefetch_state_stride(s), s.b, row_units, t_pos);
+                                                     prefetch_state_stride(s), s.b, row_units, t_pos, s.clear);
   return hipGetLastError();
 }
 
