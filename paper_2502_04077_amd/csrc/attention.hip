@@ -427,7 +427,7 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 //     place until its partials have reached memory.  (513 to 1024 workgroups, steps in us, merged inside / by a launch: fp32, 1024 tokens, g = 8,
 //     d = 128, 60 instances 42.0 / 35.9, g = 4, 40 instances 26.0 / 24.5; bf16, g = 8, d = 64, 510 x 8192 tokens 231 / 214, g = 4, d = 128,
 //     350 x 8192 250 / 246, 510 x 16384 699 / 705.  fp32 without a selection inside, d = 128, one workgroup a CU: 1024 tokens, g = 4, 30 instances
-//     13.6 / 12.1, 3 instances 11.0 / 11.6.)
+//     13.6 / 12.1, 3 instances 11.0 / 11.6.  d = 64 has half the LDS: most_sums has its figures.)
 //   - one workgroup has little to merge: few splits, and few sums in all.  (8 instances, fp32, g = 4, d = 128: 16 splits 19.4 / 21.9, 24 22.9 /
 //     22.2, 64 36.1 / 25.8; g = 1, 64 splits 29.0 / 22.1; bf16, d = 128, g = 4: 8 splits 16.2 / 20.1, 16 20.5 / 21.3, 20 23.1 / 22.0; 4 instances,
 //     g = 8, 12 splits 22.0 / 25.8, 16 24.3 / 23.5, 64 51.6 / 29.0.)
@@ -436,11 +436,23 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 // without a selection 16 splits, 8 instances 15.1 / 16.5).  Single calls, us, by a launch / inside, bf16, d = 128: 8 instances x 1024 tokens, g = 4, 11.0 /
 // 8.7, 16 x 2048 14.3 / 10.4, 64 x 2048, g = 8, 22.6 / 19.3, 100 x 1024 16.6 / 14.4, 30 x 4096 15.7 / 15.4, 128 x 4096 49.6 / 48.6.
 static_assert(kMergeInsideSplits < 1 << kTicketBits, "a ticket each");
-constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288, kMergeBehindSelectSums = 4096;
+constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288, kMergeFewSums = 4096;
 static_assert(2 * kTicketInstances >= kMergeInsideWorkgroups, "every instance in two splits or more has a word");
 bool merge_inside(const Shape& s, int ninst, int n_split, int most_sums = kMergeInsideSums) {
   return !s.no_counters && n_split > 1 && n_split <= kMergeInsideSplits && n_split * s.g * s.d <= most_sums &&
          (long)ninst * n_split <= kMergeInsideWorkgroups;
+}
+
+// Most sums that a launch without a selection of its own merges inside: a.pred tells whether a selection's launch is in front.  In a single call 16 splits
+// with many sums are left to the merge's launch, which takes eight splits at a time and is slow only on a remainder, unless the decode is over before the
+// host has the second launch ready.  (us, by a launch / inside.  bf16, d = 128, g = 4, 16 splits: 16 instances x 2048 tokens 11.5 / 9.9, 3072 11.7 / 10.9,
+// 4096 11.4 / 11.8, 8192 15.8 / 17.0; d = 64, g = 8: 30 x 2048 11.5 / 12.0, 32 x 8192 18.9 / 19.7; fp32, d = 64, g = 8, 1024 tokens: 8 instances 11.0 / 11.7,
+// 32 13.0 / 13.6; d = 128, g = 4: 8 instances 11.3 / 11.1, 10.8 / 11.0.  12 splits: bf16, 20 x 8192, g = 4, 20.6 / 19.9, g = 8 26.6 / 25.3; d = 64, g = 8, 40 x 4096 17.5 /
+// 16.0; fp32, d = 64, g = 8, 768 tokens, 8 12.9 / 11.4, 32 14.8 / 13.0.)
+constexpr int kMergeLaunchTokens = 3072;
+int most_sums(const Shape& s, const SparseArgs& a) {
+  const bool host_behind = s.kv_dtype == AP_BF16 && s.d == 128 && a.k * a.b <= kMergeLaunchTokens;
+  return a.pred != nullptr || (!s.cleared && a.n_split == kMergeInsideSplits && !host_behind) ? kMergeFewSums : kMergeInsideSums;
 }
 
 // Does the streaming decode (and the fp32 one in splits) make the selection too?  Every workgroup of an instance makes all of it, which is
@@ -451,7 +463,7 @@ bool merge_inside(const Shape& s, int ninst, int n_split, int most_sums = kMerge
 constexpr int kRankedSplits = 8;
 bool select_here(const Shape& s, int ninst, int n_split, int nb_cur) {
   const int n_mid = nb_cur - s.n_sink - s.n_local, k_mid = s.k - s.n_sink - s.n_local;
-  return (n_split == 1 || merge_inside(s, ninst, n_split)) && (long)ninst * n_split <= kMergeInsideWorkgroups &&
+  return (n_split == 1 || (s.cleared && merge_inside(s, ninst, n_split))) && (long)ninst * n_split <= kMergeInsideWorkgroups &&
          n_mid <= kSelectInsideKeys * kSelThreads && k_mid >= 1 && k_mid <= (n_split <= kRankedSplits ? kSelMaxMid : kSelFewMid);
 }
 
@@ -556,7 +568,7 @@ hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   }
   hipError_t e = select_first(s, ninst, a, st);
   if (e != hipSuccess) return e;
-  if (merge_inside(s, ninst, a.n_split, a.pred ? kMergeBehindSelectSums : kMergeInsideSums)) {
+  if (merge_inside(s, ninst, a.n_split, most_sums(s, a))) {
     const size_t lds = lds_of_form(a, lds_of(want), G, kMergeInside);
     sparse_stream_kernel<D, G, kMergeInside><<<grid, kAttnThreads, lds, st>>>(a);
     return hipGetLastError();
@@ -610,7 +622,7 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
     }
   }
   if constexpr (std::is_same<T, float>::value)
-    if (merge_inside(s, ninst, a.n_split, a.pred && !inside ? kMergeBehindSelectSums : kMergeInsideSums) && (inside || D == 64 || ninst * a.n_split <= 256)) {
+    if (inside || (merge_inside(s, ninst, a.n_split, most_sums(s, a)) && (D == 64 || ninst * a.n_split <= 256))) {
       if (inside) sparse_decode_kernel<T, D, G, kAttnWaves, false, kSelectInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_inside, st>>>(a);
       else sparse_decode_kernel<T, D, G, kAttnWaves, false, kMergeInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_of_form(a, lds, G, kMergeInside), st>>>(a);
       return hipGetLastError();

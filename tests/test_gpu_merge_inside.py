@@ -146,6 +146,31 @@ def test_fused_step_only_adds(n, g, d, block, k, nb, dtype, c1, c2):
         assert bool((at.diff() == 16).all()), i
 
 
+@pytest.mark.parametrize("n,g,d,block,k,dtype,inside", [
+    (16, 4, 128, 16, 192, "bf16", True), (16, 4, 128, 16, 208, "bf16", False),       # 16 splits of many sums: short lists, and longer ones
+    (17, 4, 128, 16, 256, "bf16", True), (16, 2, 128, 16, 256, "bf16", True),         # 15 splits; 16 of few sums
+    (32, 8, 64, 16, 128, "bf16", False), (33, 8, 64, 16, 128, "bf16", True), (20, 8, 128, 16, 128, "bf16", True),
+    (8, 8, 64, 16, 64, "f32", False), (8, 8, 64, 16, 60, "f32", True), (8, 4, 64, 16, 64, "f32", True), (64, 4, 128, 16, 16, "f32", True),
+    (65, 4, 128, 16, 16, "f32", False), (128, 4, 64, 16, 16, "f32", True), (129, 4, 64, 16, 16, "f32", False),
+])
+def test_single_call_forms(n, g, d, block, k, dtype, inside):
+    """Which single calls merge inside the decode, and that the others leave the counters alone."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=block, hist_len=8, t_cap=k * block, k_blocks=k, n_sink=0, n_local=0, c1=4, c2=4, kv_dtype=dtype)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K, V = (torch.randn((n, k * block, d), device=dev).to(dt) for _ in range(2))
+    q = torch.randn((n, g, d), device=dev).to(dt)
+    idx, cnt = torch.arange(k, dtype=torch.int32, device=dev).repeat(n, 1), torch.full((n,), k, dtype=torch.int32, device=dev)
+    got, ref = ([torch.zeros((n, g, d), device=dev), torch.zeros((n, k), device=dev)] for _ in range(2))
+    ws = torch.full((ctx.workspace_bytes(),), FILL, dtype=torch.uint8, device=dev)
+    ctx.sparse_decode(q, K, V, k * block - 3, idx, cnt, *got, ws)
+    at, held = lone_words(ws)
+    assert int((held == 0).sum()) == (n if inside else 0)
+    ctx.sparse_decode_noalloc(q, K, V, k * block - 3, idx, cnt, *ref)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+
+
 def test_offload_step_clears_the_counters():
     """The same where the launch of the appended row does it: offload steps over a workspace of garbage against the single calls."""
     from paper_2502_04077_amd.offload import OffloadRun
