@@ -159,14 +159,13 @@ struct CalibArgs {
   float ml_unit;                  // the chunks' maxima times this are exponents of 2
 };
 
-// A workgroup for every unit (a chunk of an instance).  (fp32.  With units off a counter, cleared by a launch before, 100 instances at 32K took 321 us
+// A workgroup for every unit (chunk blockIdx.x of instance blockIdx.y).  (fp32.  With units off a counter, cleared by a launch before, 100 instances at 32K took 321 us
 // instead of 304; 16 55.8, 54.4.)
 template <int D, int G>
 __global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a) {
   using T = float;
   extern __shared__ __align__(16) float smem[];
-  const int unit = blockIdx.x;
-  const int inst = unit / a.n_chunks, chunk = unit - inst * a.n_chunks;
+  const int inst = blockIdx.y, chunk = blockIdx.x;
   const int c0 = chunk * a.chunk_blocks;
   const int nblk = min(a.chunk_blocks, a.nb_cur - c0);
   const int ld = a.chunk_blocks * a.b;
@@ -654,6 +653,9 @@ int calib_chunk_tokens(const Shape& s, int t_cur) {
 // 16.7).  d = 64, with half the bytes on their way per workgroup: as many as fit (300 at 30K, two 261, three 201, five 188).
 constexpr size_t kCalibPairLds = 65536;
 
+// A launch has fewer than 2^32 threads in x: workgroups take several units each beyond this (65535 instances of 131073 tokens, in a pool that they share).
+constexpr int kCalibMostWorkgroups = 1 << 23;
+
 template <typename T, int D, int G>
 hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
   if constexpr (std::is_same<T, bf16_t>::value) {
@@ -664,7 +666,7 @@ hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
     };
     // Over PCIe 16 workgroups fill the link, and a thousand places at once cost it 15 % (8 instances at 32K, 67 MB, us: 16
     // workgroups 1178, 64 1190, 256 1272, 512 1358).
-    const int grid = s.k_on_host && a.n_units > 16 ? 16 : a.n_units;
+    const int most = s.k_on_host ? 16 : kCalibMostWorkgroups, grid = a.n_units < most ? a.n_units : most;
     const int tokens = a.chunk_blocks * a.b;
     size_t lds = lds_of(tokens, grid < a.n_units);
     if (D == 128 && !s.k_on_host) {
@@ -675,7 +677,7 @@ hipError_t run_calib(const Shape& s, CalibArgs a, hipStream_t st) {
     calibrate_stream_kernel<D, G><<<dim3(grid), kAttnThreads, lds, st>>>(a);
   } else {
     const size_t lds = sizeof(float) * ((size_t)G * a.chunk_blocks * a.b + G * a.chunk_blocks + 2 * G + a.chunk_blocks);
-    calibrate_f32_kernel<D, G><<<dim3(a.n_units), kAttnThreads, lds, st>>>(a);
+    calibrate_f32_kernel<D, G><<<dim3(a.n_chunks, s.n_inst), kAttnThreads, lds, st>>>(a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -131,3 +131,34 @@ def test_several_units_a_workgroup(n, g, d, b, t):
     ref[:, :t] = p
     ref = ref.view(g, cap // b, b).amax(dim=(0, 2))
     assert (rows[0][0].double() - ref).abs().max() <= 2e-5 * ref.max()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_more_units_than_a_launch_has_threads_for(dtype):
+    """65535 instances of 257 units, more than 2^32 / 256 in all, over one short paged pool: workgroups take several units each (bf16), or the launch has a
+    second dimension (fp32).  Against softmax in 64 bits, 2e-5 of the largest value as for the units above."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    n, d, b, n_phys = 65535, 64, 64, 40
+    t = 256 * 1024 + 70
+    nb = -(-t // b)
+    assert n * -(-t // 1024) * 256 >= 1 << 32
+    ctx = ap.Context(n_inst=n, g=1, head_dim=d, block=b, hist_len=8, t_cap=nb * b, k_blocks=1, n_sink=0, n_local=0, c1=4, c2=4, kv_dtype=dtype)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    pool = torch.randn((n_phys, b, d), generator=gen, device=dev).to(dt)
+    q = (2 * torch.randn((n, 1, d), generator=gen, device=dev)).to(dt)
+    places = torch.randint(0, n_phys, (2, nb), generator=gen, device=dev, dtype=torch.int32)
+    table = places[torch.arange(n, device=dev) % 2].contiguous()
+    ctx.set_block_table(table, n_phys)
+    row = torch.full((n, nb), 7.0, device=dev)
+    ws = torch.empty((ctx.workspace_bytes(),), dtype=torch.uint8, device=dev)
+    ctx.calibrate(q, pool, t, row, ws)
+    assert float(row.max()) <= 1.0 and float(row.min()) >= 0.0
+    for i in (0, 1, 32639, 32640, 32641, 32767, 65280, n - 2, n - 1):
+        logits = (pool.double().view(-1, d) @ q[i, 0].double() / math.sqrt(d)).view(n_phys, b)[places[i % 2].long()].view(-1)[:t]
+        p = torch.zeros(nb * b, dtype=torch.float64, device=dev)
+        p[:t] = torch.softmax(logits, dim=0)
+        ref = p.view(nb, b).amax(dim=1)
+        assert (row[i].double() - ref).abs().max() <= 2e-5 * ref.max(), i
