@@ -425,8 +425,8 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 //   - there are no more than two workgroups a CU, which are resident at once whatever LDS they have: in further rounds every workgroup holds its
 //     place until its partials have reached memory.  (513 to 1024 workgroups, steps in us, merged inside / by a launch: fp32, 1024 tokens, g = 8,
 //     d = 128, 60 instances 42.0 / 35.9, g = 4, 40 instances 26.0 / 24.5; bf16, g = 8, d = 64, 510 x 8192 tokens 231 / 214, g = 4, d = 128,
-//     350 x 8192 250 / 246, 510 x 16384 699 / 705.  fp32 without a selection inside, d = 128, one workgroup a CU: 1024 tokens, g = 4, 30 instances
-//     13.6 / 12.1, 3 instances 11.0 / 11.6.  d = 64 has half the LDS: most_sums has its figures.)
+//     350 x 8192 250 / 246, 510 x 16384 699 / 705.)  Single fp32 calls with d = 128 one workgroup a CU (1024 tokens, g = 4, 30 instances 13.6 / 12.1, 3
+//     11.0 / 11.6; d = 64, 48 x 512, g = 8, 12.1 / 12.8, 32 x 1024, g = 4, 9.6 / 10.8; behind a predictor, d = 128, 128 x 256, 18.3 / 20.5).
 //   - one workgroup has little to merge: few splits, and few sums in all.  (8 instances, fp32, g = 4, d = 128: 16 splits 19.4 / 21.9, 24 22.9 /
 //     22.2, 64 36.1 / 25.8; g = 1, 64 splits 29.0 / 22.1; bf16, d = 128, g = 4: 8 splits 16.2 / 20.1, 16 20.5 / 21.3, 20 23.1 / 22.0; 4 instances,
 //     g = 8, 12 splits 22.0 / 25.8, 16 24.3 / 23.5, 64 51.6 / 29.0.)
@@ -569,7 +569,8 @@ hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   if (e != hipSuccess) return e;
   if (merge_inside(s, ninst, a.n_split, most_sums(s, a))) {
     const size_t lds = lds_of_form(a, lds_of(want), G, kMergeInside);
-    sparse_stream_kernel<D, G, kMergeInside><<<grid, kAttnThreads, lds, st>>>(a);
+    if (s.cleared) sparse_stream_kernel<D, G, kMergeInside><<<grid, kAttnThreads, lds, st>>>(a);
+    else sparse_stream_kernel<D, G, kMergeAlone><<<grid, kAttnThreads, lds, st>>>(a);
     return hipGetLastError();
   }
   sparse_stream_kernel<D, G, kSplitsOnly><<<grid, kAttnThreads, lds_of(want), st>>>(a);
@@ -621,9 +622,12 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
     }
   }
   if constexpr (std::is_same<T, float>::value)
-    if (inside || (merge_inside(s, ninst, a.n_split, most_sums(s, a)) && (D == 64 || ninst * a.n_split <= 256))) {
-      if (inside) sparse_decode_kernel<T, D, G, kAttnWaves, false, kSelectInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_inside, st>>>(a);
-      else sparse_decode_kernel<T, D, G, kAttnWaves, false, kMergeInside><<<dim3(a.n_split, ninst), kAttnThreads, lds_of_form(a, lds, G, kMergeInside), st>>>(a);
+    if (inside || (merge_inside(s, ninst, a.n_split, most_sums(s, a)) && (s.cleared || D == 64 || ninst * a.n_split <= 256))) {
+      const dim3 grid(a.n_split, ninst);
+      const size_t lds_merge = lds_of_form(a, lds, G, kMergeInside);
+      if (inside) sparse_decode_kernel<T, D, G, kAttnWaves, false, kSelectInside><<<grid, kAttnThreads, lds_inside, st>>>(a);
+      else if (s.cleared) sparse_decode_kernel<T, D, G, kAttnWaves, false, kMergeInside><<<grid, kAttnThreads, lds_merge, st>>>(a);
+      else sparse_decode_kernel<T, D, G, kAttnWaves, false, kMergeAlone><<<grid, kAttnThreads, lds_merge, st>>>(a);
       return hipGetLastError();
     }
   sparse_decode_kernel<T, D, G, kAttnWaves, false><<<dim3(a.n_split, ninst), kAttnThreads, lds, st>>>(a);
@@ -713,7 +717,7 @@ hipError_t launch_sparse_decode(const Shape& s, int inst0, int ninst, const void
   SparseArgs a;
   a.q = q; a.K = K; a.V = V; a.idx = idx; a.cnt = cnt; a.out = out; a.row = row; a.row_stride = row_stride;
   a.merge_count = reinterpret_cast<unsigned long long*>(ws + wl.merge_count);
-  a.merge_nonce = s.cleared ? 0 : new_nonce(kTicketBits);
+  a.merge_nonce = new_nonce(kTicketBits);
   a.part_ml = ws + wl.part_ml; a.part_acc = ws + wl.part_acc; a.part_bmp = ws + wl.part_bmp;
   a.t_cap = s.t_cap; a.nb_cap = s.nb_cap; a.k = s.k; a.b = s.b; a.log2b = ilog2(s.b); a.t_cur = t_cur;
   a.nb_cur = (t_cur + s.b - 1) / s.b;

@@ -351,12 +351,12 @@ struct SparseArgs {
   const float* pred;              // scores [n_inst][nb_cap] that the decode selects by itself (kSelectInside), writing idx and cnt
   int n_sink, n_local, sel_at;    // forced blocks; where in LDS (floats) the list goes: k blocks and their number
   unsigned long long* merge_count;  // [n_inst] splits that have left their partials (take_ticket), where they are merged inside
-  unsigned long long merge_nonce;   // number of this launch in them; 0: they are zero at launch
+  unsigned long long merge_nonce; // number of this launch in them (kMergeAlone; else they are zero at launch)
 };
 
-// What a decode launch does beside its own share: nothing; merging, by the last workgroup of an instance to finish;
-// before that also the selection, by every workgroup for itself (whole lists too; see select_here).
-constexpr int kSplitsOnly = 0, kMergeInside = 1, kSelectInside = 2;
+// What a decode launch does beside its own share: nothing; merging, by the last workgroup of an instance to finish, behind a launch that has cleared
+// the counters; before that also the selection, by every workgroup for itself (whole lists too; see select_here); merging without such a launch.
+constexpr int kSplitsOnly = 0, kMergeInside = 1, kSelectInside = 2, kMergeAlone = 3;
 // Scores a thread holds: up to 2304 candidates.  (Steps of 8 / 32 / 128 instances, us, with 9, 12 and 15 scores a thread: 2042 candidates
 // 16.6 16.8 17.2 / 18.5 18.8 19.0 / 28.6 28.6 28.8, one of fp32 with 126 candidates 16.9 and 17.4; 2442, for nine too many, 18.2 17.0 17.3 / 20.4 19.1
 // 19.2 / 30.2 29.4 29.7, 2992 18.4 17.1 17.3 / 21.0 19.7 19.9 / 31.7 30.4 30.5, 3692 19.0 18.7 18.0 / 21.4 21.2 20.2 / 34.9 34.2 33.5.  More scores
@@ -394,8 +394,7 @@ __device__ __forceinline__ float ld_shared_out(const float* p) { return __hip_at
 // (begin_tickets, early, so that nobody waits for the answer: it is at zero where the last launch ended properly, and carries the number already where
 // another was faster); the one that gets the last ticket leaves it at zero (end_tickets), so that a captured launch, whose number stands still, starts afresh
 // on every replay.  What lies in a fresh workspace is taken for a count once in 2^52 words.  Called by one lane.
-// A launch behind one that has cleared the words (of the predictor, of an appended row) has the number zero and only counts; one that makes the selection
-// too always is, and has no code for more.
+// A launch behind one that has cleared the words (of the predictor, of an appended row) only counts.
 constexpr int kTicketBits = 12;                         // (kMergeInsideSplits and more)
 __device__ __forceinline__ unsigned long long begin_tickets(unsigned long long* word, unsigned long long nonce) {
   unsigned long long seen = 0ull;
@@ -419,7 +418,7 @@ __device__ __forceinline__ bool last_to_finish(unsigned long long* count, unsign
   if (threadIdx.x == 0) {
     if constexpr (TICKETS) {
       const bool last = (int)take_ticket(count, nonce, seen) == n_split - 1;
-      if (last && nonce != 0) end_tickets(count);
+      if (last) end_tickets(count);
       *s_last = last;
     } else {
       *s_last = __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(count), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(n_split - 1);
@@ -603,8 +602,8 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
 
   // (behind the first rows: answers come in order)
   auto begin = [&]() __attribute__((always_inline)) {
-    if constexpr (HOW == kMergeInside)
-      if (threadIdx.x == 0 && !whole_row && a.merge_nonce != 0) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
+    if constexpr (HOW == kMergeAlone)
+      if (threadIdx.x == 0 && !whole_row) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
   };
   if (nblk <= 0) begin();
 
@@ -754,7 +753,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
       st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, s_bmp[pair]);
     }
     if constexpr (MERGE)
-      if (last_to_finish<HOW == kMergeInside>(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
+      if (last_to_finish<HOW == kMergeAlone>(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
   }
 }
 
@@ -943,8 +942,8 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
     load_k(next);
     load_v(next);
   }
-  if constexpr (HOW == kMergeInside)
-    if (threadIdx.x == 0 && !whole_row && a.merge_nonce != 0) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
+  if constexpr (HOW == kMergeAlone)
+    if (threadIdx.x == 0 && !whole_row) tickets = begin_tickets(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce);
 
   float m = -INFINITY, l = 0.f;                          // running statistics of this lane's head and row of 16 lanes
   float acc[G][E];
@@ -1146,7 +1145,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
       st_shared_out<MERGE>(a.part_bmp + ((size_t)inst * G + h) * a.k + j0 + jb, block_max(h, jb));
     }
     if constexpr (MERGE)
-      if (last_to_finish<HOW == kMergeInside>(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
+      if (last_to_finish<HOW == kMergeAlone>(a.merge_count + (size_t)inst * kTicketStride, a.merge_nonce, tickets, a.n_split, reinterpret_cast<int*>(smem) + a.n_split * G)) merge_splits<D, G>(a, inst, cnt, listed, smem);
   }
 }
 
