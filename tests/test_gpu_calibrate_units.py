@@ -1,5 +1,5 @@
 """Dense calibration where its units and passes end: contexts a token short of or beyond a pass, a unit of 256, 512 or 1024
-tokens, blocks longer than a pass, more units than workgroups (handed out by a counter), paged caches, against float64.
+tokens, blocks longer than a pass, more units than the chip holds workgroups, paged caches, against float64.
 Tolerance: fp32 logits of bf16 products (2^-24 sqrt(128) x a few relative to the logit, which is below 16 here) and fp32 sums
 of up to 40000 exponentials: 2e-5 of the row's largest value."""
 import math
@@ -78,10 +78,10 @@ def test_calibrate_vs_float64(n, g, d, b, t, paged):
 @pytest.mark.parametrize("n,g,d,b,lengths", [
     (1, 4, 64, 16, (2051, 255, 257, 1)), (3, 8, 128, 8, (5003, 513)),      # units of 256 tokens, one a workgroup
     (700, 2, 64, 32, (1100, 2000)), (200, 4, 128, 16, (2000, 2700, 1000)),            # of 512 and 1024; d = 128: 512, 1024 and 256
-    (2100, 1, 64, 16, (1025, 300, 2000)), (1100, 2, 128, 64, (1900,)),     # more units than the chip can hold workgroups (2048): off the counter
+    (2100, 1, 64, 16, (1025, 300, 2000)), (1100, 2, 128, 64, (1900,)),     # more units than the chip can hold workgroups (2048)
 ])
 def test_fp32_units(n, g, d, b, lengths):
-    """fp32 caches: units of 256, 512 or 1024 tokens, as the length of the call goes, one a workgroup or handed out by the counter."""
+    """fp32 caches: units of 256, 512 or 1024 tokens, as the length of the call goes, one a workgroup."""
     import paper_2502_04077_amd as ap
     dev = torch.device("cuda:0")
     cap = -(-max(lengths) // b) * b + b

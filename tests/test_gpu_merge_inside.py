@@ -1,10 +1,11 @@
 """A fused step of few instances - the selection made by every split for itself, the splits merged by the last workgroup to finish -
-against the single calls, which have a launch for each: the same bytes, call after call with new queries, whichever workgroup
-happens to be the last."""
+against the selection's own launch and the decode without a workspace, whose splits are always merged by a launch of their own: the same bytes, call
+after call with new queries, whichever workgroup happens to be the last."""
 import numpy as np
 import pytest
 import torch
 
+from noalloc_size import fits
 from workloads import n_weight_floats
 
 pytestmark = pytest.mark.gpu
@@ -30,6 +31,7 @@ pytestmark = pytest.mark.gpu
 ])
 def test_same_bytes(n, g, d, block, k, nb, dtype, hist):
     import paper_2502_04077_amd as ap
+    assert fits(n, g, d, block, k)
     dev = torch.device("cuda:0")
     cap = nb + 5
     ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=block, hist_len=hist, t_cap=cap * block, k_blocks=k, n_sink=1, n_local=2, c1=4, c2=4,
@@ -56,7 +58,7 @@ def test_same_bytes(n, g, d, block, k, nb, dtype, hist):
         ctx.step(ring, pushed, q, K, V, t, out, idx, cnt, pred, pstate, ap.AP_PRED_REBASE, ws)
         ctx.select_topk(pred, nb, idx2, cnt2, ws)
         assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2), i
-        ctx.sparse_decode(q, K, V, t, idx, cnt, out2, row, ws)
+        ctx.sparse_decode_noalloc(q, K, V, t, idx, cnt, out2, row)
         assert torch.equal(out, out2), i
         assert torch.equal(ring[:, pushed % (hist + 1)], row), i
         pushed += 1
@@ -100,7 +102,7 @@ def test_every_predictor_clears_the_counters(c1, c2, fp32, hist, dtype):
         if not mode & reuse:
             ctx.select_topk(pred, -(-t // block), idx2, cnt2, ws)
             assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2), i
-        ctx.sparse_decode(q, K, V, t, idx, cnt, out2, row, ws)
+        ctx.sparse_decode_noalloc(q, K, V, t, idx, cnt, out2, row)
         assert torch.equal(out, out2), i
         assert torch.equal(ring[:, pushed % (hist + 1)], row), i
         pushed += 1
@@ -173,7 +175,8 @@ def test_single_call_forms(n, g, d, block, k, dtype, inside):
 
 
 def test_offload_step_clears_the_counters():
-    """The same where the launch of the appended row does it: offload steps over a workspace of garbage against the single calls."""
+    """The same where the launch of the appended row does it: offload steps over a workspace of garbage against the single calls, their decode without a
+    workspace."""
     from paper_2502_04077_amd.offload import OffloadRun
     from test_gpu_parity import small
     from workloads import kv_cache, predictor_weights, queries
@@ -185,6 +188,8 @@ def test_offload_step_clears_the_counters():
         hosts.append(torch.empty(x.shape, dtype=x.dtype, pin_memory=True))
         hosts[-1].copy_(x)
     runs = [OffloadRun(w, *hosts, dev, rebase_every=4, single_calls=single) for single in (False, True)]
+    for L in runs[1].layers:
+        L.ctx.sparse_decode = lambda *args, ctx=L.ctx: ctx.sparse_decode_noalloc(*args[:-1])
     for run in runs:
         run.set_weights(predictor_weights(w))
         for j in range(w.hist_len):
@@ -206,8 +211,9 @@ def test_offload_step_clears_the_counters():
 
 
 @pytest.mark.parametrize("n,g,d,block,k,nb,dtype", [
-    (8, 4, 128, 16, 64, 300, "bf16"), (1, 8, 64, 8, 300, 400, "bf16"), (50, 8, 64, 16, 128, 130, "bf16"), (3, 4, 128, 16, 64, 90, "f32"),
-    (16, 2, 64, 16, 40, 90, "f32"), (4, 8, 128, 32, 200, 200, "bf16"), (256, 1, 128, 16, 512, 513, "bf16"),
+    (8, 4, 128, 16, 64, 300, "bf16"), (1, 8, 64, 8, 240, 400, "bf16"), (50, 8, 64, 16, 128, 130, "bf16"), (3, 4, 64, 16, 64, 90, "f32"),
+    (16, 2, 64, 16, 40, 90, "f32"), (64, 4, 128, 16, 16, 90, "f32"),
+    (16, 2, 128, 16, 256, 257, "bf16"), (256, 1, 64, 16, 128, 129, "bf16"),           # most splits; most workgroups, and the last counter
 ])
 def test_single_calls_count_in_any_workspace(n, g, d, block, k, nb, dtype):
     """Single calls merge inside too, counting in words of the workspace that may hold anything - garbage, zeros, all ones, what the call before left -
@@ -247,6 +253,10 @@ def test_single_calls_count_in_any_workspace(n, g, d, block, k, nb, dtype):
         ctx.sparse_decode_noalloc(q, K, V, nb * block - 3, idx, cnt, *ref)
         assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), what
 
+    lists(0)
+    ws[:size].fill_(FILL)
+    ctx.sparse_decode(q, K, V, nb * block - 3, idx, cnt, *got, ws)
+    assert int((lone_words(ws[:size])[1] == 0).sum()) == n                           # (they are merged inside)
     for i in range(9):
         lists(i)
         fill(i)

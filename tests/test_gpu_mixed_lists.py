@@ -1,12 +1,15 @@
 """Sparse decode of a few instances more than a multiple of the CUs, which go partly whole and partly in splits, at the edges of that rule,
 against the oracle: the last whole instance and the first split one, empty and short lists on both sides, contexts that end inside a block (NaN
 rows behind), paged caches, and the no-allocation call, whose results are the same bytes.  Tolerance: as for the streaming form, 2e-5 of the largest value."""
+import math
+
 import numpy as np
 import pytest
 import torch
 
+from noalloc_size import fits
 from oracle import attnpred_oracle as orc
-from workloads import to_f64
+from workloads import n_weight_floats, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -78,8 +81,108 @@ def test_whole_and_split_lists(n, g, d, b, k, t, paged):
         ref_row[:nb] = orc.pooled_row(A, b)
         assert np.abs(o[i] - ref).max() <= 2e-5 * np.abs(ref).max(), i
         assert np.abs(r[i] - ref_row).max() <= 2e-5 * ref_row.max(), i
-    try:
-        ctx.sparse_decode_noalloc(q, Ka, Va, t, *lists, out.fill_(7.0), row.fill_(7.0))
-    except ap.binding.ApError:
-        return                                             # (partials beyond the static scratch: refused)
+    out, row = torch.full_like(out, 7.0), torch.full_like(row, 7.0)
+    if not fits(n, g, d, b, k):                            # (partials beyond the static scratch)
+        with pytest.raises(ap.ApError) as refused:
+            ctx.sparse_decode_noalloc(q, Ka, Va, t, *lists, out, row)
+        assert refused.value.code == ap.AP_ERR_RANGE
+        return
+    ctx.sparse_decode_noalloc(q, Ka, Va, t, *lists, out, row)
     assert torch.equal(out, results[0][0]) and torch.equal(row, results[0][1])
+
+
+FORMS = [(300, 4, 128, 16, 64, 120), (576, 8, 64, 16, 128, 200), (264, 8, 128, 32, 64, 70)]       # 44, 64 and 8 instances beyond, in 8, 8 and 16 splits
+
+
+def written(ws):
+    """32-bit words of a workspace of 0x5a bytes that were written."""
+    return int((ws[:ws.numel() // 4 * 4].view(torch.int32) != 0x5A5A5A5A).sum())
+
+
+def check(i, blocks, q, K, V, b, t, out, row):
+    tok = (blocks[:, None] * b + np.arange(b)).ravel()
+    tok = torch.from_numpy(tok[tok < t]).to(q.device)
+    p = torch.softmax(q[i].double() @ K[i, tok].double().T.contiguous() / math.sqrt(q.shape[-1]), dim=1)
+    ref = p @ V[i, tok].double()
+    ref_row = torch.zeros(row.shape[1], dtype=torch.float64, device=q.device)
+    ref_row.scatter_reduce_(0, tok // b, p.amax(dim=0), "amax")
+    assert (out[i].double() - ref).abs().max() <= 2e-5 * ref.abs().max(), i
+    assert (row[i].double() - ref_row).abs().max() <= 2e-5 * ref_row.max(), i
+
+
+@pytest.mark.parametrize("n,g,d,b,k,nb", FORMS)
+def test_entries_twice_and_out_of_order(n, g, d, b, k, nb):
+    """Entries outside the context, repeated and in any order, in whole lists and in split ones, whose rows are written by different code.  Against float64."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    t, first = nb * b - 5, n // 256 * 256
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=b, hist_len=8, t_cap=(nb + 3) * b, k_blocks=k, n_sink=0, n_local=0, c1=4, c2=4, kv_dtype="bf16")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n)
+    K, V = (torch.randn((n, (nb + 3) * b, d), generator=gen, device=dev).to(torch.bfloat16) for _ in range(2))
+    q = (3 * torch.randn((n, g, d), generator=gen, device=dev)).to(torch.bfloat16)
+    rng = np.random.default_rng(n)
+    idx = rng.integers(-2, nb + 2, (n, k)).astype(np.int32)
+    cnt = np.where(np.arange(n) % 4 == 1, 5, k).astype(np.int32)
+    out, row = torch.full((n, g, d), 7.0, device=dev), torch.full((n, nb + 3), 7.0, device=dev)
+    ws = torch.full((ctx.workspace_bytes(),), 0x5A, dtype=torch.uint8, device=dev)
+    ctx.sparse_decode(q, K, V, t, torch.from_numpy(idx).to(dev), torch.from_numpy(cnt).to(dev), out, row, ws)
+    beyond, splits = n - first, min(512 // (n - first), k * b // 128, 64)
+    splits = -(-k // -(-k // splits))
+    assert written(ws) == beyond * splits * g * (d + 2) + int(cnt[first:].sum()) * g           # (only those beyond leave partials: the mixed form)
+    for i in (0, 1, 2, 255, first - 2, first - 1, first, first + 1, first + 2, n - 2, n - 1):
+        check(i, np.clip(idx[i, :cnt[i]], 0, nb - 1), q, K, V, b, t, out, row)
+
+
+@pytest.mark.parametrize("n,g,d,b,k,nb", FORMS)
+def test_fused_step_and_replay(n, g, d, b, k, nb):
+    """A whole step whose decode has this form, behind the selection's launch, and the same from a captured graph, byte for byte on every replay."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    t, first, hist = nb * b - 5, n // 256 * 256, 8
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=b, hist_len=hist, t_cap=nb * b, k_blocks=k, n_sink=1, n_local=2, c1=8, c2=8, kv_dtype="bf16")
+    ctx.set_weights((0.2 * np.random.default_rng(n).standard_normal(n_weight_floats(8, 8))).astype(np.float32))
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n)
+    K, V = (torch.randn((n, nb * b, d), generator=gen, device=dev).to(torch.bfloat16) for _ in range(2))
+    q = (3 * torch.randn((n, g, d), generator=gen, device=dev)).to(torch.bfloat16)
+    ring = torch.rand((n, hist + 1, nb), generator=gen, device=dev)
+    ring0 = ring.clone()
+    pred, pstate = (torch.zeros((n, nb), device=dev) for _ in range(2))
+    out, idx, cnt = torch.zeros((n, g, d), device=dev), torch.zeros((n, k), dtype=torch.int32, device=dev), torch.zeros((n,), dtype=torch.int32, device=dev)
+    ws = torch.empty((ctx.workspace_bytes(),), dtype=torch.uint8, device=dev)
+
+    def step():
+        ctx.step(ring, 40, q, K, V, t, out, idx, cnt, pred, pstate, ap.AP_PRED_REBASE, ws)
+
+    def start_over(value):
+        for x in (out, pred, pstate):
+            x.fill_(value)
+        for x in (idx, cnt):
+            x.fill_(-1)
+        ring.copy_(ring0)
+        ws.fill_(0x5A)
+
+    start_over(7.0)
+    step()
+    beyond, splits = n - first, min(512 // (n - first), k * b // 128, 64)
+    splits = -(-k // -(-k // splits))
+    assert written(ws) == beyond * (splits * g * (d + 2) + g * k)
+    idx2, cnt2, row = torch.zeros_like(idx), torch.zeros_like(cnt), ring[:, 40 % (hist + 1)]
+    ctx.select_topk(pred, nb, idx2, cnt2, ws)
+    assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2)
+    for i in (0, 1, 255, first - 1, first, first + 1, n - 1):
+        check(i, idx[i].cpu().numpy(), q, K, V, b, t, out, row)
+    want = [x.clone() for x in (out, idx, cnt, pred, pstate, ring)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    start_over(8.0)
+    with torch.cuda.graph(graph):
+        step()
+    for replay in range(3):
+        start_over(9.0 + replay)
+        torch.cuda.synchronize()
+        graph.replay()
+        assert all(torch.equal(x, y) for x, y in zip((out, idx, cnt, pred, pstate, ring), want)), replay
+        step()                                             # (a step of the program's own in between)
+        torch.cuda.synchronize()
