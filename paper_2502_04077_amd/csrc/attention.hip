@@ -203,10 +203,10 @@ __global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a
 // the block maxima).  The waves meet once per unit, to bring their maxima and sums together, and write the block maxima.
 // A workgroup each for the units of K in device memory; over PCIe a few workgroups, each taking every gridDim.x-th, with the rows of the next unit's first pass
 // on their way as well.  run_calib says how many workgroups a CU has.
-// What bounds it: reads of K, and what little is written.  The block maxima are 0.4 % of the bytes, but of 519 us of 256 instances at 50K they cost 20
-// where every wave writes every fourth float to its XCD's L2, 14 where neighbouring lanes write neighbouring columns through to memory.  Measured, launch
-// and merge, us, before (512 workgroups, units off a counter, a wave's own blocks written by it) and now: 256 instances at 50K 519, 482 (6.8 TB/s); 2048 at 32K
-// 2678, 2488; 4096, g = 1, 5083, 4768; 62 95, 85; 24 48, 40; 300 at 30K, d = 64, 245, 185; 8 17.0, 16.7.  No difference: two or four
+// What bounds it: reads of K, and what little is written.  The block maxima are 0.4 % of the bytes, but of 510 us of 256 instances at 50K they cost 48
+// by plain stores, whichever lanes write them, and of 484 they cost 22 written through to memory, though the same bytes get there in as many requests.  Measured, launch
+// and merge, us, before (512 workgroups, units off a counter, plain stores) and now: 256 instances at 50K 520, 484 (6.8 TB/s); 2048 at 32K
+// 2698, 2530; 4096, g = 1, 5083, 4768; 62 93, 83; 24 48, 40; 300 at 30K, d = 64, 245, 185; 8 16.5, 16.3.  No difference: two or four
 // passes of rows on their way per wave, units of 63 or 65 blocks.  Merging by the last workgroup of an instance: 8 instances 17.6, 256 a wave's merge
 // holds up its workgroup's stream, 558.
 struct CalibUnit { int inst, chunk, nblk, c0; };
@@ -334,7 +334,7 @@ void calibrate_stream_kernel(CalibArgs a) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     // The unit's maximum and sum, of head lane % G; block maxima relative to that maximum, one head's columns by neighbouring lanes, written
-    // through to memory, where the merge's launch finds them.  (The next unit's maxima go to the other half of s_ml and s_qmax: a wave that gets to the one
+    // through to memory.  (The next unit's maxima go to the other half of s_ml and s_qmax: a wave that gets to the one
     // after it has met the others in between.)
     {
       const int hl = lane & (G - 1);
@@ -432,8 +432,8 @@ template <int D, int G> hipError_t run_combine(int ninst, const SparseArgs& a, h
 //     g = 8, 12 splits 22.0 / 25.8, 16 24.3 / 23.5, 64 51.6 / 29.0.)
 // Fewer sums behind a selection that is a launch of its own, where the merge's launch finds the host ahead (g = 4, d = 128: 16 splits, 126
 // places, 16 instances 23.5 / 20.6, 8 instances 21.6 / 20.6, 4 splits, 128 instances, 35.5 / 36.5; g = 1, d = 64: 15 splits, 7 instances 22.0 / 23.2;
-// without a selection 16 splits, 8 instances 15.1 / 16.5).  Single calls, us, by a launch / inside, bf16, d = 128: 8 instances x 1024 tokens, g = 4, 11.0 /
-// 8.7, 16 x 2048 14.3 / 10.4, 64 x 2048, g = 8, 22.6 / 19.3, 100 x 1024 16.6 / 14.4, 30 x 4096 15.7 / 15.4, 128 x 4096 49.6 / 48.6.
+// without a selection 16 splits, 8 instances 15.1 / 16.5).  Single calls, us, by a launch / inside, bf16, d = 128: 8 instances x 1024 tokens, g = 4, 10.8 /
+// 8.3, 16 x 2048 10.8 / 9.8, 64 x 2048, g = 8, 21.2 / 18.1, 100 x 1024 15.4 / 13.1, 32 x 4096 15.9 / 15.6, 128 x 4096 44.3 / 43.6.
 static_assert(kMergeInsideSplits < 1 << kTicketBits, "a ticket each");
 constexpr int kMergeInsideWorkgroups = 512, kMergeInsideSums = 12288, kMergeFewSums = 4096;
 static_assert(2 * kTicketInstances >= kMergeInsideWorkgroups, "every instance in two splits or more has a word");
@@ -509,12 +509,13 @@ template <int D> int stream_splits(const SparseArgs& a, int ninst, int g) {
 // Instances a little beyond a multiple of the CUs: that multiple goes a workgroup each, as many a CU, and only what is beyond it in splits, in one launch
 // with the long workgroups first.  Splitting every list alike leaves some CUs a share more than others, however short the shares, and merges all
 // instances.  Returns the splits of those beyond, 0 or 1 if all are to be treated alike.  They get one more workgroup a CU, two where they are a quarter of the CUs
-// or fewer, not more (600 instances x 2048 tokens, g = 8, 88 beyond: 111.2 us with two splits, 117.0 with three, 115.6 with five; 300 x 1024, g = 4, 44 beyond:
-// 32.3 with 11, 33.3 with five).  Not where half of the CUs would still be without one, or short lists make a merge of them cost more than the balance gives.
-// bf16, us, all alike / mixed: g = 8, d = 128, 2048 tokens, 264 instances 60.6 / 56.0, 320 67.9 / 63.3, 520 109.9 / 98.8, 640 123.3 / 117.3, 700 128.4 / 133.7 (not
-// taken), 800 162 / 144, 896 171 / 161; g = 4, 1024 tokens, 264 32.0 / 28.6, 540 55.6 / 52.1, 640 62.4 / 59.2, 350 36.1 / 39.4 (not taken); g = 2, 4096 tokens, 520
-// 186 / 173, 640 211 / 208; d = 64, g = 4, 4096 tokens, 520 108 / 91, 264 57.4 / 56.9, 2048 tokens, 280 33.0 / 35.4 (not taken); g = 1, 512 tokens, 560 27.2 / 28.1
-// (not taken).
+// or fewer, not more (600 instances x 2048 tokens, g = 8, 88 beyond: 109 us with two splits, 114 with three, 113 with five; 300 x 1024, g = 4, 44 beyond: with
+// eight, all that 1024 tokens allow, 31.2, with five 32.2, eleven 32.8, two 32.3) - so no more than half of the CUs' number beyond, or one more workgroup would take a whole
+// list.  Beyond one list a CU no more than a quarter: up to half it depends on the length (all alike / mixed, g = 8, 330 instances x 4096 tokens 127 / 120, 384 x 1024 39.1 / 42.3; g = 4, 350 x
+// 4096 129 / 122, 384 x 2048 70.4 / 73.0).  Not where half of the CUs would still be without one, or short lists make a merge of them cost more than the balance gives.
+// bf16, us, all alike / mixed: g = 8, d = 128, 2048 tokens, 264 instances 60.7 / 52.5, 320 67.9 / 62.3, 576 118.5 / 109.3, 640 127.1 / 113.9, 896 174 / 159; g = 4, 1024 tokens, 264 31.2 / 28.2,
+// 576 56.8 / 54.3, 640 61.2 / 58.0, 896 83.5 / 80.2; g = 1, 4096 tokens, 264 94.7 / 87.3, 640 208.7 / 207.4, 896 293 / 299; d = 64, g = 4, 4096 tokens, 576 115 / 104, 896 161 / 153.  Not taken:
+// 512 tokens, d = 128, g = 4, 320 17.7 / 20.3, 640 30.0 / 31.6; d = 64, 264 x 4096, g = 4, 58.0 / 57.2, g = 8, 280 x 4096 64.4 / 71.2, 1024 tokens, g = 4, 640 30.7 / 31.8.
 template <int D> int mixed_splits(const SparseArgs& a, int ninst, int g) {
   constexpr int kCUs = 256;
   const int n_whole = ninst / kCUs * kCUs, beyond = ninst - n_whole;
@@ -652,9 +653,10 @@ int calib_chunk_tokens(const Shape& s, int t_cur) {
   return tokens;
 }
 
-// LDS that leaves room for two workgroups a CU.  With d = 128 these keep memory busy, and more only spread the reads over more places (us with two / as
-// many as fit: 256 instances at 50K 482 / 501, 2048 at 32K 2488 / 2606, 62 85 / 91) - unless all fit at once and none has to wait (8 instances at 32K 19.2 /
-// 16.7).  d = 64, with half the bytes on their way per workgroup: as many as fit (300 at 30K, two 261, three 201, five 188).
+// LDS that leaves room for two workgroups a CU.  With d = 128 these keep memory busy, and more only spread the reads over more places - in calls of many units (us with two
+// / as many as fit: 256 instances at 50K 482 / 501, 2048 at 32K 2488 / 2606, 300 at 8K 100 / 104, 64 at 32K 86.2 / 90.0).  Where all units fit at once none has to wait (8 instances at 32K
+// 18.6 / 16.5, 45 at 8K 21.7 / 18.9, 33 at 32K 54.6 / 51.3, though 32 at 32K 45.9 / 50.5).  A little beyond what fits it is the length of the last round that tells, either way: 62 at 8K 28.0 / 24.4, 62 at 32K 82.5 /
+// 87.9, 50 at 16K 41.2 / 37.1, 128 at 16K 90.5 / 91.0, 64 at 32K with g = 8 91.1 / 87.6.  d = 64, with half the bytes on their way per workgroup: as many as fit (300 at 30K, two 261, three 201, five 188).
 constexpr size_t kCalibPairLds = 65536;
 
 // A launch has fewer than 2^32 threads in x: workgroups take several units each beyond this (65535 instances of 131073 tokens, in a pool that they share).
