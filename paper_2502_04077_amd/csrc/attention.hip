@@ -442,16 +442,25 @@ bool merge_inside(const Shape& s, int ninst, int n_split, int most_sums = kMerge
          (long)ninst * n_split <= kMergeInsideWorkgroups;
 }
 
-// Most sums that a launch without a selection of its own merges inside: a.pred tells whether a selection's launch is in front.  In a single call 16 splits
-// with many sums are left to the merge's launch, which takes eight splits at a time and is slow only on a remainder, unless the decode is over before the
-// host has the second launch ready.  (us, by a launch / inside.  bf16, d = 128, g = 4, 16 splits: 16 instances x 2048 tokens 11.5 / 9.9, 3072 11.7 / 10.9,
-// 4096 11.4 / 11.8, 8192 15.8 / 17.0; d = 64, g = 8: 30 x 2048 11.5 / 12.0, 32 x 8192 18.9 / 19.7; fp32, d = 64, g = 8, 1024 tokens: 8 instances 11.0 / 11.7,
-// 32 13.0 / 13.6; d = 128, g = 4: 8 instances 11.3 / 11.1, 10.8 / 11.0.  12 splits: bf16, 20 x 8192, g = 4, 20.6 / 19.9, g = 8 26.6 / 25.3; d = 64, g = 8, 40 x 4096 17.5 /
-// 16.0; fp32, d = 64, g = 8, 768 tokens, 8 12.9 / 11.4, 32 14.8 / 13.0.)
-constexpr int kMergeLaunchTokens = 3072;
-int most_sums(const Shape& s, const SparseArgs& a) {
-  const bool host_behind = s.kv_dtype == AP_BF16 && s.d == 128 && a.k * a.b <= kMergeLaunchTokens;
-  return a.pred != nullptr || (!s.cleared && a.n_split == kMergeInsideSplits && !host_behind) ? kMergeFewSums : kMergeInsideSums;
+// Does a launch without a selection of its own merge inside?  Behind a selection's launch (a.pred) with few sums.  Single calls (us, by a launch / inside) not with
+//   - 16 splits of many sums: the merge's launch takes eight splits at a time and is slow only on a remainder - unless the decode is over before the
+//     host has the second launch ready.  (bf16, d = 128, g = 4, 16 instances x 2048 tokens 11.5 / 9.9, 3072 11.7 / 10.9, 4096 11.4 / 11.8, 8192 15.8 /
+//     17.0; d = 64, g = 8: 30 x 2048 11.5 / 12.0, 32 x 8192 18.9 / 19.7; fp32, d = 64, g = 8, 1024 tokens: 8 instances 11.0 / 11.7, 32 13.0 / 13.6; d = 128,
+//     g = 4: 8 instances 11.3 / 11.1, 10.8 / 11.0.  12 splits: bf16, 20 x 8192, g = 4, 20.6 / 19.9, g = 8 26.6 / 25.3; d = 64, g = 8, 40 x 4096 17.5 / 16.0; fp32, d = 64,
+//     g = 8, 768 tokens, 8 12.9 / 11.4, 32 14.8 / 13.0.)
+//   - more than a workgroup a CU with d = 128, more than eight splits of many sums and long lists (g = 8, 52 x 8192 42.7 / 44.5, 40 x 16384, 12 splits, 114.6 / 116.9; g = 4, 52 x
+//     8192 38.0 / 38.6, 4096 22.4 / 22.6), or a long share for each (g = 4, 200 x 16384 255.4 / 259.3, 86 x 16384 113.3 / 115.3, x 8192 60.8 / 60.1, 128 x 32768 322.1 / 323.6; g = 2,
+//     200 x 32768 507.6 / 510.8; g = 8, 86 x 16384 124.4 / 123.9; g = 1, 86 x 32768 214.6 / 215.0, 100 x 32768 248.4 / 247.2).  d = 64 gains with all (128 x 32768, g = 4, 167.2 / 165.0).
+constexpr int kMergeHostTokens = 3072, kMergeLongTokens = 4096, kMergeLongShare = 2560;
+bool merge_now(const Shape& s, const SparseArgs& a, int ninst) {
+  int most = a.pred != nullptr ? kMergeFewSums : kMergeInsideSums;
+  if (a.pred == nullptr && !s.cleared) {
+    const int tokens = a.k * a.b;
+    const bool crowded = s.d == 128 && (long)ninst * a.n_split > 256, host_behind = s.kv_dtype == AP_BF16 && s.d == 128 && tokens <= kMergeHostTokens;
+    if (crowded && tokens > kMergeLongShare * a.n_split) return false;
+    if ((a.n_split == kMergeInsideSplits && !host_behind) || (crowded && a.n_split > 8 && tokens > kMergeLongTokens)) most = kMergeFewSums;
+  }
+  return merge_inside(s, ninst, a.n_split, most);
 }
 
 // Does the streaming decode (and the fp32 one in splits) make the selection too?  Every workgroup of an instance makes all of it, which is
@@ -568,7 +577,7 @@ hipError_t run_stream(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
   }
   hipError_t e = select_first(s, ninst, a, st);
   if (e != hipSuccess) return e;
-  if (merge_inside(s, ninst, a.n_split, most_sums(s, a))) {
+  if (merge_now(s, a, ninst)) {
     const size_t lds = lds_of_form(a, lds_of(want), G, kMergeInside);
     if (s.cleared) sparse_stream_kernel<D, G, kMergeInside><<<grid, kAttnThreads, lds, st>>>(a);
     else sparse_stream_kernel<D, G, kMergeAlone><<<grid, kAttnThreads, lds, st>>>(a);
@@ -623,7 +632,7 @@ hipError_t run_sparse(const Shape& s, int ninst, SparseArgs a, hipStream_t st) {
     }
   }
   if constexpr (std::is_same<T, float>::value)
-    if (inside || (merge_inside(s, ninst, a.n_split, most_sums(s, a)) && (s.cleared || D == 64 || ninst * a.n_split <= 256))) {
+    if (inside || (merge_now(s, a, ninst) && (s.cleared || D == 64 || ninst * a.n_split <= 256))) {
       const dim3 grid(a.n_split, ninst);
       const size_t lds_merge = lds_of_form(a, lds, G, kMergeInside);
       if (inside) sparse_decode_kernel<T, D, G, kAttnWaves, false, kSelectInside><<<grid, kAttnThreads, lds_inside, st>>>(a);

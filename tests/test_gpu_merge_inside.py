@@ -153,6 +153,8 @@ def test_fused_step_only_adds(n, g, d, block, k, nb, dtype, c1, c2):
     (16, 4, 128, 16, 192, "bf16", True), (16, 4, 128, 16, 208, "bf16", False),       # 16 splits of many sums: short lists, and longer ones
     (17, 4, 128, 16, 256, "bf16", True), (16, 2, 128, 16, 256, "bf16", True),         # 15 splits; 16 of few sums
     (32, 8, 64, 16, 128, "bf16", False), (33, 8, 64, 16, 128, "bf16", True), (20, 8, 128, 16, 128, "bf16", True),
+    (52, 4, 128, 16, 256, "bf16", True), (52, 4, 128, 16, 272, "bf16", False),        # more than a workgroup a CU, nine splits of many sums: 4096 tokens, and more
+    (100, 1, 128, 16, 800, "bf16", True), (100, 1, 128, 16, 805, "bf16", False),      # the same, five splits: 2560 tokens each, and more
     (8, 8, 64, 16, 64, "f32", False), (8, 8, 64, 16, 60, "f32", True), (8, 4, 64, 16, 64, "f32", True), (64, 4, 128, 16, 16, "f32", True),
     (65, 4, 128, 16, 16, "f32", False), (128, 4, 64, 16, 16, "f32", True), (129, 4, 64, 16, 16, "f32", False),
 ])
