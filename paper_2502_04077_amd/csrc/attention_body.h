@@ -343,7 +343,7 @@ struct SparseArgs {
   float* out; float* row; size_t row_stride;
   float* part_ml; float* part_acc; float* part_bmp;
   int t_cap, nb_cap, k, b, log2b, t_cur, nb_cur, n_split, blk_per_split, inst0;
-  int part_first;                 // instance that part_ml and part_acc begin with
+  int part_first;                 // instance that part_ml and part_acc begin with (0 where the splits are merged inside)
   const int32_t* table;           // block table [n_inst][nb_cap] of a paged cache, or null
   int n_phys;                     // blocks in the pool (table entries are clamped into it)
   int piece_blocks;               // list positions whose probabilities are in LDS at a time
@@ -446,8 +446,8 @@ inline size_t merge_lds_bytes(int n_split, int g) { return n_split > 1 ? sizeof(
 template <int D, int G, class BlockOf>
 __device__ __forceinline__ void merge_splits(const SparseArgs& a, int inst, int cnt, BlockOf block_of, float* s_scale) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const float* ml = a.part_ml + (size_t)(inst - a.part_first) * a.n_split * G * 2;        // [split][head] (maximum, sum relative to it)
-  const float* acc = a.part_acc + (size_t)(inst - a.part_first) * a.n_split * G * D;
+  const float* ml = a.part_ml + (size_t)inst * a.n_split * G * 2;        // [split][head] (maximum, sum relative to it)
+  const float* acc = a.part_acc + (size_t)inst * a.n_split * G * D;
   const float* bmp = a.part_bmp + (size_t)inst * G * a.k;
   // This thread's first list position, with its block maxima, and its first outputs of the first splits.
   int blk = -1;
@@ -737,7 +737,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
       row[j] = mx;
     }
   } else {
-    const size_t ps = (size_t)(inst - a.part_first) * a.n_split + split;
+    const size_t ps = (size_t)(MERGE ? inst : inst - a.part_first) * a.n_split + split;
     for (int o = threadIdx.x; o < G * D; o += NT) {
       float v = 0.f;
 #pragma unroll
@@ -1131,7 +1131,7 @@ __device__ __forceinline__ void sparse_stream_body(const SparseArgs& a, int inst
       row[s_idx[jb]] = mx;                               // (a block listed twice: either of two equal values)
     }
   } else {
-    const size_t ps = (size_t)(inst - a.part_first) * a.n_split + split;
+    const size_t ps = (size_t)(MERGE ? inst : inst - a.part_first) * a.n_split + split;
     for (int o = threadIdx.x; o < G * D; o += NT) {
       const int h = o / D;
       float v = 0.f;
