@@ -451,14 +451,19 @@ bool merge_inside(const Shape& s, int ninst, int n_split, int most_sums = kMerge
 //   - more than a workgroup a CU with d = 128, more than eight splits of many sums and long lists (g = 8, 52 x 8192 42.7 / 44.5, 40 x 16384, 12 splits, 114.6 / 116.9; g = 4, 52 x
 //     8192 38.0 / 38.6, 4096 22.4 / 22.6), or a long share for each (g = 4, 200 x 16384 255.4 / 259.3, 86 x 16384 113.3 / 115.3, x 8192 60.8 / 60.1, 128 x 32768 322.1 / 323.6; g = 2,
 //     200 x 32768 507.6 / 510.8; g = 8, 86 x 16384 124.4 / 123.9; g = 1, 86 x 32768 214.6 / 215.0, 100 x 32768 248.4 / 247.2).  d = 64 gains with all (128 x 32768, g = 4, 167.2 / 165.0).
-constexpr int kMergeHostTokens = 3072, kMergeLongTokens = 4096, kMergeLongShare = 2560;
+//   - more than eight splits of many sums with d = 128 and up to a workgroup a CU, where lists are long for that number: the more splits the launch has beyond eight, the longer it waits for
+//     the remainder.  (g = 4 and 8, 28 instances, nine splits: 4096 tokens 15.6 / 15.3, 19.3 / 19.9, 5120 17.3 / 17.7, 21.7 / 22.4, 16384 41.7 / 42.2, 47.2 / 48.4; 24, ten: 6144 17.7 / 18.5, 23.3 / 23.7,
+//     8192 21.5 / 21.7, 27.6 / 27.1, 16384 37.3 / 37.8, 43.5 / 44.5; 22, eleven: 8192 21.3 / 20.8, 26.7 / 26.2, 12288 27.7 / 28.4, 34.8 / 34.4, 24576 49.5 / 50.5, 56.6 / 57.2; 20, twelve: 12288 26.3 / 26.0, 32.5 /
+//     31.5, 16384 32.1 / 32.9, 39.8 / 39.3, 32768 57.6 / 58.6, 67.0 / 67.5; g = 4, 18, fourteen: 16384 31.7 / 31.0, 24576 42.8 / 42.6, 32768 54.4 / 54.9.)
+constexpr int kMergeHostTokens = 3072, kMergeLongTokens = 4096, kMergeLongStep = 3072, kMergeLongShare = 2560;
 bool merge_now(const Shape& s, const SparseArgs& a, int ninst) {
   int most = a.pred != nullptr ? kMergeFewSums : kMergeInsideSums;
   if (a.pred == nullptr && !s.cleared) {
     const int tokens = a.k * a.b;
     const bool crowded = s.d == 128 && (long)ninst * a.n_split > 256, host_behind = s.kv_dtype == AP_BF16 && s.d == 128 && tokens <= kMergeHostTokens;
     if (crowded && tokens > kMergeLongShare * a.n_split) return false;
-    if ((a.n_split == kMergeInsideSplits && !host_behind) || (crowded && a.n_split > 8 && tokens > kMergeLongTokens)) most = kMergeFewSums;
+    const int longest = kMergeLongTokens + (crowded ? 0 : kMergeLongStep * (a.n_split - 9));
+    if ((a.n_split == kMergeInsideSplits && !host_behind) || (s.d == 128 && a.n_split > 8 && tokens > longest)) most = kMergeFewSums;
   }
   return merge_inside(s, ninst, a.n_split, most);
 }

@@ -155,6 +155,10 @@ def test_fused_step_only_adds(n, g, d, block, k, nb, dtype, c1, c2):
     (32, 8, 64, 16, 128, "bf16", False), (33, 8, 64, 16, 128, "bf16", True), (20, 8, 128, 16, 128, "bf16", True),
     (52, 4, 128, 16, 256, "bf16", True), (52, 4, 128, 16, 272, "bf16", False),        # more than a workgroup a CU, nine splits of many sums: 4096 tokens, and more
     (100, 1, 128, 16, 800, "bf16", True), (100, 1, 128, 16, 805, "bf16", False),      # the same, five splits: 2560 tokens each, and more
+    (28, 4, 128, 16, 256, "bf16", True), (28, 4, 128, 16, 257, "bf16", False),        # up to a workgroup a CU, many sums: nine splits, 4096 tokens and more;
+    (24, 4, 128, 16, 448, "bf16", True), (24, 4, 128, 16, 449, "bf16", False),        # ten, 7168;
+    (17, 4, 128, 16, 1408, "bf16", True), (17, 4, 128, 16, 1409, "bf16", False),      # fifteen, 22528;
+    (28, 2, 128, 16, 1024, "bf16", True),             # few sums
     (8, 8, 64, 16, 64, "f32", False), (8, 8, 64, 16, 60, "f32", True), (8, 4, 64, 16, 64, "f32", True), (64, 4, 128, 16, 16, "f32", True),
     (65, 4, 128, 16, 16, "f32", False), (128, 4, 64, 16, 16, "f32", True), (129, 4, 64, 16, 16, "f32", False),
 ])
