@@ -536,6 +536,12 @@ template <int D> int mixed_splits(const SparseArgs& a, int ninst, int g) {
   const long tokens = (long)a.k * a.b;
   if (a.n_split < 2 || n_whole == 0 || beyond == 0 || beyond > (n_whole == kCUs ? kCUs / 4 : kCUs / 2) || (D == 64 && n_whole == kCUs)) return 0;
   if (4 * D * tokens < 512 * 1024 || g * tokens > 40960) return 0;         // (the latter: a whole list's logits, as in stream_splits)
+  // Contiguous instances 4 KB less or more than 512 KB apart: whole lists, which stay in step, then read from few channels at a time, shares of lists less so.  (All alike /
+  // mixed, d = 128, g = 4: 516 KB, 640 x 1024 tokens 60.8 / 67.5, x 2016 114 / 130, 896 x 1024 83 / 90; d = 64, 640 x 2048 65.2 / 69.7; 508 KB, 640 x 1024 61.5 / 67.4, 264 30.3 /
+  // 33.6.  Not so at 506 or 510, 514 or 518: 60 / 57.)  Twice that: d = 128, 1032 KB, lists of half the context or more lose, 640 x 2016 118 / 126, 300 x 1024, g = 2, 29.5 / 33.9,
+  // shorter ones are as fast, 640 x 1024 of 4128 62.7 / 62.3; d = 64 gains, 640 x 2048 of 8256 74 / 64, and 1016 KB does, 640 x 1024 of 4064 62.7 / 60.8, 264 31.3 / 28.4.
+  const size_t apart = sizeof(bf16_t) * D * (size_t)a.t_cap;
+  if (a.table == nullptr && (apart == 508 * 1024 || apart == 516 * 1024 || (D == 128 && apart == 1032 * 1024))) return 0;
   long splits = (beyond > kCUs / 4 ? kCUs : 2 * kCUs) / beyond;
   if (splits > tokens / 128) splits = tokens / 128;                        // (two passes a wave)
   if (splits > 64) splits = 64;

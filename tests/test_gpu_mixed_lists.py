@@ -110,6 +110,33 @@ def check(i, blocks, q, K, V, b, t, out, row):
     assert (row[i].double() - ref_row).abs().max() <= 2e-5 * ref_row.max(), i
 
 
+@pytest.mark.parametrize("d,cap,paged,mixed", [(128, 127, False, False), (128, 129, False, False), (128, 258, False, False),
+                                                (64, 254, False, False), (64, 258, False, False), (64, 516, False, True), (128, 254, False, True),
+                                                (128, 126, False, True), (128, 128, False, True), (128, 130, False, True), (64, 255, False, True), (128, 129, True, True)])
+def test_instances_near_512_kb_apart(d, cap, paged, mixed):
+    """Lists are split alike where contiguous instances lie 508 or 516 KB apart, or 1032 with d = 128; everywhere else those beyond 512 only."""
+    import paper_2502_04077_amd as ap
+    dev = torch.device("cuda:0")
+    n, g, b, k = 544, 4, 16, 8192 // d
+    t = cap * b - 3
+    ctx = ap.Context(n_inst=n, g=g, head_dim=d, block=b, hist_len=8, t_cap=cap * b, k_blocks=k, n_sink=0, n_local=0, c1=4, c2=4, kv_dtype="bf16")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(cap + d)
+    K, V = (torch.randn((n, cap * b, d), generator=gen, device=dev).to(torch.bfloat16) for _ in range(2))
+    q = (2 * torch.randn((n, g, d), generator=gen, device=dev)).to(torch.bfloat16)
+    if paged:
+        table = torch.arange(n * cap, dtype=torch.int32, device=dev).view(n, cap)       # (the caller's: it has to live as long as the calls)
+        ctx.set_block_table(table, n * cap)
+    idx = torch.rand((n, cap), generator=gen, device=dev).argsort(dim=1)[:, :k].sort(dim=1).values.to(torch.int32).contiguous()
+    cnt = torch.full((n,), k, dtype=torch.int32, device=dev)
+    out, row = torch.full((n, g, d), 7.0, device=dev), torch.full((n, cap), 7.0, device=dev)
+    ws = torch.full((ctx.workspace_bytes(),), 0x5A, dtype=torch.uint8, device=dev)
+    ctx.sparse_decode(q, K, V, t, idx, cnt, out, row, ws)
+    assert (written(ws) < 2 * n * g * d) == mixed          # (partials of two splits or more of everybody; of 32 instances in 8 or 16)
+    for i in (0, 255, 511, 512, n - 1):
+        check(i, idx[i].cpu().numpy(), q, K, V, b, t, out, row)
+
+
 @pytest.mark.parametrize("n,g,d,b,k,nb", FORMS)
 def test_entries_twice_and_out_of_order(n, g, d, b, k, nb):
     """Entries outside the context, repeated and in any order, in whole lists and in split ones, whose rows are written by different code.  Against float64."""
