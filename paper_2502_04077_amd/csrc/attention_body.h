@@ -343,7 +343,6 @@ struct SparseArgs {
   float* out; float* row; size_t row_stride;
   float* part_ml; float* part_acc; float* part_bmp;
   int t_cap, nb_cap, k, b, log2b, t_cur, nb_cur, n_split, blk_per_split, inst0;
-  int part_first;                 // instance that part_ml and part_acc begin with (0 where the splits are merged inside)
   const int32_t* table;           // block table [n_inst][nb_cap] of a paged cache, or null
   int n_phys;                     // blocks in the pool (table entries are clamped into it)
   int piece_blocks;               // list positions whose probabilities are in LDS at a time
@@ -352,6 +351,7 @@ struct SparseArgs {
   int n_sink, n_local, sel_at;    // forced blocks; where in LDS (floats) the list goes: k blocks and their number
   unsigned long long* merge_count;  // [n_inst] splits that have left their partials (take_ticket), where they are merged inside
   unsigned long long merge_nonce; // number of this launch in them (kMergeAlone; else they are zero at launch)
+  int part_first;                 // instance that part_ml and part_acc begin with (0 but where whole and split lists go in one launch: streaming form, merged by a launch)
 };
 
 // What a decode launch does beside its own share: nothing; merging, by the last workgroup of an instance to finish, behind a launch that has cleared
@@ -737,7 +737,7 @@ __device__ __forceinline__ void sparse_decode_body(const SparseArgs& a, int inst
       row[j] = mx;
     }
   } else {
-    const size_t ps = (size_t)(MERGE ? inst : inst - a.part_first) * a.n_split + split;
+    const size_t ps = (size_t)inst * a.n_split + split;
     for (int o = threadIdx.x; o < G * D; o += NT) {
       float v = 0.f;
 #pragma unroll
