@@ -160,7 +160,8 @@ struct CalibArgs {
 };
 
 // A workgroup for every unit (chunk blockIdx.x of instance blockIdx.y).  (fp32.  With units off a counter, cleared by a launch before, 100 instances at 32K took 321 us
-// instead of 304; 16 55.8, 54.4.)
+// instead of 304; 16 55.8, 54.4.  g = 8, d = 128 alone lost by it beyond 1024 units: 100 at 32K 326 then, 329 now, 200 at 16K 371, 377; 1024 workgroups that take every 1024th unit 340,
+// 376, LDS for three workgroups a CU 351, 384.)
 template <int D, int G>
 __global__ __launch_bounds__(kAttnThreads) void calibrate_f32_kernel(CalibArgs a) {
   using T = float;
